@@ -3,6 +3,7 @@
 #include "common.h"
 #include "index_map.h"
 #include "kernels.h"
+#include "split.h"
 
 using namespace sm;
 
@@ -73,7 +74,8 @@ int gemm_checked(GemmArgs& g, void* stream, const char* who) {
            g.act == SM_ACT_GELU ? "+gelu" : (g.act ? "+glu" : ""), g.residual ? "+res" : "", g.c_rows.identity ? "" : (g.C2 ? "+copy2" : "+scatter"));
   if (g.C2 && g.c_rows.identity) { const size_t n = strlen(label); snprintf(label + n, sizeof(label) - n, "+copy2"); }
   Timed tm(label, stream);
-  int rc = launch_gemm(g, stream);
+  int rc = 0;
+  if (!launch_split_linear(g, stream, &rc)) rc = launch_gemm(g, stream);
   if (rc) return fail(SM_ERR_DEVICE, "%s: launch failed (hip error %d)", who, rc);
   count_compute();
   return SM_OK;

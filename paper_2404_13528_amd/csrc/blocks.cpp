@@ -18,6 +18,7 @@
 #include "common.h"
 #include "index_map.h"
 #include "kernels.h"
+#include "split.h"
 #include "plan_chains.h"
 #include "copy_plan.h"
 #include "graph_build.h"
@@ -25,6 +26,8 @@
 using namespace sm;
 
 namespace {
+
+size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
 struct SwinPlan {
   // elided: what sm_layout_plan decided for the block's operator graph
@@ -164,9 +167,6 @@ int check_swin(const sm_swin_cfg* c, const char* who) {
   return SM_OK;
 }
 
-size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
-
-
 int run_norm(const void* x, const void* g, const void* b, void* y, int64_t rows, int C, float eps, int rms, int dtype,
              const RowProg* load, int nseg, const RowProg* store, void* stream) {
   NormArgs a; std::memset(&a, 0, sizeof(a));
@@ -177,15 +177,21 @@ int run_norm(const void* x, const void* g, const void* b, void* y, int64_t rows,
 }
 
 // ln_g != null: LayerNorm (gamma ln_g, beta ln_b, eps) of A's rows folded into the load
-int run_gemm(const void* A, const void* W, const void* bias, const void* res, void* C, int64_t M, int N, int K, int dtype,
-             int act, const RowProg* a_rows, const RowProg* c_rows, void* stream,
-             const void* ln_g = nullptr, const void* ln_b = nullptr, float ln_eps = 0.f) {
+GemmArgs gemm_args(const void* A, const void* W, const void* bias, const void* res, void* C, int64_t M, int N, int K, int dtype,
+                   int act, const RowProg* a_rows, const RowProg* c_rows,
+                   const void* ln_g = nullptr, const void* ln_b = nullptr, float ln_eps = 0.f) {
   GemmArgs g; std::memset(&g, 0, sizeof(g));
   g.A = A; g.W = W; g.bias = bias; g.residual = res; g.C = C; g.M = M; g.N = N; g.K = K; g.dtype = dtype; g.act = act; g.ldw = K;
   if (ln_g) { g.norm = 1; g.norm_gamma = ln_g; g.norm_beta = ln_b; g.norm_eps = ln_eps; }
   const int n_out = (act == SM_ACT_SWIGLU || act == SM_ACT_GEGLU) ? N / 2 : N;
   g.a_rows = a_rows ? *a_rows : identity_rows(K);
   g.c_rows = c_rows ? *c_rows : identity_rows(n_out);
+  return g;
+}
+int run_gemm(const void* A, const void* W, const void* bias, const void* res, void* C, int64_t M, int N, int K, int dtype,
+             int act, const RowProg* a_rows, const RowProg* c_rows, void* stream,
+             const void* ln_g = nullptr, const void* ln_b = nullptr, float ln_eps = 0.f) {
+  GemmArgs g = gemm_args(A, W, bias, res, C, M, N, K, dtype, act, a_rows, c_rows, ln_g, ln_b, ln_eps);
   return gemm_checked(g, stream, "linear");
 }
 
@@ -194,6 +200,20 @@ int run_gemm(const void* A, const void* W, const void* bias, const void* res, vo
 // wins only while the Linear has few column tiles (measured: up to N = 512).
 bool fold_norm(int n_cols) { return n_cols <= 512; }
 
+// Whether the tail of a block (projection .. the next QKV) is cut over output columns instead of over rows
+// (from 32-token tiles of the row-owning kernel alone to the chain at 6 blocks per stage, us per block: C = 512, 196 tokens
+// 101 / 35, 784 100 / 53, 1568 99 / 74, 3136 99 / 122; C = 384, 196 57 / 31, 784 55 / 46, 1568 55 / 58; C = 256, 784 34 / 31,
+// 1568 34 / 41; per-operator kernels at C = 1024, 49 tokens 121 / 73, 196 120 / 78, 392 117 / 128).  The row-owning kernel's
+// time does not depend on the rows until they fill the chip, and grows with C^2; the chain's grows with rows x C.
+bool split_tail_use(const sm_swin_cfg& c, int64_t T) {
+  if (c.dtype != SM_BF16 || c.C % 32 || c.C > 1024) return false;
+  return T <= (c.C <= 512 ? (int64_t)c.C * c.C / 112 : 256);
+}
+// rows per tile / 32: one row tile per XCD while 32-row tiles are that few
+int split_tail_mi(int64_t T, int C) {
+  return C <= 512 && T > 256 ? 2 : 1;
+}
+
 // LayerNorm-2 + FC1 + GELU + FC2 + residual as the fused MLP kernel, when the caller packed the weights for it
 bool mlp_is_fused(const sm_swin_cfg& c, const sm_swin_weights* wt) {
   return wt->mlp_packed && mlp_fused_supported(c.C, c.mlp_ratio * c.C, c.dtype);
@@ -201,6 +221,25 @@ bool mlp_is_fused(const sm_swin_cfg& c, const sm_swin_weights* wt) {
 // ... and the output projection with its window-reverse store and the first residual in front of it (elided mode)
 bool proj_is_fused(const sm_swin_cfg& c, const sm_swin_weights* wt) {
   return wt->proj_packed && wt->mlp_packed && mlp_proj_supported(c.C, c.mlp_ratio * c.C, c.dtype);
+}
+// Whether the block's tail is the chained launch of k_split.hip: where the caller packed the weights of the fused kernel
+// that it stands in for, or there is no such kernel for the width
+bool tail_is_split(const sm_swin_cfg& c, const sm_swin_weights* wt) {
+  return split_tail_use(c, (int64_t)c.B * c.H * c.W) && (proj_is_fused(c, wt) || !mlp_fused_supported(c.C, c.mlp_ratio * c.C, c.dtype));
+}
+// A caller who packed the fused kernels' weights, or a width without such kernels: norms may be folded wherever that is
+// faster (else the caller asked for one kernel per operator and fold_norm alone decides)
+bool free_form(const sm_swin_cfg& c, const sm_swin_weights* wt) { return proj_is_fused(c, wt) || !mlp_fused_supported(c.C, c.mlp_ratio * c.C, c.dtype); }
+bool split_norm_linear(const sm_swin_cfg& c, int n_cols) {
+  return split_linear_use(gemm_args(nullptr, nullptr, nullptr, nullptr, nullptr, (int64_t)c.B * c.H * c.W, n_cols, c.C, c.dtype, SM_ACT_NONE, nullptr, nullptr, c.eps > 0 ? &c : nullptr, &c, c.eps));
+}
+// LayerNorm-1 + QKV: the packed-weight Linear, one Linear with the norm folded in, or two kernels.  The packed-weight
+// kernel owns rows: below 128 of its 32-row workgroups the others win (1568 x 1152 x 384: 20 us against 11)
+enum QkvForm { QKV_PACKED, QKV_FOLDED, QKV_TWO };
+QkvForm qkv_form(const sm_swin_cfg& c, const sm_swin_weights* wt) {
+  if (free_form(c, wt) && split_norm_linear(c, 3 * c.C)) return QKV_FOLDED;
+  if (wt->qkv_packed && lin32_supported(3 * c.C, c.C, c.dtype)) return free_form(c, wt) && (int64_t)c.B * c.H * c.W < 4096 ? QKV_FOLDED : QKV_PACKED;
+  return fold_norm(3 * c.C) ? QKV_FOLDED : QKV_TWO;
 }
 // Where the row at window-major position r of a block with shift c.shift goes in the window-major tensor of a block
 // with shift next_shift: the composed map reverse(next) then partition(this), read as a store (Sec. 3.2.1: two runs of
@@ -230,11 +269,11 @@ std::shared_ptr<NextStore> next_norm_store(const sm_swin_cfg& c, int next_shift,
 enum { TBL_LN1_STORE = 1, TBL_PROJ_STORE = 2, TBL_X_GATHER = 4 };
 uint64_t el_tables_needed(const sm_swin_cfg& c, const sm_swin_weights* wt, int pre) {
   uint64_t need = TBL_PROJ_STORE;
-  if (pre == 0) need |= ((wt->qkv_packed && lin32_supported(3 * c.C, c.C, c.dtype)) || fold_norm(3 * c.C)) ? TBL_X_GATHER : TBL_LN1_STORE;
+  if (pre == 0) need |= qkv_form(c, wt) != QKV_TWO ? TBL_X_GATHER : TBL_LN1_STORE;
   return need;
 }
 
-struct NextNorm { const void* gamma; const void* beta; RowProg store; const void* wq_p; const void* bq; };   // wq_p: ... and its QKV Linear
+struct NextNorm { const void* gamma; const void* beta; RowProg store; const void* wq_p; const void* bq; const void* wq; };   // wq_p: ... and its QKV Linear
 int run_proj_mlp_fused(const sm_swin_cfg& c, const sm_swin_weights* wt, const void* attn_out, const void* x, void* y, int64_t T,
                        const RowProg& store, const NextNorm* next, void* next_out, void* stream) {      // next_out: norm or QKV slot
   MlpArgs a; std::memset(&a, 0, sizeof(a));
@@ -248,6 +287,36 @@ int run_proj_mlp_fused(const sm_swin_cfg& c, const sm_swin_weights* wt, const vo
     a.Wq_p = next->wq_p; a.bq = next->bq;
   }
   return mlp_checked(a, stream, "sm_swin_block(proj+mlp)");
+}
+// The same work cut over output columns (k_split.hip): x1 and the hidden activation stay in the window order of the
+// attention output, in x1 / hid of the workspace; counters: split_counter_ints(T) zeroed words.
+int run_split_tail(const sm_swin_cfg& c, const sm_swin_weights* wt, const void* attn_out, const void* x, void* y, void* x1, void* hid, int64_t T,
+                   const RowProg& store, const NextNorm* next, void* next_out, int* counters, void* stream) {
+  SplitArgs a; std::memset(&a, 0, sizeof(a));
+  const int C = c.C, Hd = c.mlp_ratio * C;
+  a.M = (int)T; a.n_ph = next ? 4 : 3;
+  auto lin = [&](LinPhase& p, const void* A, const void* W, const void* bias, void* out, int N, int K) {
+    p.A = A; p.W = W; p.bias = bias; p.out = out; p.N = N; p.K = K; p.a_ld = K; p.o_ld = p.r_ld = N; p.o_mul = 1; p.eps = c.eps;
+  };
+  lin(a.ph[0], attn_out, wt->wproj, wt->bproj, x1, C, C);
+  a.ph[0].res = x; a.ph[0].r_tab = store.table; if (!store.table) a.ph[0].r_ld = (int)store.ld;
+  lin(a.ph[1], x1, wt->w1, wt->b1, hid, Hd, C);
+  a.ph[1].ln_g = wt->ln2_g; a.ph[1].ln_b = wt->ln2_b; a.ph[1].act = SM_ACT_GELU;
+  lin(a.ph[2], hid, wt->w2, wt->b2, y, C, Hd);
+  a.ph[2].res = x1; a.ph[2].ring = 1; a.ph[2].o_tab = store.table; if (!store.table) a.ph[2].o_ld = (int)store.ld;
+  if (next) {
+    lin(a.ph[3], y, next->wq, next->bq, next_out, 3 * C, C);
+    a.ph[3].ln_g = next->gamma; a.ph[3].ln_b = next->beta;
+    a.ph[3].a_tab = store.table; if (!store.table) a.ph[3].a_ld = (int)store.ld;
+    a.ph[3].o_tab = next->store.table; a.ph[3].o_mul = 3; if (!next->store.table) a.ph[3].o_ld = 3 * (int)next->store.ld;
+  }
+  char label[96];
+  snprintf(label, sizeof(label), "split_proj+ln+mlp_bf16[%lld,%d,%d]%s", (long long)T, Hd, C, next ? "+ln+qkv" : "");
+  Timed tm(label, stream);
+  const int rc = launch_split_chain(a, counters, split_tail_mi(T, C), stream);
+  if (rc) return fail(SM_ERR_DEVICE, "sm_swin_block: launch failed (hip error %d)", rc);
+  count_compute(1);
+  return SM_OK;
 }
 int run_mlp_fused(const sm_swin_cfg& c, const sm_swin_weights* wt, const void* x1, void* y, int64_t T, void* stream) {
   MlpArgs a; std::memset(&a, 0, sizeof(a));
@@ -268,7 +337,12 @@ size_t swin_act_bytes(const sm_swin_cfg* c, int mode) {
   return tc * units;
 }
 int swin_block_impl(const sm_swin_cfg* c, const sm_swin_weights* wt, const void* x, void* y, void* ws, size_t ws_bytes, int mode,
-                    void* stream, const NextNorm* next, int pre, const void* tables);
+                    void* stream, const NextNorm* next, int pre, const void* tables, int* counters);
+// counters of one block's chained launch (behind the tables of a block, or of the chain)
+size_t swin_counter_bytes(const sm_swin_cfg& c, int mode) {
+  const int64_t T = (int64_t)c.B * c.H * c.W;
+  return mode == SM_ELIDED && split_tail_use(c, T) ? align256(split_counter_ints(T) * sizeof(int)) : 0;
+}
 }
 
 extern "C" size_t sm_swin_block_workspace_bytes(const sm_swin_cfg* c, int mode) {
@@ -277,12 +351,12 @@ extern "C" size_t sm_swin_block_workspace_bytes(const sm_swin_cfg* c, int mode) 
   std::string err;
   auto plan = swin_plan(*c, &err);
   if (!plan) { set_error("sm_swin_block_workspace_bytes: %s", err.c_str()); return 0; }
-  return swin_act_bytes(c, mode) + plan->tables(mode).bytes;
+  return swin_act_bytes(c, mode) + align256(plan->tables(mode).bytes) + swin_counter_bytes(*c, mode);
 }
 
 extern "C" int sm_swin_block(const sm_swin_cfg* c, const sm_swin_weights* wt, const void* x, void* y,
                              void* ws, size_t ws_bytes, int mode, void* stream) {
-  return swin_block_impl(c, wt, x, y, ws, ws_bytes, mode, stream, nullptr, 0, nullptr);
+  return swin_block_impl(c, wt, x, y, ws, ws_bytes, mode, stream, nullptr, 0, nullptr, nullptr);
 }
 
 namespace {
@@ -292,7 +366,7 @@ namespace {
 // tables: where the plan's row-offset tables for `mode` were already filled on this stream (the chain executor fills
 // them once per stage and shift); null: they go behind the activation buffers of ws and are filled here
 int swin_block_impl(const sm_swin_cfg* c, const sm_swin_weights* wt, const void* x, void* y, void* ws, size_t ws_bytes, int mode,
-                    void* stream, const NextNorm* next, int pre, const void* tables) {
+                    void* stream, const NextNorm* next, int pre, const void* tables, int* counters) {
   int rc = check_swin(c, "sm_swin_block");
   if (rc) return rc;
   if (!wt || !x || !y || !ws) return fail(SM_ERR_INVALID_ARG, "sm_swin_block: null pointer");
@@ -301,12 +375,18 @@ int swin_block_impl(const sm_swin_cfg* c, const sm_swin_weights* wt, const void*
   std::string err;
   auto plan = swin_plan(*c, &err);
   if (!plan) return fail(SM_ERR_UNSUPPORTED, "sm_swin_block: %s", err.c_str());
-  const size_t need = swin_act_bytes(c, mode) + (tables ? 0 : plan->tables(mode).bytes);
+  const size_t need = swin_act_bytes(c, mode) + (tables ? 0 : align256(plan->tables(mode).bytes) + swin_counter_bytes(*c, mode));
   if (ws_bytes < need) return fail(SM_ERR_WORKSPACE, "sm_swin_block: workspace of %zu bytes, %zu needed", ws_bytes, need);
   count_reset();
   if (!tables) {
     void* region = (char*)ws + swin_act_bytes(c, mode);
-    if ((rc = fill_tables(plan->tables(mode), region, stream, mode == SM_ELIDED ? el_tables_needed(*c, wt, pre) : ~0ull))) return rc;
+    TableFiller filler(stream);
+    if ((rc = filler.add(plan->tables(mode), region, mode == SM_ELIDED ? el_tables_needed(*c, wt, pre) : ~0ull))) return rc;
+    if (mode == SM_ELIDED && tail_is_split(*c, wt)) {
+      counters = (int*)((char*)region + align256(plan->tables(mode).bytes));
+      if ((rc = filler.add_zero(counters, (int64_t)split_counter_ints((int64_t)c->B * c->H * c->W)))) return rc;
+    }
+    if ((rc = filler.flush())) return rc;
     tables = region;
   }
   const RowProg ln1_store = bound(plan->ln1_store, tables), proj_store = bound(plan->proj_store, tables),
@@ -329,7 +409,7 @@ int swin_block_impl(const sm_swin_cfg* c, const sm_swin_weights* wt, const void*
       // nothing: the QKV slot is filled
     } else if (pre == 1) {
       if ((rc = run_gemm(bufA, wt->wqkv, wt->bqkv, nullptr, qkv, T, 3 * C, C, dt, SM_ACT_NONE, nullptr, nullptr, stream))) return rc;
-    } else if (wt->qkv_packed && lin32_supported(3 * C, C, dt)) {
+    } else if (qkv_form(*c, wt) == QKV_PACKED) {
       // LayerNorm-1 + QKV as one packed-weight Linear: x's rows gathered in window-major order (roll included), the
       // tile normalised in LDS, the weight streamed
       Lin32Args a; std::memset(&a, 0, sizeof(a));
@@ -337,7 +417,7 @@ int swin_block_impl(const sm_swin_cfg* c, const sm_swin_weights* wt, const void*
       a.norm = 1; a.norm_eps = eps; a.norm_gamma = wt->ln1_g; a.norm_beta = wt->ln1_b;
       a.x_rows = x_gather; a.y_rows = identity_rows(3 * C);
       if ((rc = lin32_checked(a, stream, "sm_swin_block(ln1+qkv)"))) return rc;
-    } else if (fold_norm(3 * C)) {
+    } else if (qkv_form(*c, wt) == QKV_FOLDED) {
       if ((rc = run_gemm(x, wt->wqkv, wt->bqkv, nullptr, qkv, T, 3 * C, C, dt, SM_ACT_NONE, &x_gather, nullptr, stream, wt->ln1_g, wt->ln1_b, eps))) return rc;
     } else {
       if ((rc = run_norm(x, wt->ln1_g, wt->ln1_b, bufA, T, C, eps, 0, dt, nullptr, 1, &ln1_store, stream))) return rc;
@@ -350,11 +430,13 @@ int swin_block_impl(const sm_swin_cfg* c, const sm_swin_weights* wt, const void*
     }
     if ((rc = attention_checked(ad, (char*)qkv + plan->qkv_base[0] * es, (char*)qkv + plan->qkv_base[1] * es, (char*)qkv + plan->qkv_base[2] * es,
                                 bufO, wt->rpb_table, stream, "window attention"))) return rc;
+    if (counters)
+      return run_split_tail(*c, wt, bufO, x, y, x1, hid, T, proj_store, next, qkv, counters, stream);
     if (proj_is_fused(*c, wt)) return run_proj_mlp_fused(*c, wt, bufO, x, y, T, proj_store, next, next && next->wq_p ? qkv : bufA, stream);
     if (next) return fail(SM_ERR_INVALID_ARG, "sm_swin_block: the next block's norm can only be emitted by the fused projection + MLP kernel");
     if ((rc = run_gemm(bufO, wt->wproj, wt->bproj, x, x1, T, C, C, dt, SM_ACT_NONE, nullptr, &proj_store, stream))) return rc;
     if (mlp_is_fused(*c, wt)) return run_mlp_fused(*c, wt, x1, y, T, stream);
-    if (fold_norm(c->mlp_ratio * C)) {
+    if (fold_norm(c->mlp_ratio * C) || (free_form(*c, wt) && split_norm_linear(*c, c->mlp_ratio * C))) {
       if ((rc = run_gemm(x1, wt->w1, wt->b1, nullptr, hid, T, c->mlp_ratio * C, C, dt, SM_ACT_GELU, nullptr, nullptr, stream, wt->ln2_g, wt->ln2_b, eps))) return rc;
     } else {
       if ((rc = run_norm(x1, wt->ln2_g, wt->ln2_b, bufA, T, C, eps, 0, dt, nullptr, 1, nullptr, stream))) return rc;
@@ -489,7 +571,9 @@ struct ChainLayout {
     std::shared_ptr<SwinPlan> plan[2]; size_t plan_off[2];       // [0] blocks without shift, [1] shifted blocks (if any)
     std::shared_ptr<NextStore> next[2]; size_t next_off[2];      // elided: store of the block after a [0] / [1] block
     std::shared_ptr<MergePlan> merge; size_t merge_off;
+    size_t counter_off = 0, counter_step = 0;                    // elided: one group of counters per block
   };
+  size_t counters = 0, counter_bytes = 0;                        // all of them, adjacent
   std::vector<Stage> stages;
 };
 int shift_of(const sm_chain_desc* c, const sm_stage_desc& st, int k) { return (k % 2 == 1 && std::min(st.H, st.W) > c->window) ? c->window / 2 : 0; }
@@ -527,6 +611,15 @@ bool chain_layout(const sm_chain_desc* c, int mode, ChainLayout* L, std::string*
       S.merge_off = at; at += S.merge->tables.bytes;
     }
   }
+  at = L->counters = align256(at);
+  for (int s = 0; s < c->n_stages; ++s) {
+    const sm_stage_desc& st = c->stages[s];
+    sm_swin_cfg bc{c->B, st.H, st.W, st.C, st.heads, c->window, 0, c->mlp_ratio, dt, c->eps};
+    ChainLayout::Stage& S = L->stages[(size_t)s];
+    S.counter_off = at; S.counter_step = swin_counter_bytes(bc, mode);
+    at += S.counter_step * (size_t)st.depth;
+  }
+  L->counter_bytes = at - L->counters;
   L->total = at;
   return true;
 }
@@ -567,7 +660,7 @@ extern "C" int sm_run_chain(const sm_chain_desc* c, const void* const* weights, 
   if (!aligned16(x) || !aligned16(y) || !aligned16(ws) || (y_feat && !aligned16(y_feat))) return fail(SM_ERR_INVALID_ARG, "sm_run_chain: pointers must be 16-byte aligned");
   const int dt = c->dtype;
   // first pass, no launches: what each block hands to the next one, hence which tables are read at all
-  struct BlockStep { bool next; bool next_qkv; int pre; };
+  struct BlockStep { bool next; bool next_qkv; int pre; bool split; };
   std::vector<std::vector<BlockStep>> steps((size_t)c->n_stages);
   std::vector<uint64_t> need[2];
   need[0].assign((size_t)c->n_stages, 0); need[1].assign((size_t)c->n_stages, 0);
@@ -584,11 +677,13 @@ extern "C" int sm_run_chain(const sm_chain_desc* c, const void* const* weights, 
         sm_swin_weights bw, nwt;
         std::memcpy(&bw, wq, sizeof(bw));
         wq += 16;
-        BlockStep b{false, false, pre};
+        BlockStep b{false, false, pre, false};
         // within a stage, elided, with the projection + MLP kernel: that kernel also writes the next block's
         // LayerNorm-1 (through the next block's own partition map) or its QKV, and the next block starts there
         // (where LayerNorm-1 is folded into the QKV Linear's load, C <= 170, only the norm + QKV form applies)
-        if (mode == SM_ELIDED && k + 1 < st.depth && proj_is_fused(bc, &bw)) {
+        if (mode == SM_ELIDED && tail_is_split(bc, &bw)) b.split = true;
+        if (b.split && k + 1 < st.depth) b.next = b.next_qkv = true;
+        else if (mode == SM_ELIDED && k + 1 < st.depth && proj_is_fused(bc, &bw)) {
           std::memcpy(&nwt, wq, sizeof(nwt));
           const bool with_qkv = nwt.qkv_packed && c->mlp_ratio >= 3;    // (the kernel keeps the QKV bias where the first MLP bias was)
           if (!fold_norm(3 * st.C) || with_qkv) { b.next = true; b.next_qkv = with_qkv; }
@@ -614,6 +709,7 @@ extern "C" int sm_run_chain(const sm_chain_desc* c, const void* const* weights, 
     }
     if (S.merge && (rc = filler.add(S.merge->tables, base + S.merge_off, mode == SM_ELIDED ? 1ull : ~1ull))) return rc;      // LayerNorm's gather | the copy
   }
+  if ((rc = filler.add_zero(base + z.counters, (int64_t)(z.counter_bytes / sizeof(int))))) return rc;
   if ((rc = filler.flush())) return rc;
   void* blk_ws = base;
   void* act[2] = {base + z.block, base + z.block + z.act};
@@ -661,10 +757,11 @@ extern "C" int sm_run_chain(const sm_chain_desc* c, const void* const* weights, 
         sm_swin_weights nw;
         std::memcpy(&nw, wp, sizeof(nw));
         nn.gamma = nw.ln1_g; nn.beta = nw.ln1_b; nn.store = bound(S.next[sh]->rows, base + S.next_off[sh]);
-        nn.wq_p = step.next_qkv ? nw.qkv_packed : nullptr; nn.bq = nw.bqkv;
+        nn.wq_p = step.next_qkv ? (step.split ? nw.wqkv : nw.qkv_packed) : nullptr; nn.bq = nw.bqkv; nn.wq = nw.wqkv;
         next = &nn;
       }
-      if ((rc = swin_block_impl(&bc, &bw, cur, out, blk_ws, z.block, mode, stream, next, step.pre, base + S.plan_off[sh]))) return rc;
+      int* counters = step.split ? (int*)(base + S.counter_off + (size_t)k * S.counter_step) : nullptr;
+      if ((rc = swin_block_impl(&bc, &bw, cur, out, blk_ws, z.block, mode, stream, next, step.pre, base + S.plan_off[sh], counters))) return rc;
       tally();
       cur = out; flip ^= 1;
     }

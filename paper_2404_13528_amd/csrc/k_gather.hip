@@ -123,6 +123,7 @@ __global__ __launch_bounds__(256) void fill_batch_kernel(FillBatch b) {
   for (int j = 1; j < bk->n_jobs; ++j) if ((int)blockIdx.x >= bk->first_block[j]) job = j;       // wave-uniform
   const int64_t r = (int64_t)((int)blockIdx.x - bk->first_block[job]) * 256 + threadIdx.x;
   if (r >= bk->n_rows[job]) return;
+  if (bk->word_off[job] < 0) { ((int32_t*)bk->dst[job])[r] = 0; return; }      // a region of counters to clear
   const SM_KARG int32_t* w = bk->words + bk->word_off[job];
   const int n_atoms = w[0], nterm = w[1];
   int64_t off = (int64_t)(uint32_t)w[2] | ((int64_t)w[3] << 32);

@@ -41,7 +41,7 @@ constexpr int FILL_MAX_JOBS = 8, FILL_MAX_WORDS = 800;
 struct FillBatch {
   int32_t n_jobs, total_blocks;
   int64_t dst[FILL_MAX_JOBS];
-  int32_t n_rows[FILL_MAX_JOBS], first_block[FILL_MAX_JOBS], word_off[FILL_MAX_JOBS];
+  int32_t n_rows[FILL_MAX_JOBS], first_block[FILL_MAX_JOBS], word_off[FILL_MAX_JOBS];      // word_off < 0: n_rows words to clear
   int32_t words[FILL_MAX_WORDS];
 };
 int fill_pack(const RowProg& p, int32_t* words, int room);      // words used, or -1 if the program does not fit in `room`
@@ -51,6 +51,7 @@ class TableFiller {
  public:
   explicit TableFiller(void* stream) : stream_(stream), used_(0) { b_.n_jobs = 0; b_.total_blocks = 0; }
   int add(const TableRegion& r, void* region, uint64_t which);      // SM_OK or an error; may launch when a batch fills up
+  int add_zero(void* words, int64_t n);                             // n 32-bit words to clear
   int flush();
  private:
   FillBatch b_; void* stream_; int used_;

@@ -54,6 +54,16 @@ int TableFiller::add(const TableRegion& r, void* region, uint64_t which) {
   }
   return SM_OK;
 }
+int TableFiller::add_zero(void* words, int64_t n) {
+  int rc;
+  if (n <= 0) return SM_OK;
+  if (n >= (1LL << 31) - 256) return fail(SM_ERR_SHAPE, "counter region of %lld words", (long long)n);
+  if (b_.n_jobs == FILL_MAX_JOBS && (rc = flush())) return rc;
+  const int j = b_.n_jobs++;
+  b_.dst[j] = (int64_t)(intptr_t)words; b_.n_rows[j] = (int32_t)n; b_.first_block[j] = b_.total_blocks; b_.word_off[j] = -1;
+  b_.total_blocks += (int32_t)((n + 255) / 256);
+  return SM_OK;
+}
 int fill_tables(const TableRegion& r, void* region, void* stream, uint64_t which) {
   TableFiller f(stream);
   const int rc = f.add(r, region, which);

@@ -1,0 +1,64 @@
+"""The column-split Linears (k_split.hip): single form against a torch fp64 Linear at the edges of its tiles (rows, columns
+and K-tiles cut, resident panels and the ring of stages, both element types), the chained form (projection .. next QKV in
+one launch) against the oracle's Swin stage."""
+import pytest
+import torch
+from oracle import swin
+from paper_2404_13528_amd import binding as sm, workloads as Wl
+from util import assert_bf16_close, dev, dev_params, np_params, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("M,N,K,norm,act,res", [
+    (1, 8, 16, False, "none", False),            # one row, one chunk of columns, one k-step
+    (31, 40, 48, True, "gelu", True),            # less than a row tile, a cut column tile, a cut K-tile
+    (33, 1000, 96, False, "none", False),        # one row of a second tile, a classifier's width
+    (49, 3072, 1024, True, "gelu", False),       # the widest normalised row (bf16): 32-column panels
+    (65, 96, 1040, False, "gelu", True),         # K past the panels: ring of stages, its last one cut
+    (196, 512, 2048, False, "none", True),       # ring, four and more stages
+    (500, 520, 320, True, "none", True),         # 64-row tiles, both ends cut
+    (97, 128, 384, True, "none", True),
+])
+def test_split_linear(M, N, K, norm, act, res, dtype):
+    g = torch.Generator().manual_seed(M + N + K)
+    A, W = (torch.randn(M, K, generator=g) + 0.3).to(dtype), (torch.randn(N, K, generator=g) * K ** -0.5).to(dtype)
+    b, R = torch.randn(N, generator=g).to(dtype), torch.randn(M, N, generator=g).to(dtype)
+    gam, bet = (1 + 0.1 * torch.randn(K, generator=g)).to(dtype), (0.1 * torch.randn(K, generator=g)).to(dtype)
+    x = A.double()
+    if norm:
+        x = torch.nn.functional.layer_norm(x, (K,), gam.double(), bet.double(), 1e-5)
+        if dtype == torch.bfloat16:
+            x = x.to(dtype).double()             # the normalised row is rounded as a norm kernel would store it
+    want = x @ W.double().t() + b.double()
+    if act == "gelu":
+        want = torch.nn.functional.gelu(want)
+    if res:
+        want = want + R.double()
+    got = sm.linear(A.cuda(), W.cuda(), b.cuda(), residual=R.cuda() if res else None, act=act,
+                    norm=("layer", gam.cuda(), bet.cuda(), 1e-5) if norm else None)
+    got = got.double().cpu()
+    err = (got - want).abs().max().item()
+    assert err <= (2e-5 if dtype == torch.float32 else 1.2e-2) * max(1.0, want.abs().max().item()), err
+
+
+@pytest.mark.parametrize("B,H,C,depth", [
+    (1, 14, 512, 3),       # 32-row tiles: one per XCD but one
+    (3, 14, 512, 2),       # 64-row tiles, two per group for some
+    (1, 14, 384, 4),
+    (2, 14, 256, 2),
+    (1, 7, 1024, 2),       # a width without a fused kernel; two row tiles
+    (5, 7, 768, 2),        # 245 rows: the last tile is cut
+])
+def test_split_chain_matches_the_oracle(B, H, C, depth):
+    h = C // 32
+    x, blocks = Wl.swin_stage_case(B, H, H, C, h, 7, depth, seed=B + C)
+    net = {"stages": [[dev_params(p, torch.bfloat16) for p in blocks]]}
+    chain = sm.SwinChain(B, [(C, h, depth, H, H)], 7, net, torch.bfloat16)
+    want = swin.swin_stage(to_np(x), [np_params(p) for p in blocks], H, H, 7, h)
+    for _ in range(2):                           # the counters are cleared by every call
+        y = chain(dev(x, torch.bfloat16))
+        torch.cuda.synchronize()
+        assert_bf16_close(y, want, "stage", x=to_np(x))
+    assert sm.launch_counts() == (1 + 2 * depth, 0)      # LayerNorm + QKV, then attention and one chained launch per block
