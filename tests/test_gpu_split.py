@@ -20,6 +20,7 @@ pytestmark = pytest.mark.gpu
     (196, 512, 2048, False, "none", True),       # ring, four and more stages
     (500, 520, 320, True, "none", True),         # 64-row tiles, both ends cut
     (97, 128, 384, True, "none", True),
+    (257, 4104, 2064, False, "none", True),      # a second round of 64-row tiles (a long K), all ends cut
 ])
 def test_split_linear(M, N, K, norm, act, res, dtype):
     g = torch.Generator().manual_seed(M + N + K)
