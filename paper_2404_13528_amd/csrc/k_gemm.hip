@@ -898,14 +898,16 @@ static std::atomic<int> g_force_rows{0}, g_force_stages{0};       // sm_gemm_tun
 // the table sm_linear_autotune filled for this shape.
 struct Tune { int rows, stages; };
 
-// Two stages (one K-tile in flight) unless the tuning hook asks for more: within a chain of kernels the operands
-// arrive from the memory-side cache, a workgroup's K step is bound by its own issue and fragment-read latencies
-// rather than by the tile's arrival, and every further stage costs a resident workgroup per CU.
+// Stages unless the rule or the tuning hook says otherwise.  Tiles of 64 and 128 rows: two (one K-tile in flight), since
+// every further stage costs a resident workgroup per CU, whose work hides the arrival as well.  256 rows: three, since
+// LDS holds one such workgroup per CU with two stages (96 KiB) or three (144), and the second K-tile in flight covers
+// the weights' way from memory (us, two stages / three: 2048 x 12288 x 4096 235 / 190, 2048 x 4096 x 11008 229 / 168,
+// 12608 x 3072 x 768 91 / 85).
 template <typename T, int MI, int EPI, int WM>
 static int gemm_launch_dma(const GemmArgs& g, const ColMap& cm, hipStream_t s, Tune tn) {
   constexpr int BM = 32 * MI * WM;
   const int64_t stage = (BM + 128) * 128;
-  const int ns = tn.stages ? std::min<int>(tn.stages, (int)((160 * 1024) / stage)) : 2;
+  const int ns = std::min<int>(tn.stages ? tn.stages : (WM == 4 ? 3 : 2), (int)((160 * 1024) / stage));
   if (ns == 4) return gemm_launch2<T, MI, EPI, false, true, WM, 4>(g, cm, s);
   if (ns == 3) return gemm_launch2<T, MI, EPI, false, true, WM, 3>(g, cm, s);
   return gemm_launch2<T, MI, EPI, false, true, WM, 2>(g, cm, s);
@@ -957,6 +959,26 @@ static TuneKey tune_key(const GemmArgs& g) {
 }
 static bool tunable(const GemmArgs& g) { return g.dtype == SM_BF16 && g.K % 64 == 0 && g.a_gran == 0 && !g.norm; }
 
+// Tile height and stages of a bf16 Linear with a long K (more than 16 K-tiles): rounds of residency times what a round
+// costs, in us at K = 4096 with the weights coming from memory (all scale with K).  A CU holds one 256-row workgroup, one
+// 128-row workgroup with three stages or two with two, two 64-row workgroups with three stages (counted in rounds of
+// 256, half a residency) or three with two.  Measured us, with the earlier choice (two stages, rounds of the 64- and
+// 128-row tiles alone) / with this one: 333 x 12288 x 4096 67 / 57, 200 x 12288 x 4096 61 / 42, 700 x 11264 x 2048 56 / 51,
+// 1100 x 12288 x 4096 169 / 121, 3152 x 768 x 3072 33 / 26, 1000 x 4096 x 11008 148 / 109.
+static Tune long_k_tile(const GemmArgs& g) {
+  const int64_t tcols = (g.N + 127) / 128;
+  auto rounds = [&](int rows, int resident) { return (double)((((g.M + rows - 1) / rows) * tcols + resident - 1) / resident); };
+  const struct { Tune t; double cost; } form[] = {{{64, 3}, 27. * rounds(64, 256)},
+                                                  {{128, 3}, 41. * rounds(128, 256)},
+                                                  {{256, 3}, 60. * rounds(256, 256)},
+                                                  {{128, 2}, 70. * rounds(128, 512)},
+                                                  {{64, 2}, 76. * rounds(64, 768)}};
+  int best = 0;
+  for (int i = 1; i < 5; ++i)
+    if (form[i].cost < form[best].cost) best = i;
+  return form[best].t;
+}
+
 template <typename T>
 static int gemm_dispatch(const GemmArgs& g, const ColMap& cm, hipStream_t s) {
   Tune tn{g_force_rows, g_force_stages};
@@ -965,6 +987,7 @@ static int gemm_dispatch(const GemmArgs& g, const ColMap& cm, hipStream_t s) {
     auto it = g_tuned.find(tune_key(g));
     if (it != g_tuned.end()) tn = it->second;
   }
+  if (!tn.rows && !tn.stages && tunable(g) && g.K > 16 * 64) tn = long_k_tile(g);
   if (tn.rows) return tn.rows >= 128 ? gemm_pick_epi<T, 2>(g, cm, s, tn) : gemm_pick_epi<T, 1>(g, cm, s, tn);
   // Tile height.  Large grids (several rounds of residency whatever the tile): the 128-row tile, or the 256-row one
   // where gemm_launch finds that it fills the chip.  Small grids are decided by rounds of residency (256 CUs hold
@@ -976,7 +999,8 @@ static int gemm_dispatch(const GemmArgs& g, const ColMap& cm, hipStream_t s) {
   if (t128 >= 1024) return gemm_pick_epi<T, 2>(g, cm, s, tn);
   const double nk = (double)((g.K + 63) / 64);
   double cost64 = (double)((t64 + 767) / 768) * (3.0 + 0.78 * nk), cost128 = (double)((t128 + 511) / 512) * (3.6 + 1.6 * nk);
-  // long K loops: the tile's L2 -> LDS traffic per flop decides, the 64-row tile being about 0.6 as efficient per row
+  // long K loops (fp32 and the register-staged forms): the tile's L2 -> LDS traffic per flop decides, the 64-row tile being
+  // about 0.6 as efficient per row
   if (nk > 16) { cost64 = (double)((t64 + 767) / 768) * 1.2; cost128 = (double)((t128 + 511) / 512) * 2.0; }
   return cost128 <= cost64 ? gemm_pick_epi<T, 2>(g, cm, s, tn) : gemm_pick_epi<T, 1>(g, cm, s, tn);
 }

@@ -63,3 +63,18 @@ def test_split_chain_matches_the_oracle(B, H, C, depth):
         torch.cuda.synchronize()
         assert_bf16_close(y, want, "stage", x=to_np(x))
     assert sm.launch_counts() == (1 + 2 * depth, 0)      # LayerNorm + QKV, then attention and one chained launch per block
+
+
+@pytest.mark.parametrize("M,N,K,act", [
+    (70, 2112, 1088, "swiglu"),        # 64-row tiles, cut ends, the shortest long K
+    (257, 5696, 1088, "swiglu"),       # 64- or 128-row tiles, more than one round of the smaller
+    (520, 22016, 1088, "swiglu"),      # several rounds
+    (1025, 6152, 1152, "none"),        # 256-row tiles, a cut row tile
+])
+def test_long_k_tiles(M, N, K, act):
+    g = torch.Generator().manual_seed(M + N)
+    A, W = torch.randn(M, K, generator=g).bfloat16(), (torch.randn(N, K, generator=g) * K ** -0.5).bfloat16()
+    z = A.cuda().float() @ W.cuda().float().t()
+    want = torch.nn.functional.silu(z[:, :N // 2]) * z[:, N // 2:] if act == "swiglu" else z
+    got = sm.linear(A.cuda(), W.cuda(), None, act=act).float()
+    assert (got - want).norm().item() <= 4e-3 * want.norm().item()      # bf16 result: relative rounding 2^-9, fp32 sums
