@@ -80,7 +80,7 @@ template <int N> __device__ __forceinline__ float lane_group_sum(float v) {
 }
 template <typename T, int MI, int NT>
 __device__ __forceinline__ void split_norm(unsigned a_at, unsigned g_at, int nkt, int K, float eps) {
-  constexpr int VEC = Elem<T>::VEC, TILE = 8 * VEC, BM = 32 * MI, TPR = NTHR / BM, TPT = TPR / 8;      // threads per row; K-tiles they take together
+  constexpr int VEC = Elem<T>::VEC, BM = 32 * MI, TPR = NTHR / BM, TPT = TPR / 8;      // threads per row; K-tiles they take together
   const int r = threadIdx.x / TPR, p0 = threadIdx.x & 7, t1 = (threadIdx.x % TPR) >> 3;
   const unsigned row = a_at + r * 128 + p0 * 16, sw = (unsigned)((r >> 1) & 7);
   const int c0 = t1 * 8 + (int)(p0 ^ sw);                  // this thread's chunk of the row; the next ones are 8 TPT further on
@@ -88,49 +88,31 @@ __device__ __forceinline__ void split_norm(unsigned a_at, unsigned g_at, int nkt
 #pragma unroll
   for (int t = 0; t < NT; ++t) v[t] = lds_read16(row + min(t * TPT + t1, nkt - 1) * BM * 128);
   wait_lds();
-  float mean, rstd;
-  if constexpr (sizeof(T) == 2) {
-    // sum and sum of squares by two-element dot products (exact products, fp32 sums): a bf16 row whose mean is so large
-    // against its spread that the difference below would lose digits has already lost them in its own rounding
-    const sp_bf16x2 one = {(__bf16)1.f, (__bf16)1.f};
-    float s2[2] = {0.f, 0.f}, q2[2] = {0.f, 0.f};
+  float sum = 0.f, sq = 0.f;
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      asm volatile("" : "+v"(v[t]));
-      const bool in = (c0 + t * 8 * TPT) * VEC < K;
+  for (int t = 0; t < NT; ++t) {
+    asm volatile("" : "+v"(v[t]));
+    const bool in = (c0 + t * 8 * TPT) * VEC < K;
+    float x[8], part = 0.f;
+    sp_unpack<T>(v[t], x);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const sp_bf16x2 x = __builtin_bit_cast(sp_bf16x2, in ? v[t][e] : 0u);
-        s2[e & 1] = __builtin_amdgcn_fdot2_f32_bf16(x, one, s2[e & 1], false);
-        q2[e & 1] = __builtin_amdgcn_fdot2_f32_bf16(x, x, q2[e & 1], false);
-      }
-    }
-    mean = lane_group_sum<TPR>(s2[0] + s2[1]) / (float)K;
-    rstd = rsqrtf(fmaxf(lane_group_sum<TPR>(q2[0] + q2[1]) / (float)K - mean * mean, 0.f) + eps);
-  } else {
-    float sum = 0.f, sq = 0.f;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      asm volatile("" : "+v"(v[t]));
-      const bool in = (c0 + t * 8 * TPT) * VEC < K;
-      float x[8], part = 0.f;
-      sp_unpack<T>(v[t], x);
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) part += x[e];
-      sum += in ? part : 0.f;
-    }
-    mean = lane_group_sum<TPR>(sum) / (float)K;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const bool in = (c0 + t * 8 * TPT) * VEC < K;
-      float x[8], part = 0.f;
-      sp_unpack<T>(v[t], x);
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) part += (x[e] - mean) * (x[e] - mean);
-      sq += in ? part : 0.f;
-    }
-    rstd = rsqrtf(lane_group_sum<TPR>(sq) / (float)K + eps);
+    for (int e = 0; e < VEC; ++e) part += x[e];
+    sum += in ? part : 0.f;
   }
+  const float mean = lane_group_sum<TPR>(sum) / (float)K;
+  // a second pass for the variance: the mean of the squares minus the square of the mean loses the variance of a row
+  // whose mean is large against its spread (768 elements of 100 and one of 100.5, all exact in bf16: nothing is left)
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    asm volatile("" : "+v"(v[t]));                         // (unpacked again: the fp32 values of all passes at once would spill)
+    const bool in = (c0 + t * 8 * TPT) * VEC < K;
+    float x[8], part = 0.f;
+    sp_unpack<T>(v[t], x);
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) part += (x[e] - mean) * (x[e] - mean);
+    sq += in ? part : 0.f;
+  }
+  const float rstd = rsqrtf(lane_group_sum<TPR>(sq) / (float)K + eps);
   const float shift = -mean * rstd;
 #pragma unroll
   for (int u0 = 0; u0 < NT; u0 += 4) {
@@ -145,7 +127,7 @@ __device__ __forceinline__ void split_norm(unsigned a_at, unsigned g_at, int nkt
     wait_lds();
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      asm volatile("" : "+v"(gv[u]), "+v"(bv[u]));
+      asm volatile("" : "+v"(gv[u]), "+v"(bv[u]), "+v"(v[u0 + u]));
       const int kt = (u0 + u) * TPT + t1;
       float x[8], g8[8], b8[8];
       sp_unpack<T>(v[u0 + u], x);

@@ -44,6 +44,25 @@ def test_split_linear(M, N, K, norm, act, res, dtype):
     assert err <= (2e-5 if dtype == torch.float32 else 1.2e-2) * max(1.0, want.abs().max().item()), err
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("M,K", [(31, 96), (97, 384), (65, 768), (49, 1024)])
+def test_split_linear_norm_of_rows_with_a_large_mean(M, K, dtype):
+    """Rows of 100 with a few elements one bf16 step (0.5) up: exact inputs whose variance, 3e-4 to 6e-2, is far below the
+    rounding of the square of their mean.  The result is the normalised row itself (W = the identity)."""
+    g = torch.Generator().manual_seed(K)
+    A = torch.full((M, K), 100.0)
+    for r in range(M):
+        A[r, torch.randperm(K, generator=g)[:1 + r % 16]] = 100.5
+    gam, bet = torch.ones(K), torch.zeros(K)
+    want = torch.nn.functional.layer_norm(A.double(), (K,), gam.double(), bet.double(), 1e-5)
+    got = sm.linear(A.to(dtype).cuda(), torch.eye(K, dtype=dtype).cuda(), norm=("layer", gam.to(dtype).cuda(), bet.to(dtype).cuda(), 1e-5))
+    # fp32 statistics: the mean (100, of fp32 sums) is off by up to 8 roundings of 2^-18 against a spread of 0.018 and more;
+    # bf16: the row rounded once for the product and its result once more, 2^-9 each
+    tol = (8 * 2.0 ** -18 / 0.018 if dtype == torch.float32 else 2.0 ** -8 + 8 * 2.0 ** -18 / 0.018)
+    err = ((got.double().cpu() - want).norm(dim=1) / want.norm(dim=1)).max().item()
+    assert err <= tol, err
+
+
 @pytest.mark.parametrize("B,H,C,depth", [
     (1, 14, 512, 3),       # 32-row tiles: one per XCD but one
     (3, 14, 512, 2),       # 64-row tiles, two per group for some
