@@ -288,27 +288,34 @@ int run_proj_mlp_fused(const sm_swin_cfg& c, const sm_swin_weights* wt, const vo
   }
   return mlp_checked(a, stream, "sm_swin_block(proj+mlp)");
 }
-// The same work cut over output columns (k_split.hip): x1 and the hidden activation stay in the window order of the
-// attention output, in x1 / hid of the workspace; counters: split_counter_ints(T) zeroed words.
+// The same work cut over output columns (k_split.hip): rows are taken in the window order of the attention output, x1 and
+// the hidden activation lie in x1 / hid of the workspace in token order, as the single kernels leave them; counters:
+// split_counter_ints(T) zeroed words.
 int run_split_tail(const sm_swin_cfg& c, const sm_swin_weights* wt, const void* attn_out, const void* x, void* y, void* x1, void* hid, int64_t T,
                    const RowProg& store, const NextNorm* next, void* next_out, int* counters, void* stream) {
   SplitArgs a; std::memset(&a, 0, sizeof(a));
-  const int C = c.C, Hd = c.mlp_ratio * C;
+  const int C = c.C, ratio = c.mlp_ratio, Hd = ratio * C;
   a.M = (int)T; a.n_ph = next ? 4 : 3;
   auto lin = [&](LinPhase& p, const void* A, const void* W, const void* bias, void* out, int N, int K) {
-    p.A = A; p.W = W; p.bias = bias; p.out = out; p.N = N; p.K = K; p.a_ld = K; p.o_ld = p.r_ld = N; p.o_mul = 1; p.eps = c.eps;
+    p.A = A; p.W = W; p.bias = bias; p.out = out; p.N = N; p.K = K; p.a_ld = K; p.o_ld = p.r_ld = N; p.a_mul = p.o_mul = 1; p.eps = c.eps;
   };
+  // rows of width mul * C at the token of the window-order row
+  auto from_tokens = [&](LinPhase& p, int mul) { p.a_tab = store.table; p.a_mul = mul; p.a_ld = mul * (int)store.ld; };
+  auto to_tokens = [&](LinPhase& p, int mul) { p.o_tab = store.table; p.o_mul = mul; p.o_ld = mul * (int)store.ld; };
+  auto res_tokens = [&](LinPhase& p, const void* res) { p.res = res; p.r_tab = store.table; p.r_ld = (int)store.ld; };
   lin(a.ph[0], attn_out, wt->wproj, wt->bproj, x1, C, C);
-  a.ph[0].res = x; a.ph[0].r_tab = store.table; if (!store.table) a.ph[0].r_ld = (int)store.ld;
+  res_tokens(a.ph[0], x); to_tokens(a.ph[0], 1);
   lin(a.ph[1], x1, wt->w1, wt->b1, hid, Hd, C);
   a.ph[1].ln_g = wt->ln2_g; a.ph[1].ln_b = wt->ln2_b; a.ph[1].act = SM_ACT_GELU;
+  from_tokens(a.ph[1], 1); to_tokens(a.ph[1], ratio);
   lin(a.ph[2], hid, wt->w2, wt->b2, y, C, Hd);
-  a.ph[2].res = x1; a.ph[2].ring = 1; a.ph[2].o_tab = store.table; if (!store.table) a.ph[2].o_ld = (int)store.ld;
+  a.ph[2].ring = 1;
+  from_tokens(a.ph[2], ratio); res_tokens(a.ph[2], x1); to_tokens(a.ph[2], 1);
   if (next) {
     lin(a.ph[3], y, next->wq, next->bq, next_out, 3 * C, C);
     a.ph[3].ln_g = next->gamma; a.ph[3].ln_b = next->beta;
-    a.ph[3].a_tab = store.table; if (!store.table) a.ph[3].a_ld = (int)store.ld;
-    a.ph[3].o_tab = next->store.table; a.ph[3].o_mul = 3; if (!next->store.table) a.ph[3].o_ld = 3 * (int)next->store.ld;
+    from_tokens(a.ph[3], 1);
+    a.ph[3].o_tab = next->store.table; a.ph[3].o_mul = 3; a.ph[3].o_ld = 3 * (int)next->store.ld;
   }
   char label[96];
   snprintf(label, sizeof(label), "split_proj+ln+mlp_bf16[%lld,%d,%d]%s", (long long)T, Hd, C, next ? "+ln+qkv" : "");

@@ -233,7 +233,7 @@ __device__ __forceinline__ void split_task(const SM_KARG LinPhase* p, int M, int
     wg_barrier();                                          // the tasks this one depends on have arrived
     asm volatile("buffer_inv sc0" ::: "memory");           // their results are in this XCD's L2: drop what this CU's L1 holds
   }
-  asrc = A + (p->a_tab ? (int64_t)araw : (int64_t)agr * p->a_ld);
+  asrc = A + (p->a_tab ? (int64_t)araw * p->a_mul : (int64_t)agr * p->a_ld);
   sp_u32x4 res[NPASS][VEC == 4 ? 2 : 1];
 #pragma unroll
   for (int q = 0; q < NPASS; ++q) {
@@ -569,7 +569,7 @@ bool launch_split_linear(const GemmArgs& g, void* stream, int* rc) {
   p.A = g.A; p.W = g.W; p.bias = g.bias; p.res = g.residual; p.out = g.C; p.N = g.N; p.K = g.K; p.act = g.act; p.ring = ring;
   if (g.norm) { p.ln_g = g.norm_gamma; p.ln_b = g.norm_beta; p.eps = g.norm_eps; }
   p.a_tab = g.a_rows.identity ? nullptr : g.a_rows.table; p.a_ld = (int)g.a_rows.ld;
-  p.o_tab = p.r_tab = g.c_rows.identity ? nullptr : g.c_rows.table; p.o_ld = p.r_ld = (int)g.c_rows.ld; p.o_mul = 1;
+  p.o_tab = p.r_tab = g.c_rows.identity ? nullptr : g.c_rows.table; p.o_ld = p.r_ld = (int)g.c_rows.ld; p.a_mul = p.o_mul = 1;
   *rc = launch_split_single(a, g.dtype, t.mi, t.wn, stream);
   return true;
 }

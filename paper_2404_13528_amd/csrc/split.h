@@ -11,8 +11,8 @@ struct LinPhase {
   const void *A, *W, *bias, *res; void* out;      // W row-major [N, K]; bias, res may be null
   const void *ln_g, *ln_b; float eps;             // ln_g != null: LayerNorm of A's rows over K first
   int act;                                        // SM_ACT_NONE or SM_ACT_GELU, before the residual
-  const int32_t *a_tab, *o_tab, *r_tab;           // row r of A at a_tab[r] (null: r * a_ld), of out at o_tab[r] * o_mul (r * o_ld), of res at r_tab[r] (r * r_ld)
-  int a_ld, o_ld, o_mul, r_ld;
+  const int32_t *a_tab, *o_tab, *r_tab;           // row r of A at a_tab[r] * a_mul (null: r * a_ld), of out at o_tab[r] * o_mul (r * o_ld), of res at r_tab[r] (r * r_ld)
+  int a_ld, a_mul, o_ld, o_mul, r_ld;
   int N, K;                                       // multiples of 8 and of 16
   int ring;                                       // 1: K-tiles through a ring of LDS stages (no LayerNorm), 0: whole panels resident
 };

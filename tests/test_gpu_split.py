@@ -84,6 +84,21 @@ def test_split_chain_matches_the_oracle(B, H, C, depth):
     assert sm.launch_counts() == (1 + 2 * depth, 0)      # LayerNorm + QKV, then attention and one chained launch per block
 
 
+@pytest.mark.parametrize("H,W,C,shift", [(14, 14, 192, 3), (7, 7, 768, 0), (14, 14, 1024, 3)])
+def test_intermediates_of_a_block_with_the_chained_tail(H, W, C, shift):
+    """Widths without a fused kernel: one kernel per operator or the chain leave x1 and the hidden activation in token order."""
+    h = C // 32
+    x, p = Wl.swin_block_case(1, H, W, C, h, 7, seed=C, bf16=True)
+    blk = sm.SwinBlock(1, H, W, C, h, 7, shift, dev_params(p, torch.bfloat16), torch.bfloat16, fuse_mlp=False)
+    y = blk(dev(x, torch.bfloat16))
+    torch.cuda.synchronize()
+    got = {k: to_np(v) for k, v in sm.swin_block_intermediates(blk).items()}
+    want = swin.swin_block(to_np(x), np_params(p), H, W, 7, h, shift, want_all=True)
+    for name in ("qkv", "o", "x1", "hid"):
+        assert_bf16_close(got[name], want[name], name)
+    assert_bf16_close(to_np(y), want["y"], "y", x=to_np(x))
+
+
 @pytest.mark.parametrize("M,N,K,act", [
     (70, 2112, 1088, "swiglu"),        # 64-row tiles, cut ends, the shortest long K
     (257, 5696, 1088, "swiglu"),       # 64- or 128-row tiles, more than one round of the smaller
