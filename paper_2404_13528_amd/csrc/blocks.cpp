@@ -222,23 +222,32 @@ bool mlp_is_fused(const sm_swin_cfg& c, const sm_swin_weights* wt) {
 bool proj_is_fused(const sm_swin_cfg& c, const sm_swin_weights* wt) {
   return wt->proj_packed && wt->mlp_packed && mlp_proj_supported(c.C, c.mlp_ratio * c.C, c.dtype);
 }
+bool there(const void* p) { return p && aligned16(p); }
 // Whether the block's tail is the chained launch of k_split.hip: where the caller packed the weights of the fused kernel
-// that it stands in for, or there is no such kernel for the width
+// that it stands in for, or there is no such kernel for the width, and all that the chain reads is there.  Where something is
+// missing or misaligned (the row-major matrices of a caller who only keeps the packed ones, an absent bias), the other forms
+// run or refuse the call as their kernels need it.
 bool tail_is_split(const sm_swin_cfg& c, const sm_swin_weights* wt) {
-  return split_tail_use(c, (int64_t)c.B * c.H * c.W) && (proj_is_fused(c, wt) || !mlp_fused_supported(c.C, c.mlp_ratio * c.C, c.dtype));
+  if (!split_tail_use(c, (int64_t)c.B * c.H * c.W) || !(proj_is_fused(c, wt) || !mlp_fused_supported(c.C, c.mlp_ratio * c.C, c.dtype))) return false;
+  return c.eps > 0.f && there(wt->wproj) && there(wt->bproj) && there(wt->ln2_g) && there(wt->ln2_b) && there(wt->w1) && there(wt->b1) &&
+         there(wt->w2) && there(wt->b2) && aligned16(wt->mlp_packed) && aligned16(wt->proj_packed);
 }
 // A caller who packed the fused kernels' weights, or a width without such kernels: norms may be folded wherever that is
 // faster (else the caller asked for one kernel per operator and fold_norm alone decides)
 bool free_form(const sm_swin_cfg& c, const sm_swin_weights* wt) { return proj_is_fused(c, wt) || !mlp_fused_supported(c.C, c.mlp_ratio * c.C, c.dtype); }
-bool split_norm_linear(const sm_swin_cfg& c, int n_cols) {
-  return split_linear_use(gemm_args(nullptr, nullptr, nullptr, nullptr, nullptr, (int64_t)c.B * c.H * c.W, n_cols, c.C, c.dtype, SM_ACT_NONE, nullptr, nullptr, c.eps > 0 ? &c : nullptr, &c, c.eps));
+bool split_norm_linear(const sm_swin_cfg& c, int n_cols, const void* gamma, const void* beta) {
+  return there(gamma) && there(beta) &&
+         split_linear_use(gemm_args(nullptr, nullptr, nullptr, nullptr, nullptr, (int64_t)c.B * c.H * c.W, n_cols, c.C, c.dtype, SM_ACT_NONE, nullptr, nullptr, c.eps > 0 ? gamma : nullptr, beta, c.eps));
 }
 // LayerNorm-1 + QKV: the packed-weight Linear, one Linear with the norm folded in, or two kernels.  The packed-weight
 // kernel owns rows: below 128 of its 32-row workgroups the others win (1568 x 1152 x 384: 20 us against 11)
 enum QkvForm { QKV_PACKED, QKV_FOLDED, QKV_TWO };
 QkvForm qkv_form(const sm_swin_cfg& c, const sm_swin_weights* wt) {
-  if (free_form(c, wt) && split_norm_linear(c, 3 * c.C)) return QKV_FOLDED;
-  if (wt->qkv_packed && lin32_supported(3 * c.C, c.C, c.dtype)) return free_form(c, wt) && (int64_t)c.B * c.H * c.W < 4096 ? QKV_FOLDED : QKV_PACKED;
+  const bool packed = wt->qkv_packed && lin32_supported(3 * c.C, c.C, c.dtype);
+  // (the packed form does without the row-major matrix, and refuses what it cannot do without)
+  if (packed && !(there(wt->wqkv) && aligned16(wt->qkv_packed) && there(wt->ln1_g) && there(wt->ln1_b) && c.eps > 0.f)) return QKV_PACKED;
+  if (free_form(c, wt) && split_norm_linear(c, 3 * c.C, wt->ln1_g, wt->ln1_b)) return QKV_FOLDED;
+  if (packed) return free_form(c, wt) && (int64_t)c.B * c.H * c.W < 4096 ? QKV_FOLDED : QKV_PACKED;
   return fold_norm(3 * c.C) ? QKV_FOLDED : QKV_TWO;
 }
 // Where the row at window-major position r of a block with shift c.shift goes in the window-major tensor of a block
@@ -312,6 +321,8 @@ int run_split_tail(const sm_swin_cfg& c, const sm_swin_weights* wt, const void* 
   a.ph[2].ring = 1;
   from_tokens(a.ph[2], ratio); res_tokens(a.ph[2], x1); to_tokens(a.ph[2], 1);
   if (next) {
+    if (!there(next->wq) || !there(next->gamma) || !there(next->beta) || !aligned16(next->bq))
+      return fail(SM_ERR_INVALID_ARG, "sm_swin_block: the next block's QKV needs 16-byte aligned weight, gamma and beta");
     lin(a.ph[3], y, next->wq, next->bq, next_out, 3 * C, C);
     a.ph[3].ln_g = next->gamma; a.ph[3].ln_b = next->beta;
     from_tokens(a.ph[3], 1);
@@ -443,7 +454,7 @@ int swin_block_impl(const sm_swin_cfg* c, const sm_swin_weights* wt, const void*
     if (next) return fail(SM_ERR_INVALID_ARG, "sm_swin_block: the next block's norm can only be emitted by the fused projection + MLP kernel");
     if ((rc = run_gemm(bufO, wt->wproj, wt->bproj, x, x1, T, C, C, dt, SM_ACT_NONE, nullptr, &proj_store, stream))) return rc;
     if (mlp_is_fused(*c, wt)) return run_mlp_fused(*c, wt, x1, y, T, stream);
-    if (fold_norm(c->mlp_ratio * C) || (free_form(*c, wt) && split_norm_linear(*c, c->mlp_ratio * C))) {
+    if (fold_norm(c->mlp_ratio * C) || (free_form(*c, wt) && split_norm_linear(*c, c->mlp_ratio * C, wt->ln2_g, wt->ln2_b))) {
       if ((rc = run_gemm(x1, wt->w1, wt->b1, nullptr, hid, T, c->mlp_ratio * C, C, dt, SM_ACT_GELU, nullptr, nullptr, stream, wt->ln2_g, wt->ln2_b, eps))) return rc;
     } else {
       if ((rc = run_norm(x1, wt->ln2_g, wt->ln2_b, bufA, T, C, eps, 0, dt, nullptr, 1, nullptr, stream))) return rc;

@@ -84,6 +84,48 @@ def test_split_chain_matches_the_oracle(B, H, C, depth):
     assert sm.launch_counts() == (1 + 2 * depth, 0)      # LayerNorm + QKV, then attention and one chained launch per block
 
 
+def _few_tokens_block(C, **kw):
+    x, p = Wl.swin_block_case(1, 14, 14, C, C // 32, 7, seed=C + 1, bf16=True)
+    blk = sm.SwinBlock(1, 14, 14, C, C // 32, 7, 3, dev_params(p, torch.bfloat16), torch.bfloat16, **kw)
+    return blk, dev(x, torch.bfloat16), to_np(x), np_params(p)
+
+
+@pytest.mark.parametrize("offset", [None, 8])
+@pytest.mark.parametrize("names", [("wqkv",), ("wproj",), ("w1", "w2"), ("wqkv", "wproj", "w1", "w2")])
+def test_row_major_weights_may_be_absent_where_packed_ones_are_given(names, offset):
+    """A caller who packed the weights need not keep the row-major matrices (absent, or at an address that no kernel may read)."""
+    blk, x, x_np, p = _few_tokens_block(512)
+    packed = sm.linear_pack(blk.params["wqkv"])
+    blk.w.qkv_packed = packed.data_ptr()
+    for n in names:
+        setattr(blk.w, n, None if offset is None else getattr(blk.w, n) + offset)
+    assert_bf16_close(blk(x), swin.swin_block(x_np, p, 14, 14, 7, 16, 3), "block", x=x_np)
+
+
+@pytest.mark.parametrize("names", [("bqkv",), ("bproj", "b2"), ("b1",), ("ln1_b",), ("ln2_b",)])
+def test_absent_biases_of_a_block_on_few_tokens(names):
+    """A width without a fused kernel: biases and norm shifts may be absent."""
+    blk, x, x_np, p = _few_tokens_block(768)
+    for n in names:
+        setattr(blk.w, n, None)
+        p[n] = 0 * p[n]
+    assert_bf16_close(blk(x), swin.swin_block(x_np, p, 14, 14, 7, 24, 3), "block", x=x_np)
+
+
+NEEDED = [(C, n) for C in (512, 768) for n in ("ln1_g", "ln2_g")] + [(768, n) for n in ("wqkv", "wproj", "w1", "w2")] + \
+    [(512, n) for n in ("ln2_b", "bproj", "b1", "b2")]
+
+
+@pytest.mark.parametrize("C,name,absent", [n + (a,) for n in NEEDED for a in (True, False)] +
+                         [(512, n, False) for n in ("mlp_packed", "proj_packed", "qkv_packed")])
+def test_missing_or_misaligned_weights_of_a_block_on_few_tokens_are_refused(C, name, absent):
+    blk, x, _, _ = _few_tokens_block(C)
+    setattr(blk.w, name, None if absent else getattr(blk.w, name) + 8)
+    with pytest.raises(sm.SmError, match="null pointer|aligned"):
+        blk(x)
+    torch.cuda.synchronize()
+
+
 @pytest.mark.parametrize("H,W,C,shift", [(14, 14, 192, 3), (7, 7, 768, 0), (14, 14, 1024, 3)])
 def test_intermediates_of_a_block_with_the_chained_tail(H, W, C, shift):
     """Widths without a fused kernel: one kernel per operator or the chain leave x1 and the hidden activation in token order."""
