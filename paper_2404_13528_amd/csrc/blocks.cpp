@@ -235,9 +235,10 @@ bool tail_is_split(const sm_swin_cfg& c, const sm_swin_weights* wt) {
 // A caller who packed the fused kernels' weights, or a width without such kernels: norms may be folded wherever that is
 // faster (else the caller asked for one kernel per operator and fold_norm alone decides)
 bool free_form(const sm_swin_cfg& c, const sm_swin_weights* wt) { return proj_is_fused(c, wt) || !mlp_fused_supported(c.C, c.mlp_ratio * c.C, c.dtype); }
+// (the separate norm kernel takes eps = 0, the folded one does not)
 bool split_norm_linear(const sm_swin_cfg& c, int n_cols, const void* gamma, const void* beta) {
-  return there(gamma) && there(beta) &&
-         split_linear_use(gemm_args(nullptr, nullptr, nullptr, nullptr, nullptr, (int64_t)c.B * c.H * c.W, n_cols, c.C, c.dtype, SM_ACT_NONE, nullptr, nullptr, c.eps > 0 ? gamma : nullptr, beta, c.eps));
+  return c.eps > 0.f && there(gamma) && there(beta) &&
+         split_linear_use(gemm_args(nullptr, nullptr, nullptr, nullptr, nullptr, (int64_t)c.B * c.H * c.W, n_cols, c.C, c.dtype, SM_ACT_NONE, nullptr, nullptr, gamma, beta, c.eps));
 }
 // LayerNorm-1 + QKV: the packed-weight Linear, one Linear with the norm folded in, or two kernels.  The packed-weight
 // kernel owns rows: below 128 of its 32-row workgroups the others win (1568 x 1152 x 384: 20 us against 11)

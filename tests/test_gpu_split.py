@@ -5,7 +5,7 @@ import pytest
 import torch
 from oracle import swin
 from paper_2404_13528_amd import binding as sm, workloads as Wl
-from util import assert_bf16_close, dev, dev_params, np_params, to_np
+from util import assert_bf16_close, assert_close, dev, dev_params, np_params, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -110,6 +110,25 @@ def test_absent_biases_of_a_block_on_few_tokens(names):
         setattr(blk.w, n, None)
         p[n] = 0 * p[n]
     assert_bf16_close(blk(x), swin.swin_block(x_np, p, 14, 14, 7, 24, 3), "block", x=x_np)
+
+
+@pytest.mark.parametrize("dtype,C", [(torch.float32, 192), (torch.bfloat16, 192), (torch.bfloat16, 768)])
+def test_blocks_with_eps_zero(dtype, C):
+    """The separate norm kernels take eps = 0 (here: every row has a spread)."""
+    h = C // 32
+    x, p = Wl.swin_block_case(1, 14, 14, C, h, 7, seed=C + 2, bf16=dtype == torch.bfloat16)
+    y = sm.SwinBlock(1, 14, 14, C, h, 7, 3, dev_params(p, dtype), dtype, eps=0.0)(dev(x, dtype))
+    want = swin.swin_block(to_np(x), np_params(p), 14, 14, 7, h, 3)      # eps 1e-5 beside variances of 1: 5e-6 of the norm's output
+    if dtype == torch.float32:
+        assert_close(y, want, dtype, "block")
+    else:
+        assert_bf16_close(y, want, "block", x=to_np(x))
+
+
+def test_eps_zero_is_refused_by_the_fused_kernels():
+    blk, x, _, _ = _few_tokens_block(512, eps=0.0)
+    with pytest.raises(sm.SmError, match="eps > 0"):
+        blk(x)
 
 
 NEEDED = [(C, n) for C in (512, 768) for n in ("ln1_g", "ln2_g")] + [(768, n) for n in ("wqkv", "wproj", "w1", "w2")] + \
