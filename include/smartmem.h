@@ -357,8 +357,9 @@ int sm_swin_block(const sm_swin_cfg*, const sm_swin_weights*, const void* x, voi
  * errors as sm_swin_block without ws / ws_bytes; a block that needs more than
  * the static buffer returns SM_ERR_WORKSPACE and launches nothing.  Calls no
  * allocating routine.  All calls on one GPU share the buffer: calls that overlap
- * on one GPU (two streams, two threads) race; calls in stream order do not, and
- * nothing in the buffer has to be cleared between them. */
+ * on one GPU (two streams, two threads) race (their results are undefined, and
+ * they may take seconds to end); calls in stream order do not, and nothing in
+ * the buffer has to be cleared between them. */
 #define SM_STATIC_WS_BYTES (32u << 20)
 size_t sm_swin_block_static_max_bytes(void);
 int sm_swin_block_static(const sm_swin_cfg*, const sm_swin_weights*, const void* x, void* y, int mode, void* stream);

@@ -23,6 +23,7 @@
 // of the same counter only, and a workgroup finishes its task before it waits for the next: the smallest unfinished
 // task of an XCD is always being worked on, so every wait ends whatever the number of resident workgroups and whatever
 // else shares the GPU.  Groups are claimed one after the other, so all of them run however the workgroups are spread.
+// split_order.h holds this order and what becomes of it when the counters are not what the launch left in them.
 #include <algorithm>
 #include <cstring>
 #include "device_common.h"
@@ -405,7 +406,14 @@ __device__ __forceinline__ int l2_add(int* p, int v) {
   return old;
 }
 
-// the chain: one more wave takes task numbers, waits for dependencies and reports arrivals
+struct L2Mem {
+  static __device__ __forceinline__ int take(int* p, int v) { return l2_add(p, v); }
+  static __device__ __forceinline__ int look(int* p) { return l2_add(p, 0); }
+  static __device__ __forceinline__ int take_device(int* p, int v) { return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+  static __device__ __forceinline__ void pause() { __builtin_amdgcn_s_sleep(1); }
+};
+
+// the chain: one more wave takes task numbers, waits for dependencies and reports arrivals (split_order.h)
 template <typename T, int MI, int WNL>
 __global__ __launch_bounds__(NTHR + 64) void split_chain_kernel(SplitArgs a) {
   const SM_KARG SplitArgs* g = kernarg_ptr<SplitArgs>();
@@ -415,26 +423,8 @@ __global__ __launch_bounds__(NTHR + 64) void split_chain_kernel(SplitArgs a) {
   const bool ctl = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == NW;
   const unsigned base = lds_offset(sp_smem);
   int* mine = g->counters + SPLIT_LINE * (1 + (__builtin_amdgcn_s_getreg((3 << 11) | 20) & 15));      // hwreg XCC_ID: this XCD's number counter and claims
-  // number n -> task k of the group that this XCD claimed for its gi-th run of numbers
-  int gi_known = -1, grp_known = 0;
-  auto resolve = [&](int n, int* to) {
-    const int gi = n / g->group_tasks, k = n - gi * g->group_tasks;
-    if (gi != gi_known) {
-      int* claim = mine + 1 + min(gi, SPLIT_LINE - 2);
-      int grp;
-      if (k == 0) {
-        grp = __hip_atomic_fetch_add(g->counters, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        l2_add(claim, grp + 1);
-      } else {
-        while ((grp = l2_add(claim, 0)) == 0) __builtin_amdgcn_s_sleep(1);      // number k = 0 of this group is with a running workgroup
-        --grp;
-      }
-      gi_known = gi; grp_known = grp;
-    }
-    to[0] = grp_known < g->n_groups ? k : -1;
-    to[1] = grp_known;
-  };
-  if (threadIdx.x == NTHR) resolve(l2_add(mine, 1), slot);
+  TaskOrder order{g->counters, mine, (unsigned)g->group_tasks, g->n_groups, SPLIT_SPINS, ~0u, 0, false};
+  if (threadIdx.x == NTHR) task_of<L2Mem>(order, (unsigned)l2_add(mine, 1), slot);
   wg_barrier();
   for (int it = 0;; ++it) {
     const int k = __builtin_amdgcn_readfirstlane(slot[2 * (it & 1)]), grp = __builtin_amdgcn_readfirstlane(slot[2 * (it & 1) + 1]);
@@ -444,16 +434,11 @@ __global__ __launch_bounds__(NTHR + 64) void split_chain_kernel(SplitArgs a) {
     const int rem = k - g->first[ph];
     const int ct = rem / g->group_rows, rl = rem - ct * g->group_rows, rt = grp * g->group_rows + rl;
     int* done = g->counters + SPLIT_LINE * 17 + grp * g->group_words + rl;
-    if (ctl && threadIdx.x == NTHR) {
-      if (ph) {
-        const int want = g->tiles_n[ph - 1];
-        while (l2_add(done + (ph - 1) * g->group_rows, 0) < want) __builtin_amdgcn_s_sleep(1);
-      }
-    }
+    if (ctl && threadIdx.x == NTHR && ph) wait_arrivals<L2Mem>(order, done + (ph - 1) * g->group_rows, g->tiles_n[ph - 1]);
     // the next number is asked for now and looked at when this task's results are on their way
     int n_next = 0;
     if (ctl && threadIdx.x == NTHR) n_next = __hip_atomic_fetch_add(mine, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    auto next = [&] { if (threadIdx.x == NTHR) resolve(n_next, slot + 2 * ((it + 1) & 1)); };
+    auto next = [&] { if (threadIdx.x == NTHR) task_of<L2Mem>(order, (unsigned)n_next, slot + 2 * ((it + 1) & 1)); };
     const SM_KARG LinPhase* p = &g->ph[ph];
     const int row0 = rt * 32 * MI;
     if (p->ln_g) split_task<T, MI, WNL, true, false, true>(p, g->M, row0, ct, ctl, g->lds_w, g->lds_g, base, sp_smem, next);

@@ -2,11 +2,11 @@
 #pragma once
 #include <cstdint>
 #include "index_map.h"
+#include "split_order.h"
 
 namespace sm {
 
 // Linears on few rows (k_split.hip), cut over output columns.  All offsets in elements.
-constexpr int SPLIT_LINE = 32;                    // words of a cache line
 struct LinPhase {
   const void *A, *W, *bias, *res; void* out;      // W row-major [N, K]; bias, res may be null
   const void *ln_g, *ln_b; float eps;             // ln_g != null: LayerNorm of A's rows over K first
