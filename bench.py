@@ -84,7 +84,7 @@ def kernel_model(label):
     m = re.match(r"concat_bf16\[(\d+),(\d+)\]", label)
     if m:      # Concat along the channels: [rows, C] written, its two halves read
         return 2 * int(m.group(1)) * int(m.group(2)) * e, 0.0
-    m = re.match(r"(?:ln\+|rms\+)?p?gemm_\w+\[(\d+),(\d+),(\d+)\](.*)", label)
+    m = re.match(r"(?:ln\+|rms\+)?(?:p|split)?gemm_\w+\[(\d+),(\d+),(\d+)\](.*)", label)
     if m:
         M, N, K = int(m.group(1)), int(m.group(2)), int(m.group(3))
         n_out = N // 2 if "+glu" in m.group(4) else N

@@ -546,13 +546,14 @@ int sm_timing_calibrate(int n, void* stream);
  * epilogue): every later sm_linear / executor launch of that shape in this process uses it.  A set-up call like
  * sm_linear_pack, and unlike the other entry points it creates events and SYNCHRONISES with the stream; C is
  * overwritten with the Linear's result.  *tile_rows = *stages = 0: the built-in choice won (a variant has to be 3 %
- * faster) or the shape has a single variant (fp32, K not a multiple of 64).  sm_linear_autotune_clear forgets all. */
+ * faster) or the shape has a single variant (fp32, K not a multiple of 64: nothing is timed; few rows, which the
+ * column-split kernel runs: its time is *best_us = *default_us).  sm_linear_autotune_clear forgets all. */
 int sm_linear_autotune(const sm_linear_desc*, const void* A, const void* W, const void* bias, const void* residual,
                        void* C, int iters, void* stream, int* tile_rows, int* stages, float* best_us, float* default_us);
 void sm_linear_autotune_clear(void);
 
-/* Tuning hook for benchmarks: overrides the tile and pipeline choice of the bf16 Linear kernel for the calling
- * process.  tile_rows: 0 (automatic), 64, 128 or 256 output rows per workgroup; stages: 0 (automatic) or 2..4
+/* Tuning hook for benchmarks: overrides the tile and pipeline choice of the tiled bf16 Linear kernel for the calling
+ * process (Linears on few rows run in the column-split kernel, which has no such choice: label "splitgemm_...").  tile_rows: 0 (automatic), 64, 128 or 256 output rows per workgroup; stages: 0 (automatic) or 2..4
  * K-tiles resident in LDS.  Returns SM_ERR_INVALID_ARG for other values.  Results do not depend on the choice. */
 int sm_gemm_tuning(int tile_rows, int stages);
 

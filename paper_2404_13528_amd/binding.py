@@ -563,7 +563,7 @@ class SwinChain:
 
 
 def gemm_tuning(tile_rows=0, stages=0):
-    """Overrides the bf16 Linear kernel's tile height (64 / 128 / 256) and LDS stage count (2..4); 0 = automatic."""
+    """Overrides the tiled bf16 Linear kernel's tile height (64 / 128 / 256) and LDS stage count (2..4); 0 = automatic."""
     check(lib().sm_gemm_tuning(int(tile_rows), int(stages)), "sm_gemm_tuning")
 
 

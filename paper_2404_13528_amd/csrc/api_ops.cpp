@@ -70,12 +70,11 @@ int gemm_checked(GemmArgs& g, void* stream, const char* who) {
     return fail(SM_ERR_INVALID_ARG, "%s: pointers must be 16-byte aligned", who);
   if ((int64_t)g.N * g.ldw > INT32_MAX * 16LL) return fail(SM_ERR_UNSUPPORTED, "%s: weight too large", who);
   char label[128];
-  snprintf(label, sizeof(label), "%sgemm_%s[%lld,%d,%d]%s%s%s", g.norm == 1 ? "ln+" : (g.norm == 2 ? "rms+" : ""), g.dtype == SM_F32 ? "f32" : "bf16", (long long)g.M, g.N, g.K,
+  snprintf(label, sizeof(label), "%s%sgemm_%s[%lld,%d,%d]%s%s%s", g.norm == 1 ? "ln+" : (g.norm == 2 ? "rms+" : ""), split_linear_use(g) ? "split" : "", g.dtype == SM_F32 ? "f32" : "bf16", (long long)g.M, g.N, g.K,
            g.act == SM_ACT_GELU ? "+gelu" : (g.act ? "+glu" : ""), g.residual ? "+res" : "", g.c_rows.identity ? "" : (g.C2 ? "+copy2" : "+scatter"));
   if (g.C2 && g.c_rows.identity) { const size_t n = strlen(label); snprintf(label + n, sizeof(label) - n, "+copy2"); }
   Timed tm(label, stream);
-  int rc = 0;
-  if (!launch_split_linear(g, stream, &rc)) rc = launch_gemm(g, stream);
+  int rc = launch_gemm(g, stream);
   if (rc) return fail(SM_ERR_DEVICE, "%s: launch failed (hip error %d)", who, rc);
   count_compute();
   return SM_OK;

@@ -26,6 +26,7 @@
 #include <type_traits>
 #include "device_common.h"
 #include "kernels.h"
+#include "split.h"
 
 namespace sm {
 
@@ -1007,6 +1008,8 @@ static int gemm_dispatch(const GemmArgs& g, const ColMap& cm, hipStream_t s) {
 
 int launch_gemm(const GemmArgs& g, void* stream) {
   if (g.M == 0 || g.N == 0) return 0;
+  int rc = 0;
+  if (launch_split_linear(g, stream, &rc)) return rc;      // few rows
   ColMap cm;
   cm.mode = 0; cm.half = g.N / 2; cm.rope_cols = g.rope_cols; cm.rope_dim = g.rope_dim;
   if (g.act == SM_ACT_SWIGLU || g.act == SM_ACT_GEGLU) cm.mode = 1;
@@ -1023,6 +1026,8 @@ int gemm_tuning(int tile_rows, int stages) {
 // The tuner (paper Sec. 3.3 "Other optimizations": an auto-tuner picks tiling and unrolling per kernel; here the
 // search space is small enough to be walked completely): every tile height x stage count the kernel has, timed on the
 // caller's operands with HIP events; the fastest is remembered for the shape.  0 in *rows / *stages = the built-in choice won.
+// A shape that the column-split kernel runs has that one variant: it is timed and nothing is remembered.  It cuts K over its
+// waves, so its sums differ from the tiled kernel's in their last bits, and a tile choice never changes a result.
 int gemm_autotune(const GemmArgs& g, int iters, void* stream, int* rows, int* stages, float* best_us, float* default_us) {
   if (!tunable(g)) return -2;
   hipStream_t s = (hipStream_t)stream;
@@ -1034,7 +1039,8 @@ int gemm_autotune(const GemmArgs& g, int iters, void* stream, int* rows, int* st
   Tune best{0, 0};
   float best_t = 1e30f, def_t = 0.f;
   int rc = 0;
-  for (int ri = 0; ri < 4 && rc == 0; ++ri) {
+  const int n_rows = split_linear_use(g) ? 1 : 4;
+  for (int ri = 0; ri < n_rows && rc == 0; ++ri) {
     for (int st = (ri == 0 ? 0 : 2); st <= (ri == 0 ? 0 : 4) && rc == 0; ++st) {
       const Tune tn{cand_rows[ri], st};
       if (tn.rows) { std::lock_guard<std::mutex> lock(g_tune_mu); g_tuned[tune_key(g)] = tn; }

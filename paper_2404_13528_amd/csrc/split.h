@@ -26,7 +26,7 @@ struct SplitArgs {
 bool split_rows_ok(const RowProg& r);             // the row program is a pitch or a table
 int launch_split_single(SplitArgs& a, int dtype, int mi, int wn, void* stream);      // tile 32 mi x 32 wn: (1, 1), (1, 2), (2, 2)
 struct GemmArgs;
-bool split_linear_use(const GemmArgs& g);                                       // whether the next call would run it
+bool split_linear_use(const GemmArgs& g);                                       // whether launch_gemm runs g in this form
 bool launch_split_linear(const GemmArgs& g, void* stream, int* rc);      // runs g as a single split Linear where that is the better form; false: not
 size_t split_counter_ints(int64_t M);             // counters of one chained launch, zero on entry
 int launch_split_chain(SplitArgs& a, int* counters, int mi, void* stream);           // bf16; rows in tiles of 32 mi

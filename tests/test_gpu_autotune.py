@@ -45,3 +45,43 @@ def test_autotune_shape_without_variants_and_bad_arguments():
     assert r["tile_rows"] == 0 and r["stages"] == 0
     with pytest.raises(sm.SmError):
         sm.linear_autotune(64, 64, 64, iters=0)
+
+
+def _labels(f):
+    sm.timing_enable(True)
+    try:
+        out = f()
+        torch.cuda.synchronize()
+        return out, sm.timing_sequence()
+    finally:
+        sm.timing_enable(False)
+
+
+@pytest.mark.parametrize("M,N,K,split", [(700, 384, 256, True), (3000, 384, 256, False), (1100, 1000, 128, False)])
+def test_a_tile_choice_never_changes_a_result(M, N, K, split):
+    """The column-split kernel has one variant, the tiled kernel's variants (ragged rows and columns among them) sum alike."""
+    g = torch.Generator().manual_seed(M)
+    A, W = torch.randn(M, K, generator=g).bfloat16(), (torch.randn(N, K, generator=g) * K ** -0.5).bfloat16()
+    b, R = (torch.randn(N, generator=g) * 0.1).bfloat16(), torch.randn(M, N, generator=g).bfloat16()
+    run = lambda: _labels(lambda: sm.linear(A.cuda(), W.cuda(), bias=b.cuda(), residual=R.cuda(), act="gelu"))
+    base, labels = run()
+    assert labels == ["%sgemm_bf16[%d,%d,%d]+gelu+res" % ("split" if split else "", M, N, K)]
+    assert_bf16_close(base, O.gelu(O.linear(to_np(A), to_np(W), to_np(b))) + to_np(R), "built-in choice")
+    try:
+        for rows in (64, 128, 256):
+            for stages in (2, 3, 4):
+                sm.gemm_tuning(rows, stages)
+                got, again = run()
+                assert again == labels and torch.equal(got, base), (rows, stages)
+    finally:
+        sm.gemm_tuning(0, 0)
+    try:
+        r = sm.linear_autotune(M, N, K, act="gelu", residual=True, iters=5)
+        assert 0 < r["best_us"] <= r["default_us"] * 1.0001
+        if split:
+            assert (r["tile_rows"], r["stages"], r["best_us"]) == (0, 0, r["default_us"])
+            assert sm.autotune_from_labels(labels, iters=2) == []
+        got, _ = run()
+        assert torch.equal(got, base)
+    finally:
+        sm.lib().sm_linear_autotune_clear()
