@@ -204,9 +204,12 @@ bool fold_norm(int n_cols) { return n_cols <= 512; }
 // (from 32-token tiles of the row-owning kernel alone to the chain at 6 blocks per stage, us per block: C = 512, 196 tokens
 // 101 / 35, 784 100 / 53, 1568 99 / 74, 3136 99 / 122; C = 384, 196 57 / 31, 784 55 / 46, 1568 55 / 58; C = 256, 784 34 / 31,
 // 1568 34 / 41; per-operator kernels at C = 1024, 49 tokens 121 / 73, 196 120 / 78, 392 117 / 128).  The row-owning kernel's
-// time does not depend on the rows until they fill the chip, and grows with C^2; the chain's grows with rows x C.
+// time does not depend on the rows until they fill the chip, and grows with C^2; the chain's grows with rows x C, from the
+// four hand-overs between its Linears on: below C = 256 the row-owning kernel is the faster one at any size (a whole block,
+// C = 128, 49 tokens: 25.1 / 20.0 us, 98: 25.3 / 20.4; C = 256, 49: 26.5 / 31.2).
 bool split_tail_use(const sm_swin_cfg& c, int64_t T) {
   if (c.dtype != SM_BF16 || c.C % 32 || c.C > 1024) return false;
+  if (c.C < 256 && mlp_fused_supported(c.C, c.mlp_ratio * c.C, c.dtype)) return false;
   return T <= (c.C <= 512 ? (int64_t)c.C * c.C / 112 : 256);
 }
 // rows per tile / 32: one row tile per XCD while 32-row tiles are that few

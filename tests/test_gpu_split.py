@@ -84,6 +84,30 @@ def test_split_chain_matches_the_oracle(B, H, C, depth):
     assert sm.launch_counts() == (1 + 2 * depth, 0)      # LayerNorm + QKV, then attention and one chained launch per block
 
 
+def _labels(f):
+    sm.timing_enable(True)
+    try:
+        f()
+        torch.cuda.synchronize()
+        return sm.timing_sequence()
+    finally:
+        sm.timing_enable(False)
+
+
+@pytest.mark.parametrize("C,T,chained", [(128, 49, False), (128, 98, False), (256, 49, True), (96, 49, True), (192, 98, True),
+                                         (256, 588, False), (384, 1274, True), (384, 1323, False), (512, 2303, True), (512, 2352, False),
+                                         (768, 245, True), (768, 294, False)])
+def test_which_blocks_run_the_chained_tail(C, T, chained):
+    x, p = Wl.swin_block_case(T // 49, 7, 7, C, C // 32, 7, seed=C, bf16=True, std=0.1)
+    blk = sm.SwinBlock(T // 49, 7, 7, C, C // 32, 7, 0, dev_params(p, torch.bfloat16), torch.bfloat16)
+    x = dev(x, torch.bfloat16)
+    y = []
+    labels = _labels(lambda: y.append(blk(x)))
+    assert any(l.startswith("split_proj+ln+mlp") for l in labels) == chained, labels
+    if T < 600:
+        assert_bf16_close(y[0], swin.swin_block(to_np(x), np_params(p), 7, 7, 7, C // 32, 0), "block", x=to_np(x))
+
+
 def _few_tokens_block(C, **kw):
     x, p = Wl.swin_block_case(1, 14, 14, C, C // 32, 7, seed=C + 1, bf16=True)
     blk = sm.SwinBlock(1, 14, 14, C, C // 32, 7, 3, dev_params(p, torch.bfloat16), torch.bfloat16, **kw)
