@@ -509,11 +509,12 @@ int launch_split_single(SplitArgs& a, int dtype, int mi, int wn, void* stream) {
 // about one round of workgroups on the 256 CUs.  Beyond that: bf16, the tiled kernel of k_gemm.hip with its lower traffic
 // per flop (from 256 tiles of 64 x 64 on, with a long K from 512; measured us, this form / the tiled one: 196 x 1536 x 512 + LN 5.8 / 12.2,
 // 3136 x 192 x 192 4.1 / 5.0, 50 x 768 x 3072 7.4 / 19.7, 64 x 4096 x 11008 32 / 142; but 784 x 1536 x 512 + LN 12.9 / 12.3,
-// 3136 x 768 x 192 9.6 / 6.5), except where LayerNorm of a wide row comes with it; fp32, whose matrix instructions
+// 3136 x 768 x 192 9.6 / 6.5); fp32, whose matrix instructions
 // are sixteen times slower so that a task is longer than its latencies, up to four rounds of 64 x 64 tiles
 // (3136 x 288 x 96 + LN 6.9 / 13.1, 784 x 384 x 1536 24 / 67, 12544 x 96 x 96 10.2 / 12.3, 50176 x 96 x 384 75 / 67).
+// Rows under LayerNorm whose panels of 64 rows or columns do not fit LDS (wide ones): wide_norm_split below.
 struct SplitTile { int mi, wn; };
-static SplitTile split_tile(int64_t M, int N, int K, int dtype, bool ln, bool ring) {
+static SplitTile split_tile(int64_t M, int N, int K, int dtype, bool ring) {
   const int64_t t11 = ((M + 31) / 32) * ((N + 31) / 32), t12 = ((M + 31) / 32) * ((N + 63) / 64), t22 = ((M + 63) / 64) * ((N + 63) / 64);
   if (t11 <= (ring && dtype == SM_F32 ? 320 : 256)) return {1, 1};
   if (!ring && t12 <= 256) return {1, 2};
@@ -524,25 +525,32 @@ static SplitTile split_tile(int64_t M, int N, int K, int dtype, bool ln, bool ri
   // 1500 x 768 x 3072 28 / 31.  Not with a third round (640 x 4096 x 11008 143 / 139), a shorter K (1500 x 1024 x 1024 14.3 / 14.0)
   // or more rows of a narrow result (2100 x 512 x 2048 22.8 / 22.4).
   if (dtype != SM_F32 && ring && K >= 2048 && M <= 2048 && t22 <= 512) return {2, 2};
-  if (dtype != SM_F32) return ln && K > 512 && t11 <= 700 ? SplitTile{1, 1} : SplitTile{0, 0};
+  if (dtype != SM_F32) return {0, 0};
   if (!ring && t12 <= 640 && K >= 384) return {1, 2};
   return t22 <= 1024 ? SplitTile{2, 2} : SplitTile{0, 0};
 }
+static bool split_fits(const SplitTile& t, int K, int es, bool ln, bool ring) {
+  size_t ab, wb, gb;
+  need(K, es, t.mi, t.wn, ln, ring, &ab, &wb, &gb);
+  return ab + wb + gb <= kLds && (!ln || (size_t)K * es <= (size_t)12 * 128 * (2 / t.mi));
+}
+// LayerNorm over a wide row in 32 x 32 tiles, one workgroup per CU: by rounds of 256 tiles against the tiled kernel with its
+// folded norm, whose time grows with K and hardly with the tiles.  Measured us, this form / the tiled one, bf16: K = 576, three
+// rounds (300 x 1728) 16.5 / 13.8; K = 768, 576 tiles (245 x 2304) 16.3 / 16.6, 600 (784 x 768) 17.0 / 16.5, 672 (196 x 3072)
+// 17.7 / 16.8; K = 896, three rounds (700 x 896) 17.9 / 18.4; K = 1024, two (500 x 1024) 13.2 / 20.3, three (196 x 3072) 19.0 / 20.8,
+// four (784 x 1024) 24.0 / 20.4.  fp32: K = 512, four (2560 x 320) 29.7 / 33.5, five (5760 x 192) 39.5 / 33.6; K = 288, seven
+// (1066 x 1536) 35.5 / 24.1.
+static bool wide_norm_split(int64_t t11, int K, int dtype) { return t11 <= (dtype == SM_F32 ? 1024 : (K > 768 ? 768 : (K == 768 ? 576 : 512))); }
 static bool split_linear_plan(const GemmArgs& g, SplitTile* t, bool* ring) {
   const int es = g.dtype == SM_F32 ? 4 : 2, vec = 16 / es;
   if (g.a_gran > 0 || g.rope_cols || g.c_transposed || g.c_cols_on || g.C2 || g.norm == 2 || (g.act != SM_ACT_NONE && g.act != SM_ACT_GELU)) return false;
   if (g.M > INT32_MAX / 2 || g.ldw != g.K || g.K % (2 * vec) || g.N % 8 || g.N < 8 || !split_rows_ok(g.a_rows) || !split_rows_ok(g.c_rows) || g.c_rows.ld % vec || g.a_rows.ld % vec) return false;
   if (g.norm && !g.norm_beta) return false;
   *ring = !g.norm && (size_t)g.K * es > 1024;
-  *t = split_tile(g.M, g.N, g.K, g.dtype, g.norm != 0, *ring);
-  if (!t->mi) return false;
-  for (int pass = 0; pass < 2; ++pass) {
-    size_t ab, wb, gb;
-    need(g.K, es, t->mi, t->wn, g.norm != 0, *ring, &ab, &wb, &gb);
-    if (ab + wb + gb <= kLds && (!g.norm || (size_t)g.K * es <= (size_t)12 * 128 * (2 / t->mi))) return true;
-    *t = SplitTile{1, 1};                                  // a wide row under LayerNorm: the narrowest panels
-  }
-  return false;
+  *t = split_tile(g.M, g.N, g.K, g.dtype, *ring);
+  if (t->mi && split_fits(*t, g.K, es, g.norm != 0, *ring)) return true;
+  *t = SplitTile{1, 1};
+  return g.norm && split_fits(*t, g.K, es, true, false) && wide_norm_split(((g.M + 31) / 32) * ((g.N + 31) / 32), g.K, g.dtype);
 }
 bool split_linear_use(const GemmArgs& g) { SplitTile t; bool ring; return split_linear_plan(g, &t, &ring); }
 bool launch_split_linear(const GemmArgs& g, void* stream, int* rc) {

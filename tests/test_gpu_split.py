@@ -108,6 +108,36 @@ def test_which_blocks_run_the_chained_tail(C, T, chained):
         assert_bf16_close(y[0], swin.swin_block(to_np(x), np_params(p), 7, 7, 7, C // 32, 0), "block", x=to_np(x))
 
 
+BF16, F32 = torch.bfloat16, torch.float32
+
+
+@pytest.mark.parametrize("M,N,K,dtype,norm,split", [
+    (500, 1024, 1024, BF16, True, True),         # LayerNorm over a wide row: two rounds of 32 x 32 tiles
+    (245, 2304, 768, BF16, True, True),          # a little more
+    (300, 3072, 768, BF16, True, False),
+    (300, 1728, 576, BF16, True, False),
+    (196, 3072, 1024, BF16, True, True),         # three rounds over a wider one
+    (784, 1024, 1024, BF16, True, False),
+    (2560, 320, 512, F32, True, True),           # fp32: four
+    (1066, 1536, 288, F32, True, False),
+    (196, 1536, 512, BF16, True, True),          # rows that fit
+    (784, 1536, 512, BF16, True, False),
+])
+def test_which_linears_are_split(M, N, K, dtype, norm, split):
+    g = torch.Generator().manual_seed(M + K)
+    A, W = torch.randn(M, K, generator=g).to(dtype), (torch.randn(N, K, generator=g) * K ** -0.5).to(dtype)
+    x, nm = A.double(), None
+    if norm:
+        nm = ("layer", torch.ones(K, dtype=dtype).cuda(), torch.zeros(K, dtype=dtype).cuda(), 1e-5)
+        x = torch.nn.functional.layer_norm(x, (K,), eps=1e-5).to(dtype).double()
+    got = []
+    labels = _labels(lambda: got.append(sm.linear(A.cuda(), W.cuda(), norm=nm)))
+    assert labels[0].startswith("%s%sgemm_" % ("ln+" if norm else "", "split" if split else "")), labels
+    want = x @ W.double().t()
+    err = (got[0].double().cpu() - want).norm().item() / want.norm().item()
+    assert err <= (2e-6 if dtype == F32 else 4e-3), err      # fp32 sums of K products; bf16: the result rounded once, 2^-9, and a few flips of the normalised row
+
+
 def _few_tokens_block(C, **kw):
     x, p = Wl.swin_block_case(1, 14, 14, C, C // 32, 7, seed=C + 1, bf16=True)
     blk = sm.SwinBlock(1, 14, 14, C, C // 32, 7, 3, dev_params(p, torch.bfloat16), torch.bfloat16, **kw)
