@@ -510,8 +510,13 @@ int launch_split_single(SplitArgs& a, int dtype, int mi, int wn, void* stream) {
 // per flop (from 256 tiles of 64 x 64 on, with a long K from 512; measured us, this form / the tiled one: 196 x 1536 x 512 + LN 5.8 / 12.2,
 // 3136 x 192 x 192 4.1 / 5.0, 50 x 768 x 3072 7.4 / 19.7, 64 x 4096 x 11008 32 / 142; but 784 x 1536 x 512 + LN 12.9 / 12.3,
 // 3136 x 768 x 192 9.6 / 6.5); fp32, whose matrix instructions
-// are sixteen times slower so that a task is longer than its latencies, up to four rounds of 64 x 64 tiles
-// (3136 x 288 x 96 + LN 6.9 / 13.1, 784 x 384 x 1536 24 / 67, 12544 x 96 x 96 10.2 / 12.3, 50176 x 96 x 384 75 / 67).
+// are sixteen times slower so that a task is longer than its latencies, up to three rounds of 64 x 64 tiles
+// (3136 x 288 x 96 + LN 6.9 / 13.1, 784 x 384 x 1536 24 / 67, 12544 x 96 x 96 10.2 / 12.3, 3466 x 768 x 1536 97 / 112, 23466 x 96 x 96 + LN
+// 17.6 / 18.7), a fourth only where the tiled kernel's 128 columns are half empty (57600 x 32 x 3072 244 / 399, but 6400 x 512 x 768
+// 70 / 62, 2133 x 1536 x 1536 127 / 112, 50176 x 96 x 384 75 / 67).  Narrower tiles while the grid is one round: with a ring up to 320
+// (620 x 512 x 288 8.8, against 9.3 in 64 x 64 tiles; 540 of them, 1440 x 384 x 384, 13.4 against 10.8); under LayerNorm from K = 384 on,
+// whose 64-row panels do not fit, up to two and a half rounds of 32 x 64 (3306 x 384 x 384 + LN 26 / 29, 1546 x 768 x 384 + LN 23.6 / 27.6;
+// 2311 x 1152 x 384 + LN, five rounds, 46.4 / 44.5).
 // Rows under LayerNorm whose panels of 64 rows or columns do not fit LDS (wide ones): wide_norm_split below.
 struct SplitTile { int mi, wn; };
 static SplitTile split_tile(int64_t M, int N, int K, int dtype, bool ring) {
@@ -527,7 +532,7 @@ static SplitTile split_tile(int64_t M, int N, int K, int dtype, bool ring) {
   if (dtype != SM_F32 && ring && K >= 2048 && M <= 2048 && t22 <= 512) return {2, 2};
   if (dtype != SM_F32) return {0, 0};
   if (!ring && t12 <= 640 && K >= 384) return {1, 2};
-  return t22 <= 1024 ? SplitTile{2, 2} : SplitTile{0, 0};
+  return t22 <= (N <= 64 ? 1024 : 768) ? SplitTile{2, 2} : SplitTile{0, 0};
 }
 static bool split_fits(const SplitTile& t, int K, int es, bool ln, bool ring) {
   size_t ab, wb, gb;

@@ -120,6 +120,10 @@ BF16, F32 = torch.bfloat16, torch.float32
     (784, 1024, 1024, BF16, True, False),
     (2560, 320, 512, F32, True, True),           # fp32: four
     (1066, 1536, 288, F32, True, False),
+    (3072, 960, 192, F32, False, True),          # fp32: three rounds of 64 x 64 tiles
+    (6400, 512, 768, F32, False, False),
+    (57600, 32, 192, F32, False, True),          # a narrow result: four
+    (66000, 32, 192, F32, False, False),
     (196, 1536, 512, BF16, True, True),          # rows that fit
     (784, 1536, 512, BF16, True, False),
 ])
