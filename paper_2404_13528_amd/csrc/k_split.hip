@@ -507,9 +507,9 @@ int launch_split_single(SplitArgs& a, int dtype, int mi, int wn, void* stream) {
 
 // Which Linears run in this form, and in which tile (32 mi x 32 wn; mi = 0: none).  The smallest tile whose grid is
 // about one round of workgroups on the 256 CUs.  Beyond that: bf16, the tiled kernel of k_gemm.hip with its lower traffic
-// per flop (from 256 tiles of 64 x 64 on, with a long K from 512; measured us, this form / the tiled one: 196 x 1536 x 512 + LN 5.8 / 12.2,
+// per flop (from 256 tiles of 64 x 64 on; measured us, this form / the tiled one: 196 x 1536 x 512 + LN 5.8 / 12.2,
 // 3136 x 192 x 192 4.1 / 5.0, 50 x 768 x 3072 7.4 / 19.7, 64 x 4096 x 11008 32 / 142; but 784 x 1536 x 512 + LN 12.9 / 12.3,
-// 3136 x 768 x 192 9.6 / 6.5); fp32, whose matrix instructions
+// 3136 x 768 x 192 9.6 / 6.5; long K, a second round: 333 x 4096 x 11008 76 / 53, 500 x 4096 x 4096 34 / 25, 342 x 3072 x 2048 19 / 12); fp32, whose matrix instructions
 // are sixteen times slower so that a task is longer than its latencies, up to three rounds of 64 x 64 tiles
 // (3136 x 288 x 96 + LN 6.9 / 13.1, 784 x 384 x 1536 24 / 67, 12544 x 96 x 96 10.2 / 12.3, 3466 x 768 x 1536 97 / 112, 23466 x 96 x 96 + LN
 // 17.6 / 18.7), a fourth only where the tiled kernel's 128 columns are half empty (57600 x 32 x 3072 244 / 399, but 6400 x 512 x 768
@@ -524,12 +524,6 @@ static SplitTile split_tile(int64_t M, int N, int K, int dtype, bool ring) {
   if (t11 <= (ring && dtype == SM_F32 ? 320 : 256)) return {1, 1};
   if (!ring && t12 <= 256) return {1, 2};
   if (t22 <= 256) return {2, 2};
-  // bf16, long K: two rounds of 64 x 64 tiles still beat one of the tiled kernel, whose workgroups (four waves, two K-tiles
-  // in flight) cost the same time per K step however few of them there are.  Measured us, this form / the tiled one:
-  // 333 x 4096 x 11008 87 / 137, 500 x 4096 x 4096 40 / 55, 1000 x 2048 x 5632 53 / 73, 640 x 2048 x 2048 20.2 / 22.6,
-  // 1500 x 768 x 3072 28 / 31.  Not with a third round (640 x 4096 x 11008 143 / 139), a shorter K (1500 x 1024 x 1024 14.3 / 14.0)
-  // or more rows of a narrow result (2100 x 512 x 2048 22.8 / 22.4).
-  if (dtype != SM_F32 && ring && K >= 2048 && M <= 2048 && t22 <= 512) return {2, 2};
   if (dtype != SM_F32) return {0, 0};
   if (!ring && t12 <= 640 && K >= 384) return {1, 2};
   return t22 <= (N <= 64 ? 1024 : 768) ? SplitTile{2, 2} : SplitTile{0, 0};

@@ -20,7 +20,7 @@ pytestmark = pytest.mark.gpu
     (196, 512, 2048, False, "none", True),       # ring, four and more stages
     (500, 520, 320, True, "none", True),         # 64-row tiles, both ends cut
     (97, 128, 384, True, "none", True),
-    (257, 4104, 2064, False, "none", True),      # a second round of 64-row tiles (a long K), all ends cut
+    (257, 4104, 2064, False, "none", True),      # more 64-row tiles than CUs, a long K, all ends cut
 ])
 def test_split_linear(M, N, K, norm, act, res, dtype):
     g = torch.Generator().manual_seed(M + N + K)
@@ -120,6 +120,9 @@ BF16, F32 = torch.bfloat16, torch.float32
     (784, 1024, 1024, BF16, True, False),
     (2560, 320, 512, F32, True, True),           # fp32: four
     (1066, 1536, 288, F32, True, False),
+    (256, 4096, 4096, BF16, False, True),        # one round of 64 x 64 tiles, more
+    (257, 4096, 4096, BF16, False, False),
+    (500, 4096, 4096, BF16, False, False),
     (3072, 960, 192, F32, False, True),          # fp32: three rounds of 64 x 64 tiles
     (6400, 512, 768, F32, False, False),
     (57600, 32, 192, F32, False, True),          # a narrow result: four
