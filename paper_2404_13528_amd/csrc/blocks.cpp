@@ -243,15 +243,19 @@ bool split_norm_linear(const sm_swin_cfg& c, int n_cols, const void* gamma, cons
   return c.eps > 0.f && there(gamma) && there(beta) &&
          split_linear_use(gemm_args(nullptr, nullptr, nullptr, nullptr, nullptr, (int64_t)c.B * c.H * c.W, n_cols, c.C, c.dtype, SM_ACT_NONE, nullptr, nullptr, gamma, beta, c.eps));
 }
-// LayerNorm-1 + QKV: the packed-weight Linear, one Linear with the norm folded in, or two kernels.  The packed-weight
-// kernel owns rows: below 128 of its 32-row workgroups the others win (1568 x 1152 x 384: 20 us against 11)
+// LayerNorm-1 + QKV: the packed-weight Linear, one Linear with the norm folded in, or two kernels.  The packed-weight kernel
+// owns rows: its time is a workgroup's weight stream, which grows with C^2, until the rows fill the chip; the folded Linear's
+// grows with the 64 x 128 tiles a CU runs side by side, and is the shorter one up to C / 128 - 1 of them (whole blocks, us, folded /
+// packed: C = 512, 3920 tokens 111.9 / 113.4; C = 384, 3528 66.8 / 68.8, 3724 74.8 / 68.7; C = 256, 2548 38.9 / 38.9, 2940 41.2 / 40.1;
+// C = 128, 2744 27.2 / 26.2; as a split Linear also C = 128, 2352 25.7 / 26.1).
 enum QkvForm { QKV_PACKED, QKV_FOLDED, QKV_TWO };
 QkvForm qkv_form(const sm_swin_cfg& c, const sm_swin_weights* wt) {
   const bool packed = wt->qkv_packed && lin32_supported(3 * c.C, c.C, c.dtype);
   // (the packed form does without the row-major matrix, and refuses what it cannot do without)
   if (packed && !(there(wt->wqkv) && aligned16(wt->qkv_packed) && there(wt->ln1_g) && there(wt->ln1_b) && c.eps > 0.f)) return QKV_PACKED;
   if (free_form(c, wt) && split_norm_linear(c, 3 * c.C, wt->ln1_g, wt->ln1_b)) return QKV_FOLDED;
-  if (packed) return free_form(c, wt) && (int64_t)c.B * c.H * c.W < 4096 ? QKV_FOLDED : QKV_PACKED;
+  const int64_t tiles = (((int64_t)c.B * c.H * c.W + 63) / 64) * ((3 * (int64_t)c.C + 127) / 128);
+  if (packed) return free_form(c, wt) && tiles <= 256 * (c.C / 128 - 1) ? QKV_FOLDED : QKV_PACKED;
   return fold_norm(3 * c.C) ? QKV_FOLDED : QKV_TWO;
 }
 // Where the row at window-major position r of a block with shift c.shift goes in the window-major tensor of a block

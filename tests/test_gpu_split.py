@@ -145,6 +145,20 @@ def test_which_linears_are_split(M, N, K, dtype, norm, split):
     assert err <= (2e-6 if dtype == F32 else 4e-3), err      # fp32 sums of K products; bf16: the result rounded once, 2^-9, and a few flips of the normalised row
 
 
+@pytest.mark.parametrize("C,T,form", [(128, 2352, "ln+splitgemm"), (128, 2744, "ln+pgemm"), (256, 2548, "ln+gemm"), (256, 2940, "ln+pgemm"),
+                                      (384, 3528, "ln+gemm"), (384, 3724, "ln+pgemm"), (512, 784, "ln+gemm")])
+def test_which_form_the_first_qkv_has(C, T, form):
+    x, p = Wl.swin_block_case(T // 49, 7, 7, C, C // 32, 7, seed=C, bf16=True, std=0.1)
+    p, x = dev_params(p, torch.bfloat16), dev(x, torch.bfloat16)
+    blk = sm.SwinBlock(T // 49, 7, 7, C, C // 32, 7, 0, p, torch.bfloat16)
+    labels = _labels(lambda: blk(x))
+    assert any(l.startswith("%s_bf16[%d,%d,%d]" % (form, T, 3 * C, C)) for l in labels), labels
+    # a 7 x 7 grid: the windows are the tokens' order
+    want = sm.linear(x, p["wqkv"], p["bqkv"], norm=("layer", p["ln1_g"], p["ln1_b"], 1e-5))
+    got = sm.swin_block_intermediates(blk)["qkv"].reshape(T, 3 * C)
+    assert (got.float() - want.reshape(T, 3 * C).float()).norm() <= 4e-3 * want.float().norm()      # bf16: rounded once each
+
+
 def _few_tokens_block(C, **kw):
     x, p = Wl.swin_block_case(1, 14, 14, C, C // 32, 7, seed=C + 1, bf16=True)
     blk = sm.SwinBlock(1, 14, 14, C, C // 32, 7, 3, dev_params(p, torch.bfloat16), torch.bfloat16, **kw)
