@@ -961,22 +961,40 @@ static TuneKey tune_key(const GemmArgs& g) {
 static bool tunable(const GemmArgs& g) { return g.dtype == SM_BF16 && g.K % 64 == 0 && g.a_gran == 0 && !g.norm; }
 
 // Tile height and stages of a bf16 Linear with a long K (more than 16 K-tiles): rounds of residency times what a round
-// costs, in us at K = 4096 with the weights coming from memory (all scale with K).  A CU holds one 256-row workgroup, one
-// 128-row workgroup with three stages or two with two, two 64-row workgroups with three stages (counted in rounds of
-// 256, half a residency) or three with two.  Measured us, with the earlier choice (two stages, rounds of the 64- and
-// 128-row tiles alone) / with this one: 333 x 12288 x 4096 67 / 57, 200 x 12288 x 4096 61 / 42, 700 x 11264 x 2048 56 / 51,
-// 1100 x 12288 x 4096 169 / 121, 3152 x 768 x 3072 33 / 26, 1000 x 4096 x 11008 148 / 109.
+// costs.  A CU holds one 256-row workgroup, one 128-row workgroup with three stages or two with two, two 64-row workgroups
+// with three stages or three with two.
+// From 64 K-tiles on: us at K = 4096 with the weights coming from memory (all scale with K); the 64-row tile with three stages
+// in rounds of 256, half a residency.  Measured us, with the earlier choice (two stages, rounds of the 64- and 128-row tiles
+// alone) / with this one: 333 x 12288 x 4096 67 / 57, 200 x 12288 x 4096 61 / 42, 1100 x 12288 x 4096 169 / 121,
+// 1000 x 4096 x 11008 148 / 109.
+// Below: a workgroup's fixed part counts as well, and a round that is not full costs less: us per round and per K-tile with one,
+// two and three workgroups on a CU, fitted to 177 shapes with K = 1088 .. 2048 and weights in the memory-side cache (over 223 with
+// K up to 3072 the choice is within 1 % of the best variant on average, the earlier one 14 to 35 % behind).  Earlier choice /
+// costs that scale with K / these: 1652 x 5120 x 1152 32.0 / 36.6 / 32.0, 1500 x 6144 x 1600 41.0 / 47.1 / 41.0,
+// 772 x 12288 x 2048 55.4 / 61.9 / 54.6, 963 x 1536 x 1536 12.3 / 10.3 / 10.3, 1059 x 3072 x 1536 18.7 / 16.9 / 16.9,
+// 1238 x 11264 x 1536 59.3 / 49.9 / 49.9; not met: the second 64-row workgroup on a few CUs (650 x 3072 x 1536 13.8 / 15.1 / 15.1, but
+// 347 x 5632 x 1280 15.7 / 13.3 / 13.3).
 static Tune long_k_tile(const GemmArgs& g) {
   const int64_t tcols = (g.N + 127) / 128;
-  auto rounds = [&](int rows, int resident) { return (double)((((g.M + rows - 1) / rows) * tcols + resident - 1) / resident); };
-  const struct { Tune t; double cost; } form[] = {{{64, 3}, 27. * rounds(64, 256)},
-                                                  {{128, 3}, 41. * rounds(128, 256)},
-                                                  {{256, 3}, 60. * rounds(256, 256)},
-                                                  {{128, 2}, 70. * rounds(128, 512)},
-                                                  {{64, 2}, 76. * rounds(64, 768)}};
+  auto tiles = [&](int rows) { return ((g.M + rows - 1) / rows) * tcols; };
+  auto rounds = [&](int rows, int resident) { return (double)((tiles(rows) + resident - 1) / resident); };
+  const struct { Tune t; double fixed, step[3]; int per_cu; } form[] = {{{64, 3}, 2.7, {.33, .57, 0}, 2},
+                                                                        {{128, 3}, 4.2, {.46, 0, 0}, 1},
+                                                                        {{256, 3}, 6.4, {.69, 0, 0}, 1},
+                                                                        {{128, 2}, 1.7, {.64, 1.06, 0}, 2},
+                                                                        {{64, 2}, .4, {.55, .71, 1.06}, 3}};
+  const double at_4096[] = {27. * rounds(64, 256), 41. * rounds(128, 256), 60. * rounds(256, 256), 70. * rounds(128, 512), 76. * rounds(64, 768)};
   int best = 0;
-  for (int i = 1; i < 5; ++i)
-    if (form[i].cost < form[best].cost) best = i;
+  double least = 0;
+  for (int i = 0; i < 5; ++i) {
+    double cost = at_4096[i];
+    if (g.K < 64 * 64) {
+      const int64_t t = tiles(form[i].t.rows), round = 256 * form[i].per_cu, full = t / round, rest = t % round;
+      const double nk = (double)(g.K / 64);
+      cost = (double)full * (form[i].fixed + nk * form[i].step[form[i].per_cu - 1]) + (rest ? form[i].fixed + nk * form[i].step[(rest + 255) / 256 - 1] : 0.);
+    }
+    if (i == 0 || cost < least) { best = i; least = cost; }
+  }
   return form[best].t;
 }
 

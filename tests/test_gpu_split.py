@@ -240,6 +240,9 @@ def test_intermediates_of_a_block_with_the_chained_tail(H, W, C, shift):
     (257, 5696, 1088, "swiglu"),       # 64- or 128-row tiles, more than one round of the smaller
     (520, 22016, 1088, "swiglu"),      # several rounds
     (1025, 6152, 1152, "none"),        # 256-row tiles, a cut row tile
+    (1652, 5120, 1152, "none"),        # 64-row tiles, two stages
+    (1059, 3080, 1536, "none"),        # 128-row tiles, three stages
+    (2300, 576, 1984, "swiglu"),       # 64-row tiles, three stages
 ])
 def test_long_k_tiles(M, N, K, act):
     g = torch.Generator().manual_seed(M + N)
