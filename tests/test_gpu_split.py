@@ -145,6 +145,50 @@ def test_which_linears_are_split(M, N, K, dtype, norm, split):
     assert err <= (2e-6 if dtype == F32 else 4e-3), err      # fp32 sums of K products; bf16: the result rounded once, 2^-9, and a few flips of the normalised row
 
 
+@pytest.mark.parametrize("C,ratio,B,H", [(160, 3, 1, 14), (96, 4, 1, 7), (512, 3, 1, 14), (384, 2, 1, 14), (384, 6, 3, 14), (640, 1, 1, 14), (1024, 5, 5, 7)])
+def test_a_block_alone_with_the_chained_tail(C, ratio, B, H):
+    """sm_swin_block's own use of the chain, widths and MLP widths around the usual ones: against the oracle, on the static
+    workspace, in place, replayed from a graph; the same bits every time."""
+    h, shift = C // 32, 3 if H > 7 else 0
+    x, p = Wl.swin_block_case(B, H, H, C, h, 7, seed=C + ratio, bf16=True, std=0.1)
+    g = torch.Generator().manual_seed(C)
+    p = dict(p, w1=(0.1 * torch.randn(ratio * C, C, generator=g)).bfloat16().to(p["w1"].dtype), b1=(0.1 * torch.randn(ratio * C, generator=g)).bfloat16().to(p["b1"].dtype),
+             w2=(0.1 * torch.randn(C, ratio * C, generator=g)).bfloat16().to(p["w2"].dtype))
+    blk = sm.SwinBlock(B, H, H, C, h, 7, shift, dev_params(p, torch.bfloat16), torch.bfloat16, mlp_ratio=ratio)
+    xd, got = dev(x, torch.bfloat16), []
+    labels = _labels(lambda: got.append(blk(xd)))
+    assert any(l.startswith("split_proj+ln+mlp") for l in labels), labels
+    assert_bf16_close(got[0], swin.swin_block(to_np(x), np_params(p), H, H, 7, h, shift), "block", x=to_np(x))
+    assert torch.equal(sm.swin_block_static(blk, xd), got[0])
+    static, out = xd.clone(), torch.empty_like(xd)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        blk(static, out=out)
+    for i in range(3):
+        x2 = xd if i != 1 else -xd
+        static.copy_(x2)
+        graph.replay()
+        torch.cuda.synchronize()
+        want = blk(x2)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        assert i == 1 or torch.equal(want, got[0])
+    assert torch.equal(blk(xd, out=xd), got[0])          # in place
+
+
+@pytest.mark.parametrize("B,H,C", [(1, 28, 256), (12, 14, 512)])
+def test_row_owning_tail_above_the_chain(B, H, C):
+    """The projection + MLP + next LayerNorm + QKV kernels of 32 and 64 tokens, at the first batch above the chain's sizes."""
+    h = C // 32
+    x, blocks = Wl.swin_stage_case(B, H, H, C, h, 7, 2, seed=C)
+    chain = sm.SwinChain(B, [(C, h, 2, H, H)], 7, {"stages": [[dev_params(p, torch.bfloat16) for p in blocks]]}, torch.bfloat16)
+    got, xd = [], dev(x, torch.bfloat16)
+    labels = _labels(lambda: got.append(chain(xd)))
+    assert "proj+ln+mlp_bf16[%d,%d,%d]+ln+qkv" % (B * H * H, 4 * C, C) in labels, labels
+    assert_bf16_close(got[0], swin.swin_stage(to_np(x), [np_params(p) for p in blocks], H, H, 7, h), "stage", x=to_np(x))
+
+
 @pytest.mark.parametrize("C,T,form", [(128, 2352, "ln+splitgemm"), (128, 2744, "ln+pgemm"), (256, 2548, "ln+gemm"), (256, 2940, "ln+pgemm"),
                                       (384, 3528, "ln+gemm"), (384, 3724, "ln+pgemm"), (512, 784, "ln+gemm")])
 def test_which_form_the_first_qkv_has(C, T, form):
