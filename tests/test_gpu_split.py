@@ -189,6 +189,42 @@ def test_row_owning_tail_above_the_chain(B, H, C):
     assert_bf16_close(got[0], swin.swin_stage(to_np(x), [np_params(p) for p in blocks], H, H, 7, h), "stage", x=to_np(x))
 
 
+@pytest.mark.parametrize("M,N,K,dtype,norm,act,res", [
+    (1100, 1000, 128, BF16, None, "gelu", True),         # LDS-DMA staging, ragged rows and columns
+    (1100, 1000, 104, BF16, None, "gelu", True),         # register staging, a cut K-tile
+    (1100, 1000, 104, BF16, "layer", "gelu", True),
+    (6500, 520, 72, F32, None, "gelu", True),
+    (6500, 520, 72, F32, "layer", "none", False),
+    (70, 100, 64, BF16, None, "gelu", True),             # columns that the column-split kernel does not take
+    (33, 40, 48, BF16, "layer without shift", "gelu", True),
+    (33, 40, 48, F32, "rms", "none", True),
+])
+def test_tiled_linear_beside_the_split_one(M, N, K, dtype, norm, act, res):
+    g = torch.Generator().manual_seed(M + K)
+    A, W = (torch.randn(M, K, generator=g) + 0.3).to(dtype), (torch.randn(N, K, generator=g) * K ** -0.5).to(dtype)
+    b, R = torch.randn(N, generator=g).to(dtype), torch.randn(M, N, generator=g).to(dtype)
+    gam, bet = (1 + 0.1 * torch.randn(K, generator=g)).to(dtype), (0.1 * torch.randn(K, generator=g)).to(dtype)
+    x, nm = A.double(), None
+    if norm == "rms":
+        x, nm = x / torch.sqrt((x * x).mean(1, keepdim=True) + 1e-5) * gam.double(), ("rms", gam.cuda(), None, 1e-5)
+    elif norm:
+        with_shift = norm == "layer"
+        x = torch.nn.functional.layer_norm(x, (K,), gam.double(), bet.double() if with_shift else None, 1e-5)
+        nm = ("layer", gam.cuda(), bet.cuda() if with_shift else None, 1e-5)
+    if norm and dtype == BF16:
+        x = x.to(dtype).double()                 # the normalised row is rounded as a norm kernel would store it
+    want = x @ W.double().t() + b.double()
+    if act == "gelu":
+        want = torch.nn.functional.gelu(want)
+    if res:
+        want = want + R.double()
+    got = []
+    labels = _labels(lambda: got.append(sm.linear(A.cuda(), W.cuda(), b.cuda(), residual=R.cuda() if res else None, act=act, norm=nm)))
+    assert len(labels) == 1 and "splitgemm" not in labels[0], labels
+    err = (got[0].double().cpu() - want).abs().max().item()
+    assert err <= (2e-5 if dtype == torch.float32 else 1.2e-2) * max(1.0, want.abs().max().item()), err      # as above
+
+
 @pytest.mark.parametrize("C,T,form", [(128, 2352, "ln+splitgemm"), (128, 2744, "ln+pgemm"), (256, 2548, "ln+gemm"), (256, 2940, "ln+pgemm"),
                                       (384, 3528, "ln+gemm"), (384, 3724, "ln+pgemm"), (512, 784, "ln+gemm")])
 def test_which_form_the_first_qkv_has(C, T, form):

@@ -79,8 +79,9 @@ def test_small_net_embed_merge_head(dtype, mode):
 @pytest.mark.parametrize("mode", MODES)
 @pytest.mark.parametrize("fuse_mlp", [True, "mlp", False])
 def test_small_net_with_fused_kernel_widths(mode, fuse_mlp):
-    # stage widths 128 and 256: the fused MLP / projection kernels are in play, and in the second stage (elided, fully
-    # fused) block 0 also computes block 1's LayerNorm-1 and QKV through the composed reverse / shifted-partition map
+    # stage widths 128 and 256 on 1568 and 392 tokens: the fused MLP / projection kernels are in play; elided and fully
+    # fused, the second stage is few enough tokens for the chained tail (the row-owning one: test_gpu_split.py), and in
+    # both stages block 0 also computes block 1's LayerNorm-1 and QKV through the composed reverse / shifted-partition map
     f, fw, l, lw = small_net_case(torch.bfloat16, mode, embed=128, heads=(4, 8), fuse_mlp=fuse_mlp)
     assert_bf16_close(f, fw, "feature map")
     assert_bf16_close(l, lw, "logits")
@@ -94,8 +95,8 @@ def test_small_net_with_fused_kernel_widths(mode, fuse_mlp):
 @pytest.mark.parametrize("mode", MODES)
 @pytest.mark.parametrize("fuse_mlp", [True, "mlp"])
 def test_small_net_with_wide_rows(mode, fuse_mlp):
-    # stage widths 256 and 512: the second stage runs the 64-token kernels (projection + MLP + the next block's
-    # LayerNorm-1 and QKV when fully fused and elided; the MLP alone otherwise)
+    # stage widths 256 and 512 on 1568 and 392 tokens: the second stage runs the chained tail when fully fused and elided
+    # (the 64-token projection + MLP + next QKV kernel on more tokens: test_gpu_split.py), the 64-token MLP otherwise
     f, fw, l, lw = small_net_case(torch.bfloat16, mode, embed=256, heads=(8, 16), fuse_mlp=fuse_mlp)
     assert_bf16_close(f, fw, "feature map")
     assert_bf16_close(l, lw, "logits")
