@@ -327,7 +327,7 @@ int sm_attention(const sm_attention_desc*, const void* q, const void* k, const v
  * One Swin block on x [B, H*W, C] -> y [B, H*W, C]:
  * LayerNorm -> (roll, window partition) -> QKV Linear -> window attention ->
  * proj Linear -> (reverse, roll back) -> +x -> LayerNorm -> MLP (GELU) -> +.
- * SM_ELIDED: 7 kernels (fewer where a norm is folded into the next Linear or the MLP is fused), the layout transformations are folded into their
+ * SM_ELIDED: 7 kernels (fewer where a norm is folded into the next Linear, the MLP is fused or the tail is chained), the layout transformations are folded into their
  * neighbours' addressing as planned by sm_layout_plan.  SM_EXPLICIT: the same
  * 7 kernels with identity maps plus one copy kernel per transformation that
  * moves data (the baseline the paper's Table 1 calls explicit). */
@@ -345,6 +345,11 @@ typedef struct {
                                    run as one packed-weight kernel; in sm_run_chain, inside a stage, when the previous
                                    block runs the fused projection + MLP kernel, that kernel computes them instead and
                                    this block starts at attention */
+                                /* On few tokens, SM_ELIDED, forms that read the row-major matrices are faster: projection ..
+                                   FC2 (and in sm_run_chain the next QKV) as one launch cut over output columns, LayerNorm-1
+                                   folded into the plain QKV Linear.  They run where the block has all three packed weights,
+                                   or its width has no fused kernel, and the row-major weights, biases and norms are there
+                                   too; a block that is given packed weights only runs the packed forms at every size */
 } sm_swin_weights;
 size_t sm_swin_block_workspace_bytes(const sm_swin_cfg*, int mode);
 int sm_swin_block(const sm_swin_cfg*, const sm_swin_weights*, const void* x, void* y,

@@ -201,12 +201,12 @@ int run_gemm(const void* A, const void* W, const void* bias, const void* res, vo
 bool fold_norm(int n_cols) { return n_cols <= 512; }
 
 // Whether the tail of a block (projection .. the next QKV) is cut over output columns instead of over rows
-// (from 32-token tiles of the row-owning kernel alone to the chain at 6 blocks per stage, us per block: C = 512, 196 tokens
-// 101 / 35, 784 100 / 53, 1568 99 / 74, 3136 99 / 122; C = 384, 196 57 / 31, 784 55 / 46, 1568 55 / 58; C = 256, 784 34 / 31,
-// 1568 34 / 41; per-operator kernels at C = 1024, 49 tokens 121 / 73, 196 120 / 78, 392 117 / 128).  The row-owning kernel's
-// time does not depend on the rows until they fill the chip, and grows with C^2; the chain's grows with rows x C, from the
-// four hand-overs between its Linears on: below C = 256 the row-owning kernel is the faster one at any size (a whole block,
-// C = 128, 49 tokens: 25.1 / 20.0 us, 98: 25.3 / 20.4; C = 256, 49: 26.5 / 31.2).
+// (row-owning kernels alone / the chain, us per block of a stage of six: C = 512, 196 tokens 101 / 31, 784 100 / 51, 1568 99 / 73,
+// 2156 100 / 98, 3136 99 / 122; C = 384, 196 56 / 28, 784 55 / 45, 1176 55 / 52, 1568 55 / 58; C = 256, 196 35 / 26, 392 34 / 30, 1568
+// 34 / 41; per-operator kernels at C = 768, 196 80 / 57, at C = 1024, 49 tokens 92 / 72, 196 93 / 79, 392 117 / 128).  The row-owning
+// kernel's time does not depend on the rows until they fill the chip, and grows with C^2; the chain's grows with rows x C, from
+// the four hand-overs between its Linears on: below C = 256 the row-owning kernel is the faster one at any size (a whole block,
+// C = 128, 49 tokens: 25.1 / 20.0 us chained / row-owning, 98: 25.3 / 20.4; C = 256, 49: 26.5 / 31.2).
 bool split_tail_use(const sm_swin_cfg& c, int64_t T) {
   if (c.dtype != SM_BF16 || c.C % 32 || c.C > 1024) return false;
   if (c.C < 256 && mlp_fused_supported(c.C, c.mlp_ratio * c.C, c.dtype)) return false;
