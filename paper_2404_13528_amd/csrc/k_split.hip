@@ -452,7 +452,14 @@ __global__ __launch_bounds__(NTHR + 64) void split_chain_kernel(SplitArgs a) {
   }
 }
 
-bool split_rows_ok(const RowProg& r) { return r.identity ? r.ld <= INT32_MAX : r.table != nullptr; }
+// a pitch or a table, whose offsets are whole vectors (sufficient: the pitch, or the program's constant and coefficients are)
+static bool split_rows_ok(const RowProg& r, int vec) {
+  if (r.identity) return r.ld <= INT32_MAX && r.ld % vec == 0;
+  if (!r.table || r.c0 % vec) return false;
+  for (int t = 0; t < r.nterm; ++t)
+    if (r.t_coef[t] % vec) return false;
+  return true;
+}
 
 namespace {
 constexpr size_t kLds = 160 * 1024;
@@ -547,7 +554,7 @@ static bool wide_norm_split(int64_t t11, int K, int dtype) { return t11 <= (dtyp
 static bool split_linear_plan(const GemmArgs& g, SplitTile* t, bool* ring) {
   const int es = g.dtype == SM_F32 ? 4 : 2, vec = 16 / es;
   if (g.a_gran > 0 || g.rope_cols || g.c_transposed || g.c_cols_on || g.C2 || g.norm == 2 || (g.act != SM_ACT_NONE && g.act != SM_ACT_GELU)) return false;
-  if (g.M > INT32_MAX / 2 || g.ldw != g.K || g.K % (2 * vec) || g.N % 8 || g.N < 8 || !split_rows_ok(g.a_rows) || !split_rows_ok(g.c_rows) || g.c_rows.ld % vec || g.a_rows.ld % vec) return false;
+  if (g.M > INT32_MAX / 2 || g.ldw != g.K || g.K % (2 * vec) || g.N % 8 || g.N < 8 || !split_rows_ok(g.a_rows, vec) || !split_rows_ok(g.c_rows, vec)) return false;
   if (g.norm && !g.norm_beta) return false;
   *ring = !g.norm && (size_t)g.K * es > 1024;
   *t = split_tile(g.M, g.N, g.K, g.dtype, *ring);

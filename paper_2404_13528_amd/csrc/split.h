@@ -23,7 +23,6 @@ struct SplitArgs {
   int group_rows, n_groups, group_words, group_tasks;      // chained form: row tiles, groups, counters and tasks of a group
   int* counters;
 };
-bool split_rows_ok(const RowProg& r);             // the row program is a pitch or a table
 int launch_split_single(SplitArgs& a, int dtype, int mi, int wn, void* stream);      // tile 32 mi x 32 wn: (1, 1), (1, 2), (2, 2)
 struct GemmArgs;
 bool split_linear_use(const GemmArgs& g);                                       // whether launch_gemm runs g in this form

@@ -239,6 +239,17 @@ def test_which_form_the_first_qkv_has(C, T, form):
     assert (got.float() - want.reshape(T, 3 * C).float()).norm() <= 4e-3 * want.float().norm()      # bf16: rounded once each
 
 
+def test_per_operator_blocks_on_few_tokens_run_split_linears():
+    """fuse_mlp=False at a fused width: one kernel per operator, the projection with its row table among the split ones."""
+    x, p = Wl.swin_block_case(1, 14, 14, 256, 8, 7, seed=9, bf16=True, std=0.1)
+    blk = sm.SwinBlock(1, 14, 14, 256, 8, 7, 3, dev_params(p, BF16), BF16, fuse_mlp=False)
+    xd, got = dev(x, BF16), []
+    labels = _labels(lambda: got.append(blk(xd)))
+    for want in ("splitgemm_bf16[196,768,256]", "splitgemm_bf16[196,256,256]+res+scatter", "splitgemm_bf16[196,1024,256]+gelu", "splitgemm_bf16[196,256,1024]+res"):
+        assert want in labels, (want, labels)
+    assert_bf16_close(got[0], swin.swin_block(to_np(x), np_params(p), 14, 14, 7, 8, 3), "block", x=to_np(x))
+
+
 def _few_tokens_block(C, **kw):
     x, p = Wl.swin_block_case(1, 14, 14, C, C // 32, 7, seed=C + 1, bf16=True)
     blk = sm.SwinBlock(1, 14, 14, C, C // 32, 7, 3, dev_params(p, torch.bfloat16), torch.bfloat16, **kw)
