@@ -27,6 +27,7 @@
 #include "device_common.h"
 #include "kernels.h"
 #include "split.h"
+#include "tile.h"
 
 namespace sm {
 
@@ -974,7 +975,7 @@ static bool tunable(const GemmArgs& g) { return g.dtype == SM_BF16 && g.K % 64 =
 // 772 x 12288 x 2048 55.4 / 61.9 / 54.6, 963 x 1536 x 1536 12.3 / 10.3 / 10.3, 1059 x 3072 x 1536 18.7 / 16.9 / 16.9,
 // 1238 x 11264 x 1536 59.3 / 49.9 / 49.9; not met: the second 64-row workgroup on a few CUs (650 x 3072 x 1536 13.8 / 15.1 / 15.1, but
 // 347 x 5632 x 1280 15.7 / 13.3 / 13.3).
-static Tune long_k_tile(const GemmArgs& g) {
+static Tune long_k_tile(const GemmArgs& g, double* cost_us = nullptr) {
   const int64_t tcols = (g.N + 127) / 128;
   auto tiles = [&](int rows) { return ((g.M + rows - 1) / rows) * tcols; };
   auto rounds = [&](int rows, int resident) { return (double)((tiles(rows) + resident - 1) / resident); };
@@ -995,7 +996,35 @@ static Tune long_k_tile(const GemmArgs& g) {
     }
     if (i == 0 || cost < least) { best = i; least = cost; }
   }
+  if (cost_us) *cost_us = g.K < 64 * 64 ? least : least * g.K / 4096.;
   return form[best].t;
+}
+
+// Tile height of Linears with a short K.  Large grids (several rounds of residency whatever the tile): the 128-row tile, or the
+// 256-row one where gemm_launch finds that it fills the chip.  Small grids are decided by rounds of residency (256 CUs hold
+// 768 workgroups of the 64-row tile, 512 of the 128-row one) times the time a workgroup lives: a fixed part plus
+// its K steps, both measured on the chip (microseconds; the 128-row step moves twice the rows in about twice the time,
+// so the smaller tile wins unless it needs an extra round).
+static bool short_k_128(const GemmArgs& g, double* cost_us = nullptr) {
+  const int64_t tcols = (g.N + 127) / 128;
+  const int64_t t128 = ((g.M + 127) / 128) * tcols, t64 = ((g.M + 63) / 64) * tcols;
+  const double nk = (double)((g.K + 63) / 64);
+  double cost64 = (double)((t64 + 767) / 768) * (3.0 + 0.78 * nk), cost128 = (double)((t128 + 511) / 512) * (3.6 + 1.6 * nk);
+  // long K loops (fp32 and the register-staged forms): the tile's L2 -> LDS traffic per flop decides, the 64-row tile being
+  // about 0.6 as efficient per row
+  if (nk > 16) { cost64 = (double)((t64 + 767) / 768) * 1.2; cost128 = (double)((t128 + 511) / 512) * 2.0; }
+  const bool tall = t128 >= 1024 || cost128 <= cost64;
+  if (cost_us) *cost_us = tall ? .78 * cost128 : 1.15 * cost64;
+  return tall;
+}
+
+// What the kernel takes for a Linear with its own choice of tile, us: the two rules' costs, scaled to 134 measured shapes
+// (K = 320 .. 11008; standard deviation 7 to 12 % from K = 1280 on, 15 to 20 % below).  launch_tile_linear compares its own with it.
+double gemm_kernel_cost(const GemmArgs& g) {
+  double us = 0;
+  if (g.K <= 16 * 64) { (void)short_k_128(g, &us); return us; }
+  (void)long_k_tile(g, &us);
+  return us * (g.K < 2048 ? 1.24 : (g.K < 4096 ? 1.14 : .92));
 }
 
 template <typename T>
@@ -1008,26 +1037,21 @@ static int gemm_dispatch(const GemmArgs& g, const ColMap& cm, hipStream_t s) {
   }
   if (!tn.rows && !tn.stages && tunable(g) && g.K > 16 * 64) tn = long_k_tile(g);
   if (tn.rows) return tn.rows >= 128 ? gemm_pick_epi<T, 2>(g, cm, s, tn) : gemm_pick_epi<T, 1>(g, cm, s, tn);
-  // Tile height.  Large grids (several rounds of residency whatever the tile): the 128-row tile, or the 256-row one
-  // where gemm_launch finds that it fills the chip.  Small grids are decided by rounds of residency (256 CUs hold
-  // 768 workgroups of the 64-row tile, 512 of the 128-row one) times the time a workgroup lives: a fixed part plus
-  // its K steps, both measured on the chip (microseconds; the 128-row step moves twice the rows in about twice the time,
-  // so the smaller tile wins unless it needs an extra round).
-  const int64_t tcols = (g.N + 127) / 128;
-  const int64_t t128 = ((g.M + 127) / 128) * tcols, t64 = ((g.M + 63) / 64) * tcols;
-  if (t128 >= 1024) return gemm_pick_epi<T, 2>(g, cm, s, tn);
-  const double nk = (double)((g.K + 63) / 64);
-  double cost64 = (double)((t64 + 767) / 768) * (3.0 + 0.78 * nk), cost128 = (double)((t128 + 511) / 512) * (3.6 + 1.6 * nk);
-  // long K loops (fp32 and the register-staged forms): the tile's L2 -> LDS traffic per flop decides, the 64-row tile being
-  // about 0.6 as efficient per row
-  if (nk > 16) { cost64 = (double)((t64 + 767) / 768) * 1.2; cost128 = (double)((t128 + 511) / 512) * 2.0; }
-  return cost128 <= cost64 ? gemm_pick_epi<T, 2>(g, cm, s, tn) : gemm_pick_epi<T, 1>(g, cm, s, tn);
+  return short_k_128(g) ? gemm_pick_epi<T, 2>(g, cm, s, tn) : gemm_pick_epi<T, 1>(g, cm, s, tn);
+}
+
+static bool tile_chosen(const GemmArgs& g) {
+  if (g_force_rows || g_force_stages) return true;
+  if (!tunable(g)) return false;
+  std::lock_guard<std::mutex> lock(g_tune_mu);
+  return g_tuned.count(tune_key(g)) != 0;
 }
 
 int launch_gemm(const GemmArgs& g, void* stream) {
   if (g.M == 0 || g.N == 0) return 0;
   int rc = 0;
   if (launch_split_linear(g, stream, &rc)) return rc;      // few rows
+  if (!tile_chosen(g) && launch_tile_linear(g, stream, &rc)) return rc;      // large tiles, unless the caller or the tuner has picked one of gemm_kernel's
   ColMap cm;
   cm.mode = 0; cm.half = g.N / 2; cm.rope_cols = g.rope_cols; cm.rope_dim = g.rope_dim;
   if (g.act == SM_ACT_SWIGLU || g.act == SM_ACT_GEGLU) cm.mode = 1;
