@@ -29,10 +29,26 @@ template <>
 __device__ __forceinline__ float4 pack<float>(const float* f) { return make_float4(f[0], f[1], f[2], f[3]); }
 template <>
 __device__ __forceinline__ uint4 pack<bf16_t>(const float* f) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
   unsigned w[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) w[i] = (unsigned)f2bf(f[2 * i]) | ((unsigned)f2bf(f[2 * i + 1]) << 16);
+  for (int i = 0; i < 4; ++i) { const f32x2 p = {f[2 * i], f[2 * i + 1]}; w[i] = __builtin_bit_cast(unsigned, __builtin_convertvector(p, bf16x2)); }
   return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// sums over 16 adjacent lanes by DPP, over the wave with two exchanges more
+__device__ __forceinline__ float norm_sum16(float v) {
+  v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true));      // xor 1
+  v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, true));      // xor 2
+  v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x141, 0xF, 0xF, true));     // mirror within 8
+  v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x140, 0xF, 0xF, true));     // mirror within 16
+  return v;
+}
+__device__ __forceinline__ float norm_sum64(float v) {
+  v = norm_sum16(v);
+  v += __shfl_xor(v, 16, 64);
+  return v + __shfl_xor(v, 32, 64);
 }
 
 // Each wave owns RPW consecutive logical rows; lane l owns 16-byte chunks l, l+64, ... of each.  All loads
@@ -79,23 +95,22 @@ __global__ __launch_bounds__(256) void norm_rows_kernel(NormArgs a) {
     if (!l_ident && l_tab) seg_off[r] = (int64_t)lt[r];
     if (!s_ident && s_tab) out_off[r] = (int64_t)st[r];
   }
+  // every load of the wave's rows is requested before the first value is touched, lanes past the row's last chunk read that one
+  // again (a load inside a condition is waited for there: eight of them one after the other were 8 of 11 us of a 333 x 4096 norm)
+  V raw[RPW][MAXCH];
   float v[RPW][MAXCH][VEC];
   float sum[RPW];
 #pragma unroll
   for (int r = 0; r < RPW; ++r) {
     const int64_t my_seg = seg_off[r];
-    sum[r] = 0.f;
 #pragma unroll
     for (int i = 0; i < MAXCH; ++i) {
-      const int ch = lane + 64 * i;
-      const int seg = ch < nchunk ? ch / seg_chunks : 0;
-      const int64_t base = __shfl(my_seg, seg, 64);
-      if (ch < nchunk) {
-        V raw = *(const V*)(x + base + (int64_t)(ch - seg * seg_chunks) * VEC);
-        unpack<T>(raw, v[r][i]);
-      } else {
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) v[r][i][e] = 0.f;
+      const int ch = min(lane + 64 * i, nchunk - 1);
+      if (nseg == 1) raw[r][i] = *(const V*)(x + my_seg + (int64_t)ch * VEC);
+      else {
+        const int seg = ch / seg_chunks;
+        const int64_t base = __shfl(my_seg, seg, 64);
+        raw[r][i] = *(const V*)(x + base + (int64_t)(ch - seg * seg_chunks) * VEC);
       }
     }
   }
@@ -109,29 +124,37 @@ __global__ __launch_bounds__(256) void norm_rows_kernel(NormArgs a) {
     graw[i] = *(const V*)(g + ch * VEC);
     braw[i] = *(const V*)((!rms && bta ? bta : g) + ch * VEC);
   }
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
   float mean[RPW], rstd[RPW];
 #pragma unroll
   for (int r = 0; r < RPW; ++r) {
+    sum[r] = 0.f;
 #pragma unroll
-    for (int i = 0; i < MAXCH; ++i)
+    for (int i = 0; i < MAXCH; ++i) {
+      unpack<T>(raw[r][i], v[r][i]);
+      float part = 0.f;
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) sum[r] += v[r][i][e];
+      for (int e = 0; e < VEC; ++e) part += v[r][i][e];
+      sum[r] += lane + 64 * i < nchunk ? part : 0.f;
+    }
   }
 #pragma unroll
-  for (int r = 0; r < RPW; ++r) mean[r] = rms ? 0.f : wave_sum(sum[r]) / (float)n_ch;
+  for (int r = 0; r < RPW; ++r) mean[r] = rms ? 0.f : norm_sum64(sum[r]) / (float)n_ch;
 #pragma unroll
   for (int r = 0; r < RPW; ++r) {
     float ss = 0.f;
 #pragma unroll
-    for (int i = 0; i < MAXCH; ++i)
-      if (lane + 64 * i < nchunk) {
+    for (int i = 0; i < MAXCH; ++i) {
+      float part = 0.f;
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) { const float dlt = v[r][i][e] - mean[r]; ss += dlt * dlt; }
-      }
+      for (int e = 0; e < VEC; ++e) { const float dlt = v[r][i][e] - mean[r]; part += dlt * dlt; }
+      ss += lane + 64 * i < nchunk ? part : 0.f;
+    }
     sum[r] = ss;
   }
 #pragma unroll
-  for (int r = 0; r < RPW; ++r) rstd[r] = rsqrtf(wave_sum(sum[r]) / (float)n_ch + eps);
+  for (int r = 0; r < RPW; ++r) rstd[r] = rsqrtf(norm_sum64(sum[r]) / (float)n_ch + eps);
   T* y = (T*)a.y;
 #pragma unroll
   for (int i = 0; i < MAXCH; ++i) {
@@ -160,13 +183,6 @@ __global__ __launch_bounds__(256) void norm_rows_kernel(NormArgs a) {
 // Rows of at most LPR 16-byte chunks (LPR = 16 or 32 lanes per row): 64 / LPR rows side by side in a wave, RPL such groups
 // per wave one after the other; the statistics are sums over the LPR lanes of a row (DPP row operations, and one
 // cross-row-of-16 exchange when LPR = 32).  One segment per row; the same row maps as norm_rows_kernel.
-__device__ __forceinline__ float norm_sum16(float v) {
-  v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true));      // xor 1
-  v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, true));      // xor 2
-  v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x141, 0xF, 0xF, true));     // mirror within 8
-  v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x140, 0xF, 0xF, true));     // mirror within 16
-  return v;
-}
 template <typename T, int LPR, int RPL>
 __global__ __launch_bounds__(256) void norm_short_rows_kernel(NormArgs a) {
   constexpr int VEC = Elem<T>::VEC, RPP = 64 / LPR;      // rows per pass of the wave
@@ -179,7 +195,7 @@ __global__ __launch_bounds__(256) void norm_short_rows_kernel(NormArgs a) {
   const bool on = ch < nchunk;
   const T* x = (const T*)a.x;
   int64_t in_off[RPL], out_off[RPL];
-  float v[RPL][VEC];
+  V raw[RPL];
 #pragma unroll
   for (int r = 0; r < RPL; ++r) {
     const int64_t row = min(row0 + r * RPP + sub, a.rows - 1);      // a clamped duplicate row is computed and not stored
@@ -188,34 +204,34 @@ __global__ __launch_bounds__(256) void norm_short_rows_kernel(NormArgs a) {
   }
 #pragma unroll
   for (int r = 0; r < RPL; ++r) {
-    if (on) { V raw = *(const V*)(x + in_off[r] + (int64_t)ch * VEC); unpack<T>(raw, v[r]); }
-    else {
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) v[r][e] = 0.f;
-    }
+    raw[r] = *(const V*)(x + in_off[r] + (int64_t)min(ch, nchunk - 1) * VEC);      // unconditional: all of them in flight together
   }
   const T* g = (const T*)a.gamma;
   const T* bta = (const T*)a.beta;
   float gg[VEC], bb[VEC];
-  { V graw = *(const V*)(g + min(ch, nchunk - 1) * VEC); unpack<T>(graw, gg); }
-  if (!a.rms && bta) { V braw = *(const V*)(bta + min(ch, nchunk - 1) * VEC); unpack<T>(braw, bb); }
-  else {
+  {
+    const V graw = *(const V*)(g + min(ch, nchunk - 1) * VEC), braw = *(const V*)((!a.rms && bta ? bta : g) + min(ch, nchunk - 1) * VEC);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    unpack<T>(graw, gg);
+    unpack<T>(braw, bb);
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) bb[e] = 0.f;
+    for (int e = 0; e < VEC; ++e) bb[e] = !a.rms && bta ? bb[e] : 0.f;
   }
   T* y = (T*)a.y;
 #pragma unroll
   for (int r = 0; r < RPL; ++r) {
-    float s = 0.f;
+    float v[VEC], s = 0.f;
+    unpack<T>(raw[r], v);
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) s += v[r][e];
-    s = norm_sum16(s);
+    for (int e = 0; e < VEC; ++e) s += v[e];
+    s = norm_sum16(on ? s : 0.f);
     if (LPR == 32) s += __shfl_xor(s, 16, 64);
     const float mean = a.rms ? 0.f : s / (float)a.C;
     float ss = 0.f;
     if (on) {
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) { const float d = v[r][e] - mean; ss += d * d; }
+      for (int e = 0; e < VEC; ++e) { const float d = v[e] - mean; ss += d * d; }
     }
     ss = norm_sum16(ss);
     if (LPR == 32) ss += __shfl_xor(ss, 16, 64);
@@ -223,7 +239,7 @@ __global__ __launch_bounds__(256) void norm_short_rows_kernel(NormArgs a) {
     if (on && row0 + r * RPP + sub < a.rows) {
       float o[VEC];
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) o[e] = (v[r][e] - mean) * rstd * gg[e] + bb[e];
+      for (int e = 0; e < VEC; ++e) o[e] = (v[e] - mean) * rstd * gg[e] + bb[e];
       *(V*)(y + out_off[r] + (int64_t)ch * VEC) = pack<T>(o);
     }
   }
@@ -426,20 +442,38 @@ int launch_groupnorm(const GroupNormArgs& a, void* stream) {
   return (int)hipGetLastError();
 }
 
-// ---- mean over tokens: x [B, L, C] -> y [B, C]
+// ---- mean over tokens: x [B, L, C] -> y [B, C].  A thread sums one column, eight tokens in flight at a time and added in
+// order (one load per sum step was one latency per token: 12.5 us for one image of 49 x 1024); workgroups of one wave, so that
+// a single image's columns spread over more CUs
 template <typename T>
-__global__ __launch_bounds__(256) void mean_tokens_kernel(const T* x, T* y, int L, int C) {
+__global__ __launch_bounds__(64) void mean_tokens_kernel(const T* x, T* y, int L, int C) {
   const int b = blockIdx.y;
   const int c = blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= C) return;
   float s = 0.f;
   const T* p = x + (int64_t)b * L * C + c;
-  for (int t = 0; t < L; ++t) s += Elem<T>::ld(p + (int64_t)t * C);
+  constexpr int U = 8;
+  T v[2][U];
+  auto load = [&](int t, T (&r)[U]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) r[u] = p[(int64_t)min(t + u, L - 1) * C];
+  };
+  auto add = [&](int t, const T (&r)[U]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) s += t + u < L ? Elem<T>::ld(&r[u]) : 0.f;
+  };
+  load(0, v[0]);
+  for (int t = 0; t < L; t += 2 * U) {
+    load(t + U, v[1]);
+    add(t, v[0]);
+    load(t + 2 * U, v[0]);
+    add(t + U, v[1]);
+  }
   Elem<T>::st(y + (int64_t)b * C + c, s / (float)L);
 }
 
 int launch_mean_tokens(const void* x, void* y, int B, int L, int C, int dtype, void* stream) {
-  dim3 grid((unsigned)((C + 255) / 256), (unsigned)B), block(256);
+  dim3 grid((unsigned)((C + 63) / 64), (unsigned)B), block(64);
   if (dtype == SM_F32) mean_tokens_kernel<float><<<grid, block, 0, (hipStream_t)stream>>>((const float*)x, (float*)y, L, C);
   else mean_tokens_kernel<bf16_t><<<grid, block, 0, (hipStream_t)stream>>>((const bf16_t*)x, (bf16_t*)y, L, C);
   return (int)hipGetLastError();
