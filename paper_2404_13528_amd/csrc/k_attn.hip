@@ -800,7 +800,108 @@ __global__ __launch_bounds__(256, 4) void attn_window7_kernel(sm_attention_desc 
   }
 }
 
-// fp32 window attention: nq, nk <= 64, d <= 4 DV.  One workgroup of 256 threads per (window, head); the four lanes of
+// fp32 window attention on the matrix instructions: nq, nk <= 64, d <= 32.  One workgroup of four waves per (window, head); wave
+// (qb, kb) takes 32 queries and 32 keys: S^T = K . Q^T (fp32 products of 32 x 32 x 2), so that a lane owns one query and sixteen of
+// the keys, the row maximum over the lane pair and the partner wave, P^T straight from those registers as the second operand of
+// O^T = V^T . P^T, and the two key halves' results and sums added through LDS, each wave finishing half of the features.  Q, K and V
+// rows go from memory to the operand registers.  Latency bound (192 workgroups of one pass each on the 56 x 56 grid at C = 96).
+// On plain FMA, a quad of lanes per query, a key at a time with its table index and region worked out again per pair, 19.3 us there.
+__global__ __launch_bounds__(256) void attn_window_f32m_kernel(sm_attention_desc a, const float* __restrict__ q, const float* __restrict__ k,
+                                                               const float* __restrict__ v, float* __restrict__ o, const float* __restrict__ table) {
+  __shared__ float bias_s[232];              // (2 w - 1)^2 <= 225 entries (w <= 8)
+  __shared__ float mx_s[2][64], sum_s[2][64];
+  __shared__ float o_s[4][16][33];           // [wave][feature of the partner's half][query]
+  const int b = blockIdx.x / a.heads, hh = blockIdx.x % a.heads;
+  const float* qp = q + (int64_t)b * a.q_stride[0] + (int64_t)hh * a.q_stride[1];
+  const float* kp = k + (int64_t)b * a.k_stride[0] + (int64_t)hh * a.k_stride[1];
+  const float* vp = v + (int64_t)b * a.v_stride[0] + (int64_t)hh * a.v_stride[1];
+  float* op = o + (int64_t)b * a.o_stride[0] + (int64_t)hh * a.o_stride[1];
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), qb = wave >> 1, kb = wave & 1;
+  const int qi = qb * 32 + l32, kj = kb * 32 + l32, iq = min(qi, a.nq - 1), jk = min(kj, a.nk - 1);
+  // everything from memory is requested at once; rows past the end repeat the last one, chunks and features past the head size the
+  // last of them (their values are set to zero)
+  float4 qv[4], kv[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int f = min(8 * c + 4 * hf, a.d - 4);
+    qv[c] = *(const float4*)(qp + (int64_t)iq * a.q_stride[2] + f);
+    kv[c] = *(const float4*)(kp + (int64_t)jk * a.k_stride[2] + f);
+  }
+  float vv[16];                              // V[key of step i][feature l32]; the key of step i: kb 32 + 8 (i / 4) + 4 hf + i % 4
+#pragma unroll
+  for (int i = 0; i < 16; ++i)
+    vv[i] = vp[(int64_t)min(kb * 32 + 8 * (i >> 2) + 4 * hf + (i & 3), a.nk - 1) * a.v_stride[2] + min(l32, a.d - 1)];
+  const int w = a.window, nt = (2 * w - 1) * (2 * w - 1);
+  if (tid < nt) bias_s[tid] = table[(int64_t)tid * a.heads + hh];
+  const int nWx = a.W / w, win = b % ((a.H / w) * nWx), wy = win / nWx, wx = win - wy * nWx;
+  const float inv_w = 1.0f / (float)w;       // token -> (row, column): exact for the small integers involved
+  auto place = [&](int t, int& at, int& reg) __attribute__((always_inline)) {
+    const int y = (int)(((float)t + 0.5f) * inv_w), x = t - y * w;
+    at = y * (2 * w - 1) + x;
+    reg = a.shift > 0 ? 3 * region(wy * w + y, a.H, w, a.shift) + region(wx * w + x, a.W, w, a.shift) : 0;
+  };
+  int q_at, q_reg;
+  place(iq, q_at, q_reg);
+  q_at += (w - 1) * (2 * w - 1) + w - 1;
+  __syncthreads();
+
+  f32x16_t s;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) s[i] = 0.f;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const bool in = 8 * c + 4 * hf < a.d;
+    const float qf[4] = {qv[c].x, qv[c].y, qv[c].z, qv[c].w}, kf[4] = {kv[c].x, kv[c].y, kv[c].z, kv[c].w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? kf[e] : 0.f, in ? qf[e] * a.scale : 0.f, s, 0, 0, 0);
+  }
+  float mx = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int j = kb * 32 + 8 * (i >> 2) + 4 * hf + (i & 3);
+    int k_at, k_reg;
+    place(min(j, a.nk - 1), k_at, k_reg);
+    float t = s[i] + (bias_s[q_at - k_at] + (k_reg != q_reg ? -100.f : 0.f));
+    t = j < a.nk ? t : -INFINITY;
+    s[i] = t;
+    mx = fmaxf(mx, t);
+  }
+  mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+  if (hf == 0) mx_s[kb][qi] = mx;
+  __syncthreads();
+  mx = fmaxf(mx, mx_s[kb ^ 1][qi]);
+  float sum = 0.f;
+  f32x16_t acc;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const float p = expf(s[i] - mx);         // (a key past the end: exactly 0)
+    sum += p;
+    const bool in = l32 < a.d && kb * 32 + 8 * (i >> 2) + 4 * hf + (i & 3) < a.nk;
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? vv[i] : 0.f, p, acc, 0, 0, 0);
+  }
+  sum += __shfl_xor(sum, 32, 64);
+  if (hf == 0) sum_s[kb][qi] = sum;
+  // acc[i]: query l32, feature 8 (i / 4) + 4 hf + i % 4.  Wave kb finishes features 16 kb .. + 15 and hands over the others
+#pragma unroll
+  for (int i = 0; i < 8; ++i) o_s[wave][8 * (i >> 2) + 4 * hf + (i & 3)][l32] = kb ? acc[i] : acc[8 + i];
+  __syncthreads();
+  if (qi >= a.nq) return;
+  const float inv = 1.f / (sum + sum_s[kb ^ 1][qi]);
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    const int f = 16 * kb + 8 * g + 4 * hf;
+    if (f >= a.d) continue;
+    float r[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) r[e] = ((kb ? acc[8 + 4 * g + e] : acc[4 * g + e]) + o_s[wave ^ 1][8 * g + 4 * hf + e][l32]) * inv;
+    *(float4*)(op + (int64_t)qi * a.o_stride[2] + f) = float4{r[0], r[1], r[2], r[3]};
+  }
+}
+
+// fp32 window attention with wider heads: nq, nk <= 64, d <= 4 DV.  One workgroup of 256 threads per (window, head); the four lanes of
 // a quad own query i = tid / 4 and a quarter of the head's features each: a score is four partial dot products added
 // across the quad, the product with V is taken per quarter.  K and V rows sit in LDS as 16-byte chunks (all quads read
 // the same chunks at the same time: a broadcast), the head's column of the relative-position table as well; the
@@ -968,8 +1069,8 @@ int launch_attention(const sm_attention_desc& d, const void* q, const void* k, c
                      const void* rpb_table, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   if (d.dtype == SM_F32) {
-    if (d.d <= 32) attn_window_f32_kernel<8><<<dim3((unsigned)(d.nb * d.heads)), dim3(256), 0, s>>>(d, (const float*)q, (const float*)k, (const float*)v,
-                                                                                                     (float*)o, (const float*)rpb_table);
+    if (d.d <= 32) attn_window_f32m_kernel<<<dim3((unsigned)(d.nb * d.heads)), dim3(256), 0, s>>>(d, (const float*)q, (const float*)k, (const float*)v,
+                                                                                                   (float*)o, (const float*)rpb_table);
     else attn_window_f32_kernel<16><<<dim3((unsigned)(d.nb * d.heads)), dim3(256), 0, s>>>(d, (const float*)q, (const float*)k, (const float*)v,
                                                                                           (float*)o, (const float*)rpb_table);
     return (int)hipGetLastError();

@@ -536,3 +536,37 @@ def test_linear_reads_a_transposed_operand_in_place(dtype, M, N, K):
     am = sm.Map.create((K, M), [("permute", (1, 0))])
     got = sm.linear(dev(At, dtype), dev(W, dtype), dev(b, dtype), a_map=am, M=M)
     assert_close(got, want, dtype, "Linear over a transposed A", float(np.abs(want).max()) + 1.0)
+
+
+# fp32 window attention on the matrix instructions: one token, key blocks exactly full, cut and empty, head sizes that fill a quarter
+# to all of the 32 features
+@pytest.mark.parametrize("w,d,shift", [(1, 4, 0), (2, 12, 1), (4, 32, 2), (5, 20, 2), (6, 28, 0), (7, 8, 3), (8, 32, 4)])
+def test_window_attention_f32_edges(w, d, shift):
+    B, H, W, h = 2, 2 * w, 3 * w, 3
+    N, C, B_ = w * w, h * d, 2 * 2 * 3
+    qkv, table = draw((B_, N, 3 * C), 37, torch.float32), draw(((2 * w - 1) ** 2, h), 38, torch.float32)
+    dq, dt = dev(qkv, torch.float32), dev(table, torch.float32)
+    out = torch.full((B_, N, C), 7.0, device="cuda")
+    st = (N * 3 * C, d, 3 * C)
+    sm.attention(dq, dq[..., C:], dq[..., 2 * C:], kind="window", rpb_table=dt, window=w, shift=shift, H=H, W=W,
+                 shape=(B_, h, N, N, d), q_stride=st, k_stride=st, v_stride=st, o_stride=(N * C, d, C), out=out)
+    t = V.apply_chain(to_np(qkv), V.qkv_split_chain(B_, N, h, d))
+    add = swin.rel_pos_bias(to_np(table), w, h)[None]
+    if shift:
+        add = add + np.tile(swin.shift_mask(H, W, w, shift), (B, 1, 1))[:, None]
+    o, _ = O.attention(t[0], t[1], t[2], d ** -0.5, add=add)
+    assert_close(out, V.apply_chain(o, V.head_merge_chain(B_, N, h, d)), torch.float32, "fp32 window attention")
+
+
+# rows of one chunk more than a whole number of chunks per lane, and the widest; rows that do not fill the last workgroup
+@pytest.mark.parametrize("dtype", DT)
+@pytest.mark.parametrize("rms", [False, True])
+@pytest.mark.parametrize("chunks,rows", [(1, 33), (17, 5), (33, 9), (65, 3), (129, 5), (257, 2), (512, 7)])
+def test_norm_row_widths(chunks, rows, rms, dtype):
+    C = chunks * (4 if dtype == torch.float32 else 8)
+    x, g, b = draw((rows, C), 39, dtype), draw((C,), 40, dtype), draw((C,), 41, dtype)
+    y = sm.norm(dev(x, dtype), dev(g, dtype), None if rms else dev(b, dtype), eps=1e-5, rms=rms)
+    v = to_np(x)
+    v = v if rms else v - v.mean(-1, keepdims=True)
+    want = v / np.sqrt((v * v).mean(-1, keepdims=True) + 1e-5) * to_np(g) + (0 if rms else to_np(b))
+    assert_close(y.reshape(want.shape), want, dtype, "norm", 4.0)
