@@ -89,15 +89,22 @@ __device__ __forceinline__ void split_norm(unsigned a_at, unsigned g_at, int nkt
 #pragma unroll
   for (int t = 0; t < NT; ++t) v[t] = lds_read16(row + min(t * TPT + t1, nkt - 1) * BM * 128);
   wait_lds();
-  float sum = 0.f, sq = 0.f;
+  // the row stays in fp32 registers between the passes where there is room (unpacked again for each, the norm of 32 x 512 took 2.0 us
+  // of a task)
+  constexpr bool HELD = NT * VEC <= 64;
+  float x[HELD ? NT : 1][8], sum = 0.f, sq = 0.f;
+  auto values = [&](int t, bool first) __attribute__((always_inline)) -> float* {
+    float* f = x[HELD ? t : 0];
+    if (!HELD || first) { asm volatile("" : "+v"(v[t])); sp_unpack<T>(v[t], f); }
+    return f;
+  };
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    asm volatile("" : "+v"(v[t]));
     const bool in = (c0 + t * 8 * TPT) * VEC < K;
-    float x[8], part = 0.f;
-    sp_unpack<T>(v[t], x);
+    const float* f = values(t, true);
+    float part = 0.f;
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) part += x[e];
+    for (int e = 0; e < VEC; ++e) part += f[e];
     sum += in ? part : 0.f;
   }
   const float mean = lane_group_sum<TPR>(sum) / (float)K;
@@ -105,38 +112,36 @@ __device__ __forceinline__ void split_norm(unsigned a_at, unsigned g_at, int nkt
   // whose mean is large against its spread (768 elements of 100 and one of 100.5, all exact in bf16: nothing is left)
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    asm volatile("" : "+v"(v[t]));                         // (unpacked again: the fp32 values of all passes at once would spill)
     const bool in = (c0 + t * 8 * TPT) * VEC < K;
-    float x[8], part = 0.f;
-    sp_unpack<T>(v[t], x);
+    float* f = values(t, false);
+    float part = 0.f;
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) part += (x[e] - mean) * (x[e] - mean);
+    for (int e = 0; e < VEC; ++e) { f[e] -= mean; part += f[e] * f[e]; }
     sq += in ? part : 0.f;
   }
   const float rstd = rsqrtf(lane_group_sum<TPR>(sq) / (float)K + eps);
-  const float shift = -mean * rstd;
 #pragma unroll
-  for (int u0 = 0; u0 < NT; u0 += 4) {
+  for (int u0 = 0; u0 < NT; u0 += 2) {
     if (u0 * TPT >= nkt) break;
-    sp_u32x4 gv[4], bv[4];
+    sp_u32x4 gv[2], bv[2];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < 2; ++u) {
       const unsigned gc = min(c0 + (u0 + u) * 8 * TPT, K / VEC - 1);
       gv[u] = lds_read16(g_at + gc * 16);
       bv[u] = lds_read16(g_at + (K / VEC + gc) * 16);
     }
     wait_lds();
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      asm volatile("" : "+v"(gv[u]), "+v"(bv[u]), "+v"(v[u0 + u]));
+    for (int u = 0; u < 2; ++u) {
+      asm volatile("" : "+v"(gv[u]), "+v"(bv[u]));
       const int kt = (u0 + u) * TPT + t1;
-      float x[8], g8[8], b8[8];
-      sp_unpack<T>(v[u0 + u], x);
+      float* f = values(u0 + u, false);
+      float g8[8], b8[8];
       sp_unpack<T>(gv[u], g8);
       sp_unpack<T>(bv[u], b8);
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) x[e] = fmaf(fmaf(x[e], rstd, shift), g8[e], b8[e]);
-      if (kt < nkt) lds_write16(row + kt * BM * 128, sp_pack<T>(x));      // (chunks past K: never read)
+      for (int e = 0; e < VEC; ++e) f[e] = fmaf((HELD ? f[e] : f[e] - mean) * rstd, g8[e], b8[e]);
+      if (kt < nkt) lds_write16(row + kt * BM * 128, sp_pack<T>(f));      // (chunks past K: never read)
     }
   }
 }
@@ -146,9 +151,10 @@ __device__ __forceinline__ void split_norm(unsigned a_at, unsigned g_at, int nkt
 // 16-byte chunks at an XOR swizzle (chunk c of row r in slot c ^ ((r >> 1) & 7), conflict-free for the fragment reads).
 //   RING = false: the whole A panel (32 MI x K) and W panel (32 WN x K) are resident; LN normalises the A panel in place;
 //   RING = true:  four stages of KS K-tiles (no LN), for a K too long for that.
-// CHAIN: a task of the chained form; a ninth wave (`ctl`) takes part in the barriers only.
+// CHAIN: a task of the chained form; a ninth wave (`ctl`) takes part in the barriers only.  keep (with LN): the workgroup's previous
+// task was of the same Linear and rows, the normalised A panel is still there (the result tile lies over W then).
 template <typename T, int MI, int WN, bool LN, bool RING, bool CHAIN, typename Next>
-__device__ __forceinline__ void split_task(const SM_KARG LinPhase* p, int M, int row0, int ct, bool ctl, unsigned lds_w, unsigned lds_g, unsigned lds_base, unsigned char* smem, Next&& next) {
+__device__ __forceinline__ void split_task(const SM_KARG LinPhase* p, int M, int row0, int ct, bool ctl, bool keep, unsigned lds_w, unsigned lds_g, unsigned lds_base, unsigned char* smem, Next&& next) {
   constexpr int VEC = Elem<T>::VEC, TILE = 8 * VEC, BM = 32 * MI, BN = 32 * WN, WK = NW / WN;
   constexpr int KS = 4 / MI, NS = 4;
   constexpr int EP = BN + 4;                               // pitch of the fp32 result tile
@@ -159,7 +165,7 @@ __device__ __forceinline__ void split_task(const SM_KARG LinPhase* p, int M, int
   if (CHAIN && ctl) {
     wg_barrier();                                          // dependencies arrived
     wg_barrier();                                          // operands landed (RING: stage 0)
-    if (LN) wg_barrier();
+    if (LN && !keep) wg_barrier();
     if (RING) for (int s = 1; s < nst; ++s) wg_barrier();
     wg_barrier();                                          // main loop done
     wg_barrier();                                          // result tile in LDS
@@ -212,7 +218,7 @@ __device__ __forceinline__ void split_task(const SM_KARG LinPhase* p, int M, int
     if constexpr (VEC == 4) braw[q][1] = *(const sp_u32x4*)(bp + 4);
   }
 
-  if constexpr (LN) {
+  if (LN && !keep) {
     const int nch = K / VEC;
     for (int c0 = wave * 64; c0 < nch; c0 += NTHR)
       if (c0 + lane < nch) {
@@ -293,15 +299,16 @@ __device__ __forceinline__ void split_task(const SM_KARG LinPhase* p, int M, int
   };
 
   if constexpr (!RING) {
-    for (int kt = at1; kt < nkt; kt += TA) load_a(kt, kt * ATB);
+    if (!keep)
+      for (int kt = at1; kt < nkt; kt += TA) load_a(kt, kt * ATB);
     wait_mem();
     wg_barrier();
-    if constexpr (LN) {
+    if (LN && !keep) {
       // LayerNorm of the A panel in place: TPR threads per row, each with its chunks in registers (one pass over LDS), fp32
       // two-pass statistics, rounded as a norm kernel stores it
       if (nkt <= 4 * TA) split_norm<T, MI, 4>(lds_base, lds_base + lds_g, nkt, K, p->eps);
       else if (nkt <= 8 * TA) split_norm<T, MI, 8>(lds_base, lds_base + lds_g, nkt, K, p->eps);
-      else split_norm<T, MI, 12>(lds_base, lds_base + lds_g, nkt, K, p->eps);
+      else if constexpr (!CHAIN) split_norm<T, MI, 12>(lds_base, lds_base + lds_g, nkt, K, p->eps);      // (the chain's rows are 8 TA K-tiles at most)
       wg_barrier();
     }
     for (int kt = 0; kt < nkt; kt += KS) compute(kt, kt * ATB, lds_w + kt * WTB);
@@ -330,14 +337,15 @@ __device__ __forceinline__ void split_task(const SM_KARG LinPhase* p, int M, int
     wait_mem();
   }
 
-  // the partial sums of the WK wave groups, through LDS (over the A panel): lane owns row mi 32 + l32, columns
+  // the partial sums of the WK wave groups, through LDS (over the A panel, over W where A may be kept): lane owns row mi 32 + l32, columns
   // wn 32 + 8 g4 + 4 hf .. + 3
+  const unsigned r_at = lds_base + (CHAIN && LN ? lds_w : 0u);
   wg_barrier();
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
     for (int g4 = 0; g4 < 4; ++g4)
-      lds_write16(lds_base + (((wk * BM + mi * 32 + l32) * EP) + wn * 32 + g4 * 8 + hf * 4) * 4,
+      lds_write16(r_at + (((wk * BM + mi * 32 + l32) * EP) + wn * 32 + g4 * 8 + hf * 4) * 4,
                   sp_u32x4{__float_as_uint(acc[mi][4 * g4]), __float_as_uint(acc[mi][4 * g4 + 1]), __float_as_uint(acc[mi][4 * g4 + 2]), __float_as_uint(acc[mi][4 * g4 + 3])});
   wg_barrier();
 #pragma unroll
@@ -347,7 +355,7 @@ __device__ __forceinline__ void split_task(const SM_KARG LinPhase* p, int M, int
 #pragma unroll
     for (int w = 0; w < WK; ++w)
 #pragma unroll
-      for (int e = 0; e < 2; ++e) part[w][e] = lds_read16(lds_base + ((w * BM + o / OPR) * EP + (o % OPR) * 8 + e * 4) * 4);
+      for (int e = 0; e < 2; ++e) part[w][e] = lds_read16(r_at + ((w * BM + o / OPR) * EP + (o % OPR) * 8 + e * 4) * 4);
     wait_lds();
     float v[8];
 #pragma unroll
@@ -399,7 +407,7 @@ __global__ __launch_bounds__(NTHR) void split_single_kernel(SplitArgs a) {
   const int minor = tall ? g->tiles_n[0] : g->tiles_m, major = at / minor, rest = at - major * minor;
   const int ct = tall ? rest : major, rt = tall ? major : rest;
   if (ct >= g->tiles_n[0] || rt >= g->tiles_m) return;
-  split_task<T, MI, WN, LN, RING, false>(&g->ph[0], g->M, rt * 32 * MI, ct, false, g->lds_w, g->lds_g, lds_offset(sp_smem), sp_smem, [] {});
+  split_task<T, MI, WN, LN, RING, false>(&g->ph[0], g->M, rt * 32 * MI, ct, false, false, g->lds_w, g->lds_g, lds_offset(sp_smem), sp_smem, [] {});
 }
 
 // Counters: read-modify-write at the L2, also to look at one (as assembly: the compiler turns an addition of zero into
@@ -430,6 +438,7 @@ __global__ __launch_bounds__(NTHR + 64) void split_chain_kernel(SplitArgs a) {
   TaskOrder order{g->counters, mine, (unsigned)g->group_tasks, g->n_groups, SPLIT_SPINS, ~0u, 0, false};
   if (threadIdx.x == NTHR) task_of<L2Mem>(order, (unsigned)l2_add(mine, 1), slot);
   wg_barrier();
+  int last_ph = -1, last_rt = -1;
   for (int it = 0;; ++it) {
     const int k = __builtin_amdgcn_readfirstlane(slot[2 * (it & 1)]), grp = __builtin_amdgcn_readfirstlane(slot[2 * (it & 1) + 1]);
     if (k < 0) break;
@@ -437,17 +446,19 @@ __global__ __launch_bounds__(NTHR + 64) void split_chain_kernel(SplitArgs a) {
     while (k >= g->first[ph + 1]) ++ph;
     const int rem = k - g->first[ph];
     const int ct = rem / g->group_rows, rl = rem - ct * g->group_rows, rt = grp * g->group_rows + rl;
+    const SM_KARG LinPhase* p = &g->ph[ph];
     int* done = g->counters + SPLIT_LINE * 17 + grp * g->group_words + rl;
-    if (ctl && threadIdx.x == NTHR && ph) wait_arrivals<L2Mem>(order, done + (ph - 1) * g->group_rows, g->tiles_n[ph - 1]);
+    const bool keep = ph == last_ph && rt == last_rt && p->ln_g;      // (what it depends on has arrived already)
+    last_ph = ph; last_rt = rt;
+    if (ctl && threadIdx.x == NTHR && ph && !keep) wait_arrivals<L2Mem>(order, done + (ph - 1) * g->group_rows, g->tiles_n[ph - 1]);
     // the next number is asked for now and looked at when this task's results are on their way
     int n_next = 0;
     if (ctl && threadIdx.x == NTHR) n_next = __hip_atomic_fetch_add(mine, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     auto next = [&] { if (threadIdx.x == NTHR) task_of<L2Mem>(order, (unsigned)n_next, slot + 2 * ((it + 1) & 1)); };
-    const SM_KARG LinPhase* p = &g->ph[ph];
     const int row0 = rt * 32 * MI;
-    if (p->ln_g) split_task<T, MI, WNL, true, false, true>(p, g->M, row0, ct, ctl, g->lds_w, g->lds_g, base, sp_smem, next);
-    else if (p->ring) split_task<T, MI, WNP, false, true, true>(p, g->M, row0, ct, ctl, g->lds_w, g->lds_g, base, sp_smem, next);
-    else split_task<T, MI, WNP, false, false, true>(p, g->M, row0, ct, ctl, g->lds_w, g->lds_g, base, sp_smem, next);
+    if (p->ln_g) split_task<T, MI, WNL, true, false, true>(p, g->M, row0, ct, ctl, keep, g->lds_w, g->lds_g, base, sp_smem, next);
+    else if (p->ring) split_task<T, MI, WNP, false, true, true>(p, g->M, row0, ct, ctl, keep, g->lds_w, g->lds_g, base, sp_smem, next);
+    else split_task<T, MI, WNP, false, false, true>(p, g->M, row0, ct, ctl, keep, g->lds_w, g->lds_g, base, sp_smem, next);
     if (ctl && threadIdx.x == NTHR) asm volatile("global_atomic_add %0, %1, off" ::"v"(done + ph * g->group_rows), "v"(1) : "memory");
   }
 }
@@ -602,6 +613,7 @@ int launch_split_chain(SplitArgs& a, int* counters, int mi, void* stream) {
   a.group_rows = gr.rows; a.n_groups = gr.n; a.group_words = gr.words; a.counters = counters;
   int kmax = 0;
   for (int i = 0; i < a.n_ph; ++i) if (a.ph[i].ln_g) kmax = std::max(kmax, a.ph[i].K);
+  if (kmax > (mi == 2 ? 512 : 1024)) return (int)hipErrorInvalidValue;      // rows under LayerNorm: 8 K-tiles per thread of split_norm
   const int wnl = mi == 2 || kmax <= 512 ? 2 : 1;
   size_t ab = 0, wb = 0, gb = 0;
   int most = 0;
@@ -610,6 +622,7 @@ int launch_split_chain(SplitArgs& a, int* counters, int mi, void* stream) {
     const int wn = a.ph[i].ln_g ? wnl : mi;
     size_t x, y, z;
     need(a.ph[i].K, 2, mi, wn, a.ph[i].ln_g != nullptr, a.ph[i].ring, &x, &y, &z);
+    if (a.ph[i].ln_g) { const size_t panel = y / (32 * wn) * (32 * mi); y = std::max(y, x); x = panel; }      // the result tile over W
     ab = std::max(ab, x); wb = std::max(wb, y); gb = std::max(gb, z);
     a.tiles_n[i] = (a.ph[i].N + 32 * wn - 1) / (32 * wn);
     a.first[i + 1] = a.first[i] + a.tiles_n[i] * gr.rows;
