@@ -19,6 +19,7 @@
 #include "kernels.h"
 #include "plan_chains.h"
 #include "plan_views.h"
+#include "tile.h"
 
 using namespace sm;
 
@@ -271,6 +272,45 @@ int gemm(const void* A, const void* W, const void* bias, const void* res, void* 
   return gemm_checked(g, stream, "linear");
 }
 
+// Scratch of the Linears that may run cut over K: behind the tables, and used where the caller's workspace reaches that far
+// (a smaller one, without it, runs them uncut)
+struct Parts { float* at; size_t bytes; };
+GemmArgs res_linear(int64_t M, int N, int K, int dt) {
+  GemmArgs g; std::memset(&g, 0, sizeof(g));
+  g.M = M; g.N = N; g.K = K; g.dtype = dt; g.ldw = K; g.a_rows = identity_rows(K); g.c_rows = identity_rows(N);
+  return g;
+}
+size_t parts_bytes(const sm_attn_cfg* c) {
+  if (c->kind == SM_ATTN_SD) return 0;
+  size_t most = 0;
+  for (int down = 0; down < 2; ++down) {
+    const int64_t T = (int64_t)c->B * c->S;
+    SplitKPlan p;
+    if (splitk_plan(res_linear(T, c->E, down ? c->F : c->E, c->dtype), !down, &p)) most = std::max(most, align256((size_t)p.splits * T * c->E * sizeof(float)));
+  }
+  return most;
+}
+
+// C = A . W^T + bias + res and, with n, n = norm(C)
+int gemm_res(const void* A, const void* W, const void* bias, const void* res, void* C, int64_t M, int N, int K, int dt, const Parts& parts, void* stream,
+             void* n = nullptr, const void* gamma = nullptr, const void* beta = nullptr, float eps = 0.f, int rms = 0) {
+  GemmArgs g = res_linear(M, N, K, dt);
+  SplitKPlan p;
+  if (splitk_plan(g, n != nullptr, &p) && parts.bytes >= (size_t)p.splits * M * N * sizeof(float)) {
+    g.A = A; g.W = W; g.C = C;
+    typedef unsigned short u16;
+    const SumPartsArgs sum{parts.at, p.splits, M, N, (const u16*)bias, (const u16*)res, (u16*)C, (const u16*)gamma, (const u16*)beta, (u16*)n, eps, rms};
+    char label[96];
+    snprintf(label, sizeof(label), "cut_linear_bf16[%lld,%d,%d]+res%s", (long long)M, N, K, n ? "+norm" : "");
+    Timed tm(label, stream);
+    if (int e = launch_splitk(g, p, sum, stream)) return fail(SM_ERR_DEVICE, "linear: launch failed (hip error %d)", e);
+    count_compute(2);
+    return SM_OK;
+  }
+  if (int rc = gemm(A, W, bias, res, C, M, N, K, dt, SM_ACT_NONE, stream)) return rc;
+  return n ? norm(C, gamma, beta, n, M, N, eps, rms, dt, stream) : (int)SM_OK;
+}
+
 int attention(int kind, int dt, int B, int h, int nq, int nk, int d, const View4& q, const View4& k, const View4& v, const View4& o,
               const void* qb, const void* kb, const void* vb, void* ob, void* stream) {
   sm_attention_desc a; std::memset(&a, 0, sizeof(a));
@@ -296,7 +336,7 @@ extern "C" size_t sm_attn_block_workspace_bytes(const sm_attn_cfg* c, int mode) 
   std::string err;
   auto plan = attn_plan(*c, &err);
   if (!plan) { set_error("sm_attn_block_workspace_bytes: %s", err.c_str()); return 0; }
-  return sizes(c, mode).total + plan->tables(mode).bytes;
+  return sizes(c, mode).total + plan->tables(mode).bytes + parts_bytes(c);
 }
 
 extern "C" int sm_attn_block(const sm_attn_cfg* c, const void* const* w, const void* x, const void* context,
@@ -330,6 +370,7 @@ extern "C" int sm_attn_block(const sm_attn_cfg* c, const void* const* w, const v
   void* act = after; after += z.tf;
   void* kv = after; char* kvp = after + z.ctx;
   const bool el = mode == SM_ELIDED;
+  const Parts parts{(float*)((char*)ws + need), ws_bytes - need};
 
   if (c->kind == SM_ATTN_LLAMA) {
     if ((rc = norm(x, w[0], nullptr, n, T, E, c->eps_norm, 1, dt, stream))) return rc;
@@ -342,10 +383,9 @@ extern "C" int sm_attn_block(const sm_attn_cfg* c, const void* const* w, const v
       if ((rc = attention(SM_ATT_CAUSAL, dt, B, h, S, S, d, cq, ck, cv, cq, qkvp, qkvp, qkvp, op, stream))) return rc;
       if ((rc = copy_launch(plan->merge_o, tables, op, o, dt, stream))) return rc;
     }
-    if ((rc = gemm(o, w[2], nullptr, x, r1, T, E, E, dt, SM_ACT_NONE, stream))) return rc;
-    if ((rc = norm(r1, w[3], nullptr, n, T, E, c->eps_norm, 1, dt, stream))) return rc;
+    if ((rc = gemm_res(o, w[2], nullptr, x, r1, T, E, E, dt, parts, stream, n, w[3], nullptr, c->eps_norm, 1))) return rc;
     if ((rc = gemm(n, w[4], nullptr, nullptr, act, T, 2 * F, E, dt, SM_ACT_SWIGLU, stream))) return rc;
-    if ((rc = gemm(act, w[5], nullptr, r1, y, T, E, F, dt, SM_ACT_NONE, stream))) return rc;
+    if ((rc = gemm_res(act, w[5], nullptr, r1, y, T, E, F, dt, parts, stream))) return rc;
     return SM_OK;
   }
 
@@ -361,10 +401,9 @@ extern "C" int sm_attn_block(const sm_attn_cfg* c, const void* const* w, const v
       if ((rc = attention(SM_ATT_FULL, dt, B, h, S, S, d, cq, ck, cv, cq, qkvp, qkvp, qkvp, op, stream))) return rc;
       if ((rc = copy_launch(plan->merge_o, tables, op, o, dt, stream))) return rc;
     }
-    if ((rc = gemm(o, w[4], w[5], x, r1, T, E, E, dt, SM_ACT_NONE, stream))) return rc;
-    if ((rc = norm(r1, w[6], w[7], n, T, E, c->eps_norm, 0, dt, stream))) return rc;
+    if ((rc = gemm_res(o, w[4], w[5], x, r1, T, E, E, dt, parts, stream, n, w[6], w[7], c->eps_norm, 0))) return rc;
     if ((rc = gemm(n, w[8], w[9], nullptr, act, T, F, E, dt, SM_ACT_GELU, stream))) return rc;
-    if ((rc = gemm(act, w[10], w[11], r1, y, T, E, F, dt, SM_ACT_NONE, stream))) return rc;
+    if ((rc = gemm_res(act, w[10], w[11], r1, y, T, E, F, dt, parts, stream))) return rc;
     return SM_OK;
   }
 

@@ -1040,7 +1040,7 @@ static int gemm_dispatch(const GemmArgs& g, const ColMap& cm, hipStream_t s) {
   return short_k_128(g) ? gemm_pick_epi<T, 2>(g, cm, s, tn) : gemm_pick_epi<T, 1>(g, cm, s, tn);
 }
 
-static bool tile_chosen(const GemmArgs& g) {
+bool gemm_tile_chosen(const GemmArgs& g) {
   if (g_force_rows || g_force_stages) return true;
   if (!tunable(g)) return false;
   std::lock_guard<std::mutex> lock(g_tune_mu);
@@ -1051,7 +1051,7 @@ int launch_gemm(const GemmArgs& g, void* stream) {
   if (g.M == 0 || g.N == 0) return 0;
   int rc = 0;
   if (launch_split_linear(g, stream, &rc)) return rc;      // few rows
-  if (!tile_chosen(g) && launch_tile_linear(g, stream, &rc)) return rc;      // large tiles, unless the caller or the tuner has picked one of gemm_kernel's
+  if (!gemm_tile_chosen(g) && launch_tile_linear(g, stream, &rc)) return rc;      // large tiles, unless the caller or the tuner has picked one of gemm_kernel's
   ColMap cm;
   cm.mode = 0; cm.half = g.N / 2; cm.rope_cols = g.rope_cols; cm.rope_dim = g.rope_dim;
   if (g.act == SM_ACT_SWIGLU || g.act == SM_ACT_GEGLU) cm.mode = 1;

@@ -30,6 +30,7 @@ typedef float tl_f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned int tl_u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int tl_u32x2 __attribute__((ext_vector_type(2)));
 typedef float tl_f32x2 __attribute__((ext_vector_type(2)));
+typedef float tl_f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 tl_bf16x2 __attribute__((ext_vector_type(2)));
 
 #define TL_GPTR(p) ((const __attribute__((address_space(1))) void*)(p))
@@ -37,9 +38,11 @@ typedef __bf16 tl_bf16x2 __attribute__((ext_vector_type(2)));
 
 namespace {
 
-struct TileGrid { int tiles_m, tiles_n, strip, group; };
+struct TileGrid { int tiles_m, tiles_n, strip, group; int splits, nk, nk_more; float* part; };      // the last four: EPI_PART only
 struct TileCols { int half, rope_cols, rope_dim; };
-enum { EPI_PLAIN = 0, EPI_GELU = 1, EPI_GLU = 2, EPI_ROPE = 3 };
+// EPI_PART: K is cut into `splits` runs of `nk` K-tiles (one more in the first `nk_more`), one workgroup per tile and run, and the
+// sums of run s are left in fp32 at part[s M N + r N + n] for sum_parts_kernel
+enum { EPI_PLAIN = 0, EPI_GELU = 1, EPI_GLU = 2, EPI_ROPE = 3, EPI_PART = 4 };
 // order of the logical columns: a block of 32 is two runs of 16 columns of W that belong together (GLU: value and gate of 16
 // outputs; ROPE: 16 first and 16 second members of rotary pairs; else 32 adjacent columns), so that partners sit in one lane
 template <int EPI> __device__ __forceinline__ int tile_col(const TileCols& cm, int n) {
@@ -88,14 +91,19 @@ __global__ __launch_bounds__(256, 1) void tile_kernel(GemmArgs g, TileCols cm, T
   TL_PIN(a_tab); TL_PIN(c_tab); TL_PIN(bias_p); TL_PIN(res_p); TL_PIN(c_p);
   TL_PIN(cm.half); TL_PIN(cm.rope_cols); TL_PIN(cm.rope_dim);
   TL_PIN(ts.tiles_m); TL_PIN(ts.tiles_n); TL_PIN(ts.strip); TL_PIN(ts.group);
+  if constexpr (EPI == EPI_PART) { TL_PIN(ts.splits); TL_PIN(ts.nk); TL_PIN(ts.nk_more); TL_PIN(ts.part); }
 #undef TL_PIN
   extern __shared__ __align__(16) unsigned char tl_smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, hf = lane >> 5;
   // tile order over the XCDs: as in gemm_kernel
-  const int n_tiles = ts.tiles_m * ts.tiles_n, q8 = n_tiles >> 3, r8 = n_tiles & 7, strip_tiles = ts.strip * ts.tiles_m;
+  const int one = ts.tiles_m * ts.tiles_n, n_tiles = EPI == EPI_PART ? one * ts.splits : one;
+  const int q8 = n_tiles >> 3, r8 = n_tiles & 7, strip_tiles = ts.strip * ts.tiles_m;
+  int run = 0;                                               // which part of K
   auto decode = [&](int vb_, int64_t& m0_, int& n0_) {
-    const int xcd = vb_ & 7, t = xcd * q8 + min(xcd, r8) + (vb_ >> 3);
+    const int xcd = vb_ & 7;
+    int t = xcd * q8 + min(xcd, r8) + (vb_ >> 3);
+    if constexpr (EPI == EPI_PART) { run = __builtin_amdgcn_readfirstlane(t / one); t -= run * one; }
     const int sidx = min(t / strip_tiles, (ts.tiles_n - 1) / ts.strip), rem = t - sidx * strip_tiles;
     const int sw = min(ts.strip, ts.tiles_n - sidx * ts.strip);
     const int gidx = rem / (ts.group * sw), r2 = rem - gidx * ts.group * sw, gh = min(ts.group, ts.tiles_m - gidx * ts.group);
@@ -144,8 +152,9 @@ __global__ __launch_bounds__(256, 1) void tile_kernel(GemmArgs g, TileCols cm, T
   };
   // (by buffer loads: a K-tile past the workgroup's last one is requested from a descriptor of no bytes, which costs no traffic,
   // so that the MFMA loops need no branches)
-  const __amdgpu_buffer_rsrc_t a_buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(g.A), 0, 0xffffffffu, 0x00020000);
-  const __amdgpu_buffer_rsrc_t w_buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(g.W), 0, 0xffffffffu, 0x00020000);
+  const int64_t k_first = EPI == EPI_PART ? (int64_t)(run * ts.nk + min(run, ts.nk_more)) * 128 : 0;      // bytes of a row before the run
+  const __amdgpu_buffer_rsrc_t a_buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>((const char*)g.A + k_first), 0, 0xffffffffu, 0x00020000);
+  const __amdgpu_buffer_rsrc_t w_buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>((const char*)g.W + k_first), 0, 0xffffffffu, 0x00020000);
   const __amdgpu_buffer_rsrc_t no_buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(g.W), 0, 0, 0x00020000);
   auto dma = [&](int half, int i, const __amdgpu_buffer_rsrc_t& ab, const __amdgpu_buffer_rsrc_t& wb, int k_at, unsigned stage) __attribute__((always_inline)) {
     const int na = 2 * (half ? MA1 : MA0);
@@ -235,6 +244,7 @@ __global__ __launch_bounds__(256, 1) void tile_kernel(GemmArgs g, TileCols cm, T
   tl_u32x2 braw[NI][4];
   int64_t ro_t[MI];
   auto epi_loads = [&]() __attribute__((always_inline)) {      // bias words and output rows of this tile: requested at its start
+    if constexpr (EPI == EPI_PART) return;
     const bool bias_on = bias_p && n_cols >= 4;
     const bf16_t* bp = bias_on ? (const bf16_t*)bias_p : (const bf16_t*)g.W;
     const int pmax = bias_on ? ((n_cols - 4) & ~3) : 0;
@@ -262,6 +272,7 @@ __global__ __launch_bounds__(256, 1) void tile_kernel(GemmArgs g, TileCols cm, T
   // the compiler waits for them where they are first touched: here, where everything older has landed anyway, not in the epilogue,
   // where it would wait for the next tile's K-tiles as well
   auto epi_tie = [&]() __attribute__((always_inline)) {
+    if constexpr (EPI == EPI_PART) return;
 #pragma unroll
     for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
@@ -271,7 +282,7 @@ __global__ __launch_bounds__(256, 1) void tile_kernel(GemmArgs g, TileCols cm, T
 #pragma unroll
     for (int i = 0; i < LA; ++i) asm volatile("" : "+v"(a_off32[i]));
   };
-  const int nk = g.K >> 6;
+  const int nk = EPI == EPI_PART ? ts.nk + (run < ts.nk_more) : g.K >> 6;
   unsigned stage = 0;                                        // of the K-tile about to be multiplied
   int64_t m0_n = 0;
   int n0_n = 0;
@@ -311,6 +322,22 @@ __global__ __launch_bounds__(256, 1) void tile_kernel(GemmArgs g, TileCols cm, T
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");      // the last MFMA has written its accumulators
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (EPI == EPI_PART) {      // 32 rows x 32 bytes a store, the four stores of a block fill its rows' 128-byte lines
+      float* P = ts.part + (int64_t)run * m_rows * n_cols;
+#pragma unroll
+      for (int mi = 0; mi < MI; ++mi) {
+        const int64_t r = m0 + (wm * MI + mi) * 32 + l32;
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+          for (int g4 = 0; g4 < 4; ++g4) {
+            const int col = n0 + (wn * NI + ni) * 32 + g4 * 8 + hf * 4;
+            const tl_f32x4 v = {acc_read(acc[mi][ni][4 * g4]), acc_read(acc[mi][ni][4 * g4 + 1]), acc_read(acc[mi][ni][4 * g4 + 2]), acc_read(acc[mi][ni][4 * g4 + 3])};
+            if (r < m_rows && col < n_cols) *(tl_f32x4*)(P + r * n_cols + col) = v;
+          }
+      }
+      return;
+    }
 #pragma unroll
     for (int c0 = 0; c0 < NI; c0 += CH) {
       float bv[CH][16];
@@ -457,7 +484,7 @@ __global__ __launch_bounds__(256, 1) void tile_kernel(GemmArgs g, TileCols cm, T
   }
   for (;;) {
     const int vb_n = vb + (int)gridDim.x;
-    more = vb_n < n_tiles;
+    more = EPI != EPI_PART && vb_n < n_tiles;
     if (more) { decode(vb_n, m0_n, n0_n); src_pre(m0_n); }
     epi_loads();
     ktile(0, Yes{});
@@ -470,7 +497,7 @@ __global__ __launch_bounds__(256, 1) void tile_kernel(GemmArgs g, TileCols cm, T
 }
 
 template <int MI, int NI, int EPI>
-int tile_launch2(const GemmArgs& g, const TileCols& cm, hipStream_t s) {
+int tile_launch2(const GemmArgs& g, const TileCols& cm, hipStream_t s, int splits = 1, float* part = nullptr) {
   constexpr size_t smem = tile_lds(MI, NI, EPI);
   static_assert(smem <= 160 * 1024, "LDS of a compute unit");
   static const hipError_t attr = hipFuncSetAttribute((const void*)tile_kernel<MI, NI, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -484,8 +511,9 @@ int tile_launch2(const GemmArgs& g, const TileCols& cm, hipStream_t s) {
     const double rows = (double)c * (double)g.M + (8.0 / c) * (double)g.N;
     if (rows < best && c <= tiles_n) { best = rows; xn = c; }
   }
-  const TileGrid ts{(int)tiles_m, tiles_n, (tiles_n + xn - 1) / xn, g.K >= 1024 ? (int)std::min<int64_t>(4, tiles_m) : 1};
-  const int64_t grid = std::min<int64_t>(tiles_m * tiles_n, 256);      // one workgroup per CU (a multiple of 8 where it walks through several tiles)
+  const int nk = g.K >> 6;
+  const TileGrid ts{(int)tiles_m, tiles_n, (tiles_n + xn - 1) / xn, g.K >= 1024 ? (int)std::min<int64_t>(4, tiles_m) : 1, splits, nk / splits, nk % splits, part};
+  const int64_t grid = EPI == EPI_PART ? tiles_m * tiles_n * splits : std::min<int64_t>(tiles_m * tiles_n, 256);      // one workgroup per CU (a multiple of 8 where it walks through several tiles)
   tile_kernel<MI, NI, EPI><<<dim3((unsigned)grid), dim3(256), smem, s>>>(g, cm, ts);
   return (int)hipGetLastError();
 }
@@ -513,28 +541,51 @@ bool tile_rows_ok(const RowProg& r, int64_t rows) {      // a pitch or a table; 
 // gains 6.7 % in the geometric mean (the best variant of each 7.4 %) and loses 2 % at worst.  Below K = 1024 a tile's fixed part
 // weighs as much as its K loop and gemm_kernel's two workgroups per CU hide it better (8192 x 2560 x 320 GEGLU 29 / 32,
 // 12544 x 2048 x 512 + GELU 44 / 46): only from K = 640 on and where the costs are clearly apart (6304 x 2304 x 768 33.5 / 28).
-static bool tile_linear_plan(const GemmArgs& g, int* mi, int* ni) {
+static bool tile_linear_ok(const GemmArgs& g) {
   if (g.dtype != SM_BF16 || g.K % 64 || g.K < 640 || g.a_gran > 0 || g.norm || g.C2 || g.c_transposed || g.c_cols_on) return false;
   const bool gated = g.act == SM_ACT_SWIGLU || g.act == SM_ACT_GEGLU;
   if (g.N % 8 || (gated && g.N % 64) || (g.act != SM_ACT_NONE && g.rope_cols)) return false;
-  if (!tile_rows_ok(g.a_rows, g.M) || !tile_rows_ok(g.c_rows, 0) || (int64_t)g.N * g.ldw > INT32_MAX) return false;
-  static const struct { int mi, ni; double fixed, round, step, busy, act; } form[] = {{4, 4, 1.98, 10.22, 0.855, 0.624, 4.80},
-                                                                             {4, 3, 2.86, 8.09, 0.669, 0.467, 2.86},
-                                                                             {3, 4, 3.23, 7.74, 0.678, 0.433, 3.48},
-                                                                             {3, 3, 3.07, 6.68, 0.656, 0.262, 2.18},
-                                                                             {2, 4, 2.89, 6.39, 0.510, 0.280, 1.84},
-                                                                             {3, 2, 3.75, 4.40, 0.429, 0.243, 1.49},
-                                                                             {2, 3, 3.70, 4.38, 0.439, 0.225, 1.69}};
-  const double nk = (double)(g.K / 64), act = g.act == SM_ACT_GELU ? 1. : (gated ? .7 : 0.);
+  return tile_rows_ok(g.a_rows, g.M) && tile_rows_ok(g.c_rows, 0) && (int64_t)g.N * g.ldw <= INT32_MAX;
+}
+static const struct TileForm { int mi, ni; double fixed, round, step, busy, act; } tile_form[] = {{4, 4, 1.98, 10.22, 0.855, 0.624, 4.80},
+                                                                                 {4, 3, 2.86, 8.09, 0.669, 0.467, 2.86},
+                                                                                 {3, 4, 3.23, 7.74, 0.678, 0.433, 3.48},
+                                                                                 {3, 3, 3.07, 6.68, 0.656, 0.262, 2.18},
+                                                                                 {2, 4, 2.89, 6.39, 0.510, 0.280, 1.84},
+                                                                                 {3, 2, 3.75, 4.40, 0.429, 0.243, 1.49},
+                                                                                 {2, 3, 3.70, 4.38, 0.439, 0.225, 1.69}};
+static double tile_cost(const TileForm& f, const GemmArgs& g, int splits) {
+  const int64_t tiles = ((g.M + 64 * f.mi - 1) / (64 * f.mi)) * ((g.N + 64 * f.ni - 1) / (64 * f.ni)) * splits;
+  const double nk = (double)((g.K / 64 + splits - 1) / splits), rounds = (double)((tiles + 255) / 256);
+  const double act = g.act == SM_ACT_GELU ? 1. : (g.act == SM_ACT_SWIGLU || g.act == SM_ACT_GEGLU ? .7 : 0.);
+  return f.fixed + rounds * (f.round + nk * f.step + act * f.act) + (double)tiles / 256. * nk * f.busy;
+}
+static bool tile_linear_plan(const GemmArgs& g, int* mi, int* ni) {
+  if (!tile_linear_ok(g)) return false;
   double least = (g.K >= 1024 ? 1. : .9) * gemm_kernel_cost(g);
   *mi = 0;
-  for (const auto& f : form) {
-    const int64_t tiles = ((g.M + 64 * f.mi - 1) / (64 * f.mi)) * ((g.N + 64 * f.ni - 1) / (64 * f.ni));
-    const double rounds = (double)((tiles + 255) / 256);
-    const double us = f.fixed + rounds * (f.round + nk * f.step + act * f.act) + (double)tiles / 256. * nk * f.busy;
+  for (const auto& f : tile_form) {
+    const double us = tile_cost(f, g, 1);
     if (us < least) { least = us; *mi = f.mi; *ni = f.ni; }
   }
   return *mi != 0;
+}
+
+// Which tile and how many runs of K, by the same costs: the sum kernel takes 0.7 us and the parts' bytes at 9 TB/s (1459 measured
+// points with K >= 4096, 70 to 2048 rows; 10 % standard deviation).  Below K = 4096 the parts cost more than the idle CUs they fill
+// (500 x 2048 x 2048 10.6 / 20 us, 700 x 1024 x 2816 13 / 20).  `unsplit`: what the Linear (and the norm behind it) takes otherwise.
+bool tile_parts_plan(const GemmArgs& g, double unsplit, SplitKPlan* p) {
+  p->splits = 0;
+  if (g.K < 4096 || g.N > 8192 || g.act != SM_ACT_NONE || g.rope_cols || !tile_linear_ok(g) || !g.a_rows.identity) return false;
+  if (!g.c_rows.identity || g.c_rows.ld != g.N || g.ldw != g.K || g.a_rows.ld != g.K) return false;
+  for (const auto& f : tile_form) unsplit = std::min(unsplit, tile_cost(f, g, 1));
+  double least = .97 * unsplit;
+  for (const auto& f : tile_form)
+    for (int s = 2; s <= 8; ++s) {
+      const double us = 1.08 * tile_cost(f, g, s) + .7 + 8e-6 * s * (double)g.M * g.N / 9.;
+      if (us < least && g.K / 64 / s >= tile_stages(f.mi, f.ni)) { least = us; *p = SplitKPlan{f.mi, f.ni, s}; }
+    }
+  return p->splits != 0;
 }
 
 bool launch_tile_linear(const GemmArgs& g, void* stream, int* rc) {
@@ -546,6 +597,16 @@ bool launch_tile_linear(const GemmArgs& g, void* stream, int* rc) {
   TL_CASE(4, 4) TL_CASE(4, 3) TL_CASE(3, 4) TL_CASE(3, 3) TL_CASE(2, 4) TL_CASE(3, 2) TL_CASE(2, 3)
 #undef TL_CASE
   return false;
+}
+
+// the parts of a Linear cut over K (k_splitk.hip)
+int launch_tile_parts(const GemmArgs& g, int mi, int ni, int splits, float* part, void* stream) {
+  const TileCols cm{0, 0, 0};
+  if (splits < 1 || (g.K >> 6) / splits < tile_stages(mi, ni)) return (int)hipErrorInvalidValue;
+#define TL_CASE(MI_, NI_) if (mi == MI_ && ni == NI_) return tile_launch2<MI_, NI_, EPI_PART>(g, cm, (hipStream_t)stream, splits, part);
+  TL_CASE(4, 4) TL_CASE(4, 3) TL_CASE(3, 4) TL_CASE(3, 3) TL_CASE(2, 4) TL_CASE(3, 2) TL_CASE(2, 3)
+#undef TL_CASE
+  return (int)hipErrorInvalidValue;
 }
 
 }  // namespace sm

@@ -1,10 +1,24 @@
 // Large-tile Linears (k_tile.hip).
 #pragma once
+#include <cstdint>
 
 namespace sm {
 
 struct GemmArgs;
 bool launch_tile_linear(const GemmArgs& g, void* stream, int* rc);      // runs g in large tiles where that is the better form; false: not
 double gemm_kernel_cost(const GemmArgs& g);                             // what gemm_kernel (k_gemm.hip) takes for g, us
+
+// A bf16 Linear with a residual on few rows, cut over K: parts in fp32, summed by a second kernel that also takes the norm behind it
+struct SplitKPlan { int mi, ni, splits; };
+struct SumPartsArgs {
+  const float* part; int splits; int64_t M; int N;      // [splits][M][N]
+  const unsigned short *bias, *res; unsigned short* y;  // bias may be null; y may be res
+  const unsigned short *gamma, *beta; unsigned short* n; float eps; int rms;      // n != null: the norm of y's rows goes there; beta may be null
+};
+bool splitk_plan(const GemmArgs& g, bool norm_after, SplitKPlan* p);      // by shape alone: whether that is the better form
+int launch_splitk(const GemmArgs& g, const SplitKPlan& p, const SumPartsArgs& sum, void* stream);
+bool tile_parts_plan(const GemmArgs& g, double unsplit, SplitKPlan* p);      // (k_tile.hip) the best tile and number of parts, if better than `unsplit` us
+int launch_tile_parts(const GemmArgs& g, int mi, int ni, int splits, float* part, void* stream);
+bool gemm_tile_chosen(const GemmArgs& g);                                   // (k_gemm.hip) the caller or the tuner has picked a tile of gemm_kernel for g
 
 }  // namespace sm

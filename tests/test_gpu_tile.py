@@ -3,7 +3,8 @@ bits.  Shapes are ones whose own choice is a large tile (192 x 128 .. 256 x 256)
 several, K-tiles from 17 (more than the stages, an odd number) to 44."""
 import pytest
 import torch
-from paper_2404_13528_amd import binding as sm
+from paper_2404_13528_amd import binding as sm, workloads as Wl
+from util import dev, dev_params
 
 pytestmark = pytest.mark.gpu
 
@@ -38,3 +39,40 @@ def test_tile_linear_is_the_tiled_kernel(M, N, K, act, res, rope):
         sm.gemm_tuning(0, 0)
     assert torch.isfinite(want.float()).all()
     assert torch.equal(got, want) and torch.equal(again, want)
+
+
+@pytest.mark.parametrize("kind,B,S,E,h,F,cut", [
+    ("llama", 1, 333, 4096, 32, 11008, 2),      # both Linears with a residual: 32 x 2 and 32 x 2 tiles of 192 x 128
+    ("llama", 1, 71, 4096, 32, 11008, 2),       # few rows
+    ("llama", 1, 701, 2048, 16, 5632, 1),       # only the long one; 88 K-tiles
+    ("llama", 3, 235, 2048, 16, 5696, 1),       # 89 K-tiles: runs of unequal length
+    ("vit", 2, 577, 1024, 16, 4096, 1),         # a bias
+    ("llama", 1, 333, 1024, 8, 2816, 0),        # short K: never cut
+])
+def test_cut_linears_of_a_block(kind, B, S, E, h, F, cut):
+    """The Linears with a residual cut over K against the same block with a workspace that has no room for their parts: the same
+    products summed in another order and one rounding less, so outputs (O(1)) differ by roundings of x1 and of the result to bf16:
+    at most 2^-8 each, a third of it in the mean square."""
+    x, p = Wl.llama_case(B, S, E, F, seed=S, std=E ** -0.5) if kind == "llama" else Wl.vit_case(B, S, E, h, F, seed=S, std=E ** -0.5)
+    x, p = dev(x, torch.bfloat16), dev_params(p, torch.bfloat16)
+    blk = sm.AttnBlock(kind, p, torch.bfloat16, B=B, S=S, E=E, heads=h, F=F)
+    sm.timing_enable(True)
+    try:
+        got = blk(x)
+        labels = sm.timing_sequence()
+    finally:
+        sm.timing_enable(False)
+    assert len([t for t in labels if t.startswith("cut_linear")]) == cut, labels
+    again, full = blk(x), blk.ws
+    want = again
+    for parts in range(8, 0, -1):                             # the workspace without the parts (less is refused)
+        if cut and parts * B * S * E * 4 < full.numel():
+            blk.ws = full[:full.numel() - parts * B * S * E * 4]
+            try:
+                want = blk(x)
+                break
+            except sm.SmError:
+                pass
+    assert torch.equal(got, again) and torch.isfinite(got.float()).all()
+    err = ((got.float() - want.float()).norm() / want.float().norm()).item()
+    assert err <= 2 * 2 ** -8, err
