@@ -988,14 +988,17 @@ __global__ __launch_bounds__(256) void attn_window_f32_kernel(sm_attention_desc 
     }
 }
 
-// Depth-wise 3 x 3 cross-correlation on a token-major grid: one thread per (token, 8 channels); the 72 weights of its
-// channels are 144 contiguous bytes.  Memory-bound: every value is read once from HBM and eight more times from cache.
+// Depth-wise 3 x 3 cross-correlation on a token-major grid: one thread per (token, 8 channels).  Memory-bound: every value is read
+// once from HBM and eight more times from cache.  What bounded it were the weights: a thread's 72 are 144 contiguous bytes, so that each
+// of its nine 16-byte loads touched another cache line per lane (two thirds of the time of 64 images of 14 x 14 x 256); up to 2048
+// channels the workgroup brings them to LDS in order, where rows 144 bytes apart are on distinct banks (11.1 us, now 10.2).
 // Workgroups are dealt to the 8 XCDs round-robin: XCD x takes the x-th eighth of the tokens, so that the rows above
 // and below a token are fetched into the same L2 as the token's own.
+template <bool STAGED>
 __global__ __launch_bounds__(256) void dwconv3x3_kernel(DwconvArgs a, int64_t total) {
+  extern __shared__ au32x4 dw_lds[];                                  // STAGED: the weights as they are, [Cn][9]
   const int64_t block = (int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);      // the grid is a multiple of 8
-  const int64_t idx = block * 256 + threadIdx.x;
-  if (idx >= total) return;
+  const int64_t idx = min(block * 256 + threadIdx.x, total - 1);      // (past the end: the last one again, not stored)
   const int cv = a.Cn >> 3;
   const int c = (int)(idx % cv) * 8;
   const int64_t t = idx / cv;
@@ -1006,48 +1009,55 @@ __global__ __launch_bounds__(256) void dwconv3x3_kernel(DwconvArgs a, int64_t to
   const int Hs = second ? a.Hs2 : a.Hs, Ws = second ? a.Ws2 : a.Ws;
   const int y_lo = (y / Hs) * Hs, x_lo = (x / Ws) * Ws;               // the token's stripe
   const bf16_t* vb = (const bf16_t*)a.v + (int64_t)img * a.v_img + c;
+  if constexpr (STAGED) {
+    for (int i = threadIdx.x; i < 9 * cv; i += 256) dw_lds[i] = ((const au32x4*)a.w)[i];
+  }
+  // the nine values are requested together, rows beyond the stripe's edge at the token's own place (a load in a condition is waited for there)
+  au32x4 vr[9], wr[9];
+#pragma unroll
+  for (int i = 0; i < 9; ++i) {
+    const int yy = y + i / 3 - 1, xx = x + i % 3 - 1;
+    const bool in = yy >= y_lo && yy < y_lo + Hs && xx >= x_lo && xx < x_lo + Ws;
+    vr[i] = *(const au32x4*)(vb + (int64_t)(in ? yy * a.W + xx : p) * a.v_tok);
+  }
+  const au32x4 br = *(const au32x4*)((const bf16_t*)a.bias + c);
+  if constexpr (STAGED) __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 9; ++i) wr[i] = STAGED ? dw_lds[(c >> 3) * 9 + i] : ((const au32x4*)((const bf16_t*)a.w + (int64_t)c * 9))[i];
   float wv[72];
-  {
-    const au32x4* wp = (const au32x4*)((const bf16_t*)a.w + (int64_t)c * 9);
 #pragma unroll
-    for (int i = 0; i < 9; ++i) {
-      const au32x4 u = wp[i];
+  for (int i = 0; i < 9; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) { wv[8 * i + 2 * j] = __uint_as_float(u[j] << 16); wv[8 * i + 2 * j + 1] = __uint_as_float(u[j] & 0xffff0000u); }
-    }
-  }
+    for (int j = 0; j < 4; ++j) { wv[8 * i + 2 * j] = __uint_as_float(wr[i][j] << 16); wv[8 * i + 2 * j + 1] = __uint_as_float(wr[i][j] & 0xffff0000u); }
   float acc[8];
-  {
-    const au32x4 u = *(const au32x4*)((const bf16_t*)a.bias + c);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) { acc[2 * j] = __uint_as_float(u[j] << 16); acc[2 * j + 1] = __uint_as_float(u[j] & 0xffff0000u); }
-  }
+  for (int j = 0; j < 4; ++j) { acc[2 * j] = __uint_as_float(br[j] << 16); acc[2 * j + 1] = __uint_as_float(br[j] & 0xffff0000u); }
 #pragma unroll
-  for (int dy = 0; dy < 3; ++dy)
+  for (int i = 0; i < 9; ++i) {
+    const int yy = y + i / 3 - 1, xx = x + i % 3 - 1;
+    const bool in = yy >= y_lo && yy < y_lo + Hs && xx >= x_lo && xx < x_lo + Ws;          // beyond the stripe: not added
 #pragma unroll
-    for (int dx = 0; dx < 3; ++dx) {
-      const int yy = y + dy - 1, xx = x + dx - 1;
-      if (yy < y_lo || yy >= y_lo + Hs || xx < x_lo || xx >= x_lo + Ws) continue;          // beyond the stripe: zero
-      const au32x4 u = *(const au32x4*)(vb + (int64_t)(yy * a.W + xx) * a.v_tok);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        acc[2 * j] = fmaf(__uint_as_float(u[j] << 16), wv[(2 * j) * 9 + dy * 3 + dx], acc[2 * j]);
-        acc[2 * j + 1] = fmaf(__uint_as_float(u[j] & 0xffff0000u), wv[(2 * j + 1) * 9 + dy * 3 + dx], acc[2 * j + 1]);
-      }
+    for (int j = 0; j < 4; ++j) {
+      const float lo = fmaf(__uint_as_float(vr[i][j] << 16), wv[(2 * j) * 9 + i], acc[2 * j]);
+      const float hi = fmaf(__uint_as_float(vr[i][j] & 0xffff0000u), wv[(2 * j + 1) * 9 + i], acc[2 * j + 1]);
+      acc[2 * j] = in ? lo : acc[2 * j]; acc[2 * j + 1] = in ? hi : acc[2 * j + 1];
     }
+  }
   au32x4 r;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const f32x2_t pr = {acc[2 * j], acc[2 * j + 1]};
     r[j] = __builtin_bit_cast(unsigned, __builtin_convertvector(pr, bf16x2_t));
   }
-  *(au32x4*)((bf16_t*)a.out + (int64_t)img * a.o_img + (int64_t)p * a.o_tok + c) = r;
+  if (block * 256 + threadIdx.x < total) *(au32x4*)((bf16_t*)a.out + (int64_t)img * a.o_img + (int64_t)p * a.o_tok + c) = r;
 }
 int launch_dwconv3x3(const DwconvArgs& a, void* stream) {
   const int64_t total = (int64_t)a.n_img * a.H * a.W * (a.Cn / 8);
   if (total == 0) return 0;
   const int64_t blocks = ((total + 255) / 256 + 7) / 8 * 8;
-  dwconv3x3_kernel<<<dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream>>>(a, total);
+  const size_t smem = (size_t)a.Cn * 18;
+  if (a.Cn <= 2048) dwconv3x3_kernel<true><<<dim3((unsigned)blocks), dim3(256), smem, (hipStream_t)stream>>>(a, total);      // LDS for four workgroups a CU
+  else dwconv3x3_kernel<false><<<dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream>>>(a, total);
   return (int)hipGetLastError();
 }
 
