@@ -538,9 +538,10 @@ bool tile_rows_ok(const RowProg& r, int64_t rows) {      // a pitch or a table; 
 // falls as more of the chip multiplies).  Measured us, gemm_kernel / this: 2048 x 22016 x 4096 SwiGLU 391 / 317 (256 x 256),
 // 2048 x 12288 x 4096 184 / 168 (256 x 192), 333 x 22016 x 4096 SwiGLU 112 / 67 (192 x 192), 333 x 12288 x 4096 53 / 43 (192 x 128),
 // 6304 x 768 x 3072 40 / 38, 6977 x 1280 x 3072 77 / 59, 1115 x 4096 x 4096 58 / 45; over the 89 shapes with K >= 1024 the choice
-// gains 6.7 % in the geometric mean (the best variant of each 7.4 %) and loses 2 % at worst.  Below K = 1024 a tile's fixed part
+// gains 6.7 % in the geometric mean (the best variant of each 7.4 %) and loses 2 % at worst.  Up to K = 1024 a tile's fixed part
 // weighs as much as its K loop and gemm_kernel's two workgroups per CU hide it better (8192 x 2560 x 320 GEGLU 29 / 32,
-// 12544 x 2048 x 512 + GELU 44 / 46): only from K = 640 on and where the costs are clearly apart (6304 x 2304 x 768 33.5 / 28).
+// 12544 x 2048 x 512 + GELU 44 / 46): only from K = 640 on and where the costs are clearly apart (6304 x 2304 x 768 33.5 / 28).  At K = 1024
+// near ties lose too (a decoder layer of 1266 tokens, E = 1024: 123 us with ratios of .89 to .99 in large tiles, 116 without).
 static bool tile_linear_ok(const GemmArgs& g) {
   if (g.dtype != SM_BF16 || g.K % 64 || g.K < 640 || g.a_gran > 0 || g.norm || g.C2 || g.c_transposed || g.c_cols_on) return false;
   const bool gated = g.act == SM_ACT_SWIGLU || g.act == SM_ACT_GEGLU;
@@ -562,7 +563,7 @@ static double tile_cost(const TileForm& f, const GemmArgs& g, int splits) {
 }
 static bool tile_linear_plan(const GemmArgs& g, int* mi, int* ni) {
   if (!tile_linear_ok(g)) return false;
-  double least = (g.K >= 1024 ? 1. : .9) * gemm_kernel_cost(g);
+  double least = (g.K > 1024 ? 1. : .88) * gemm_kernel_cost(g);
   *mi = 0;
   for (const auto& f : tile_form) {
     const double us = tile_cost(f, g, 1);
