@@ -533,7 +533,9 @@ int sm_last_launch_counts(int* n_compute, int* n_copy);
  * kernel launch of this library record a HIP event before and after itself on its stream (a small
  * perturbation: do not enable it inside a region timed as a whole); sm_timing_enable(0) stops and
  * clears.  sm_timing_report waits for the recorded events and writes one line per kernel label,
- * "label<TAB>launches<TAB>total_ms", into buf (host pointer, n bytes). */
+ * "label<TAB>launches<TAB>total_ms", into buf (host pointer, n bytes).  A Linear's label names the kernel that ran it:
+ * "gemm_..." the tiled one, "...+tile256x192" the large-tile one in tiles of that size, "splitgemm_..." the column-split
+ * one, "pgemm_..." the packed-weight one. */
 int sm_timing_enable(int on);
 int sm_timing_report(char* buf, int n);
 /* the labels of the launches recorded since sm_timing_enable(1), in launch order, one per line (host buffer; a label

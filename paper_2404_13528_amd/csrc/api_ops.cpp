@@ -4,6 +4,7 @@
 #include "index_map.h"
 #include "kernels.h"
 #include "split.h"
+#include "tile.h"
 
 using namespace sm;
 
@@ -73,6 +74,8 @@ int gemm_checked(GemmArgs& g, void* stream, const char* who) {
   snprintf(label, sizeof(label), "%s%sgemm_%s[%lld,%d,%d]%s%s%s", g.norm == 1 ? "ln+" : (g.norm == 2 ? "rms+" : ""), split_linear_use(g) ? "split" : "", g.dtype == SM_F32 ? "f32" : "bf16", (long long)g.M, g.N, g.K,
            g.act == SM_ACT_GELU ? "+gelu" : (g.act ? "+glu" : ""), g.residual ? "+res" : "", g.c_rows.identity ? "" : (g.C2 ? "+copy2" : "+scatter"));
   if (g.C2 && g.c_rows.identity) { const size_t n = strlen(label); snprintf(label + n, sizeof(label) - n, "+copy2"); }
+  int mi, ni;
+  if (timing_on() && !split_linear_use(g) && tile_linear_use(g, &mi, &ni)) { const size_t n = strlen(label); snprintf(label + n, sizeof(label) - n, "+tile%dx%d", 64 * mi, 64 * ni); }
   Timed tm(label, stream);
   int rc = launch_gemm(g, stream);
   if (rc) return fail(SM_ERR_DEVICE, "%s: launch failed (hip error %d)", who, rc);

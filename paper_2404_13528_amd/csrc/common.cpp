@@ -42,6 +42,7 @@ Timed::~Timed() {
   std::lock_guard<std::mutex> lock(t_mu);
   (void)hipEventRecord(t_recs[slot_].b, (hipStream_t)stream_);
 }
+bool timing_on() { return t_on; }
 int timing_enable(int on) {
   std::lock_guard<std::mutex> lock(t_mu);
   for (auto& r : t_recs) { (void)hipEventDestroy(r.a); (void)hipEventDestroy(r.b); }

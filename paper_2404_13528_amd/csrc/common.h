@@ -22,6 +22,7 @@ int counts(int* a, int* b);
 int timing_enable(int on);
 int timing_report(char* buf, int n);
 int timing_sequence(char* buf, int n);      // the labels of the recorded launches in launch order, one per line
+bool timing_on();                            // whether launches are recorded (labels may say more then)
 struct Timed {
   Timed(const char* label, void* stream);
   ~Timed();

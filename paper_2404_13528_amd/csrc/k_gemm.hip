@@ -1051,7 +1051,8 @@ int launch_gemm(const GemmArgs& g, void* stream) {
   if (g.M == 0 || g.N == 0) return 0;
   int rc = 0;
   if (launch_split_linear(g, stream, &rc)) return rc;      // few rows
-  if (!gemm_tile_chosen(g) && launch_tile_linear(g, stream, &rc)) return rc;      // large tiles, unless the caller or the tuner has picked one of gemm_kernel's
+  int mi, ni;
+  if (tile_linear_use(g, &mi, &ni)) return launch_tile_linear(g, mi, ni, stream);
   ColMap cm;
   cm.mode = 0; cm.half = g.N / 2; cm.rope_cols = g.rope_cols; cm.rope_dim = g.rope_dim;
   if (g.act == SM_ACT_SWIGLU || g.act == SM_ACT_GEGLU) cm.mode = 1;

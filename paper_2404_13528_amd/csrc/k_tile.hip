@@ -589,15 +589,15 @@ bool tile_parts_plan(const GemmArgs& g, double unsplit, SplitKPlan* p) {
   return p->splits != 0;
 }
 
-bool launch_tile_linear(const GemmArgs& g, void* stream, int* rc) {
-  int mi, ni;
-  if (!tile_linear_plan(g, &mi, &ni)) return false;
+// (not where the caller or the tuner has picked one of gemm_kernel's tiles)
+bool tile_linear_use(const GemmArgs& g, int* mi, int* ni) { return !gemm_tile_chosen(g) && tile_linear_plan(g, mi, ni); }
+int launch_tile_linear(const GemmArgs& g, int mi, int ni, void* stream) {
   const TileCols cm{g.N / 2, g.rope_cols, g.rope_dim};
   hipStream_t s = (hipStream_t)stream;
-#define TL_CASE(MI_, NI_) if (mi == MI_ && ni == NI_) { *rc = tile_launch<MI_, NI_>(g, cm, s); return true; }
+#define TL_CASE(MI_, NI_) if (mi == MI_ && ni == NI_) return tile_launch<MI_, NI_>(g, cm, s);
   TL_CASE(4, 4) TL_CASE(4, 3) TL_CASE(3, 4) TL_CASE(3, 3) TL_CASE(2, 4) TL_CASE(3, 2) TL_CASE(2, 3)
 #undef TL_CASE
-  return false;
+  return (int)hipErrorInvalidValue;
 }
 
 // the parts of a Linear cut over K (k_splitk.hip)

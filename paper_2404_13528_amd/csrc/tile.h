@@ -5,7 +5,8 @@
 namespace sm {
 
 struct GemmArgs;
-bool launch_tile_linear(const GemmArgs& g, void* stream, int* rc);      // runs g in large tiles where that is the better form; false: not
+bool tile_linear_use(const GemmArgs& g, int* mi, int* ni);      // whether launch_gemm runs g in large tiles, if it gets past the column-split kernel, and in which (64 mi x 64 ni)
+int launch_tile_linear(const GemmArgs& g, int mi, int ni, void* stream);
 double gemm_kernel_cost(const GemmArgs& g);                             // what gemm_kernel (k_gemm.hip) takes for g, us
 
 // A bf16 Linear with a residual on few rows, cut over K: parts in fp32, summed by a second kernel that also takes the norm behind it

@@ -1,6 +1,6 @@
 """The large-tile Linear (k_tile.hip) against gemm_kernel's 64-row form, which sums in the same order: the results are the same
-bits.  Shapes are ones whose own choice is a large tile (192 x 128 .. 256 x 256), rows and columns cut, one round of tiles and
-several, K-tiles from 17 (more than the stages, an odd number) to 44."""
+bits.  Every case names the tile that its shape is to run in: each of the seven, rows and columns cut, one round of tiles and
+several, K-tiles from 12 to 64, odd counts among them."""
 import pytest
 import torch
 from paper_2404_13528_amd import binding as sm, workloads as Wl
@@ -9,34 +9,48 @@ from util import dev, dev_params
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M,N,K,act,res,rope", [
-    (4147, 928, 1088, "none", True, None),           # 128 x 192
-    (834, 4672, 1088, "swiglu", False, None),
-    (1292, 5440, 1280, "gelu", False, None),         # 128 x 256
-    (4685, 832, 1088, "none", True, None),           # 192 x 128
-    (5705, 656, 1088, "gelu", True, None),
-    (1677, 4680, 1088, "gelu", False, None),         # 192 x 192
-    (3335, 2368, 1088, "geglu", True, None),
-    (2148, 4096, 1088, "swiglu", False, None),       # 192 x 256
-    (5436, 1544, 1088, "gelu", True, None),          # 256 x 192
-    (2041, 8184, 1088, "none", True, None),          # 256 x 256, one round
-    (2041, 6144, 1088, "none", False, (4096, 128, 700, 10000.0)),
-    (4100, 9984, 1088, "swiglu", True, None),        # several rounds
-    (333, 5632, 2816, "swiglu", False, None),        # few rows
-    (6304, 2304, 768, "none", True, None),           # a short K
+def labelled(f):
+    """f's result and the labels of the kernels it launched"""
+    sm.timing_enable(True)
+    try:
+        return f(), sm.timing_sequence()
+    finally:
+        sm.timing_enable(False)
+
+
+@pytest.mark.parametrize("M,N,K,act,res,rope,tile", [
+    (4147, 928, 1088, "none", True, None, "128x192"),
+    (834, 4672, 1088, "swiglu", False, None, "128x192"),
+    (1292, 5440, 1280, "gelu", False, None, "128x256"),
+    (4685, 832, 1088, "none", True, None, "192x128"),
+    (5705, 656, 1088, "gelu", True, None, "192x128"),
+    (1677, 4680, 1088, "gelu", False, None, "192x192"),
+    (3335, 2368, 1088, "geglu", True, None, "192x192"),
+    (2148, 4096, 1088, "swiglu", False, None, "192x256"),
+    (5436, 1544, 1088, "gelu", True, None, "256x192"),
+    (2041, 6144, 1088, "none", False, (4096, 128, 700, 10000.0), "256x192"),
+    (2041, 8184, 1088, "none", True, None, "256x256"),                          # one round
+    (1025, 12288, 4096, "none", False, (8192, 128, 1025, 10000.0), "256x256"),
+    (4100, 9984, 1088, "swiglu", True, None, "256x256"),                        # several rounds
+    (333, 11264, 2048, "swiglu", False, None, "192x128"),                       # few rows
+    (1025, 4096, 4096, "none", True, None, "192x128"),                          # 64 K-tiles
+    (6304, 2304, 768, "none", False, None, "256x256"),                          # 12
 ])
-def test_tile_linear_is_the_tiled_kernel(M, N, K, act, res, rope):
+def test_tile_linear_is_the_tiled_kernel(M, N, K, act, res, rope, tile):
     g = torch.Generator().manual_seed(M + N + K)
     A, W = torch.randn(M, K, generator=g).bfloat16().cuda(), (torch.randn(N, K, generator=g) * K ** -0.5).bfloat16().cuda()
     b = None if rope else torch.randn(N, generator=g).bfloat16().cuda()
     R = torch.randn(M, N // 2 if "glu" in act else N, generator=g).bfloat16().cuda() if res else None
-    got = sm.linear(A, W, b, residual=R, act=act, rope=rope)
-    again = sm.linear(A, W, b, residual=R, act=act, rope=rope)
+    run = lambda: sm.linear(A, W, b, residual=R, act=act, rope=rope)
+    got, labels = labelled(run)
+    assert len(labels) == 1 and labels[0].endswith("+tile" + tile), labels
+    again = run()
     try:
         sm.gemm_tuning(64, 2)
-        want = sm.linear(A, W, b, residual=R, act=act, rope=rope)
+        want, labels = labelled(run)
     finally:
         sm.gemm_tuning(0, 0)
+    assert len(labels) == 1 and "+tile" not in labels[0], labels
     assert torch.isfinite(want.float()).all()
     assert torch.equal(got, want) and torch.equal(again, want)
 
