@@ -23,6 +23,7 @@
 #include <mutex>
 #include <tuple>
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 #include "device_common.h"
 #include "kernels.h"
@@ -915,6 +916,13 @@ static int gemm_launch_dma(const GemmArgs& g, const ColMap& cm, hipStream_t s, T
   return gemm_launch2<T, MI, EPI, false, true, WM, 2>(g, cm, s);
 }
 
+// Whether 256 x 128 tiles fill the chip (one 8-wave workgroup per CU) about as well as the smaller ones; with a short K loop only
+// on grids of several rounds, where their lower L2 -> LDS traffic per flop pays
+static bool fills_256(const GemmArgs& g) {
+  const int64_t t256 = ((g.M + 255) / 256) * ((g.N + 127) / 128), rounds = (t256 + 255) / 256;
+  return t256 >= (g.K >= 1024 ? 200 : 512) && (double)t256 / (double)(rounds * 256) >= 0.8;
+}
+
 template <typename T, int MI, int EPI, bool AGRAN>
 static int gemm_launch(const GemmArgs& g, const ColMap& cm, hipStream_t s, Tune tn) {
   if constexpr (!AGRAN && (EPI == EPI_PLAIN || EPI == EPI_GELU)) {
@@ -928,11 +936,7 @@ static int gemm_launch(const GemmArgs& g, const ColMap& cm, hipStream_t s, Tune 
         if constexpr (MI == 1) return gemm_launch_dma<T, 1, EPI, 2>(g, cm, s, tn);
       }
       if constexpr (MI == 2) {
-        // 256 x 128 tiles when they fill the chip (one 8-wave workgroup per CU) about as well as the smaller ones; with a
-        // short K loop only on grids of several rounds, where their lower L2 -> LDS traffic per flop pays
-        const int64_t t256 = ((g.M + 255) / 256) * ((g.N + 127) / 128);
-        const int64_t rounds = (t256 + 255) / 256;
-        if (t256 >= (g.K >= 1024 ? 200 : 512) && (double)t256 / (double)(rounds * 256) >= 0.8) return gemm_launch_dma<T, 2, EPI, 4>(g, cm, s, tn);
+        if (fills_256(g)) return gemm_launch_dma<T, 2, EPI, 4>(g, cm, s, tn);
       }
       return gemm_launch_dma<T, MI, EPI, 2>(g, cm, s, tn);
     }
@@ -1005,7 +1009,7 @@ static Tune long_k_tile(const GemmArgs& g, double* cost_us = nullptr) {
 // 768 workgroups of the 64-row tile, 512 of the 128-row one) times the time a workgroup lives: a fixed part plus
 // its K steps, both measured on the chip (microseconds; the 128-row step moves twice the rows in about twice the time,
 // so the smaller tile wins unless it needs an extra round).
-static bool short_k_128(const GemmArgs& g, double* cost_us = nullptr) {
+static bool short_k_128(const GemmArgs& g) {
   const int64_t tcols = (g.N + 127) / 128;
   const int64_t t128 = ((g.M + 127) / 128) * tcols, t64 = ((g.M + 63) / 64) * tcols;
   const double nk = (double)((g.K + 63) / 64);
@@ -1013,18 +1017,28 @@ static bool short_k_128(const GemmArgs& g, double* cost_us = nullptr) {
   // long K loops (fp32 and the register-staged forms): the tile's L2 -> LDS traffic per flop decides, the 64-row tile being
   // about 0.6 as efficient per row
   if (nk > 16) { cost64 = (double)((t64 + 767) / 768) * 1.2; cost128 = (double)((t128 + 511) / 512) * 2.0; }
-  const bool tall = t128 >= 1024 || cost128 <= cost64;
-  if (cost_us) *cost_us = tall ? .78 * cost128 : 1.15 * cost64;
-  return tall;
+  return t128 >= 1024 || cost128 <= cost64;
 }
 
-// What the kernel takes for a Linear with its own choice of tile, us: the two rules' costs, scaled to 134 measured shapes
-// (K = 320 .. 11008; standard deviation 7 to 12 % from K = 1280 on, 15 to 20 % below).  launch_tile_linear compares its own with it.
+// What the kernel takes for a Linear with its own choice of tile, us; tile_linear_plan and splitk_plan compare their own with it.
+// Above K = 1024 the cost that long_k_tile decides by, scaled to measured times (standard deviation 7 to 12 %).  Up to there whole
+// rounds are too coarse (13 % over 311 shapes with K = 640 .. 1024, and RoPE's epilogue was missing: 33 x 3072 x 1024 estimated at 17.8,
+// takes 13.4): rounds of the tile's residency, of which a partial one costs .71 and its share of the rest, the bytes of the
+// residual, and the epilogues (8 %, on shapes that the fit has not seen as well).
 double gemm_kernel_cost(const GemmArgs& g) {
   double us = 0;
-  if (g.K <= 16 * 64) { (void)short_k_128(g, &us); return us; }
-  (void)long_k_tile(g, &us);
-  return us * (g.K < 2048 ? 1.24 : (g.K < 4096 ? 1.14 : .92));
+  if (g.K > 16 * 64) {
+    (void)long_k_tile(g, &us);
+    return us * (g.K < 2048 ? 1.24 : (g.K < 4096 ? 1.14 : .92));
+  }
+  const bool gated = g.act == SM_ACT_SWIGLU || g.act == SM_ACT_GEGLU, tall = short_k_128(g);
+  const struct { int rows, resident; double fixed, step; } form[] = {{64, 768, 3.85, .84}, {128, 512, 7.3, .75}, {256, 256, 4.5, .96}};
+  auto rounds = [&](int i) { return (double)(((g.M + form[i].rows - 1) / form[i].rows) * ((g.N + 127) / 128)) / form[i].resident; };
+  const int i = tall ? (fills_256(g) ? 2 : 1) : 0;
+  const double full = std::floor(rounds(i)), part = rounds(i) - full;
+  us = (full + (part > 0 ? .71 + .29 * part : 0.)) * (form[i].fixed + g.K / 64 * form[i].step + (g.act == SM_ACT_NONE ? 0. : (tall ? .72 : .36)));
+  if (g.residual) us += .18e-6 * (double)g.M * (gated ? g.N / 2 : g.N);
+  return g.rope_cols ? us + 6.2 * std::min(1., rounds(0)) : us;
 }
 
 template <typename T>

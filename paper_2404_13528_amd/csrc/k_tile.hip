@@ -532,16 +532,22 @@ bool tile_rows_ok(const RowProg& r, int64_t rows) {      // a pitch or a table; 
 }
 }  // namespace
 
-// Which Linears run here, and in which tile: us of each tile fitted to the measured times of 134 shapes (K = 320 .. 11008, 24 to 1800
-// tiles of 128 x 128, five epilogues; 5 to 7 % standard deviation) against gemm_kernel's own.  A round of workgroups (one per CU)
+// Which Linears run here, and in which tile: us of each tile, fitted to measured times (K = 640 .. 11008, five epilogues; 2 to 5 %
+// standard deviation, 7 % with K >= 4096 and weights from memory), against gemm_kernel's own.  A round of workgroups (one per CU)
 // costs a fixed part, a part per K-tile and a part per K-tile that grows with the share of the CUs that work in it (the clock
-// falls as more of the chip multiplies).  Measured us, gemm_kernel / this: 2048 x 22016 x 4096 SwiGLU 391 / 317 (256 x 256),
-// 2048 x 12288 x 4096 184 / 168 (256 x 192), 333 x 22016 x 4096 SwiGLU 112 / 67 (192 x 192), 333 x 12288 x 4096 53 / 43 (192 x 128),
-// 6304 x 768 x 3072 40 / 38, 6977 x 1280 x 3072 77 / 59, 1115 x 4096 x 4096 58 / 45; over the 89 shapes with K >= 1024 the choice
-// gains 6.7 % in the geometric mean (the best variant of each 7.4 %) and loses 2 % at worst.  Up to K = 1024 a tile's fixed part
-// weighs as much as its K loop and gemm_kernel's two workgroups per CU hide it better (8192 x 2560 x 320 GEGLU 29 / 32,
-// 12544 x 2048 x 512 + GELU 44 / 46): only from K = 640 on and where the costs are clearly apart (6304 x 2304 x 768 33.5 / 28).  At K = 1024
-// near ties lose too (a decoder layer of 1266 tokens, E = 1024: 123 us with ratios of .89 to .99 in large tiles, 116 without).
+// falls as more of the chip multiplies); below K = 2048 the residual's bytes at 5 TB/s, which nothing hides.
+// Measured us, gemm_kernel / this: 2048 x 22016 x 4096 SwiGLU 370 / 305 (256 x 256), 2048 x 12288 x 4096 + RoPE 198 / 175 (256 x 192),
+// 333 x 22016 x 4096 SwiGLU 114 / 77 (192 x 192), 333 x 12288 x 4096 + RoPE 61 / 54 (128 x 192), 6304 x 768 x 3072 41.5 / 38 (128 x 192),
+// 6304 x 2304 x 768 34 / 27 (256 x 256).  Over 823 shapes of 16 to 16384 rows that the column-split kernel leaves, each tile and
+// gemm_kernel timed in turn, the choice takes .929 of gemm_kernel's time in the geometric mean (the best variant of each .923), three
+// lose more than 2 %, 4.7 % at most.  The lines:
+//  - at least 160 tiles: what a tile leaves idle the costs do not tell (16 tiles, 33 x 3072 x 1024 + RoPE 13.4 / 17.8; 110 tiles,
+//    600 x 4096 x 11008 99 / 127; every shape of 172 tiles and more that the costs choose is a gain or even);
+//  - between K = 1024 and 2048 only where the costs are 5 % apart (4702 x 5184 x 1088 + GELU 68 / 72 at .99 of it);
+//  - from K = 8192 on with a residual only where they are 10 % apart: with weights from memory 128 x 256 tiles take 143 to 168 us from
+//    one allocation to the next (1550 to 2048 x 4096 x 11008; gemm_kernel 149 to 163);
+//  - not below K = 640: a tile's fixed part weighs as much as its K loop and gemm_kernel's two workgroups per CU hide it better
+//    (8192 x 2560 x 320 GEGLU 29 / 32, 12544 x 2048 x 512 + GELU 44 / 46).
 static bool tile_linear_ok(const GemmArgs& g) {
   if (g.dtype != SM_BF16 || g.K % 64 || g.K < 640 || g.a_gran > 0 || g.norm || g.C2 || g.c_transposed || g.c_cols_on) return false;
   const bool gated = g.act == SM_ACT_SWIGLU || g.act == SM_ACT_GEGLU;
@@ -559,13 +565,17 @@ static double tile_cost(const TileForm& f, const GemmArgs& g, int splits) {
   const int64_t tiles = ((g.M + 64 * f.mi - 1) / (64 * f.mi)) * ((g.N + 64 * f.ni - 1) / (64 * f.ni)) * splits;
   const double nk = (double)((g.K / 64 + splits - 1) / splits), rounds = (double)((tiles + 255) / 256);
   const double act = g.act == SM_ACT_GELU ? 1. : (g.act == SM_ACT_SWIGLU || g.act == SM_ACT_GEGLU ? .7 : 0.);
-  return f.fixed + rounds * (f.round + nk * f.step + act * f.act) + (double)tiles / 256. * nk * f.busy;
+  double us = f.fixed + rounds * (f.round + nk * f.step + act * f.act) + (double)tiles / 256. * nk * f.busy;
+  if (g.residual && g.K < 2048) us += .4e-6 * (double)g.M * (act == .7 ? g.N / 2 : g.N);
+  if (g.rope_cols && g.K <= 1024) us += 3.;
+  return us;
 }
 static bool tile_linear_plan(const GemmArgs& g, int* mi, int* ni) {
   if (!tile_linear_ok(g)) return false;
-  double least = (g.K > 1024 ? 1. : .88) * gemm_kernel_cost(g);
+  double least = (g.K <= 1024 ? 1. : (g.K < 2048 ? .95 : (g.K >= 8192 && g.residual ? .9 : 1.))) * gemm_kernel_cost(g);
   *mi = 0;
   for (const auto& f : tile_form) {
+    if (((g.M + 64 * f.mi - 1) / (64 * f.mi)) * ((g.N + 64 * f.ni - 1) / (64 * f.ni)) < 160) continue;
     const double us = tile_cost(f, g, 1);
     if (us < least) { least = us; *mi = f.mi; *ni = f.ni; }
   }

@@ -29,9 +29,9 @@ def labelled(f):
     (2148, 4096, 1088, "swiglu", False, None, "192x256"),
     (5436, 1544, 1088, "gelu", True, None, "256x192"),
     (2041, 6144, 1088, "none", False, (4096, 128, 700, 10000.0), "256x192"),
-    (2041, 8184, 1088, "none", True, None, "256x256"),                          # one round
+    (2041, 8184, 2048, "none", True, None, "256x256"),                          # one round
     (1025, 12288, 4096, "none", False, (8192, 128, 1025, 10000.0), "256x256"),
-    (4100, 9984, 1088, "swiglu", True, None, "256x256"),                        # several rounds
+    (4100, 9984, 2048, "swiglu", True, None, "256x256"),                        # several rounds
     (333, 11264, 2048, "swiglu", False, None, "192x128"),                       # few rows
     (1025, 4096, 4096, "none", True, None, "192x128"),                          # 64 K-tiles
     (6304, 2304, 768, "none", False, None, "256x256"),                          # 12
@@ -53,6 +53,22 @@ def test_tile_linear_is_the_tiled_kernel(M, N, K, act, res, rope, tile):
     assert len(labels) == 1 and "+tile" not in labels[0], labels
     assert torch.isfinite(want.float()).all()
     assert torch.equal(got, want) and torch.equal(again, want)
+
+
+@pytest.mark.parametrize("M,N,K,act,res,rope", [
+    (33, 3072, 1024, "none", False, (2048, 128, 33, 10000.0)),      # 16 tiles: a fifth and more slower there than in gemm_kernel
+    (241, 3072, 1024, "none", False, (2048, 128, 241, 10000.0)),    # 32
+    (577, 4096, 11008, "none", True, None),                         # 110
+    (354, 6464, 10240, "swiglu", False, None),                      # 102
+    (14848, 640, 640, "none", True, None),                          # a short K and a residual
+    (4702, 5184, 1088, "gelu", False, None),                        # near ties
+    (1661, 4096, 11008, "none", True, None),
+])
+def test_large_tiles_only_where_they_are_faster(M, N, K, act, res, rope):
+    A, W = torch.zeros(M, K, device="cuda").bfloat16(), torch.zeros(N, K, device="cuda").bfloat16()
+    R = torch.zeros(M, N, device="cuda").bfloat16() if res else None
+    _, labels = labelled(lambda: sm.linear(A, W, residual=R, act=act, rope=rope))
+    assert len(labels) == 1 and labels[0].startswith("gemm_bf16[") and "+tile" not in labels[0], labels
 
 
 @pytest.mark.parametrize("kind,B,S,E,h,F,cut", [
