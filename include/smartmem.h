@@ -554,14 +554,17 @@ int sm_timing_calibrate(int n, void* stream);
  * sm_linear_pack, and unlike the other entry points it creates events and SYNCHRONISES with the stream; C is
  * overwritten with the Linear's result.  *tile_rows = *stages = 0: the built-in choice won (a variant has to be 3 %
  * faster) or the shape has a single variant (fp32, K not a multiple of 64: nothing is timed; few rows, which the
- * column-split kernel runs: its time is *best_us = *default_us).  sm_linear_autotune_clear forgets all. */
+ * column-split kernel runs: its time is *best_us = *default_us).  sm_linear_autotune_clear forgets all.  Results do not
+ * depend on the variant, but for the Linears that sm_attn_block runs cut over K: a remembered
+ * variant takes the place of the cut. */
 int sm_linear_autotune(const sm_linear_desc*, const void* A, const void* W, const void* bias, const void* residual,
                        void* C, int iters, void* stream, int* tile_rows, int* stages, float* best_us, float* default_us);
 void sm_linear_autotune_clear(void);
 
 /* Tuning hook for benchmarks: overrides the tile and pipeline choice of the tiled bf16 Linear kernel for the calling
  * process (Linears on few rows run in the column-split kernel, which has no such choice: label "splitgemm_...").  tile_rows: 0 (automatic), 64, 128 or 256 output rows per workgroup; stages: 0 (automatic) or 2..4
- * K-tiles resident in LDS.  Returns SM_ERR_INVALID_ARG for other values.  Results do not depend on the choice. */
+ * K-tiles resident in LDS.  Returns SM_ERR_INVALID_ARG for other values.  Results do not depend on the choice; but
+ * with one, sm_attn_block runs no Linear cut over K, and those results differ in low bits. */
 int sm_gemm_tuning(int tile_rows, int stages);
 
 #ifdef __cplusplus

@@ -275,18 +275,18 @@ int gemm(const void* A, const void* W, const void* bias, const void* res, void* 
 // Scratch of the Linears that may run cut over K: behind the tables, and used where the caller's workspace reaches that far
 // (a smaller one, without it, runs them uncut)
 struct Parts { float* at; size_t bytes; };
-GemmArgs res_linear(int64_t M, int N, int K, int dt) {
+GemmArgs res_linear(const void* res, int64_t M, int N, int K, int dt) {
   GemmArgs g; std::memset(&g, 0, sizeof(g));
-  g.M = M; g.N = N; g.K = K; g.dtype = dt; g.ldw = K; g.a_rows = identity_rows(K); g.c_rows = identity_rows(N);
+  g.residual = res; g.M = M; g.N = N; g.K = K; g.dtype = dt; g.ldw = K; g.a_rows = identity_rows(K); g.c_rows = identity_rows(N);
   return g;
 }
-size_t parts_bytes(const sm_attn_cfg* c) {
+size_t parts_bytes(const sm_attn_cfg* c) {      // (the residual: any pointer that is not null)
   if (c->kind == SM_ATTN_SD) return 0;
   size_t most = 0;
   for (int down = 0; down < 2; ++down) {
     const int64_t T = (int64_t)c->B * c->S;
     SplitKPlan p;
-    if (splitk_plan(res_linear(T, c->E, down ? c->F : c->E, c->dtype), !down, &p)) most = std::max(most, align256((size_t)p.splits * T * c->E * sizeof(float)));
+    if (splitk_plan(res_linear(c, T, c->E, down ? c->F : c->E, c->dtype), !down, &p)) most = std::max(most, align256((size_t)p.splits * T * c->E * sizeof(float)));
   }
   return most;
 }
@@ -294,9 +294,9 @@ size_t parts_bytes(const sm_attn_cfg* c) {
 // C = A . W^T + bias + res and, with n, n = norm(C)
 int gemm_res(const void* A, const void* W, const void* bias, const void* res, void* C, int64_t M, int N, int K, int dt, const Parts& parts, void* stream,
              void* n = nullptr, const void* gamma = nullptr, const void* beta = nullptr, float eps = 0.f, int rms = 0) {
-  GemmArgs g = res_linear(M, N, K, dt);
+  GemmArgs g = res_linear(res, M, N, K, dt);
   SplitKPlan p;
-  if (splitk_plan(g, n != nullptr, &p) && parts.bytes >= (size_t)p.splits * M * N * sizeof(float)) {
+  if (splitk_plan(g, n != nullptr, &p) && !gemm_tile_chosen(g) && parts.bytes >= (size_t)p.splits * M * N * sizeof(float)) {
     g.A = A; g.W = W; g.C = C;
     typedef unsigned short u16;
     const SumPartsArgs sum{parts.at, p.splits, M, N, (const u16*)bias, (const u16*)res, (u16*)C, (const u16*)gamma, (const u16*)beta, (u16*)n, eps, rms};

@@ -1084,7 +1084,8 @@ int gemm_tuning(int tile_rows, int stages) {
 // search space is small enough to be walked completely): every tile height x stage count the kernel has, timed on the
 // caller's operands with HIP events; the fastest is remembered for the shape.  0 in *rows / *stages = the built-in choice won.
 // A shape that the column-split kernel runs has that one variant: it is timed and nothing is remembered.  It cuts K over its
-// waves, so its sums differ from the tiled kernel's in their last bits, and a tile choice never changes a result.
+// waves, so its sums differ from the tiled kernel's in their last bits, and a tile choice never changes a result.  (A Linear that
+// sm_attn_block runs cut over K is tuned as the uncut one that sm_linear runs, and a remembered tile takes the place of the cut.)
 int gemm_autotune(const GemmArgs& g, int iters, void* stream, int* rows, int* stages, float* best_us, float* default_us) {
   if (!tunable(g)) return -2;
   hipStream_t s = (hipStream_t)stream;

@@ -118,7 +118,7 @@ __global__ __launch_bounds__(256) void sum_parts_kernel(SumPartsArgs a) {
 // estimated 25); the sum kernel saves 3 to 4 us of the norm's launch
 bool splitk_plan(const GemmArgs& g, bool norm_after, SplitKPlan* p) {
   p->splits = 0;
-  if (g.M < 1 || gemm_tile_chosen(g)) return false;
+  if (g.M < 1) return false;
   const bool narrow = split_linear_use(g);
   if (narrow && ((g.M + 31) / 32) * ((g.N + 31) / 32) <= 256) return false;
   const double us = narrow ? 3. + 1e-6 * g.N * (double)g.K : 1.1 * gemm_kernel_cost(g);

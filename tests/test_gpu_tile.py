@@ -106,3 +106,25 @@ def test_cut_linears_of_a_block(kind, B, S, E, h, F, cut):
     assert torch.equal(got, again) and torch.isfinite(got.float()).all()
     err = ((got.float() - want.float()).norm() / want.float().norm()).item()
     assert err <= 2 * 2 ** -8, err
+
+
+def test_a_picked_tile_takes_the_place_of_the_cut():
+    """A tile forced or remembered for the Linear that runs, and only for that one: the tuner's entry of a Linear without the
+    residual is another shape's."""
+    B, S, E, F = 1, 333, 4096, 11008
+    x, p = Wl.llama_case(B, S, E, F, seed=5, std=E ** -0.5)
+    x = dev(x, torch.bfloat16)
+    blk = sm.AttnBlock("llama", dev_params(p, torch.bfloat16), torch.bfloat16, B=B, S=S, E=E, heads=32, F=F)
+    cuts = lambda: sorted(int(t.split("[")[1].split("]")[0].split(",")[2]) for t in labelled(lambda: blk(x))[1] if t.startswith("cut"))
+    assert cuts() == [E, F]
+    try:
+        sm.gemm_tuning(64, 2)
+        assert cuts() == []
+        sm.gemm_tuning(0, 0)
+        picked = [sm.linear_autotune(S, E, K, residual=False, iters=5)["tile_rows"] for K in (E, F)]
+        assert cuts() == [E, F], picked
+        tuned = {K: sm.linear_autotune(S, E, K, residual=True, iters=5)["tile_rows"] for K in (E, F)}
+        assert cuts() == [K for K in (E, F) if not tuned[K]], tuned
+    finally:
+        sm.gemm_tuning(0, 0)
+        sm.lib().sm_linear_autotune_clear()
