@@ -74,10 +74,14 @@ def kernel_model(label):
     if m:
         B, h, n, d = [int(m.group(i)) for i in range(1, 5)]
         return B * h * (2 * n * d + 2 * d) * e, 4.0 * B * h * n * d
-    m = re.match(r"cut_linear_bf16\[(\d+),(\d+),(\d+)\]\+res(\+norm)?", label)
-    if m:      # cut over K; with +norm the normalised rows are written as well
+    m = re.match(r"cutgemm_bf16\[(\d+),(\d+),(\d+)\]", label)
+    if m:      # cut over K: the operands (the fp32 parts are this form's own, as a fused operator's intermediates are)
         M, N, K = int(m.group(1)), int(m.group(2)), int(m.group(3))
-        return (M * K + N * K + (3 if m.group(4) else 2) * M * N) * e, 2.0 * M * N * K
+        return (M * K + N * K) * e, 2.0 * M * N * K
+    m = re.match(r"sum_parts_bf16\[(\d+),(\d+),\d+\]\+res(\+norm)?", label)
+    if m:      # ... and its result and residual; with +norm the normalised rows are written as well
+        M, N = int(m.group(1)), int(m.group(2))
+        return (3 if m.group(3) else 2) * M * N * e, 0.0
     m = re.match(r"concat_bf16\[(\d+),(\d+),(\d+)\]", label)
     if m:
         return 2 * int(m.group(1)) * int(m.group(2)) * int(m.group(3)) * e, 0.0

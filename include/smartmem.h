@@ -535,7 +535,8 @@ int sm_last_launch_counts(int* n_compute, int* n_copy);
  * clears.  sm_timing_report waits for the recorded events and writes one line per kernel label,
  * "label<TAB>launches<TAB>total_ms", into buf (host pointer, n bytes).  A Linear's label names the kernel that ran it:
  * "gemm_..." the tiled one, "...+tile256x192" the large-tile one in tiles of that size, "splitgemm_..." the column-split
- * one, "pgemm_..." the packed-weight one. */
+ * one, "pgemm_..." the packed-weight one; "cutgemm_...+tile192x128x4" is one cut over K into four parts in large tiles,
+ * followed by the "sum_parts_..." that adds them, the residual and the norm behind it. */
 int sm_timing_enable(int on);
 int sm_timing_report(char* buf, int n);
 /* the labels of the launches recorded since sm_timing_enable(1), in launch order, one per line (host buffer; a label

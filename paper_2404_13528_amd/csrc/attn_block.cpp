@@ -301,9 +301,15 @@ int gemm_res(const void* A, const void* W, const void* bias, const void* res, vo
     typedef unsigned short u16;
     const SumPartsArgs sum{parts.at, p.splits, M, N, (const u16*)bias, (const u16*)res, (u16*)C, (const u16*)gamma, (const u16*)beta, (u16*)n, eps, rms};
     char label[96];
-    snprintf(label, sizeof(label), "cut_linear_bf16[%lld,%d,%d]+res%s", (long long)M, N, K, n ? "+norm" : "");
-    Timed tm(label, stream);
-    if (int e = launch_splitk(g, p, sum, stream)) return fail(SM_ERR_DEVICE, "linear: launch failed (hip error %d)", e);
+    int e;
+    snprintf(label, sizeof(label), "cutgemm_bf16[%lld,%d,%d]+tile%dx%dx%d", (long long)M, N, K, 64 * p.mi, 64 * p.ni, p.splits);
+    { Timed tm(label, stream); e = launch_tile_parts(g, p.mi, p.ni, p.splits, parts.at, stream); }
+    if (!e) {
+      snprintf(label, sizeof(label), "sum_parts_bf16[%lld,%d,%d]+res%s", (long long)M, N, p.splits, n ? "+norm" : "");
+      Timed tm(label, stream);
+      e = launch_sum_parts(sum, stream);
+    }
+    if (e) return fail(SM_ERR_DEVICE, "linear: launch failed (hip error %d)", e);
     count_compute(2);
     return SM_OK;
   }

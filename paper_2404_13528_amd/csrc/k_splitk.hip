@@ -125,9 +125,8 @@ bool splitk_plan(const GemmArgs& g, bool norm_after, SplitKPlan* p) {
   return tile_parts_plan(g, .97 * (us + (norm_after ? 3. : 0.)), p);
 }
 
-int launch_splitk(const GemmArgs& g, const SplitKPlan& p, const SumPartsArgs& sum, void* stream) {
-  if (sum.N > 4 * kSumCols || sum.N % 8 || sum.N != g.N || sum.M != g.M || sum.splits != p.splits || sum.M > INT32_MAX) return (int)hipErrorInvalidValue;
-  if (const int rc = launch_tile_parts(g, p.mi, p.ni, p.splits, const_cast<float*>(sum.part), stream)) return rc;
+int launch_sum_parts(const SumPartsArgs& sum, void* stream) {
+  if (sum.N > 4 * kSumCols || sum.N % 8 || sum.M > INT32_MAX) return (int)hipErrorInvalidValue;
   hipStream_t s = (hipStream_t)stream;
   const dim3 grid((unsigned)sum.M);
   if (sum.N <= kSumCols) sum_parts_kernel<1><<<grid, dim3(256), 0, s>>>(sum);

@@ -17,7 +17,7 @@ struct SumPartsArgs {
   const unsigned short *gamma, *beta; unsigned short* n; float eps; int rms;      // n != null: the norm of y's rows goes there; beta may be null
 };
 bool splitk_plan(const GemmArgs& g, bool norm_after, SplitKPlan* p);      // whether that is the better form; by shape alone (a caller who has picked a tile of gemm_kernel, gemm_tile_chosen, gets that)
-int launch_splitk(const GemmArgs& g, const SplitKPlan& p, const SumPartsArgs& sum, void* stream);
+int launch_sum_parts(const SumPartsArgs& sum, void* stream);
 bool tile_parts_plan(const GemmArgs& g, double unsplit, SplitKPlan* p);      // (k_tile.hip) the best tile and number of parts, if better than `unsplit` us
 int launch_tile_parts(const GemmArgs& g, int mi, int ni, int splits, float* part, void* stream);
 bool gemm_tile_chosen(const GemmArgs& g);                                   // (k_gemm.hip) the caller or the tuner has picked a tile of gemm_kernel for g

@@ -86,13 +86,10 @@ def test_cut_linears_of_a_block(kind, B, S, E, h, F, cut):
     x, p = Wl.llama_case(B, S, E, F, seed=S, std=E ** -0.5) if kind == "llama" else Wl.vit_case(B, S, E, h, F, seed=S, std=E ** -0.5)
     x, p = dev(x, torch.bfloat16), dev_params(p, torch.bfloat16)
     blk = sm.AttnBlock(kind, p, torch.bfloat16, B=B, S=S, E=E, heads=h, F=F)
-    sm.timing_enable(True)
-    try:
-        got = blk(x)
-        labels = sm.timing_sequence()
-    finally:
-        sm.timing_enable(False)
-    assert len([t for t in labels if t.startswith("cut_linear")]) == cut, labels
+    got, labels = labelled(lambda: blk(x))
+    assert len([t for t in labels if t.startswith("cutgemm_bf16")]) == cut, labels
+    # a label stands for one kernel: a dispatch list of the same call can be matched to them
+    assert len([t for t in labels if not t.startswith("fill_row_tables")]) == sum(sm.launch_counts()), labels
     again, full = blk(x), blk.ws
     want = again
     for parts in range(8, 0, -1):                             # the workspace without the parts (less is refused)
@@ -115,7 +112,7 @@ def test_a_picked_tile_takes_the_place_of_the_cut():
     x, p = Wl.llama_case(B, S, E, F, seed=5, std=E ** -0.5)
     x = dev(x, torch.bfloat16)
     blk = sm.AttnBlock("llama", dev_params(p, torch.bfloat16), torch.bfloat16, B=B, S=S, E=E, heads=32, F=F)
-    cuts = lambda: sorted(int(t.split("[")[1].split("]")[0].split(",")[2]) for t in labelled(lambda: blk(x))[1] if t.startswith("cut"))
+    cuts = lambda: sorted(int(t.split("[")[1].split("]")[0].split(",")[2]) for t in labelled(lambda: blk(x))[1] if t.startswith("cutgemm_"))
     assert cuts() == [E, F]
     try:
         sm.gemm_tuning(64, 2)
