@@ -126,12 +126,11 @@ bool splitk_plan(const GemmArgs& g, bool norm_after, SplitKPlan* p) {
 }
 
 int launch_sum_parts(const SumPartsArgs& sum, void* stream) {
-  if (sum.N > 4 * kSumCols || sum.N % 8 || sum.M > INT32_MAX) return (int)hipErrorInvalidValue;
+  if (sum.N > 2 * kSumCols || sum.N % 8 || sum.M > INT32_MAX) return (int)hipErrorInvalidValue;
   hipStream_t s = (hipStream_t)stream;
   const dim3 grid((unsigned)sum.M);
   if (sum.N <= kSumCols) sum_parts_kernel<1><<<grid, dim3(256), 0, s>>>(sum);
-  else if (sum.N <= 2 * kSumCols) sum_parts_kernel<2><<<grid, dim3(256), 0, s>>>(sum);
-  else sum_parts_kernel<4><<<grid, dim3(256), 0, s>>>(sum);
+  else sum_parts_kernel<2><<<grid, dim3(256), 0, s>>>(sum);
   return (int)hipGetLastError();
 }
 

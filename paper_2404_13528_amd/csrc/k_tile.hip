@@ -587,7 +587,7 @@ static bool tile_linear_plan(const GemmArgs& g, int* mi, int* ni) {
 // (500 x 2048 x 2048 10.6 / 20 us, 700 x 1024 x 2816 13 / 20).  `unsplit`: what the Linear (and the norm behind it) takes otherwise.
 bool tile_parts_plan(const GemmArgs& g, double unsplit, SplitKPlan* p) {
   p->splits = 0;
-  if (g.K < 4096 || g.N > 8192 || g.act != SM_ACT_NONE || g.rope_cols || !tile_linear_ok(g) || !g.a_rows.identity) return false;
+  if (g.K < 4096 || g.N > 4096 || g.act != SM_ACT_NONE || g.rope_cols || !tile_linear_ok(g) || !g.a_rows.identity) return false;
   if (!g.c_rows.identity || g.c_rows.ld != g.N || g.ldw != g.K || g.a_rows.ld != g.K) return false;
   for (const auto& f : tile_form) unsplit = std::min(unsplit, tile_cost(f, g, 1));
   double least = .97 * unsplit;
