@@ -20,7 +20,8 @@
  *     the size needed (activation buffers plus the per-row offset tables of the
  *     call's index maps, which the executors fill with small kernels at the
  *     start of every call; nothing in `ws` has to survive between calls).  An
- *     undersized workspace returns SM_ERR_WORKSPACE before anything is launched.
+ *     undersized workspace returns SM_ERR_WORKSPACE before anything is launched
+ *     (sm_attn_block_workspace_bytes names a part that a call can do without).
  *     The executors keep the plans of the configurations they have seen in a
  *     bounded, mutex-guarded cache of host objects.  Two exceptions, both
  *     diagnostics a caller switches on: sm_timing_enable() brackets launches
@@ -390,6 +391,10 @@ typedef struct {
   int32_t Hs, Ws, groups, Sc, Dc;     /* SD only */
   float rope_base, eps_norm, eps_gn;
 } sm_attn_cfg;
+/* The workspace holds, after what every call needs, the partial sums of the Linears with a residual that run cut over K
+ * (decoder and encoder layer on few rows, MLP or model width from 4096 on; the size depends on the configuration alone).
+ * sm_attn_block also takes a workspace without that last part and then runs them uncut, in one sum over K: the same result
+ * to rounding, not to the bit.  What is smaller than that returns SM_ERR_WORKSPACE. */
 size_t sm_attn_block_workspace_bytes(const sm_attn_cfg*, int mode);
 int sm_attn_block(const sm_attn_cfg*, const void* const* weights, const void* x, const void* context,
                   void* y, void* ws, size_t ws_bytes, int mode, void* stream);

@@ -72,10 +72,8 @@ def test_large_tiles_only_where_they_are_faster(M, N, K, act, res, rope):
 
 
 @pytest.mark.parametrize("kind,B,S,E,h,F,cut", [
-    ("llama", 1, 333, 4096, 32, 11008, 2),      # both Linears with a residual: 32 x 2 and 32 x 2 tiles of 192 x 128
-    ("llama", 1, 71, 4096, 32, 11008, 2),       # few rows
-    ("llama", 1, 701, 2048, 16, 5632, 1),       # only the long one; 88 K-tiles
-    ("llama", 3, 235, 2048, 16, 5696, 1),       # 89 K-tiles: runs of unequal length
+    ("llama", 1, 333, 4096, 32, 11008, 2),      # both Linears with a residual
+    ("llama", 3, 235, 2048, 16, 5696, 1),       # only the long one; 89 K-tiles, runs of unequal length
     ("vit", 2, 577, 1024, 16, 4096, 1),         # a bias
     ("llama", 1, 333, 1024, 8, 2816, 0),        # short K: never cut
 ])
@@ -91,16 +89,18 @@ def test_cut_linears_of_a_block(kind, B, S, E, h, F, cut):
     # a label stands for one kernel: a dispatch list of the same call can be matched to them
     assert len([t for t in labels if not t.startswith("fill_row_tables")]) == sum(sm.launch_counts()), labels
     again, full = blk(x), blk.ws
-    want = again
-    for parts in range(8, 0, -1):                             # the workspace without the parts (less is refused)
-        if cut and parts * B * S * E * 4 < full.numel():
-            blk.ws = full[:full.numel() - parts * B * S * E * 4]
-            try:
-                want = blk(x)
-                break
-            except sm.SmError:
-                pass
     assert torch.equal(got, again) and torch.isfinite(got.float()).all()
+    blk.ws = full[:16]
+    with pytest.raises(sm.SmError, match="needed") as e:      # the error names what every call needs
+        blk(x)
+    need = int(str(e.value).split(",")[-1].split()[0])
+    assert need <= full.numel() and (need < full.numel()) == (cut > 0)
+    blk.ws = full[:need - 1]
+    with pytest.raises(sm.SmError):
+        blk(x)
+    blk.ws = full[:need]
+    want, labels = labelled(lambda: blk(x))
+    assert not any("cutgemm" in t or "sum_parts" in t for t in labels), labels
     err = ((got.float() - want.float()).norm() / want.float().norm()).item()
     assert err <= 2 * 2 ** -8, err
 
