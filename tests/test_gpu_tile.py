@@ -105,6 +105,56 @@ def test_cut_linears_of_a_block(kind, B, S, E, h, F, cut):
     assert err <= 2 * 2 ** -8, err
 
 
+# the tiles and numbers of parts that the plan takes; runs of unequal length (88 K-tiles in five, 172 in three, eight), rows of half a
+# step of the sum kernel, one, one and a part, and two, the last with either norm behind it
+@pytest.mark.parametrize("kind,T,E,F,first,second", [
+    ("llama", 333, 4096, 11008, "192x128x4", "192x128x4"),
+    ("llama", 71, 4096, 11008, "128x192x8", "128x192x8"),
+    ("llama", 600, 4096, 11008, "128x256x3", "128x256x3"),
+    ("llama", 700, 4096, 11008, "192x128x2", "192x256x4"),
+    ("llama", 530, 2048, 5632, None, "192x128x5"),
+    ("vit", 300, 4096, 4096, "192x128x4", "192x128x4"),
+    ("vit", 90, 4096, 4096, "128x192x8", "128x192x8"),
+    ("vit", 1171, 2560, 10240, None, "256x256x5"),
+    ("vit", 1170, 1024, 4096, None, "192x128x4"),
+])
+def test_cut_linears_against_float64(kind, T, E, F, first, second):
+    """One token per sequence, so that attention returns its values, a part of the QKV Linear's result.  With an MLP of zeros the
+    block returns x1 = v Wo^T + bo + x: where that Linear is cut, one rounding to bf16 (half a unit in the last of eight places)
+    and sums in fp32 (K terms of about K^-1/2: below 1e-5), else a second rounding in front of the residual.  With it, y - x1
+    is the MLP of the norm of that x1, within the roundings of the activation and of y: at most 2^-8 of each."""
+    g = torch.Generator(device="cuda").manual_seed(T + E)
+    rnd = lambda *s, std=1.0, mean=0.0: (torch.randn(*s, generator=g, device="cuda") * std + mean).bfloat16()
+    mat = lambda n, k: rnd(n, k, std=k ** -0.5)
+    llama, F1 = kind == "llama", F * (2 if kind == "llama" else 1)
+    x, wqkv, wo, w1, w2 = rnd(T, 1, E), mat(3 * E, E), mat(E, E), mat(F1, E), mat(E, F)
+    vec = lambda n: None if llama else rnd(n, std=0.5)
+    g1, g2, be1, be2, bqkv, bo, b1, b2 = rnd(E, std=0.2, mean=1.0), rnd(E, std=0.2, mean=1.0), vec(E), vec(E), vec(3 * E), vec(E), vec(F), vec(E)
+    if llama:
+        p = {"rms1_g": g1, "wq": wqkv[:E], "wk": wqkv[E:2 * E], "wv": wqkv[2 * E:], "wo": wo, "rms2_g": g2, "wgate": w1[:F], "wup": w1[F:], "wdown": w2}
+    else:
+        p = {"ln1_g": g1, "ln1_b": be1, "wqkv": wqkv, "bqkv": bqkv, "wo": wo, "bo": bo, "ln2_g": g2, "ln2_b": be2, "w1": w1, "b1": b1, "w2": w2, "b2": b2}
+    run = lambda q: labelled(lambda: sm.AttnBlock(kind, q, torch.bfloat16, B=T, S=1, E=E, heads=E // 128, F=F)(x))
+    zero = {n: torch.zeros_like(p[n]) for n in (("wdown",) if llama else ("w2", "b2"))}
+    y, labels = run(p)
+    assert [t.split("+tile")[1] for t in labels if t.startswith("cutgemm_")] == [t for t in (first, second) if t], labels
+    x1, _ = run({**p, **zero})
+    x1, y = x1.view(T, E).double(), y.view(T, E).double()
+    add = lambda t: 0 if t is None else t.double()
+    n0 = sm.norm(x.view(T, E), g1, be1, eps=1e-5, rms=llama)
+    qkv = sm.linear(n0, wqkv, bqkv, rope=(2 * E, 128, 1, 10000.0) if llama else None)      # as the block runs it: the same bits
+    want = qkv[:, 2 * E:].double() @ wo.double().t() + add(bo) + x.view(T, E).double()
+    half = lambda t: 2 ** -8 * torch.exp2(torch.floor(torch.log2(t.abs().clamp_min(1e-6))))
+    assert ((x1 - want).abs() <= 1.01 * (half(want) + (0 if first else half(want - x.view(T, E).double()))) + 1e-5).all()
+    d = x1 if llama else x1 - x1.mean(-1, keepdim=True)
+    n = (d * (d.square().mean(-1, keepdim=True) + 1e-5).rsqrt() * g2.double() + add(be2)).bfloat16().double()
+    h = n @ w1.double().t() + add(b1)
+    h = torch.nn.functional.silu(h[:, :F]) * h[:, F:] if llama else torch.nn.functional.gelu(h)
+    branch = h.bfloat16().double() @ w2.double().t() + add(b2)
+    err = ((y - x1 - branch).norm() / branch.norm()).item()
+    assert err <= 2 ** -8 * (1 + (y.norm() / branch.norm()).item()), err
+
+
 def test_a_picked_tile_takes_the_place_of_the_cut():
     """A tile forced or remembered for the Linear that runs, and only for that one: the tuner's entry of a Linear without the
     residual is another shape's."""
