@@ -1,6 +1,7 @@
 // Mapped Linear, large tiles: the bf16 products of launch_gemm whose grid fills the chip with tiles of 128 .. 256 rows and
-// columns (tile_linear_plan below says which).  Same operands, row maps and epilogues as gemm_kernel (k_gemm.hip) and the same
-// sums in the same order: a choice between the two never changes a result.
+// columns (tile_linear_plan below says which).  Same epilogues as gemm_kernel (k_gemm.hip) and the same sums in the same order: a
+// choice between the two never changes a result.  Rows of A at a pitch (who gathers them folds a norm in as well, which is
+// gemm_kernel's), rows of the result and residual at a pitch or by a table of offsets.
 //
 // What bounds it: the LDS.  A wave that owns 64 x 64 outputs reads 1 KiB of fragments per 32 x 32 x 16 MFMA, which at eight waves
 // and 128 bytes a clock is more LDS time than matrix time; 128 x 128 outputs per wave need half of it, 96 x 96 two thirds, and the
@@ -80,15 +81,14 @@ __global__ __launch_bounds__(256, 1) void tile_kernel(GemmArgs g, TileCols cm, T
   constexpr int MA0 = (MI + 1) / 2, MA1 = MI - MA0, NB0 = (NI + 1) / 2, NB1 = NI - NB0;      // blocks of a wave in each half
   constexpr int H0 = 2 * (MA0 + NB0), H1 = LPT - H0;
 #define TL_PIN(x) asm volatile("" : "+s"(x))
-  int a_ident = g.a_rows.identity, c_ident = g.c_rows.identity, n_cols = g.N;
+  int c_ident = g.c_rows.identity, n_cols = g.N;
   int64_t a_ld = g.a_rows.ld, c_ld = g.c_rows.ld, m_rows = g.M, ldw = g.ldw;
-  const int32_t* a_tab = g.a_rows.table;
   const int32_t* c_tab = g.c_rows.table;
   const void* bias_p = g.bias;
   const void* res_p = g.residual;
   void* c_p = g.C;
-  TL_PIN(a_ident); TL_PIN(c_ident); TL_PIN(n_cols); TL_PIN(a_ld); TL_PIN(c_ld); TL_PIN(m_rows); TL_PIN(ldw);
-  TL_PIN(a_tab); TL_PIN(c_tab); TL_PIN(bias_p); TL_PIN(res_p); TL_PIN(c_p);
+  TL_PIN(c_ident); TL_PIN(n_cols); TL_PIN(a_ld); TL_PIN(c_ld); TL_PIN(m_rows); TL_PIN(ldw);
+  TL_PIN(c_tab); TL_PIN(bias_p); TL_PIN(res_p); TL_PIN(c_p);
   TL_PIN(cm.half); TL_PIN(cm.rope_cols); TL_PIN(cm.rope_dim);
   TL_PIN(ts.tiles_m); TL_PIN(ts.tiles_n); TL_PIN(ts.strip); TL_PIN(ts.group);
   if constexpr (EPI == EPI_PART) { TL_PIN(ts.splits); TL_PIN(ts.nk); TL_PIN(ts.nk_more); TL_PIN(ts.part); }
@@ -128,20 +128,13 @@ __global__ __launch_bounds__(256, 1) void tile_kernel(GemmArgs g, TileCols cm, T
     return idx / per * 4 * NI + (half ? 4 * NB0 : 0) + idx % per;
   };
   unsigned src_a[LA], src_b[LB];
-  int a_off32[LA];
-  auto src_pre = [&](int64_t m0_) __attribute__((always_inline)) {
-    if (!a_ident) {
-#pragma unroll
-      for (int i = 0; i < LA; ++i) a_off32[i] = a_tab[min(m0_ + a_group(i) * 8 + lrow, m_rows - 1)];
-    }
-  };
-  auto src_fin = [&](int64_t m0_, int n0_, int half) __attribute__((always_inline)) {
+  auto src_at = [&](int64_t m0_, int n0_, int half) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < LA; ++i) {
       if ((i >= 2 * MA0) != half) continue;
       const int rr = a_group(i) * 8 + lrow;
       const int64_t r = min(m0_ + rr, m_rows - 1);      // rows past M repeat the last row: their outputs are never stored
-      src_a[i] = (unsigned)(a_ident ? r * a_ld : (int64_t)a_off32[i]) * 2u + (unsigned)((lpos ^ ((rr >> 1) & 7)) * 16);
+      src_a[i] = (unsigned)(r * a_ld) * 2u + (unsigned)((lpos ^ ((rr >> 1) & 7)) * 16);
     }
 #pragma unroll
     for (int i = 0; i < LB; ++i) {
@@ -279,8 +272,6 @@ __global__ __launch_bounds__(256, 1) void tile_kernel(GemmArgs g, TileCols cm, T
       for (int q = 0; q < 4; ++q) asm volatile("" : "+v"(braw[ni][q]));
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi) asm volatile("" : "+v"(ro_t[mi]));
-#pragma unroll
-    for (int i = 0; i < LA; ++i) asm volatile("" : "+v"(a_off32[i]));
   };
   const int nk = EPI == EPI_PART ? ts.nk + (run < ts.nk_more) : g.K >> 6;
   unsigned stage = 0;                                        // of the K-tile about to be multiplied
@@ -293,7 +284,7 @@ __global__ __launch_bounds__(256, 1) void tile_kernel(GemmArgs g, TileCols cm, T
     // A1, B1 of this K-tile have landed: younger are A0, B0 of the next one and the whole tiles after it
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(H0 + (NS - 2) * LPT) : "memory");
     __builtin_amdgcn_s_barrier();
-    if (kt == nk - NS + 1 && more) src_fin(m0_n, n0_n, 1);
+    if (kt == nk - NS + 1 && more) src_at(m0_n, n0_n, 1);
     {
       const __amdgpu_buffer_rsrc_t ab = on ? a_buf : no_buf, wb = on ? w_buf : no_buf;
       phase(P0{}, FIRST, stage, sn, ab, wb, k_at, sp);      // A1, B1 of K-tile kt + NS - 1
@@ -304,7 +295,7 @@ __global__ __launch_bounds__(256, 1) void tile_kernel(GemmArgs g, TileCols cm, T
     __builtin_amdgcn_s_barrier();
     if constexpr (decltype(FIRST)::value) epi_tie();
     k_at += 128;
-    if (kt == nk - NS) { if (more) src_fin(m0_n, n0_n, 0); k_at = 0; }
+    if (kt == nk - NS) { if (more) src_at(m0_n, n0_n, 0); k_at = 0; }
     on = kt + NS < nk || more;
     {
       const __amdgpu_buffer_rsrc_t ab = on ? a_buf : no_buf, wb = on ? w_buf : no_buf;
@@ -452,9 +443,8 @@ __global__ __launch_bounds__(256, 1) void tile_kernel(GemmArgs g, TileCols cm, T
   };
 
   // ---- start: the first NS K-tiles but for the last one's second half, the first phase's fragments  (nk >= NS)
-  src_pre(m0);
-  src_fin(m0, n0, 0);
-  src_fin(m0, n0, 1);
+  src_at(m0, n0, 0);
+  src_at(m0, n0, 1);
 #pragma unroll
   for (int t = 0; t < NS; ++t) {
     k_at = t * 128;
@@ -485,7 +475,7 @@ __global__ __launch_bounds__(256, 1) void tile_kernel(GemmArgs g, TileCols cm, T
   for (;;) {
     const int vb_n = vb + (int)gridDim.x;
     more = EPI != EPI_PART && vb_n < n_tiles;
-    if (more) { decode(vb_n, m0_n, n0_n); src_pre(m0_n); }
+    if (more) decode(vb_n, m0_n, n0_n);
     epi_loads();
     ktile(0, Yes{});
     for (int kt = 1; kt < nk; ++kt) ktile(kt, No{});
@@ -523,8 +513,8 @@ int tile_launch(const GemmArgs& g, const TileCols& cm, hipStream_t s) {
   if (g.rope_cols > 0) return tile_launch2<MI, NI, EPI_ROPE>(g, cm, s);
   return g.act == SM_ACT_GELU ? tile_launch2<MI, NI, EPI_GELU>(g, cm, s) : tile_launch2<MI, NI, EPI_PLAIN>(g, cm, s);
 }
-bool tile_rows_ok(const RowProg& r, int64_t rows) {      // a pitch or a table; whole 16-byte vectors, offsets below 2^31 elements
-  if (r.identity) return r.ld % 8 == 0 && rows * r.ld <= INT32_MAX;
+bool tile_rows_ok(const RowProg& r) {      // a pitch or a table of whole 16-byte vectors
+  if (r.identity) return r.ld % 8 == 0;
   if (!r.table || r.c0 % 8) return false;
   for (int t = 0; t < r.nterm; ++t)
     if (r.t_coef[t] % 8) return false;
@@ -552,7 +542,7 @@ static bool tile_linear_ok(const GemmArgs& g) {
   if (g.dtype != SM_BF16 || g.K % 64 || g.K < 640 || g.a_gran > 0 || g.norm || g.C2 || g.c_transposed || g.c_cols_on) return false;
   const bool gated = g.act == SM_ACT_SWIGLU || g.act == SM_ACT_GEGLU;
   if (g.N % 8 || (gated && g.N % 64) || (g.act != SM_ACT_NONE && g.rope_cols)) return false;
-  return tile_rows_ok(g.a_rows, g.M) && tile_rows_ok(g.c_rows, 0) && (int64_t)g.N * g.ldw <= INT32_MAX;
+  return g.a_rows.identity && g.a_rows.ld % 8 == 0 && g.M * g.a_rows.ld <= INT32_MAX && tile_rows_ok(g.c_rows) && (int64_t)g.N * g.ldw <= INT32_MAX;
 }
 static const struct TileForm { int mi, ni; double fixed, round, step, busy, act; } tile_form[] = {{4, 4, 1.98, 10.22, 0.855, 0.624, 4.80},
                                                                                  {4, 3, 2.86, 8.09, 0.669, 0.467, 2.86},
@@ -587,7 +577,7 @@ static bool tile_linear_plan(const GemmArgs& g, int* mi, int* ni) {
 // (500 x 2048 x 2048 10.6 / 20 us, 700 x 1024 x 2816 13 / 20).  `unsplit`: what the Linear (and the norm behind it) takes otherwise.
 bool tile_parts_plan(const GemmArgs& g, double unsplit, SplitKPlan* p) {
   p->splits = 0;
-  if (g.K < 4096 || g.N > 4096 || g.act != SM_ACT_NONE || g.rope_cols || !tile_linear_ok(g) || !g.a_rows.identity) return false;
+  if (g.K < 4096 || g.N > 4096 || g.act != SM_ACT_NONE || g.rope_cols || !tile_linear_ok(g)) return false;
   if (!g.c_rows.identity || g.c_rows.ld != g.N || g.ldw != g.K || g.a_rows.ld != g.K) return false;
   for (const auto& f : tile_form) unsplit = std::min(unsplit, tile_cost(f, g, 1));
   double least = .97 * unsplit;

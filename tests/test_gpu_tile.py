@@ -71,6 +71,31 @@ def test_large_tiles_only_where_they_are_faster(M, N, K, act, res, rope):
     assert len(labels) == 1 and labels[0].startswith("gemm_bf16[") and "+tile" not in labels[0], labels
 
 
+@pytest.mark.parametrize("B,C,tile", [
+    (65, 704, "192x256"),       # one round, the last row of tiles and the last column of them cut
+    (130, 960, "256x192"),      # 500 tiles: a workgroup's second one
+])
+def test_result_and_residual_by_a_row_table(B, C, tile):
+    """The output projection of a Swin block stores its rows in token order and adds the residual there."""
+    H, w, h = 14, 7, C // 32
+    g = torch.Generator(device="cuda").manual_seed(C)
+    rnd = lambda *s, std=1.0, mean=0.0: (torch.randn(*s, generator=g, device="cuda") * std + mean).bfloat16()
+    p = {"ln1_g": rnd(C, std=0.1, mean=1.0), "ln1_b": rnd(C), "wqkv": rnd(3 * C, C, std=C ** -0.5), "bqkv": rnd(3 * C), "rpb_table": rnd(169, h),
+         "wproj": rnd(C, C, std=C ** -0.5), "bproj": rnd(C), "ln2_g": rnd(C, std=0.1, mean=1.0), "ln2_b": rnd(C), "w1": rnd(4 * C, C, std=C ** -0.5),
+         "b1": rnd(4 * C), "w2": rnd(C, 4 * C, std=(4 * C) ** -0.5), "b2": rnd(C)}
+    x = rnd(B, H * H, C)
+    blk = sm.SwinBlock(B, H, H, C, h, w, 3, p, torch.bfloat16)
+    got, labels = labelled(lambda: blk(x))
+    assert "gemm_bf16[%d,%d,%d]+res+scatter+tile%s" % (B * H * H, C, C, tile) in labels, labels
+    try:
+        sm.gemm_tuning(64, 2)
+        want, labels = labelled(lambda: blk(x))
+    finally:
+        sm.gemm_tuning(0, 0)
+    assert not any("+tile" in t for t in labels), labels
+    assert torch.isfinite(want.float()).all() and torch.equal(got, want)
+
+
 @pytest.mark.parametrize("kind,B,S,E,h,F,cut", [
     ("llama", 1, 333, 4096, 32, 11008, 2),      # both Linears with a residual
     ("llama", 3, 235, 2048, 16, 5696, 1),       # only the long one; 89 K-tiles, runs of unequal length
