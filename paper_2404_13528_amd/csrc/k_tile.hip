@@ -525,7 +525,8 @@ bool tile_rows_ok(const RowProg& r) {      // a pitch or a table of whole 16-byt
 // Which Linears run here, and in which tile: us of each tile, fitted to measured times (K = 640 .. 11008, five epilogues; 2 to 5 %
 // standard deviation, 7 % with K >= 4096 and weights from memory), against gemm_kernel's own.  A round of workgroups (one per CU)
 // costs a fixed part, a part per K-tile and a part per K-tile that grows with the share of the CUs that work in it (the clock
-// falls as more of the chip multiplies); below K = 2048 the residual's bytes at 5 TB/s, which nothing hides.
+// falls as more of the chip multiplies); below K = 2048 the residual's bytes at 5 TB/s, which nothing hides (without one
+// the costs up to K = 1024 are 4 % high, so that even ones go to the large tile).
 // Measured us, gemm_kernel / this: 2048 x 22016 x 4096 SwiGLU 370 / 305 (256 x 256), 2048 x 12288 x 4096 + RoPE 198 / 175 (256 x 192),
 // 333 x 22016 x 4096 SwiGLU 114 / 77 (192 x 192), 333 x 12288 x 4096 + RoPE 61 / 54 (128 x 192), 6304 x 768 x 3072 41.5 / 38 (128 x 192),
 // 6304 x 2304 x 768 34 / 27 (256 x 256).  Over 823 shapes of 16 to 16384 rows that the column-split kernel leaves, each tile and
@@ -557,12 +558,12 @@ static double tile_cost(const TileForm& f, const GemmArgs& g, int splits) {
   const double act = g.act == SM_ACT_GELU ? 1. : (g.act == SM_ACT_SWIGLU || g.act == SM_ACT_GEGLU ? .7 : 0.);
   double us = f.fixed + rounds * (f.round + nk * f.step + act * f.act) + (double)tiles / 256. * nk * f.busy;
   if (g.residual && g.K < 2048) us += .4e-6 * (double)g.M * (act == .7 ? g.N / 2 : g.N);
-  if (g.rope_cols && g.K <= 1024) us += 3.;
+  if (g.rope_cols && g.K <= 1024) us += 3.5;
   return us;
 }
 static bool tile_linear_plan(const GemmArgs& g, int* mi, int* ni) {
   if (!tile_linear_ok(g)) return false;
-  double least = (g.K <= 1024 ? 1. : (g.K < 2048 ? .95 : (g.K >= 8192 && g.residual ? .9 : 1.))) * gemm_kernel_cost(g);
+  double least = (g.K <= 1024 ? 1.02 : (g.K < 2048 ? .95 : (g.K >= 8192 && g.residual ? .9 : 1.))) * gemm_kernel_cost(g);
   *mi = 0;
   for (const auto& f : tile_form) {
     if (((g.M + 64 * f.mi - 1) / (64 * f.mi)) * ((g.N + 64 * f.ni - 1) / (64 * f.ni)) < 160) continue;
