@@ -66,6 +66,33 @@ __device__ __forceinline__ float erf_as(float x) {
 }
 __device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.f + erf_as(x * 0.70710678118654752f)); }
 
+// (the tiled and the large-tile Linear give the same bits: what their epilogues compute is here)
+// sin and cos of an angle given in revolutions (position x frequency / 2 pi, up to a few hundred): the fraction goes to
+// the hardware sine / cosine.  The fp32 product carries the angle to about 1e-7 of its size, i.e. 3e-4 rad at 2048
+// positions, a tenth of a bf16 ulp of the rotated value; the library sincosf costs the 2048 x 12288 x 4096 projection
+// a third of its time in argument reduction.
+__device__ __forceinline__ void rope_sincos(float rev, float* sn, float* cs) {
+  const float f = __builtin_amdgcn_fractf(rev);
+  *sn = __builtin_amdgcn_sinf(f);
+  *cs = __builtin_amdgcn_cosf(f);
+}
+__device__ __forceinline__ float silu_f(float x) { return x / (1.f + __expf(-x)); }
+
+// eight bf16 of a 16-byte word, to nearest even
+typedef unsigned int bf16_word __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void unpack8(bf16_word v, float* f) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) { f[2 * e] = __uint_as_float(v[e] << 16); f[2 * e + 1] = __uint_as_float(v[e] & 0xffff0000u); }
+}
+__device__ __forceinline__ bf16_word pack8(const float* f) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  bf16_word o;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) { const f32x2 p = {f[2 * e], f[2 * e + 1]}; o[e] = __builtin_bit_cast(unsigned, __builtin_convertvector(p, bf16x2)); }
+  return o;
+}
+
 // value of atom list for one variable assignment; vars[] are the view indices
 template <int NV>
 __device__ __forceinline__ void eval_atoms(const ProgAtom* atoms, int n_atoms, const int* vars, int* val) {

@@ -65,17 +65,6 @@ template <typename T> __device__ __forceinline__ float gelu_t(float x) {
   if constexpr (sizeof(T) == 2) return gelu_poly(x);
   else return gelu_erf(x);
 }
-// sin and cos of an angle given in revolutions (position x frequency / 2 pi, up to a few hundred): the fraction goes to
-// the hardware sine / cosine.  The fp32 product carries the angle to about 1e-7 of its size, i.e. 3e-4 rad at 2048
-// positions, a tenth of a bf16 ulp of the rotated value; the library sincosf costs the 2048 x 12288 x 4096 projection
-// a third of its time in argument reduction.
-__device__ __forceinline__ void rope_sincos(float rev, float* sn, float* cs) {
-  const float f = __builtin_amdgcn_fractf(rev);
-  *sn = __builtin_amdgcn_sinf(f);
-  *cs = __builtin_amdgcn_cosf(f);
-}
-__device__ __forceinline__ float silu_f(float x) { return x / (1.f + __expf(-x)); }
-
 enum { EPI_PLAIN = 0, EPI_GELU = 1, EPI_GLU = 2, EPI_ROPE = 3 };
 
 #define SM_GPTR(p) ((const __attribute__((address_space(1))) void*)(p))
@@ -842,14 +831,7 @@ static int gemm_launch3(const GemmArgs& g, const ColMap& cm, hipStream_t s) {
   const int64_t tiles_m = (g.M + BM - 1) / BM;
   if (tiles_m * tiles_n > INT32_MAX) return (int)hipErrorInvalidValue;
   const size_t smem = (size_t)NS * (BM * 8 + 128 * 8) * sizeof(u32x4);
-  // strips: xn of them, 8 / xn XCDs per strip; an XCD then reads M / (8 / xn) rows of A and N / xn rows of W, in
-  // total xn M + (8 / xn) N rows of K elements: take the xn that makes that smallest
-  int xn = 1;
-  double best = 1e300;
-  for (int c = 1; c <= 8; c *= 2) {
-    const double rows = (double)c * (double)g.M + (8.0 / c) * (double)g.N;
-    if (rows < best && c <= tiles_n) { best = rows; xn = c; }
-  }
+  const int xn = xcd_strips(g.M, g.N, tiles_n);
   TileOrder ts;
   ts.tiles_m = (int)tiles_m; ts.tiles_n = tiles_n;
   ts.strip = (tiles_n + xn - 1) / xn;

@@ -34,9 +34,6 @@ namespace sm {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 sp_bf16x8;
 typedef float sp_f32x16 __attribute__((ext_vector_type(16)));
-typedef float sp_f32x4 __attribute__((ext_vector_type(4)));
-typedef float sp_f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 sp_bf16x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int sp_u32x4 __attribute__((ext_vector_type(4)));
 
 #define SP_GPTR(p) ((const __attribute__((address_space(1))) void*)(p))
@@ -49,23 +46,17 @@ __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)"
 __device__ __forceinline__ void wait_mem() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 __device__ __forceinline__ void wg_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 template <typename T> __device__ __forceinline__ void sp_unpack(sp_u32x4 v, float* f) {
-  if constexpr (sizeof(T) == 2) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) { f[2 * e] = __uint_as_float(v[e] << 16); f[2 * e + 1] = __uint_as_float(v[e] & 0xffff0000u); }
-  } else {
+  if constexpr (sizeof(T) == 2) unpack8(v, f);
+  else {
 #pragma unroll
     for (int e = 0; e < 4; ++e) f[e] = __uint_as_float(v[e]);
   }
 }
 template <typename T> __device__ __forceinline__ sp_u32x4 sp_pack(const float* f) {
+  if constexpr (sizeof(T) == 2) return pack8(f);
   sp_u32x4 o;
-  if constexpr (sizeof(T) == 2) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) { const sp_f32x2 p = {f[2 * e], f[2 * e + 1]}; o[e] = __builtin_bit_cast(unsigned, __builtin_convertvector(p, sp_bf16x2)); }
-  } else {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) o[e] = __float_as_uint(f[e]);
-  }
+  for (int e = 0; e < 4; ++e) o[e] = __float_as_uint(f[e]);
   return o;
 }
 

@@ -12,23 +12,11 @@
 namespace sm {
 
 typedef unsigned int sp_u32x4 __attribute__((ext_vector_type(4)));
-typedef float sp_f32x2 __attribute__((ext_vector_type(2)));
 typedef float sp_f32x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 sp_bf16x2 __attribute__((ext_vector_type(2)));
 
 namespace {
 constexpr int kSumCols = 2048;      // columns per step of sum_parts_kernel
 
-__device__ __forceinline__ void sp_unpack8(sp_u32x4 v, float* f) {
-#pragma unroll
-  for (int e = 0; e < 4; ++e) { f[2 * e] = __uint_as_float(v[e] << 16); f[2 * e + 1] = __uint_as_float(v[e] & 0xffff0000u); }
-}
-__device__ __forceinline__ sp_u32x4 sp_pack8(const float* f) {
-  sp_u32x4 o;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) { const sp_f32x2 p = {f[2 * e], f[2 * e + 1]}; o[e] = __builtin_bit_cast(unsigned, __builtin_convertvector(p, sp_bf16x2)); }
-  return o;
-}
 __device__ __forceinline__ float sp_block_sum(float v, float* red) {
   v = wave_sum(v);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
@@ -83,12 +71,12 @@ __global__ __launch_bounds__(256) void sum_parts_kernel(SumPartsArgs a) {
   for (int j = 0; j < MAXP; ++j) {
     const int c = threadIdx.x + 256 * j;
     float r[8], b[8];
-    sp_unpack8(res[j], r); sp_unpack8(bias[j], b);
+    unpack8(res[j], r); unpack8(bias[j], b);
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[j][e] = (v[j][e] + (a.bias ? b[e] : 0.f)) + r[e];
-    const sp_u32x4 o = sp_pack8(v[j]);
+    const sp_u32x4 o = pack8(v[j]);
     if (c < nch) *(sp_u32x4*)(a.y + base + 8 * c) = o;
-    sp_unpack8(o, v[j]);
+    unpack8(o, v[j]);
 #pragma unroll
     for (int e = 0; e < 8; ++e) sum += c < nch ? v[j][e] : 0.f;
   }
@@ -104,10 +92,10 @@ __global__ __launch_bounds__(256) void sum_parts_kernel(SumPartsArgs a) {
   for (int j = 0; j < MAXP; ++j) {
     const int c = threadIdx.x + 256 * j;
     float g[8], b[8];
-    sp_unpack8(gam[j], g); sp_unpack8(bet[j], b);
+    unpack8(gam[j], g); unpack8(bet[j], b);
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[j][e] = fmaf((v[j][e] - mean) * rstd, g[e], a.beta ? b[e] : 0.f);
-    if (c < nch) *(sp_u32x4*)(a.n + base + 8 * c) = sp_pack8(v[j]);
+    if (c < nch) *(sp_u32x4*)(a.n + base + 8 * c) = pack8(v[j]);
   }
 }
 }  // namespace

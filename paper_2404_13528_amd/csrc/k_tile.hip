@@ -54,20 +54,14 @@ template <int EPI> __device__ __forceinline__ int tile_col(const TileCols& cm, i
   }
   return n;
 }
-__device__ __forceinline__ void tile_sincos(float rev, float* sn, float* cs) {      // angle in revolutions, as rope_sincos of k_gemm.hip
-  const float f = __builtin_amdgcn_fractf(rev);
-  *sn = __builtin_amdgcn_sinf(f);
-  *cs = __builtin_amdgcn_cosf(f);
-}
 // LDS accesses as assembly: next to outstanding LDS-DMA loads the compiler would wait for all of them first
 __device__ __forceinline__ void lds_write8(unsigned at, int off, tl_u32x2 v) { asm volatile("ds_write_b64 %0, %1 offset:%2" ::"v"(at), "v"(v), "n"(off) : "memory"); }
 // an accumulator register's value.  As assembly, so that the accumulators stay where they are until their turn comes (the compiler
 // copies all of them to vector registers after the K loop, and spills); the caller has waited for the last MFMA
 __device__ __forceinline__ float acc_read(float a) { float v; asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v) : "a"(a)); return v; }
-__device__ __forceinline__ float tile_silu(float x) { return x / (1.f + __expf(-x)); }
 
 // stages of K-tiles; blocks of 32 columns that a wave stores at a time (their LDS beside the stages: 32 rows of 16 PIECES + 16 bytes per wave)
-constexpr int tile_stages(int mi, int ni) { return mi + ni >= 7 ? 2 : (mi + ni >= 5 ? 3 : 4); }
+constexpr int tile_stages(int mi, int ni) { return mi + ni >= 7 ? 2 : 3; }
 constexpr int tile_chunk(int mi, int ni, int epi) { return epi == EPI_GLU ? (mi == 2 && ni == 4 ? 2 : ni) : (ni % 2 || mi + ni == 6 ? 1 : 2); }
 constexpr int tile_pieces(int mi, int ni, int epi) { return tile_chunk(mi, ni, epi) * (epi == EPI_GLU ? 2 : 4); }
 constexpr size_t tile_lds(int mi, int ni, int epi) {
@@ -367,7 +361,7 @@ __global__ __launch_bounds__(256, 1) void tile_kernel(GemmArgs g, TileCols cm, T
           for (int i = 0; i < 16; ++i) v[i] = acc_read(acc[mi][c0 + nb][i]) + bv[nb][i];
           if constexpr (EPI == EPI_GLU) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = g.act == SM_ACT_SWIGLU ? tile_silu(v[i]) * v[8 + i] : v[i] * gelu_poly(v[8 + i]);
+            for (int i = 0; i < 8; ++i) v[i] = g.act == SM_ACT_SWIGLU ? silu_f(v[i]) * v[8 + i] : v[i] * gelu_poly(v[8 + i]);
           } else if constexpr (EPI == EPI_GELU) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) v[i] = gelu_poly(v[i]);
@@ -377,7 +371,7 @@ __global__ __launch_bounds__(256, 1) void tile_kernel(GemmArgs g, TileCols cm, T
 #pragma unroll
               for (int i = 0; i < 8; ++i) {
                 float sn, cs;
-                tile_sincos(pos * theta[nb][i], &sn, &cs);
+                rope_sincos(pos * theta[nb][i], &sn, &cs);
                 const float a = v[i], b = v[8 + i];
                 v[i] = a * cs - b * sn;
                 v[8 + i] = b * cs + a * sn;
@@ -495,12 +489,7 @@ int tile_launch2(const GemmArgs& g, const TileCols& cm, hipStream_t s, int split
   const int tiles_n = (g.N + 64 * NI - 1) / (64 * NI);
   const int64_t tiles_m = (g.M + 64 * MI - 1) / (64 * MI);
   if (tiles_m * tiles_n > INT32_MAX) return (int)hipErrorInvalidValue;
-  int xn = 1;                                 // strips, as in gemm_launch3
-  double best = 1e300;
-  for (int c = 1; c <= 8; c *= 2) {
-    const double rows = (double)c * (double)g.M + (8.0 / c) * (double)g.N;
-    if (rows < best && c <= tiles_n) { best = rows; xn = c; }
-  }
+  const int xn = xcd_strips(g.M, g.N, tiles_n);
   const int nk = g.K >> 6;
   const TileGrid ts{(int)tiles_m, tiles_n, (tiles_n + xn - 1) / xn, g.K >= 1024 ? (int)std::min<int64_t>(4, tiles_m) : 1, splits, nk / splits, nk % splits, part};
   const int64_t grid = EPI == EPI_PART ? tiles_m * tiles_n * splits : std::min<int64_t>(tiles_m * tiles_n, 256);      // one workgroup per CU (a multiple of 8 where it walks through several tiles)

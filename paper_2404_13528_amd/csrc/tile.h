@@ -9,6 +9,18 @@ bool tile_linear_use(const GemmArgs& g, int* mi, int* ni);      // whether launc
 int launch_tile_linear(const GemmArgs& g, int mi, int ni, void* stream);
 double gemm_kernel_cost(const GemmArgs& g);                             // what gemm_kernel (k_gemm.hip) takes for g, us
 
+// Strips of the tile grid: xn of them, 8 / xn XCDs per strip; an XCD then reads M / (8 / xn) rows of A and N / xn rows of W, in total
+// xn M + (8 / xn) N rows of K elements: the xn that makes that smallest
+inline int xcd_strips(int64_t M, int N, int tiles_n) {
+  int xn = 1;
+  double best = 1e300;
+  for (int c = 1; c <= 8; c *= 2) {
+    const double rows = (double)c * (double)M + (8.0 / c) * (double)N;
+    if (rows < best && c <= tiles_n) { best = rows; xn = c; }
+  }
+  return xn;
+}
+
 // A bf16 Linear with a residual on few rows, cut over K: parts in fp32, summed by a second kernel that also takes the norm behind it
 struct SplitKPlan { int mi, ni, splits; };
 struct SumPartsArgs {
