@@ -46,6 +46,19 @@ __device__ __forceinline__ void mlp_unpack8(mlp_u32x4 v, float* f) {
   for (int e = 0; e < 4; ++e) { f[2 * e] = __uint_as_float(v[e] << 16); f[2 * e + 1] = __uint_as_float(v[e] & 0xffff0000u); }
 }
 
+// eight elements times rstd plus sh (the normalised value), times gamma plus beta, rounded to bf16
+__device__ __forceinline__ mlp_u32x4 mlp_scale8(const mlp_u32x4& v, float rstd, float sh, const mlp_u32x4& gam, const mlp_u32x4& bet) {
+  float f[8], g[8], b[8];
+  mlp_unpack8(v, f);
+  mlp_unpack8(gam, g);
+  mlp_unpack8(bet, b);
+  mlp_u32x4 o;
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    o[e] = mlp_pack2(fmaf(fmaf(f[2 * e], rstd, sh), g[2 * e], b[2 * e]), fmaf(fmaf(f[2 * e + 1], rstd, sh), g[2 * e + 1], b[2 * e + 1]));
+  return o;
+}
+
 // one thread per 16-byte chunk of the packed buffer: [W1 fragments | W2 fragments]
 __global__ void mlp_pack_kernel(const bf16_t* W1, const bf16_t* W2, mlp_u32x4* packed, int C, int Hd) {
   const int KK = C / 16, nsub = Hd / 32;
@@ -68,76 +81,157 @@ __global__ void mlp_pack_kernel(const bf16_t* W1, const bf16_t* W2, mlp_u32x4* p
   packed[o] = *(const mlp_u32x4*)src;
 }
 
-// X tile of 32 token rows -> LDS, rows at an odd pitch of 16-byte slots (rows past M as zeros); 256 threads
-template <int C, int NTHR = 256>
-__device__ __forceinline__ void mlp_load_x_tile(mlp_u32x4* x_l, const bf16_t* X, int64_t row0, int64_t M, int ident, int64_t ld,
-                                                const SM_KARG RowProg* rows) {
-  constexpr int XS = C / 8, XP = XS + 1, NIT = (32 * XS + NTHR - 1) / NTHR;
-  // three passes, so that the offset lookups (a table load each, where the rows go through one) are in flight together,
-  // and then the data loads: one latency each instead of one per chunk
-  const int32_t* tab = ident ? nullptr : rows->table;
-  int64_t off[NIT];
-  int toff[NIT];
-#pragma unroll
-  for (int i = 0; i < NIT; ++i) {
-    const int s = threadIdx.x + i * NTHR, r = s / XS;
-    const int64_t row = min(row0 + min(r, 31), M - 1);
-    if (ident) off[i] = row * ld;
-    else if (tab) toff[i] = tab[row];
-    else off[i] = eval_rows_k(rows, row);
-  }
+// ROWS token rows -> LDS, rows at an odd pitch of 16-byte slots (rows past M as zeros), in two steps: request() puts every
+// row-offset lookup and then every load in flight, store() waits for them.  What a kernel requests in between (a second
+// tile, the weight stream) travels at the same time.
+template <int C, int NTHR, int ROWS>
+struct MlpTile {
+  static constexpr int XS = C / 8, XP = XS + 1, NIT = (ROWS * XS + NTHR - 1) / NTHR;
   mlp_u32x4 v[NIT];
+  __device__ __forceinline__ void request(const bf16_t* X, int64_t row0, int64_t M, int ident, int64_t ld, const SM_KARG RowProg* rows) {
+    int64_t row[NIT], off[NIT];
 #pragma unroll
-  for (int i = 0; i < NIT; ++i) {
-    const int s = threadIdx.x + i * NTHR, r = s / XS, c = s - r * XS;
-    if (!ident && tab) off[i] = (int64_t)toff[i];
-    v[i] = *(const mlp_u32x4*)(X + off[i] + (s < 32 * XS ? c : 0) * 8);
-  }
+    for (int i = 0; i < NIT; ++i) row[i] = min(row0 + min((int)(threadIdx.x + i * NTHR) / XS, ROWS - 1), M - 1);
+    if (ident) {
 #pragma unroll
-  for (int i = 0; i < NIT; ++i) {
-    const int s = threadIdx.x + i * NTHR, r = s / XS, c = s - r * XS;
-    if (s < 32 * XS) x_l[r * XP + c] = row0 + r < M ? v[i] : mlp_u32x4{0u, 0u, 0u, 0u};
+      for (int i = 0; i < NIT; ++i) off[i] = row[i] * ld;
+    } else if (const int32_t* tab = rows->table) {
+      int32_t t[NIT];
+#pragma unroll
+      for (int i = 0; i < NIT; ++i) t[i] = tab[row[i]];
+#pragma unroll
+      for (int i = 0; i < NIT; ++i) off[i] = t[i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < NIT; ++i) off[i] = eval_rows_k(rows, row[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < NIT; ++i) {
+      const int s = threadIdx.x + i * NTHR, c = s - s / XS * XS;
+      v[i] = *(const mlp_u32x4*)(X + off[i] + (s < ROWS * XS ? c : 0) * 8);
+    }
   }
-}
+  __device__ __forceinline__ void store(mlp_u32x4* x_l, int64_t row0, int64_t M) const {
+#pragma unroll
+    for (int i = 0; i < NIT; ++i) {
+      const int s = threadIdx.x + i * NTHR, r = s / XS, c = s - r * XS;
+      if (s < ROWS * XS) x_l[r * XP + c] = row0 + r < M ? v[i] : mlp_u32x4{0u, 0u, 0u, 0u};
+    }
+  }
+};
 
-// LayerNorm of the tile's rows in place (the norm that precedes the product, folded): eight lanes per token,
-// two-pass fp32 statistics, the result rounded to bf16 as a separate norm kernel would have stored it
-template <int C, int NTOK = 32>
+// LayerNorm of the tile's rows in place (the norm that precedes the product, folded): TPT adjacent lanes per token, each
+// holding its chunks of the row in registers; two-pass fp32 statistics, the result rounded to bf16 as a separate norm
+// kernel would have stored it.  No barrier inside.
+template <int C, int NTHR, int NTOK>
 __device__ __forceinline__ void mlp_norm_x_tile(mlp_u32x4* x_l, float eps, const mlp_u32x4* gam, const mlp_u32x4* bet) {
-  constexpr int XS = C / 8, XP = XS + 1;
-  const int p = threadIdx.x & 7;                // eight threads per token; no barrier inside
-  for (int r = threadIdx.x >> 3; r < NTOK; r += blockDim.x >> 3) {
-    mlp_u32x4* xr = x_l + r * XP;
-    float sum = 0.f;
-    for (int c = p; c < XS; c += 8) {
-      float f[8];
-      mlp_unpack8(xr[c], f);
+  constexpr int XS = C / 8, XP = XS + 1, Q = NTHR / NTOK, TPT = Q >= 16 ? 16 : Q >= 8 ? 8 : 4, NCH = (XS + TPT - 1) / TPT;
+  static_assert(Q >= 4, "at least four lanes per token");
+  const int r = threadIdx.x / TPT, p = threadIdx.x & (TPT - 1);
+  if (r >= NTOK) return;                        // (whole groups of TPT lanes)
+  mlp_u32x4* xr = x_l + r * XP;
+  mlp_u32x4 x[NCH], gv[NCH], bv[NCH];
+#pragma unroll
+  for (int i = 0; i < NCH; ++i) {
+    const int c = min(p + TPT * i, XS - 1);
+    x[i] = xr[c]; gv[i] = gam[c]; bv[i] = bet[c];
+  }
+  float sum = 0.f, var = 0.f;
+#pragma unroll
+  for (int i = 0; i < NCH; ++i) {
+    float f[8];
+    mlp_unpack8(x[i], f);
+    if (XS % TPT == 0 || p + TPT * i < XS)
 #pragma unroll
       for (int e = 0; e < 8; ++e) sum += f[e];
-    }
-    sum += __shfl_xor(sum, 1, 64); sum += __shfl_xor(sum, 2, 64); sum += __shfl_xor(sum, 4, 64);
-    const float mean = sum / (float)C;
-    float var = 0.f;
-    for (int c = p; c < XS; c += 8) {
-      float f[8];
-      mlp_unpack8(xr[c], f);
+  }
+#pragma unroll
+  for (int o = 1; o < TPT; o <<= 1) sum += __shfl_xor(sum, o, 64);
+  const float mean = sum / (float)C;
+#pragma unroll
+  for (int i = 0; i < NCH; ++i) {
+    float f[8];
+    mlp_unpack8(x[i], f);
+    if (XS % TPT == 0 || p + TPT * i < XS)
 #pragma unroll
       for (int e = 0; e < 8; ++e) { const float d = f[e] - mean; var += d * d; }
-    }
-    var += __shfl_xor(var, 1, 64); var += __shfl_xor(var, 2, 64); var += __shfl_xor(var, 4, 64);
-    const float rstd = rsqrtf(var / (float)C + eps), sh = -mean * rstd;
-    for (int c = p; c < XS; c += 8) {
-      float f[8], gf[8], bf[8];
-      mlp_unpack8(xr[c], f);
-      mlp_unpack8(gam[c], gf);
-      mlp_unpack8(bet[c], bf);
-      mlp_u32x4 o;
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        o[e] = mlp_pack2(fmaf(fmaf(f[2 * e], rstd, sh), gf[2 * e], bf[2 * e]), fmaf(fmaf(f[2 * e + 1], rstd, sh), gf[2 * e + 1], bf[2 * e + 1]));
-      xr[c] = o;
-    }
   }
+#pragma unroll
+  for (int o = 1; o < TPT; o <<= 1) var += __shfl_xor(var, o, 64);
+  const float rstd = rsqrtf(var / (float)C + eps), sh = -mean * rstd;
+#pragma unroll
+  for (int i = 0; i < NCH; ++i)
+    if (XS % TPT == 0 || p + TPT * i < XS) xr[p + TPT * i] = mlp_scale8(x[i], rstd, sh, gv[i], bv[i]);
+}
+
+// Statistics of rows whose features lie in the registers of NW waves, NB blocks of 32 each (lane (token, hf): 16 features of a
+// block): every wave leaves its own mean and sum of squared deviations, and after one barrier a lane joins them,
+//   C var = sum over waves of [squares + 32 NB (mean of the wave - mean)^2],
+// which loses no more than a second pass over the row would.
+template <int NB>
+__device__ __forceinline__ void mlp_stats_put(const mlp_u32x4 (&v)[NB][2], int hf, float2* st) {
+  float f[NB][16];
+  float sum = 0.f, sq = 0.f;
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    mlp_unpack8(v[b][0], f[b]);
+    mlp_unpack8(v[b][1], f[b] + 8);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) sum += f[b][e];
+  }
+  sum += __shfl_xor(sum, 32, 64);
+  const float m = sum * (1.f / (32 * NB));
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) { const float d = f[b][e] - m; sq += d * d; }
+  sq += __shfl_xor(sq, 32, 64);
+  if (hf == 0) *st = make_float2(m, sq);
+}
+// st: the token's word of wave 0, the next wave's `pitch` further on
+template <int NB, int NW>
+__device__ __forceinline__ void mlp_stats_get(const float2* st, int pitch, float eps, float* rstd, float* sh) {
+  float mean = 0.f, sq = 0.f;
+#pragma unroll
+  for (int i = 0; i < NW; ++i) mean += st[i * pitch].x;
+  mean *= 1.f / NW;
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    const float2 s = st[i * pitch];
+    const float d = s.x - mean;
+    sq += s.y + (float)(32 * NB) * d * d;
+  }
+  *rstd = rsqrtf(sq * (1.f / (32 * NB * NW)) + eps);
+  *sh = -mean * *rstd;
+}
+
+// the lane's number computed afresh (a register that is live over all rounds for the epilogue's sake would be spilled)
+__device__ __forceinline__ int mlp_lane() {
+  unsigned z = 0;
+  asm volatile("" : "+s"(z));
+  return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, z));
+}
+// A 32 x 32 block of results that a wave holds as 16-byte runs (lane (token, hf): runs 2 gp + hf of the token's four) goes to
+// memory in whole 64-byte pieces, a piece in four adjacent lanes, by way of 2 KiB of LDS that only this wave uses.  Stored from
+// where they are, an instruction touches 32 rows for 32 bytes each, and the Linears that write more than they read wait for the
+// store path (packed Linear with LayerNorm, us: 200704 x 384 x 128 74.9 -> 62.2, 50176 x 768 x 256 51.0 -> 45.0, 12544 x 768 x 256
+// 17.0 -> 13.3).  mlp_stage_get(i): token 16 i + lane / 4, run lane % 4.
+__device__ __forceinline__ void mlp_stage_put(mlp_u32x4* st, int l32, int hf, const mlp_u32x4& v0, const mlp_u32x4& v1) {
+  const int k = (l32 >> 2) & 3;                 // (16 lanes of a write, and of a read, in 16 different bank groups)
+  st[l32 * 4 + (hf ^ k)] = v0;
+  st[l32 * 4 + ((2 + hf) ^ k)] = v1;
+  __builtin_amdgcn_wave_barrier();
+}
+__device__ __forceinline__ mlp_u32x4 mlp_stage_get(const mlp_u32x4* st, int lane, int i) {
+  const int t = 16 * i + (lane >> 2);
+  return st[t * 4 + ((lane & 3) ^ ((t >> 2) & 3))];
+}
+// Stores are written as assembly so that the compiler's wait-count bookkeeping sees loads only: with stores pending next to
+// loads it stops counting and waits for everything (vmcnt 0) at the next use of a load, which exposes the latency of the whole
+// weight prefetch.  Its counts stay safe: it may wait for more operations than needed, never fewer (loads return in issue
+// order among themselves).
+__device__ __forceinline__ void mlp_store16(bf16_t* p, const mlp_u32x4& v) {
+  asm volatile("global_store_dwordx4 %0, %1, off\n\ts_nop 1" :: "v"(p), "v"(v) : "memory");
 }
 
 // bias, optional GELU, optional residual of one 32 x 32 accumulator: register 4b + i of lane (token, hf) is row
@@ -164,11 +258,29 @@ __device__ __forceinline__ mlp_u32x4 mlp_finish_half(const mlp_f32x16& h, int gp
   }
   return o;
 }
+// ... and back: an accumulator that starts from the block's values instead of zeros (the residual of a sum of products needs
+// no registers of its own then)
+__device__ __forceinline__ void mlp_start_from(mlp_f32x16& h, const mlp_u32x4 (&v)[2]) {
+#pragma unroll
+  for (int gp = 0; gp < 2; ++gp) {
+    float f[8];
+    mlp_unpack8(v[gp], f);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(f[q]), __float_as_uint(f[4 + q]), false, false);
+      h[8 * gp + q] = __uint_as_float(sw[0]);
+      h[8 * gp + 4 + q] = __uint_as_float(sw[1]);
+    }
+  }
+}
 __device__ __forceinline__ void mlp_finish(const mlp_f32x16& h, const mlp_u32x4& bias_v, const mlp_u32x4& bias_w, const mlp_u32x4* res,
                                            bool gelu_on, mlp_u32x4* outv) {
 #pragma unroll
   for (int gp = 0; gp < 2; ++gp) outv[gp] = mlp_finish_half(h, gp, gp ? bias_w : bias_v, res[gp], gelu_on);
 }
+
+// vectors of C elements beside b1 in the kernel's LDS: b2; bproj, gamma, beta; gamma, beta of the second output; bq (three)
+constexpr int mlp_vectors(bool proj, int lnout) { return 1 + (proj ? 3 : 0) + (lnout ? 2 : 0) + (lnout == 2 ? 3 : 0); }
 
 // PROJ: the Linear that precedes the MLP's residual stream is computed here as well (a transformer block's attention
 // output projection): x1 = A . Wp^T + bp + x0 for the tile's 32 tokens, x0 read (and Y written) through y_rows, then
@@ -179,7 +291,7 @@ __device__ __forceinline__ void mlp_finish(const mlp_f32x16& h, const mlp_u32x4&
 // LNOUT = 2 (with PROJ): that norm stays in LDS and the Linear that follows it (the next block's QKV, N = 3 C, packed
 // like lin_pack_kernel's) runs here too, three slices of 32 outputs per wave, stored through the same row map.
 template <int C, bool PROJ, int LNOUT>
-__global__ __launch_bounds__(64 * (C / 32), 1) void mlp_fused_kernel(MlpArgs g) {
+__global__ __launch_bounds__(64 * (C / 32), C <= 256 ? 4 : 3) void mlp_fused_kernel(MlpArgs g) {
   constexpr int KK = C / 16;            // 16-wide steps of the first product
   constexpr int T = C / 32;             // 32-row blocks of Y^T = waves of the workgroup
   constexpr int NTHR = 64 * T;
@@ -189,14 +301,16 @@ __global__ __launch_bounds__(64 * (C / 32), 1) void mlp_fused_kernel(MlpArgs g) 
   constexpr size_t TILE = (size_t)32 * XP * 16, HTILE = (size_t)32 * HP * 16;
   const SM_KARG MlpArgs* gk = kernarg_ptr<MlpArgs>();
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  // PROJ: [A tile | x1 normalised | x1 plain | H x 2 | b1 | bp]; else [X tile | H x 2 | b1]
+  // [A tile (PROJ) | X tile | H x 2 | b1 | b2 | bproj, gamma, beta (PROJ) | gamma, beta of the second output | bq | row offsets | statistics]
   mlp_u32x4* a_l = (mlp_u32x4*)smem_raw;
-  mlp_u32x4* x_l = (mlp_u32x4*)(smem_raw + (PROJ ? TILE : 0));            // [32][XP]
-  mlp_u32x4* r_l = (mlp_u32x4*)(smem_raw + 2 * TILE);                     // PROJ only
-  mlp_u32x4* h_l = (mlp_u32x4*)(smem_raw + (PROJ ? 3 : 1) * TILE);        // [2][32][HP]
-  mlp_u32x4* b1_l = (mlp_u32x4*)(smem_raw + (PROJ ? 3 : 1) * TILE + 2 * HTILE);   // [Hd / 8]
-  mlp_u32x4* bp_l = b1_l + g.Hd / 8;                                      // PROJ only: [C / 8]
-  float* st_l = (float*)(b1_l + g.Hd / 8 + (PROJ ? XS : 0));              // LNOUT only: [2][T][32] row statistics
+  mlp_u32x4* x_l = (mlp_u32x4*)(smem_raw + (PROJ ? TILE : 0));            // [32][XP]; PROJ: x0, then x1 normalised
+  mlp_u32x4* h_l = (mlp_u32x4*)(smem_raw + (PROJ ? 2 : 1) * TILE);        // [2][32][HP]
+  mlp_u32x4* b1_l = (mlp_u32x4*)(smem_raw + (PROJ ? 2 : 1) * TILE + 2 * HTILE);   // [Hd / 8]
+  mlp_u32x4* vec_l = b1_l + g.Hd / 8;                                     // [NV][XS]
+  constexpr int V_BP = 1, V_G1 = 2, V_E1 = 3, V_G2 = PROJ ? 4 : 1, V_E2 = V_G2 + 1, V_BQ = V_E2 + 1;   // (b2 first)
+  constexpr int NV = mlp_vectors(PROJ, LNOUT);
+  int64_t* ro_l = (int64_t*)(vec_l + NV * XS);                            // [2][32]: of Y and of the second output; -1 past M
+  float2* st_l = (float2*)(ro_l + 64);                                    // [T][32] row statistics
 
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave index as a scalar: fragment bases become scalar addresses
@@ -221,29 +335,48 @@ __global__ __launch_bounds__(64 * (C / 32), 1) void mlp_fused_kernel(MlpArgs g) 
   __amdgpu_buffer_rsrc_t rp = rw, rq = rw;
   if constexpr (PROJ) rp = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(g.Wproj_p), 0, 2 * C * C, 0x00020000);
   if constexpr (LNOUT == 2) rq = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(g.Wq_p), 0, 6 * C * C, 0x00020000);
+
+  // Everything the tile needs from memory is requested before anything is waited for, the rows before the weight stream (loads
+  // return in the order they were asked for): the tile, PROJ's residual x0 (through y_rows), the vectors, the row offsets
+  MlpTile<C, NTHR, 32> xt, rt;
+  xt.request((const bf16_t*)g.X, row0, g.M, g.x_rows.identity, g.x_rows.ld, &gk->x_rows);
+  if constexpr (PROJ) rt.request((const bf16_t*)g.resid0, row0, g.M, g.y_rows.identity, g.y_rows.ld, &gk->y_rows);
+  if (tid < 32 || (LNOUT != 0 && tid < 64)) {
+    const int64_t row = row0 + (tid & 31), prow = row < g.M ? row : g.M - 1;
+    int64_t o;
+    if (LNOUT == 0 || tid < 32) o = g.y_rows.identity ? prow * g.y_rows.ld : eval_rows_k(&gk->y_rows, prow);
+    else o = g.y2_rows.identity ? prow * g.y2_rows.ld : eval_rows_k(&gk->y2_rows, prow);
+    ro_l[tid] = row < g.M ? o : -1;
+  }
+  for (int s = tid; s < Hd / 8; s += NTHR) b1_l[s] = ((const mlp_u32x4*)g.b1)[s];
+  if (tid < XS) {
+    mlp_u32x4 v[6];
+    v[0] = ((const mlp_u32x4*)g.b2)[tid];
+    if constexpr (PROJ) {
+      v[V_BP] = ((const mlp_u32x4*)g.bproj)[tid];
+      v[V_G1] = v[V_E1] = mlp_u32x4{0u, 0u, 0u, 0u};
+      if (g.norm) { v[V_G1] = ((const mlp_u32x4*)g.norm_gamma)[tid]; v[V_E1] = ((const mlp_u32x4*)g.norm_beta)[tid]; }
+    }
+    if constexpr (LNOUT != 0) { v[V_G2] = ((const mlp_u32x4*)g.ln2_gamma)[tid]; v[V_E2] = ((const mlp_u32x4*)g.ln2_beta)[tid]; }
+#pragma unroll
+    for (int i = 0; i < (LNOUT == 2 ? V_BQ : NV); ++i) vec_l[i * XS + tid] = v[i];
+  }
+  if constexpr (LNOUT == 2) for (int s = tid; s < 3 * XS; s += NTHR) vec_l[V_BQ * XS + s] = ((const mlp_u32x4*)g.bq)[s];
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk) wf[kk] = PROJ ? wload(rp, (w * KK + kk) * 1024) : wload(rw, (sc0 * KK + kk) * 1024);
-
-  // the lane's output-row offsets (table lookups, where the rows are mapped) are requested before the tile's loads,
-  // not where they are first used
-  const int64_t prow = row0 + l32 < g.M ? row0 + l32 : g.M - 1;          // lanes past M read the last row and store nothing
-  const bool row_ok = row0 + l32 < g.M;
-  const int64_t ro = g.y_rows.identity ? prow * g.y_rows.ld : eval_rows_k(&gk->y_rows, prow);
-  int64_t ro2 = 0;
-  if constexpr (LNOUT != 0) ro2 = g.y2_rows.identity ? prow * g.y2_rows.ld : eval_rows_k(&gk->y2_rows, prow);
-  mlp_load_x_tile<C, NTHR>(PROJ ? a_l : x_l, (const bf16_t*)g.X, row0, g.M, g.x_rows.identity, g.x_rows.ld, &gk->x_rows);
-  for (int s = tid; s < Hd / 8; s += NTHR) b1_l[s] = ((const mlp_u32x4*)g.b1)[s];
-  if constexpr (PROJ) for (int s = tid; s < XS; s += NTHR) bp_l[s] = ((const mlp_u32x4*)g.bproj)[s];
+  xt.store(PROJ ? a_l : x_l, row0, g.M);
+  if constexpr (PROJ) rt.store(x_l, row0, g.M);
   __syncthreads();
 
-  const int fo = w * 32 + hf * 8;                                         // first of the lane's features in the wave's block
+  const mlp_u32x4 zero4[2] = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}};
+  const int fs = w * 4 + hf;                                              // first of the lane's two feature slots (the other: fs + 2)
+  const int xs = l32 * XP + fs;
 
-  mlp_u32x4 resid[2] = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}};              // residual of the final sum (lane's two runs of eight)
+  mlp_f32x16 out;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) out[e] = 0.f;
   if constexpr (PROJ) {
     // wave w forms features 32 w ..+31 of x1
-    const bf16_t* R0 = (const bf16_t*)g.resid0;
-    const mlp_u32x4 res[2] = {*(const mlp_u32x4*)(R0 + ro + fo), *(const mlp_u32x4*)(R0 + ro + fo + 16)};
-    const mlp_u32x4 bias_v = bp_l[w * 4 + hf], bias_w = bp_l[w * 4 + 2 + hf];
     int ao = l32 * XP + hf;
     asm volatile("" : "+v"(ao));
     mlp_f32x16 h;
@@ -263,23 +396,26 @@ __global__ __launch_bounds__(64 * (C / 32), 1) void mlp_fused_kernel(MlpArgs g) 
       __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
       __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
     }
-    mlp_finish(h, bias_v, bias_w, res, false, resid);          // x1 rounded to bf16, as the separate Linear stores it
+    const mlp_u32x4 res[2] = {x_l[xs], x_l[xs + 2]};           // x0, of which every lane reads the slots that it overwrites below
+    mlp_u32x4 x1[1][2];
+    mlp_finish(h, vec_l[V_BP * XS + fs], vec_l[V_BP * XS + fs + 2], res, false, x1[0]);          // x1 rounded to bf16, as the separate Linear stores it
+    mlp_start_from(out, x1[0]);
+    if (g.norm) {
+      mlp_stats_put<1>(x1, hf, st_l + w * 32 + l32);
+      __syncthreads();
+      float rstd, sh;
+      mlp_stats_get<1, T>(st_l + l32, 32, g.norm_eps, &rstd, &sh);
 #pragma unroll
-    for (int gp = 0; gp < 2; ++gp) {
-      x_l[l32 * XP + w * 4 + 2 * gp + hf] = resid[gp];
-      r_l[l32 * XP + w * 4 + 2 * gp + hf] = resid[gp];
+      for (int gp = 0; gp < 2; ++gp) x_l[xs + 2 * gp] = mlp_scale8(x1[0][gp], rstd, sh, vec_l[V_G1 * XS + fs + 2 * gp], vec_l[V_E1 * XS + fs + 2 * gp]);
+    } else {
+#pragma unroll
+      for (int gp = 0; gp < 2; ++gp) x_l[xs + 2 * gp] = x1[0][gp];
     }
     __syncthreads();
-  }
-  if (g.norm) {
-    mlp_norm_x_tile<C>(x_l, g.norm_eps, (const mlp_u32x4*)g.norm_gamma, (const mlp_u32x4*)g.norm_beta);
+  } else if (g.norm) {
+    mlp_norm_x_tile<C, NTHR, 32>(x_l, g.norm_eps, (const mlp_u32x4*)g.norm_gamma, (const mlp_u32x4*)g.norm_beta);
     __syncthreads();
   }
-
-  mlp_f32x16 out;
-#pragma unroll
-  for (int e = 0; e < 16; ++e) out[e] = 0.f;
-  const mlp_u32x4 zero4[2] = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}};
 
   for (int r = 0; r < rounds; ++r) {
     // ---- first product: this wave's slice of the round -> H (bias, GELU, bf16) into LDS
@@ -341,80 +477,55 @@ __global__ __launch_bounds__(64 * (C / 32), 1) void mlp_fused_kernel(MlpArgs g) 
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) wf[kk] = wload(rq, (w * KK + kk) * 1024);
   }
-  // every wave holds its 32 features of Y^T complete: bias, residual, two 16-byte stores per lane
-  if constexpr (PROJ) { resid[0] = r_l[l32 * XP + w * 4 + hf]; resid[1] = r_l[l32 * XP + w * 4 + 2 + hf]; }
-  else if (g.residual) {          // (asked for here, not before the rounds: eight more live registers there mean spills)
-    const bf16_t* R = (const bf16_t*)g.residual;
-    resid[0] = *(const mlp_u32x4*)(R + ro + fo);
-    resid[1] = *(const mlp_u32x4*)(R + ro + fo + 16);
+  {
+  // every wave holds its 32 features of Y^T complete: bias, residual, and out in 64-byte pieces through the wave's 2 KiB of
+  // the X tile (nobody has read that since the last barrier)
+  const int lane = mlp_lane(), l32 = lane & 31, hf = lane >> 5, fs = w * 4 + hf, xs = l32 * XP + fs;
+  mlp_u32x4* stage = x_l + w * 128;
+  auto emit = [&](bf16_t* base, int scale, const int64_t* ro, int col, const mlp_u32x4& v0, const mlp_u32x4& v1) __attribute__((always_inline)) {
+    mlp_stage_put(stage, l32, hf, v0, v1);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const mlp_u32x4 v = mlp_stage_get(stage, lane, i);
+      const int64_t o = ro[16 * i + (lane >> 2)];
+      if (o >= 0) mlp_store16(base + o * scale + col + (lane & 3) * 8, v);
+    }
+  };
+  mlp_u32x4 resid[2] = {zero4[0], zero4[0]};              // (PROJ: x1, which the sum started from)
+  if constexpr (!PROJ) {
+    if (g.residual) {          // (asked for here, not before the rounds: eight more live registers there mean spills)
+      const int64_t o = ro_l[l32];
+      const bf16_t* R = (const bf16_t*)g.residual + (o < 0 ? ro_l[0] : o);      // (lanes past M: the tile's first row)
+      resid[0] = *(const mlp_u32x4*)(R + fs * 8);
+      resid[1] = *(const mlp_u32x4*)(R + fs * 8 + 16);
+    }
   }
-  const mlp_u32x4 b2v = *(const mlp_u32x4*)((const bf16_t*)g.b2 + fo), b2w = *(const mlp_u32x4*)((const bf16_t*)g.b2 + fo + 16);
-  mlp_u32x4 yv[2];
-  mlp_finish(out, b2v, b2w, resid, false, yv);
-  if (row_ok) {
-    bf16_t* Y = (bf16_t*)g.Y;
-    *(mlp_u32x4*)(Y + ro + fo) = yv[0];
-    *(mlp_u32x4*)(Y + ro + fo + 16) = yv[1];
-  }
+  mlp_u32x4 yv[1][2];
+  mlp_finish(out, vec_l[fs], vec_l[fs + 2], resid, false, yv[0]);
+  if constexpr (LNOUT != 0) mlp_stats_put<1>(yv, hf, st_l + w * 32 + l32);
+  emit((bf16_t*)g.Y, 1, ro_l, w * 32, yv[0][0], yv[0][1]);
   if constexpr (LNOUT != 0) {
-    // two-pass fp32 statistics of the bf16 row, as the norm kernel would compute them from the stored Y: a lane holds
-    // 16 of its token's features, its partner lane (other hf) 16 more, the other waves the rest
-    const mlp_u32x4 gv[2] = {*(const mlp_u32x4*)((const bf16_t*)g.ln2_gamma + fo), *(const mlp_u32x4*)((const bf16_t*)g.ln2_gamma + fo + 16)};
-    const mlp_u32x4 bv[2] = {*(const mlp_u32x4*)((const bf16_t*)g.ln2_beta + fo), *(const mlp_u32x4*)((const bf16_t*)g.ln2_beta + fo + 16)};
-    float f[16];
-    mlp_unpack8(yv[0], f);
-    mlp_unpack8(yv[1], f + 8);
-    float sum = 0.f;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) sum += f[e];
-    sum += __shfl_xor(sum, 32, 64);
-    if (hf == 0) st_l[w * 32 + l32] = sum;
+    // LayerNorm of the bf16 row, as the norm kernel would compute it from the stored Y
     __syncthreads();
-    float tot = 0.f;
-#pragma unroll
-    for (int ww = 0; ww < T; ++ww) tot += st_l[ww * 32 + l32];
-    const float mean = tot / (float)C;
-    float var = 0.f;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) { const float d = f[e] - mean; var += d * d; }
-    var += __shfl_xor(var, 32, 64);
-    if (hf == 0) st_l[(T + w) * 32 + l32] = var;
-    __syncthreads();
-    tot = 0.f;
-#pragma unroll
-    for (int ww = 0; ww < T; ++ww) tot += st_l[(T + ww) * 32 + l32];
-    const float rstd = rsqrtf(tot / (float)C + g.ln2_eps), sh = -mean * rstd;
+    float rstd, sh;
+    mlp_stats_get<1, T>(st_l + l32, 32, g.ln2_eps, &rstd, &sh);
     mlp_u32x4 nv[2];
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      float gf[8], bf[8];
-      mlp_unpack8(gv[q], gf);
-      mlp_unpack8(bv[q], bf);
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        nv[q][e] = mlp_pack2(fmaf(fmaf(f[8 * q + 2 * e], rstd, sh), gf[2 * e], bf[2 * e]), fmaf(fmaf(f[8 * q + 2 * e + 1], rstd, sh), gf[2 * e + 1], bf[2 * e + 1]));
-    }
+    for (int q = 0; q < 2; ++q) nv[q] = mlp_scale8(yv[0][q], rstd, sh, vec_l[V_G2 * XS + fs + 2 * q], vec_l[V_E2 * XS + fs + 2 * q]);
     if constexpr (LNOUT == 1) {
-      if (row_ok) {
-        bf16_t* Y2 = (bf16_t*)g.Y2;
-        *(mlp_u32x4*)(Y2 + ro2 + fo) = nv[0];
-        *(mlp_u32x4*)(Y2 + ro2 + fo + 16) = nv[1];
-      }
+      emit((bf16_t*)g.Y2, 1, ro_l + 32, w * 32, nv[0], nv[1]);
     } else {
       static_assert(LNOUT != 2 || PROJ, "the fused following Linear needs the projection variant's spare LDS tile");
-      // the normalised tile (bf16, as a norm kernel would have stored it) into the A tile's LDS, the following
-      // Linear's bias over the first bias (both dead by now), then wave w forms outputs 32 (w + T j) ..+31, j < 3
+      // the normalised tile (bf16, as a norm kernel would have stored it) into the A tile's LDS, dead since the projection; then
+      // wave w forms outputs 32 (w + T j) ..+31, j < 3
       mlp_u32x4* n_l = a_l;
-      n_l[l32 * XP + w * 4 + hf] = nv[0];
-      n_l[l32 * XP + w * 4 + 2 + hf] = nv[1];
-      for (int s = tid; s < 3 * XS; s += NTHR) b1_l[s] = ((const mlp_u32x4*)g.bq)[s];
+      n_l[xs] = nv[0];
+      n_l[xs + 2] = nv[1];
       __syncthreads();
-      bf16_t* Q = (bf16_t*)g.Y2;
-      const int64_t qo = ro2 * 3;                       // same row map, rows three times as long
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
         const int sc = w + T * j;
-        const mlp_u32x4 bias_v = b1_l[sc * 4 + hf], bias_w = b1_l[sc * 4 + 2 + hf];
+        const mlp_u32x4 bias_v = vec_l[V_BQ * XS + sc * 4 + hf], bias_w = vec_l[V_BQ * XS + sc * 4 + 2 + hf];
         int no = l32 * XP + hf;
         asm volatile("" : "+v"(no));
         mlp_f32x16 h;
@@ -436,14 +547,10 @@ __global__ __launch_bounds__(64 * (C / 32), 1) void mlp_fused_kernel(MlpArgs g) 
         }
         mlp_u32x4 qv[2];
         mlp_finish(h, bias_v, bias_w, zero4, false, qv);
-        if (row_ok) {
-          // (assembly: with stores pending next to loads the compiler's wait counting falls back to waiting for all
-          // of them before the next slice's first fragment; its counts stay safe, see lin32_kernel)
-          bf16_t* qp = Q + qo + sc * 32 + hf * 8;
-          asm volatile("global_store_dwordx4 %0, %1, off\n\tglobal_store_dwordx4 %0, %2, off offset:32\n\ts_nop 2" :: "v"(qp), "v"(qv[0]), "v"(qv[1]) : "memory");
-        }
+        emit((bf16_t*)g.Y2, 3, ro_l + 32, sc * 32, qv[0], qv[1]);        // same row map, rows three times as long
       }
     }
+  }
   }
 }
 
@@ -501,13 +608,13 @@ __global__ __launch_bounds__(C, (C >= 384 ? 1 : 2)) void mlp64_kernel(MlpArgs g)
     const int64_t prow = row_ok[tb] ? row : g.M - 1;
     ro[tb] = g.y_rows.identity ? prow * g.y_rows.ld : eval_rows_k(&gk->y_rows, prow);
   }
-  mlp_load_x_tile<C, NTHR>(x_l, (const bf16_t*)g.X, row0, g.M, g.x_rows.identity, g.x_rows.ld, &gk->x_rows);
-  if (row0 + 32 < g.M) mlp_load_x_tile<C, NTHR>(x_l + 32 * XP, (const bf16_t*)g.X, row0 + 32, g.M, g.x_rows.identity, g.x_rows.ld, &gk->x_rows);
-  else for (int s = tid; s < 32 * XP; s += NTHR) x_l[32 * XP + s] = mlp_u32x4{0u, 0u, 0u, 0u};
+  MlpTile<C, NTHR, 64> xt;
+  xt.request((const bf16_t*)g.X, row0, g.M, g.x_rows.identity, g.x_rows.ld, &gk->x_rows);
+  xt.store(x_l, row0, g.M);
   for (int s = tid; s < Hd / 8; s += NTHR) b1_l[s] = ((const mlp_u32x4*)g.b1)[s];
   __syncthreads();
   if (g.norm) {
-    mlp_norm_x_tile<C, 64>(x_l, g.norm_eps, (const mlp_u32x4*)g.norm_gamma, (const mlp_u32x4*)g.norm_beta);
+    mlp_norm_x_tile<C, NTHR, 64>(x_l, g.norm_eps, (const mlp_u32x4*)g.norm_gamma, (const mlp_u32x4*)g.norm_beta);
     __syncthreads();
   }
 
@@ -612,15 +719,15 @@ __global__ __launch_bounds__(C, (C >= 384 ? 1 : 2)) void mlp64_kernel(MlpArgs g)
 
 // mlp64_kernel with the attention output projection in front and, optionally, the next block's LayerNorm-1 (LNOUT = 1)
 // or LayerNorm-1 + QKV Linear (LNOUT = 2) behind it: the C = 512 form of mlp_fused_kernel<C, true, LNOUT>, 64-token
-// tiles.  x1 = A . Wproj^T + bproj + x0 (x0 read and Y written through y_rows); x1 (bf16) goes to LDS, where it is
-// normalised for the first product, and to Y in memory, from where every lane reads back what it stored itself as the
-// residual of the final sum (three 64-token tiles do not fit the LDS).  LDS: [x1 normalised | A tile, then the two
-// hidden tiles, then the normalised Y for the QKV Linear | b1, then bq | bproj | row statistics].
+// tiles.  x1 = A . Wproj^T + bproj + x0 (x0 read and Y written through y_rows); x1 (bf16) stays in registers as the residual of
+// the final sum's first addend in its accumulators, normalised it goes to LDS for the first product.  LDS: [x0, then x1 normalised, then the waves' stages of
+// mlp_stage_put | A tile, then the two hidden tiles, then the normalised Y for the QKV Linear | b1, then bq | row offsets |
+// row statistics].
 // One weight stream per wave through the ring of 16 fragment registers, in blocks of 32 fragments: two blocks of Wproj
 // ((step, feature block) order, the wave's two slices of lin_pack_kernel's layout), the blocks of mlp64_kernel, then
 // the wave's six QKV slices.
 template <int C, int LNOUT>
-__global__ __launch_bounds__(C, (C >= 384 ? 1 : 2)) void mlp64p_kernel(MlpArgs g) {
+__global__ __launch_bounds__(C, (C >= 384 ? 1 : 2)) void mlp64p_kernel(MlpArgs g, int vec_lds) {
   constexpr int KK = C / 16, XS = C / 8, XP = XS + 1, NW = C / 64, NTHR = 64 * NW, RING = KK % 16 == 0 ? 16 : 8, HP = 4 * NW + 1, NQ = 3 * C / 32 / NW;
   constexpr int UG = NW / 2;                            // steps of the second product between two quarters of the bias + GELU work
   constexpr size_t TILE = (size_t)64 * XP * 16, HTILE = (size_t)64 * HP * 16;
@@ -632,8 +739,10 @@ __global__ __launch_bounds__(C, (C >= 384 ? 1 : 2)) void mlp64p_kernel(MlpArgs g
   mlp_u32x4* h_l = a_l;                                                // [2][64][HP] hidden tiles
   mlp_u32x4* n_l = a_l;                                                // [64][XP] normalised Y (LNOUT = 2), after the last round
   mlp_u32x4* b1_l = (mlp_u32x4*)(smem_raw + TILE + 2 * HTILE);         // [Hd / 8], later bq [3 C / 8]
-  mlp_u32x4* bp_l = b1_l + g.Hd / 8;                                   // [C / 8]
-  float* st_l = (float*)(bp_l + XS);                                   // [2][NW][64] row statistics
+  int64_t* ro_l = (int64_t*)(b1_l + g.Hd / 8);                         // [2][64]: of Y and of the second output; -1 past M
+  float2* st_l = (float2*)(ro_l + 128);                                // [NW][64] row statistics
+  mlp_u32x4* vec_l = (mlp_u32x4*)(st_l + NW * 64);                     // vec_lds: [NV][C / 8], else read from memory where they are used
+  constexpr int NV = LNOUT != 0 ? 6 : 4;                               // bproj, gamma, beta, b2, gamma and beta of the second output
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t row0 = (int64_t)blockIdx.x * 64;
@@ -662,34 +771,51 @@ __global__ __launch_bounds__(C, (C >= 384 ? 1 : 2)) void mlp64p_kernel(MlpArgs g
     j = j < NQ ? j : NQ - 1;
     return __builtin_amdgcn_raw_buffer_load_b128(rq, lo, ((w + NW * j) * KK + s) * 1024, 0);
   };
+  // The tile and the residual x0 (through y_rows) are requested together, before the weight stream (loads return in the order
+  // they were asked for).  One workgroup per CU has nothing to run beside its row phases, in which the matrix cores wait: tile,
+  // projection's epilogue, both norms and Y took 23 of the 96 us of 12544 x 512 with the next QKV
+  MlpTile<C, NTHR, 64> xt, rt;
+  xt.request((const bf16_t*)g.X, row0, g.M, g.x_rows.identity, g.x_rows.ld, &gk->x_rows);
+  rt.request((const bf16_t*)g.resid0, row0, g.M, g.y_rows.identity, g.y_rows.ld, &gk->y_rows);
+  if (tid < (LNOUT != 0 ? 128 : 64)) {
+    const int64_t row = row0 + (tid & 63), prow = row < g.M ? row : g.M - 1;
+    int64_t o;
+    if (LNOUT == 0 || tid < 64) o = g.y_rows.identity ? prow * g.y_rows.ld : eval_rows_k(&gk->y_rows, prow);
+    else o = g.y2_rows.identity ? prow * g.y2_rows.ld : eval_rows_k(&gk->y2_rows, prow);
+    ro_l[tid] = row < g.M ? o : -1;
+  }
+  for (int s = tid; s < Hd / 8; s += NTHR) b1_l[s] = ((const mlp_u32x4*)g.b1)[s];
   mlp_u32x4 wf[RING];
 #pragma unroll
   for (int s = 0; s < RING; ++s) wf[s] = frag_p(s);
-
-  int64_t ro[2], ro2[2] = {0, 0}; bool row_ok[2];
+  // vector i of C elements: a lane's slots are those of blocks 2 w + bt, runs 2 gp + hf
+  auto vec = [&](int i) __attribute__((always_inline)) -> const mlp_u32x4* {
+    return (const mlp_u32x4*)(i == 0 ? g.bproj : i == 1 ? g.norm_gamma : i == 2 ? g.norm_beta : i == 3 ? g.b2 : i == 4 ? g.ln2_gamma : g.ln2_beta);
+  };
+  typedef mlp_u32x4 Slots[2][2];
+  const int fs = w * 8 + hf;
+  auto slots = [&](Slots& v, int i) __attribute__((always_inline)) {
+    if (vec_lds) {
 #pragma unroll
-  for (int tb = 0; tb < 2; ++tb) {
-    const int64_t row = row0 + 32 * tb + l32;
-    row_ok[tb] = row < g.M;
-    const int64_t prow = row_ok[tb] ? row : g.M - 1;
-    ro[tb] = g.y_rows.identity ? prow * g.y_rows.ld : eval_rows_k(&gk->y_rows, prow);
-    if constexpr (LNOUT != 0) ro2[tb] = g.y2_rows.identity ? prow * g.y2_rows.ld : eval_rows_k(&gk->y2_rows, prow);
+      for (int k = 0; k < 4; ++k) v[k >> 1][k & 1] = vec_l[i * XS + fs + 2 * k];
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k >> 1][k & 1] = vec(i)[fs + 2 * k];
+    }
+  };
+  if (vec_lds && tid < XS) {
+    mlp_u32x4 v[NV];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) v[i] = vec(i)[tid];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) vec_l[i * XS + tid] = v[i];
   }
-  mlp_load_x_tile<C, NTHR>(a_l, (const bf16_t*)g.X, row0, g.M, g.x_rows.identity, g.x_rows.ld, &gk->x_rows);
-  if (row0 + 32 < g.M) mlp_load_x_tile<C, NTHR>(a_l + 32 * XP, (const bf16_t*)g.X, row0 + 32, g.M, g.x_rows.identity, g.x_rows.ld, &gk->x_rows);
-  else for (int s = tid; s < 32 * XP; s += NTHR) a_l[32 * XP + s] = mlp_u32x4{0u, 0u, 0u, 0u};
-  for (int s = tid; s < Hd / 8; s += NTHR) b1_l[s] = ((const mlp_u32x4*)g.b1)[s];
-  for (int s = tid; s < XS; s += NTHR) bp_l[s] = ((const mlp_u32x4*)g.bproj)[s];
+  xt.store(a_l, row0, g.M);
+  rt.store(x_l, row0, g.M);
   __syncthreads();
 
   mlp_f32x16 out[2][2];                                 // [feature block][token block]: the projection, then Y^T
   const mlp_u32x4 zero4[2] = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}};
-  auto clear_out = [&]() __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) out[i >> 1][i & 1][e] = 0.f;
-  };
   // out[bt][tb] += W(step i, feature block bt) x tile(token block tb, step i) for `steps` steps: the wave's 64 features
   // against a 64-token tile in LDS (row pitch `pitch` slots); refill(t) loads the fragment at position t of the call's
   // stream (t >= 2 * steps: what follows it).  between(q) after steps 4 q .. 4 q + 3.
@@ -741,37 +867,53 @@ __global__ __launch_bounds__(C, (C >= 384 ? 1 : 2)) void mlp64p_kernel(MlpArgs g
     }
   };
   auto nothing = [&](int) __attribute__((always_inline)) {};
-  bf16_t* Y = (bf16_t*)g.Y;
-
   // ---- projection: x1 = A . Wproj^T + bproj + x0 for the wave's 64 features
-  clear_out();
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) out[i >> 1][i & 1][e] = 0.f;
   pair_product(a_l, XP, KK, [&](int t) __attribute__((always_inline)) { return t < 2 * KK ? frag_p(t) : frag_m(0, t - 2 * KK); }, nothing);
-  {
-    const bf16_t* R0 = (const bf16_t*)g.resid0;
+#pragma unroll
+  for (int tb = 0; tb < 2; ++tb) {
+    mlp_u32x4 x1[2][2];
 #pragma unroll
     for (int bt = 0; bt < 2; ++bt) {
-      const int fb = 2 * w + bt, fo = fb * 32 + hf * 8;
-      const mlp_u32x4 bias_v = bp_l[fb * 4 + hf], bias_w = bp_l[fb * 4 + 2 + hf];
-#pragma unroll
-      for (int tb = 0; tb < 2; ++tb) {
-        const mlp_u32x4 res[2] = {*(const mlp_u32x4*)(R0 + ro[tb] + fo), *(const mlp_u32x4*)(R0 + ro[tb] + fo + 16)};
-        mlp_u32x4 xv[2];
-        mlp_finish(out[bt][tb], bias_v, bias_w, res, false, xv);          // x1 rounded to bf16, as the separate Linear stores it
-#pragma unroll
-        for (int gp = 0; gp < 2; ++gp) x_l[(32 * tb + l32) * XP + fb * 4 + 2 * gp + hf] = xv[gp];
-        if (row_ok[tb]) {                                                  // the residual of the final sum, read back below
-          *(mlp_u32x4*)(Y + ro[tb] + fo) = xv[0];
-          *(mlp_u32x4*)(Y + ro[tb] + fo + 16) = xv[1];
-        }
-      }
+      mlp_u32x4* x0 = x_l + (32 * tb + l32) * XP + fs + 4 * bt;           // (a lane's own slots: x0, x1, x1 normalised)
+      const mlp_u32x4 res[2] = {x0[0], x0[2]};
+      mlp_u32x4 bp[2];
+      if (vec_lds) { bp[0] = vec_l[fs + 4 * bt]; bp[1] = vec_l[fs + 4 * bt + 2]; } else { bp[0] = vec(0)[fs + 4 * bt]; bp[1] = vec(0)[fs + 4 * bt + 2]; }
+      mlp_finish(out[bt][tb], bp[0], bp[1], res, false, x1[bt]);          // x1 rounded to bf16, as the separate Linear stores it
+      mlp_start_from(out[bt][tb], x1[bt]);
+      x0[0] = x1[bt][0]; x0[2] = x1[bt][1];
+      __builtin_amdgcn_sched_barrier(0);                                  // (one block at a time: together they spill)
     }
+    mlp_stats_put<2>(x1, hf, st_l + w * 64 + 32 * tb + l32);
+    __builtin_amdgcn_sched_barrier(0);
   }
+  // (rows of the norm: a lane's runs get(tb, bt) -> put(tb, bt, normalised runs); their statistics lie in st_l)
+  auto normalised = [&](float eps, int vec0, auto get, auto put) __attribute__((always_inline)) {
+    Slots gam, bet;
+    slots(gam, vec0); slots(bet, vec0 + 1);
+#pragma unroll
+    for (int tb = 0; tb < 2; ++tb) {
+      float rstd, sh;
+      mlp_stats_get<2, NW>(st_l + 32 * tb + l32, 64, eps, &rstd, &sh);
+#pragma unroll
+      for (int bt = 0; bt < 2; ++bt)
+        put(tb, bt, mlp_scale8(get(tb, bt, 0), rstd, sh, gam[bt][0], bet[bt][0]), mlp_scale8(get(tb, bt, 1), rstd, sh, gam[bt][1], bet[bt][1]));
+    }
+  };
+  auto into = [&](mlp_u32x4* tile) __attribute__((always_inline)) {
+    return [=](int tb, int bt, const mlp_u32x4& n0, const mlp_u32x4& n1) __attribute__((always_inline)) {
+      mlp_u32x4* t = tile + (32 * tb + l32) * XP + fs + 4 * bt;
+      t[0] = n0; t[2] = n1;
+    };
+  };
   __syncthreads();
-  mlp_norm_x_tile<C, 64>(x_l, g.norm_eps, (const mlp_u32x4*)g.norm_gamma, (const mlp_u32x4*)g.norm_beta);
+  normalised(g.norm_eps, 1, [&](int tb, int bt, int gp) __attribute__((always_inline)) { return x_l[(32 * tb + l32) * XP + fs + 4 * bt + 2 * gp]; }, into(x_l));
   __syncthreads();
 
   // ---- the MLP's rounds, as in mlp64_kernel (stream blocks 2 ..)
-  clear_out();
   auto finish_unit = [&](int r, int u, const mlp_f32x16 (&h)[2], mlp_u32x4* hb) __attribute__((always_inline)) {
     const int sc = NW * r + w, tb = u >> 1, gp = u & 1;
     hb[(32 * tb + l32) * HP + w * 4 + 2 * gp + hf] = mlp_finish_half(h[tb], gp, b1_l[sc * 4 + 2 * gp + hf], zero4[0], true);
@@ -794,106 +936,70 @@ __global__ __launch_bounds__(C, (C >= 384 ? 1 : 2)) void mlp64p_kernel(MlpArgs g
                  [&](int s) __attribute__((always_inline)) { return (LNOUT == 2 && s >= KK) ? frag_q(0, s - KK) : frag_m(lastm, s < KK ? s : KK - 1); }, nothing);
   }
 
-  // ---- Y = x1 + MLP: bias, the residual this lane stored above, two 16-byte stores per block and lane
+  // ---- Y = x1 + MLP, out in 64-byte pieces through the wave's 2 KiB of the X tile (not read since the last round's barrier)
+  Slots b2;
+  slots(b2, 3);
+  mlp_u32x4 bq[(3 * XS + NTHR - 1) / NTHR];
+  if constexpr (LNOUT == 2)
+#pragma unroll
+    for (int i = 0; i < (3 * XS + NTHR - 1) / NTHR; ++i) bq[i] = ((const mlp_u32x4*)g.bq)[min(tid + i * NTHR, 3 * XS - 1)];
+  mlp_u32x4* stage = x_l + w * 128;
+  auto emit = [&](bf16_t* base, int scale, const int64_t* ro, int col, const mlp_u32x4& v0, const mlp_u32x4& v1) __attribute__((always_inline)) {
+    mlp_stage_put(stage, l32, hf, v0, v1);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const mlp_u32x4 v = mlp_stage_get(stage, lane, i);
+      const int64_t o = ro[16 * i + (lane >> 2)];
+      if (o >= 0) mlp_store16(base + o * scale + col + (lane & 3) * 8, v);
+    }
+  };
   mlp_u32x4 yv[2][2][2];
+  auto yget = [&](int tb, int bt, int gp) __attribute__((always_inline)) { return yv[tb][bt][gp]; };
 #pragma unroll
-  for (int bt = 0; bt < 2; ++bt) {
-    const int fo = (2 * w + bt) * 32 + hf * 8;
-    const mlp_u32x4 b2v = *(const mlp_u32x4*)((const bf16_t*)g.b2 + fo), b2w = *(const mlp_u32x4*)((const bf16_t*)g.b2 + fo + 16);
+  for (int tb = 0; tb < 2; ++tb) {
 #pragma unroll
-    for (int tb = 0; tb < 2; ++tb) {
-      const mlp_u32x4 resid[2] = {*(const mlp_u32x4*)(Y + ro[tb] + fo), *(const mlp_u32x4*)(Y + ro[tb] + fo + 16)};
-      mlp_finish(out[bt][tb], b2v, b2w, resid, false, yv[bt][tb]);
-      if (row_ok[tb]) {
-        *(mlp_u32x4*)(Y + ro[tb] + fo) = yv[bt][tb][0];
-        *(mlp_u32x4*)(Y + ro[tb] + fo + 16) = yv[bt][tb][1];
-      }
-    }
+    for (int bt = 0; bt < 2; ++bt) mlp_finish(out[bt][tb], b2[bt][0], b2[bt][1], zero4, false, yv[tb][bt]);
+    if constexpr (LNOUT != 0) mlp_stats_put<2>(yv[tb], hf, st_l + w * 64 + 32 * tb + l32);
   }
-  if constexpr (LNOUT != 0) {
-    // LayerNorm of the bf16 rows of Y (two-pass fp32 statistics, as the norm kernel computes them from the stored
-    // tensor): a lane holds 32 of its token's features per token block, its partner lane 32 more, the other waves the rest
-    float mean[2], rstd[2];
 #pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
+  for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
-      for (int tb = 0; tb < 2; ++tb) {
-        float acc = 0.f;
+    for (int bt = 0; bt < 2; ++bt) emit((bf16_t*)g.Y, 1, ro_l + 32 * tb, (2 * w + bt) * 32, yv[tb][bt][0], yv[tb][bt][1]);
+  if constexpr (LNOUT == 1) {
+    __syncthreads();
+    normalised(g.ln2_eps, 4, yget, [&](int tb, int bt, const mlp_u32x4& n0, const mlp_u32x4& n1) __attribute__((always_inline)) {
+      emit((bf16_t*)g.Y2, 1, ro_l + 64 + 32 * tb, (2 * w + bt) * 32, n0, n1);
+    });
+  }
+  if constexpr (LNOUT == 2) {
+    // LayerNorm of the bf16 rows of Y into the hidden tiles' LDS (dead: every wave is past them at the barrier), bq over b1, then the
+    // next block's QKV Linear: wave w forms outputs 32 (w + NW j) ..+31, j < NQ
 #pragma unroll
-        for (int bt = 0; bt < 2; ++bt)
-#pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            float f[8];
-            mlp_unpack8(yv[bt][tb][q], f);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) { const float d = pass ? f[e] - mean[tb] : f[e]; acc += pass ? d * d : d; }
-          }
-        acc += __shfl_xor(acc, 32, 64);
-        if (hf == 0) st_l[(pass * NW + w) * 64 + 32 * tb + l32] = acc;
-      }
-      __syncthreads();
-#pragma unroll
-      for (int tb = 0; tb < 2; ++tb) {
-        float tot = 0.f;
-#pragma unroll
-        for (int ww = 0; ww < NW; ++ww) tot += st_l[(pass * NW + ww) * 64 + 32 * tb + l32];
-        if (pass == 0) mean[tb] = tot / (float)C; else rstd[tb] = rsqrtf(tot / (float)C + g.ln2_eps);
-      }
-    }
-#pragma unroll
-    for (int bt = 0; bt < 2; ++bt) {
-      const int fb = 2 * w + bt, fo = fb * 32 + hf * 8;
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        float gf[8], bf[8];
-        mlp_unpack8(*(const mlp_u32x4*)((const bf16_t*)g.ln2_gamma + fo + 16 * q), gf);
-        mlp_unpack8(*(const mlp_u32x4*)((const bf16_t*)g.ln2_beta + fo + 16 * q), bf);
-#pragma unroll
-        for (int tb = 0; tb < 2; ++tb) {
-          float f[8];
-          mlp_unpack8(yv[bt][tb][q], f);
-          const float sh = -mean[tb] * rstd[tb];
-          mlp_u32x4 nv;
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            nv[e] = mlp_pack2(fmaf(fmaf(f[2 * e], rstd[tb], sh), gf[2 * e], bf[2 * e]), fmaf(fmaf(f[2 * e + 1], rstd[tb], sh), gf[2 * e + 1], bf[2 * e + 1]));
-          if constexpr (LNOUT == 1) {
-            if (row_ok[tb]) *(mlp_u32x4*)((bf16_t*)g.Y2 + ro2[tb] + fo + 16 * q) = nv;
-          } else {
-            n_l[(32 * tb + l32) * XP + fb * 4 + 2 * q + hf] = nv;        // (the hidden tiles are dead: two barriers ago)
-          }
-        }
-      }
-    }
-    if constexpr (LNOUT == 2) {
-      // the next block's QKV Linear on the normalised tile: wave w forms outputs 32 (w + NW j) ..+31, j < NQ
-      for (int s = tid; s < 3 * XS; s += NTHR) b1_l[s] = ((const mlp_u32x4*)g.bq)[s];
-      __syncthreads();
-      bf16_t* Q = (bf16_t*)g.Y2;
-      // bias and store of slice j (a quarter at a time: token block u / 2, half u % 2 of its 32 outputs) are issued
-      // between the quarters of slice j + 1's product
-      auto emit = [&](int j, int u, const mlp_f32x16 (&h)[2]) __attribute__((always_inline)) {
-        const int sc = w + NW * j, tb = u >> 1, gp = u & 1;
-        const mlp_u32x4 qv = mlp_finish_half(h[tb], gp, b1_l[sc * 4 + 2 * gp + hf], zero4[0], false);
-        if (row_ok[tb]) {
-          bf16_t* qp = Q + 3 * ro2[tb] + sc * 32 + hf * 8 + 16 * gp;      // same row map, rows three times as long
-          asm volatile("global_store_dwordx4 %0, %1, off\n\ts_nop 1" :: "v"(qp), "v"(qv) : "memory");
-        }
-      };
-      static_assert(NQ % 2 == 0, "slices are taken two at a time");
-      mlp_f32x16 ha[2], hb2[2];
-      slice_product(n_l, ha, [&](int s) __attribute__((always_inline)) { return frag_q(0, s); }, nothing);
+    for (int i = 0; i < (3 * XS + NTHR - 1) / NTHR; ++i) if (tid + i * NTHR < 3 * XS) b1_l[tid + i * NTHR] = bq[i];
+    __syncthreads();
+    normalised(g.ln2_eps, 4, yget, into(n_l));
+    __syncthreads();
+    // bias and store of slice j (a token block u / 2 at a time, on odd u) are issued between the quarters of slice j + 1's product
+    auto emit_q = [&](int j, int u, const mlp_f32x16 (&h)[2]) __attribute__((always_inline)) {
+      if (!(u & 1)) return;
+      const int sc = w + NW * j, tb = u >> 1;
+      mlp_u32x4 qv[2];
+      mlp_finish(h[tb], b1_l[sc * 4 + hf], b1_l[sc * 4 + 2 + hf], zero4, false, qv);
+      emit((bf16_t*)g.Y2, 3, ro_l + 64 + 32 * tb, sc * 32, qv[0], qv[1]);      // same row map, rows three times as long
+    };
+    static_assert(NQ % 2 == 0, "slices are taken two at a time");
+    mlp_f32x16 ha[2], hb2[2];
+    slice_product(n_l, ha, [&](int s) __attribute__((always_inline)) { return frag_q(0, s); }, nothing);
 #pragma unroll 1
-      for (int j = 0; j < NQ; j += 2) {
-        slice_product(n_l, hb2, [&](int s) __attribute__((always_inline)) { return frag_q(j + 1, s); },
-                      [&](int u) __attribute__((always_inline)) { emit(j, u, ha); });
-        if (j + 2 < NQ) {
-          slice_product(n_l, ha, [&](int s) __attribute__((always_inline)) { return frag_q(j + 2, s); },
-                        [&](int u) __attribute__((always_inline)) { emit(j + 1, u, hb2); });
-        } else {
+    for (int j = 0; j < NQ; j += 2) {
+      slice_product(n_l, hb2, [&](int s) __attribute__((always_inline)) { return frag_q(j + 1, s); },
+                    [&](int u) __attribute__((always_inline)) { emit_q(j, u, ha); });
+      if (j + 2 < NQ) {
+        slice_product(n_l, ha, [&](int s) __attribute__((always_inline)) { return frag_q(j + 2, s); },
+                      [&](int u) __attribute__((always_inline)) { emit_q(j + 1, u, hb2); });
+      } else {
 #pragma unroll
-          for (int u = 0; u < 4; ++u) emit(j + 1, u, hb2);
-        }
+        for (int u = 0; u < 4; ++u) emit_q(j + 1, u, hb2);
       }
     }
   }
@@ -901,19 +1007,21 @@ __global__ __launch_bounds__(C, (C >= 384 ? 1 : 2)) void mlp64p_kernel(MlpArgs g
 
 static size_t mlp64p_smem(int C, int Hd) {
   const int NW = C / 64;
-  return (size_t)64 * (C / 8 + 1) * 16 + 2 * (size_t)64 * (4 * NW + 1) * 16 + (size_t)Hd * 2 + (size_t)C * 2 + (size_t)2 * NW * 64 * 4;
+  return (size_t)64 * (C / 8 + 1) * 16 + 2 * (size_t)64 * (4 * NW + 1) * 16 + (size_t)Hd * 2 + 2 * 64 * 8 + (size_t)NW * 64 * 8;
 }
 
 template <int C, int LNOUT>
 static int mlp64p_launch(const MlpArgs& g, void* stream) {
-  const size_t smem = mlp64p_smem(C, g.Hd);
+  constexpr size_t vec = (size_t)(LNOUT ? 6 : 4) * C * 2;
+  const int vec_lds = mlp64p_smem(C, g.Hd) + vec <= 160 * 1024;      // (a very wide hidden layer's bias takes their place)
+  const size_t smem = mlp64p_smem(C, g.Hd) + (vec_lds ? vec : 0);
   static std::atomic<size_t> allowed{0};
   if (smem > allowed.load()) {
     const hipError_t e = hipFuncSetAttribute((const void*)mlp64p_kernel<C, LNOUT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return (int)e;
     allowed.store(smem);
   }
-  mlp64p_kernel<C, LNOUT><<<dim3((unsigned)((g.M + 63) / 64)), dim3(C), smem, (hipStream_t)stream>>>(g);
+  mlp64p_kernel<C, LNOUT><<<dim3((unsigned)((g.M + 63) / 64)), dim3(C), smem, (hipStream_t)stream>>>(g, vec_lds);
   return (int)hipGetLastError();
 }
 
@@ -950,14 +1058,14 @@ static int mlp64_launch(const MlpArgs& g, void* stream) {
   return (int)hipGetLastError();
 }
 
-static size_t mlp_smem(int C, int Hd, bool proj, bool lnout) {
+static size_t mlp_smem(int C, int Hd, bool proj, int lnout) {
   const size_t tile = (size_t)32 * (C / 8 + 1) * 16, htile = (size_t)32 * (C / 8 + 1) * 16;
-  return (proj ? 3 : 1) * tile + 2 * htile + (size_t)Hd * 2 + (proj ? (size_t)C * 2 : 0) + (lnout ? (size_t)2 * (C / 32) * 32 * 4 : 0);
+  return (proj ? 2 : 1) * tile + 2 * htile + (size_t)Hd * 2 + (size_t)mlp_vectors(proj, lnout) * C * 2 + 2 * 32 * 8 + (size_t)(C / 32) * 32 * 8;
 }
 
 template <int C, bool PROJ, int LNOUT>
 static int mlp_launch3(const MlpArgs& g, void* stream) {
-  const size_t smem = mlp_smem(C, g.Hd, PROJ, LNOUT != 0);
+  const size_t smem = mlp_smem(C, g.Hd, PROJ, LNOUT);
   static std::atomic<size_t> allowed{0};   // raised on demand: the attribute is per kernel, the hidden size varies
   if (smem > allowed.load()) {
     const hipError_t e = hipFuncSetAttribute((const void*)mlp_fused_kernel<C, PROJ, LNOUT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -982,7 +1090,7 @@ static int mlp_launch(const MlpArgs& g, void* stream) {
 bool mlp_proj_supported(int C, int Hd, int dtype) {
   if (!mlp_fused_supported(C, Hd, dtype)) return false;
   if (C == 512) return mlp64_shape(C, Hd) && Hd >= 3 * C && mlp64p_smem(C, Hd) <= 160 * 1024;
-  return mlp_smem(C, Hd, true, true) <= 160 * 1024;
+  return mlp_smem(C, Hd, true, 2) <= 160 * 1024;
 }
 
 bool mlp_fused_supported(int C, int Hd, int dtype) {
@@ -1021,8 +1129,8 @@ int launch_mlp_fused(const MlpArgs& g, void* stream) {
 // W[32 sc + l32][16 kk + 8 hf ..+7]); every wave finishes its 32 x 32 outputs in registers and stores them: no
 // barrier after the prologue.  Against the tiled kernel of k_gemm.hip this trades L2 -> CU traffic (W once per 32
 // rows) for the absence of K-loop barriers and of a separate norm kernel.  Measured (with LayerNorm, against norm
-// kernel + tiled kernel resp. the tiled kernel's own folded norm): 200704 x 384 x 128: 69 us against 89;
-// 50176 x 768 x 256: 55 against 71; 6272 x 1152 x 384: 23.7 against 26.
+// kernel + tiled kernel resp. the tiled kernel's own folded norm): 200704 x 384 x 128: 62 us against 89;
+// 50176 x 768 x 256: 45 against 71; 6272 x 1152 x 384: 15 against 26.
 // NW waves per workgroup: 4 (two workgroups per CU, X fragments in registers: large grids) or C / 32 (one workgroup
 // per CU with three waves per SIMD at C = 384, X fragments re-read from LDS: grids of about one workgroup per CU)
 template <int C, bool RES, int NW>
@@ -1032,7 +1140,8 @@ __global__ __launch_bounds__(64 * NW, 1) void lin32_kernel(Lin32Args g) {
   const SM_KARG Lin32Args* gk = kernarg_ptr<Lin32Args>();
   extern __shared__ __align__(16) unsigned char smem_raw[];
   mlp_u32x4* x_l = (mlp_u32x4*)smem_raw;                                  // [32][XP]
-  mlp_u32x4* b_l = (mlp_u32x4*)(smem_raw + (size_t)32 * XP * 16);         // [N / 8]
+  mlp_u32x4* st_l = x_l + 32 * XP;                                        // [NW][128]: the waves' stages of mlp_stage_put
+  mlp_u32x4* b_l = st_l + NW * 128;                                       // [N / 8]
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave index as a scalar: slice bases become scalar addresses
   const int64_t row0 = (int64_t)blockIdx.x * 32;
@@ -1046,11 +1155,13 @@ __global__ __launch_bounds__(64 * NW, 1) void lin32_kernel(Lin32Args g) {
   mlp_u32x4 w1[KK];
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk) w1[kk] = __builtin_amdgcn_raw_buffer_load_b128(rw, lo, ((w < nsub ? w : 0) * KK + kk) * 1024, 0);
-  mlp_load_x_tile<C, NTHR>(x_l, (const bf16_t*)g.X, row0, g.M, g.x_rows.identity, g.x_rows.ld, &gk->x_rows);
+  MlpTile<C, NTHR, 32> xt;
+  xt.request((const bf16_t*)g.X, row0, g.M, g.x_rows.identity, g.x_rows.ld, &gk->x_rows);
+  xt.store(x_l, row0, g.M);
   for (int s = tid; s < g.N / 8; s += NTHR) b_l[s] = g.bias ? ((const mlp_u32x4*)g.bias)[s] : mlp_u32x4{0u, 0u, 0u, 0u};
   __syncthreads();
   if (g.norm) {
-    mlp_norm_x_tile<C>(x_l, g.norm_eps, (const mlp_u32x4*)g.norm_gamma, (const mlp_u32x4*)g.norm_beta);
+    mlp_norm_x_tile<C, NTHR, 32>(x_l, g.norm_eps, (const mlp_u32x4*)g.norm_gamma, (const mlp_u32x4*)g.norm_beta);
     __syncthreads();
   }
 
@@ -1060,10 +1171,17 @@ __global__ __launch_bounds__(64 * NW, 1) void lin32_kernel(Lin32Args g) {
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) xf[kk] = x_l[l32 * XP + hf + 2 * kk];
   }
-  const int64_t row = row0 + l32;                 // the lane's token: accumulator column
-  const bool row_ok = row < g.M;
-  const int64_t rowc = row_ok ? row : g.M - 1;    // lanes past M read the last row's residual and store nothing
-  const int64_t ro = g.y_rows.identity ? rowc * g.y_rows.ld : eval_rows_k(&gk->y_rows, rowc);
+  auto y_off = [&](int64_t row) __attribute__((always_inline)) { return g.y_rows.identity ? row * g.y_rows.ld : eval_rows_k(&gk->y_rows, row); };
+  int64_t ro = 0;                                 // the residual's row: the lane's token (accumulator column); past M the last row's
+  if constexpr (RES) ro = y_off(min(row0 + l32, g.M - 1));
+  int64_t so[2];                                  // the rows that the lane stores a 16-byte run of (mlp_stage_get)
+  bool s_ok[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int64_t row = row0 + 16 * i + (lane >> 2);
+    s_ok[i] = row < g.M;
+    so[i] = y_off(s_ok[i] ? row : g.M - 1) + (lane & 3) * 8;
+  }
   const bf16_t* R = (const bf16_t*)g.residual;
   bf16_t* Y = (bf16_t*)g.Y;
   const bool gelu_on = g.act == SM_ACT_GELU;
@@ -1101,14 +1219,11 @@ __global__ __launch_bounds__(64 * NW, 1) void lin32_kernel(Lin32Args g) {
     mlp_u32x4 outv[2];
     // (a literal flag in each branch: with a run-time flag the polynomial is evaluated for every value and thrown away)
     if (gelu_on) mlp_finish(h, bias_v, bias_w, res, true, outv); else mlp_finish(h, bias_v, bias_w, res, false, outv);
-    if (row_ok) {
-      // Written as assembly so that the compiler's wait-count bookkeeping sees loads only: with stores pending next to
-      // loads it stops counting and waits for everything (vmcnt 0) at the top of the next slice, which exposes the
-      // latency of the whole weight prefetch.  Its counts stay safe: it may wait for up to two operations more than
-      // needed, never fewer (loads return in issue order among themselves).
-      bf16_t* yp = Y + ro + sc * 32 + hf * 8;
-      asm volatile("global_store_dwordx4 %0, %1, off\n\tglobal_store_dwordx4 %0, %2, off offset:32\n\ts_nop 2"
-                   :: "v"(yp), "v"(outv[0]), "v"(outv[1]) : "memory");
+    mlp_stage_put(st_l + w * 128, l32, hf, outv[0], outv[1]);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const mlp_u32x4 v = mlp_stage_get(st_l + w * 128, lane, i);
+      if (s_ok[i]) mlp_store16(Y + so[i] + sc * 32, v);
     }
   }
 }
@@ -1128,11 +1243,12 @@ __global__ void lin_pack_kernel(const bf16_t* W, mlp_u32x4* packed, int N, int K
 // through a ring of 16 registers, as in mlp64_kernel.  LayerNorm folded as above.
 template <int C, bool RES>
 __global__ __launch_bounds__(512, 1) void lin64_kernel(Lin32Args g) {
-  constexpr int KK = C / 16, XS = C / 8, XP = XS + 1, NW = 8, RING = 16;
+  constexpr int KK = C / 16, XS = C / 8, XP = XS + 1, NW = 8, NTHR = 512, RING = 16;
   const SM_KARG Lin32Args* gk = kernarg_ptr<Lin32Args>();
   extern __shared__ __align__(16) unsigned char smem_raw[];
   mlp_u32x4* x_l = (mlp_u32x4*)smem_raw;                                  // [64][XP]
-  mlp_u32x4* b_l = (mlp_u32x4*)(smem_raw + (size_t)64 * XP * 16);         // [N / 8]
+  mlp_u32x4* st_l = x_l + 64 * XP;                                        // [NW][128]: the waves' stages of mlp_stage_put
+  mlp_u32x4* b_l = st_l + NW * 128;                                       // [N / 8]
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t row0 = (int64_t)blockIdx.x * 64;
@@ -1150,21 +1266,25 @@ __global__ __launch_bounds__(512, 1) void lin64_kernel(Lin32Args g) {
   mlp_u32x4 wf[RING];
 #pragma unroll
   for (int s = 0; s < RING; ++s) wf[s] = wload(foff(0, s));
-  int64_t ro[2]; bool row_ok[2];
+  auto y_off = [&](int64_t row) __attribute__((always_inline)) { return g.y_rows.identity ? row * g.y_rows.ld : eval_rows_k(&gk->y_rows, row); };
+  int64_t ro[2] = {0, 0}, so[2][2]; bool s_ok[2][2];
 #pragma unroll
   for (int tb = 0; tb < 2; ++tb) {
-    const int64_t row = row0 + 32 * tb + l32;
-    row_ok[tb] = row < g.M;
-    const int64_t prow = row_ok[tb] ? row : g.M - 1;
-    ro[tb] = g.y_rows.identity ? prow * g.y_rows.ld : eval_rows_k(&gk->y_rows, prow);
+    if constexpr (RES) ro[tb] = y_off(min(row0 + 32 * tb + l32, g.M - 1));      // the residual's rows: the lane's tokens
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {                                               // the rows that the lane stores a 16-byte run of
+      const int64_t row = row0 + 32 * tb + 16 * i + (lane >> 2);
+      s_ok[tb][i] = row < g.M;
+      so[tb][i] = y_off(s_ok[tb][i] ? row : g.M - 1) + (lane & 3) * 8;
+    }
   }
-  mlp_load_x_tile<C, 512>(x_l, (const bf16_t*)g.X, row0, g.M, g.x_rows.identity, g.x_rows.ld, &gk->x_rows);
-  if (row0 + 32 < g.M) mlp_load_x_tile<C, 512>(x_l + 32 * XP, (const bf16_t*)g.X, row0 + 32, g.M, g.x_rows.identity, g.x_rows.ld, &gk->x_rows);
-  else for (int s = tid; s < 32 * XP; s += 512) x_l[32 * XP + s] = mlp_u32x4{0u, 0u, 0u, 0u};
+  MlpTile<C, NTHR, 64> xt;
+  xt.request((const bf16_t*)g.X, row0, g.M, g.x_rows.identity, g.x_rows.ld, &gk->x_rows);
+  xt.store(x_l, row0, g.M);
   for (int s = tid; s < g.N / 8; s += 512) b_l[s] = g.bias ? ((const mlp_u32x4*)g.bias)[s] : mlp_u32x4{0u, 0u, 0u, 0u};
   __syncthreads();
   if (g.norm) {
-    mlp_norm_x_tile<C, 64>(x_l, g.norm_eps, (const mlp_u32x4*)g.norm_gamma, (const mlp_u32x4*)g.norm_beta);
+    mlp_norm_x_tile<C, NTHR, 64>(x_l, g.norm_eps, (const mlp_u32x4*)g.norm_gamma, (const mlp_u32x4*)g.norm_beta);
     __syncthreads();
   }
   const bf16_t* R = (const bf16_t*)g.residual;
@@ -1206,12 +1326,11 @@ __global__ __launch_bounds__(512, 1) void lin64_kernel(Lin32Args g) {
     for (int tb = 0; tb < 2; ++tb) {
       mlp_u32x4 outv[2];
       if (gelu_on) mlp_finish(h[tb], bias_v, bias_w, res[tb], true, outv); else mlp_finish(h[tb], bias_v, bias_w, res[tb], false, outv);
-      if (row_ok[tb]) {
-        // (assembly, as in lin32_kernel: with stores pending next to loads the compiler's wait counting falls back to
-        // waiting for everything before the next slice's first fragment)
-        bf16_t* yp = Y + ro[tb] + sc * 32 + hf * 8;
-        asm volatile("global_store_dwordx4 %0, %1, off\n\tglobal_store_dwordx4 %0, %2, off offset:32\n\ts_nop 2"
-                     :: "v"(yp), "v"(outv[0]), "v"(outv[1]) : "memory");
+      mlp_stage_put(st_l + w * 128, l32, hf, outv[0], outv[1]);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const mlp_u32x4 v = mlp_stage_get(st_l + w * 128, lane, i);
+        if (s_ok[tb][i]) mlp_store16(Y + so[tb][i] + sc * 32, v);
       }
     }
   }
@@ -1219,7 +1338,7 @@ __global__ __launch_bounds__(512, 1) void lin64_kernel(Lin32Args g) {
 
 template <int C>
 static int lin64_launch(const Lin32Args& g, void* stream) {
-  const size_t smem = (size_t)64 * (C / 8 + 1) * 16 + (size_t)g.N * 2;
+  const size_t smem = (size_t)64 * (C / 8 + 1) * 16 + 8 * 2048 + (size_t)g.N * 2;
   static std::atomic<size_t> allowed{0};
   if (smem > allowed.load()) {
     hipError_t e = hipFuncSetAttribute((const void*)lin64_kernel<C, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -1235,7 +1354,7 @@ static int lin64_launch(const Lin32Args& g, void* stream) {
 
 template <int C, bool RES, int NW>
 static int lin32_launch3(const Lin32Args& g, void* stream) {
-  const size_t smem = (size_t)32 * (C / 8 + 1) * 16 + (size_t)g.N * 2;
+  const size_t smem = (size_t)32 * (C / 8 + 1) * 16 + (size_t)NW * 2048 + (size_t)g.N * 2;
   static std::atomic<size_t> allowed{0};
   if (smem > allowed.load()) {
     const hipError_t e = hipFuncSetAttribute((const void*)lin32_kernel<C, RES, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
