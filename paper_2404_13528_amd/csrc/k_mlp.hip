@@ -554,6 +554,99 @@ __global__ __launch_bounds__(64 * (C / 32), C <= 256 ? 4 : 3) void mlp_fused_ker
   }
 }
 
+// What the 64-token kernels have in common.  The order in which a step's instructions are issued is pinned (a fence behind every
+// step, groups inside): an MFMA keeps the matrix pipe for eight issue slots, the vector work (`piece`, a step's share of it) goes
+// into the slots behind each, a weight register is asked for again right behind its last MFMA, and the tile's fragments are read
+// two steps ahead.  Left alone the compiler gathers the refills at the end of a phase, reads each fragment right before its MFMA
+// and puts the vector work of a phase in one piece, in which the matrix pipe idles (mlp64p_kernel<512, 2>, 196 workgroups, weights
+// in the caches: rounds 86 -> 71 thousand clocks, of which the MFMAs take 57, QKV 32 -> 25, of 24; 88 -> 80 us).
+template <int VALU> __device__ __forceinline__ void mlp64_mfma_order() {
+  __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+  if constexpr (VALU > 0) __builtin_amdgcn_sched_group_barrier(0x002, VALU, 0);
+}
+// out[bt][tb] += W(step i, feature block bt) x tile(token block tb, step i) for STEPS steps: the wave's 64 features against a
+// 64-token tile in LDS (row pitch `pitch` slots); refill(t) loads the fragment at position t of the call's stream (t >= 2 STEPS:
+// what follows it).
+template <int STEPS, int VALU, int RING, typename Refill, typename Piece>
+__device__ __forceinline__ void mlp64_pair(const mlp_u32x4* tile, int pitch, int l32, int hf, mlp_u32x4 (&wf)[RING], mlp_f32x16 (&out)[2][2],
+                                           Refill refill, Piece piece) {
+  int to = l32 * pitch + hf;
+  asm volatile("" : "+v"(to));                          // opaque per call: the tile's fragments are re-read, not hoisted
+  const int hi = 32 * pitch;
+  mlp_u32x4 ga[2][2] = {{tile[to], tile[to + hi]}, {tile[to + 2], tile[to + 2 + hi]}};
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < STEPS; ++i) {
+#pragma unroll
+    for (int bt = 0; bt < 2; ++bt) {
+      const int t = 2 * i + bt;
+      const mlp_bf16x8 wv = __builtin_bit_cast(mlp_bf16x8, wf[t % RING]);
+#pragma unroll
+      for (int tb = 0; tb < 2; ++tb) out[bt][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv, __builtin_bit_cast(mlp_bf16x8, ga[i & 1][tb]), out[bt][tb], 0, 0, 0);
+      wf[t % RING] = refill(t + RING);
+    }
+    if (i + 2 < STEPS) { ga[i & 1][0] = tile[to + 2 * (i + 2)]; ga[i & 1][1] = tile[to + 2 * (i + 2) + hi]; }
+    piece(i);
+#pragma unroll
+    for (int bt = 0; bt < 2; ++bt) {
+      mlp64_mfma_order<VALU>();
+      mlp64_mfma_order<0>();
+      __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+      if (bt) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+      if constexpr (VALU > 0) __builtin_amdgcn_sched_group_barrier(0x002, VALU, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+// h[tb] = bias + W(the wave's slice) x tile(token block tb): 32 features of a slice for the 64 tokens.  bias: the slice's four
+// slots of eight (bf16, LDS)
+template <int KK, int VALU, int RING, typename Refill, typename Piece>
+__device__ __forceinline__ void mlp64_slice(const mlp_u32x4* tile, int pitch, int l32, int hf, const mlp_u32x4* bias, mlp_u32x4 (&wf)[RING],
+                                            mlp_f32x16 (&h)[2], Refill refill, Piece piece) {
+  int xo = l32 * pitch + hf;
+  asm volatile("" : "+v"(xo));
+  const int hi = 32 * pitch;
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {                         // register 4 b + i of lane (token, hf) is feature 8 b + 4 hf + i
+    const uint2 v = ((const uint2*)(bias + b))[hf];
+    h[0][4 * b] = __uint_as_float(v.x << 16); h[0][4 * b + 1] = __uint_as_float(v.x & 0xffff0000u);
+    h[0][4 * b + 2] = __uint_as_float(v.y << 16); h[0][4 * b + 3] = __uint_as_float(v.y & 0xffff0000u);
+  }
+  h[1] = h[0];
+  mlp_u32x4 fa[2][2] = {{tile[xo], tile[xo + hi]}, {tile[xo + 2], tile[xo + 2 + hi]}};
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) {
+    const mlp_bf16x8 wv = __builtin_bit_cast(mlp_bf16x8, wf[kk % RING]);
+#pragma unroll
+    for (int tb = 0; tb < 2; ++tb) h[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv, __builtin_bit_cast(mlp_bf16x8, fa[kk & 1][tb]), h[tb], 0, 0, 0);
+    wf[kk % RING] = refill(kk + RING);
+    if (kk + 2 < KK) { fa[kk & 1][0] = tile[xo + 2 * (kk + 2)]; fa[kk & 1][1] = tile[xo + 2 * (kk + 2) + hi]; }
+    piece(kk);
+    mlp64_mfma_order<VALU>();
+    mlp64_mfma_order<0>();
+    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+    if constexpr (VALU > 0) __builtin_amdgcn_sched_group_barrier(0x002, VALU, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+// Piece i of n of a slice's way out of its accumulators: the 16 pairs of values are dealt to the pieces, act(a), packed to bf16,
+// and every four pairs make one run of eight features (run 2 gp + hf of token 32 tb + l32) by two v_permlane32_swap: put(tb, gp, run)
+template <typename Act, typename Put>
+__device__ __forceinline__ void mlp64_out_piece(int i, int n, const mlp_f32x16 (&h)[2], unsigned (&pk)[4], Act act, Put put) {
+#pragma unroll
+  for (int d = 16 * i / n; d < 16 * (i + 1) / n; ++d) {
+    const int tb = d >> 3, e = 2 * (d & 7);
+    pk[d & 3] = mlp_pack2(act(h[tb][e]), act(h[tb][e + 1]));
+    if ((d & 3) == 3) {
+      const auto s0 = __builtin_amdgcn_permlane32_swap(pk[0], pk[2], false, false);
+      const auto s1 = __builtin_amdgcn_permlane32_swap(pk[1], pk[3], false, false);
+      put(tb, (d >> 2) & 1, mlp_u32x4{s0[0], s1[0], s0[1], s1[1]});
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------------------------------------------
 // The fused MLP for wide rows (C = 512): Y = residual + W2 . gelu(W1 . LayerNorm(x) + b1) + b2 with a tile of 64 tokens
 // per workgroup and eight waves, each owning 64 output features.  With 32 tokens every weight fragment feeds one MFMA
@@ -568,7 +661,7 @@ __global__ __launch_bounds__(64 * (C / 32), C <= 256 ? 4 : 3) void mlp_fused_ker
 template <int C>
 __global__ __launch_bounds__(C, (C >= 384 ? 1 : 2)) void mlp64_kernel(MlpArgs g) {
   constexpr int KK = C / 16, XS = C / 8, XP = XS + 1, NW = C / 64, NTHR = 64 * NW, RING = KK % 16 == 0 ? 16 : 8;
-  constexpr int UG = NW / 2;                            // steps of the second product between two quarters of the bias + GELU work
+  constexpr int GV = 48 / NW;                           // vector instructions behind an MFMA of the second product (bias + GELU)
   constexpr int HP = 4 * NW + 1;                        // slots of a token's row of the round's hidden tile (+1: odd pitch)
   constexpr size_t TILE = (size_t)64 * XP * 16, HTILE = (size_t)64 * HP * 16;
   static_assert(C % 64 == 0 && KK % RING == 0 && 4 * NW == KK && NW % 2 == 0, "the ring position of a fragment must be a compile-time constant");
@@ -623,77 +716,29 @@ __global__ __launch_bounds__(C, (C >= 384 ? 1 : 2)) void mlp64_kernel(MlpArgs g)
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int e = 0; e < 16; ++e) out[i >> 1][i & 1][e] = 0.f;
-  const mlp_u32x4 zero4[2] = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}};
 
-  // first product of round r: slice NW r + w of the hidden units, both token blocks (block `blk` of the stream)
-  auto first = [&](int blk, mlp_f32x16 (&h)[2]) __attribute__((always_inline)) {
-    int xo = l32 * XP + hf;
-    asm volatile("" : "+v"(xo));                        // opaque per round: the X fragments are re-read, not hoisted
-#pragma unroll
-    for (int e = 0; e < 16; ++e) { h[0][e] = 0.f; h[1][e] = 0.f; }
-    mlp_u32x4 fa[2][2] = {{x_l[xo], x_l[xo + 32 * XP]}, {x_l[xo + 2], x_l[xo + 2 + 32 * XP]}};     // two steps ahead
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      const mlp_bf16x8 wv = __builtin_bit_cast(mlp_bf16x8, wf[kk % RING]);
-      h[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv, __builtin_bit_cast(mlp_bf16x8, fa[kk & 1][0]), h[0], 0, 0, 0);
-      h[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv, __builtin_bit_cast(mlp_bf16x8, fa[kk & 1][1]), h[1], 0, 0, 0);
-      wf[kk % RING] = wload(foff(blk, kk + RING));
-      if (kk + 2 < KK) { fa[kk & 1][0] = x_l[xo + 2 * (kk + 2)]; fa[kk & 1][1] = x_l[xo + 2 * (kk + 2) + 32 * XP]; }
-    }
-    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-      __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-    }
+  // bias + GELU of the slice just formed, bf16, into the round's hidden tile, a piece per step of the second product of the round
+  // before: both depend on the last barrier only
+  unsigned pk[4];
+  auto gelu_piece = [&](int i, int n, const mlp_f32x16 (&h)[2], mlp_u32x4* hb) __attribute__((always_inline)) {
+    mlp64_out_piece(i, n, h, pk, gelu_poly, [&](int tb, int gp, const mlp_u32x4& v) __attribute__((always_inline)) {
+      hb[(32 * tb + l32) * HP + w * 4 + 2 * gp + hf] = v;
+    });
   };
-  // bias + GELU of a quarter (token block u / 2, half u % 2 of its 32 hidden units) of the slice just formed, bf16, into `hb`
-  auto finish_unit = [&](int r, int u, const mlp_f32x16 (&h)[2], mlp_u32x4* hb) __attribute__((always_inline)) {
-    const int sc = NW * r + w, tb = u >> 1, gp = u & 1;
-    hb[(32 * tb + l32) * HP + w * 4 + 2 * gp + hf] = mlp_finish_half(h[tb], gp, b1_l[sc * 4 + 2 * gp + hf], zero4[0], true);
-  };
-  // second product of a round: the wave's 64 features over the 256 hidden units of tile `hp` (16 steps), both token
-  // blocks.  between(q), q < 4, runs after every UG steps.
-  auto second = [&](int blk, const mlp_u32x4* hp, auto between) __attribute__((always_inline)) {
-    int ho = l32 * HP + hf;
-    asm volatile("" : "+v"(ho));
-    mlp_u32x4 ga[2][2] = {{hp[ho], hp[ho + 32 * HP]}, {hp[ho + 2], hp[ho + 2 + 32 * HP]}};
-#pragma unroll
-    for (int i = 0; i < 2 * NW; ++i) {
-#pragma unroll
-      for (int bt = 0; bt < 2; ++bt) {
-        const int s = 2 * i + bt;
-        const mlp_bf16x8 wv = __builtin_bit_cast(mlp_bf16x8, wf[s % RING]);
-        out[bt][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv, __builtin_bit_cast(mlp_bf16x8, ga[i & 1][0]), out[bt][0], 0, 0, 0);
-        out[bt][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv, __builtin_bit_cast(mlp_bf16x8, ga[i & 1][1]), out[bt][1], 0, 0, 0);
-        wf[s % RING] = wload(foff(blk, s + RING));
-      }
-      if (i + 2 < 2 * NW) { ga[i & 1][0] = hp[ho + 2 * (i + 2)]; ga[i & 1][1] = hp[ho + 2 * (i + 2) + 32 * HP]; }
-      if (i % UG == UG - 1) {
-        __builtin_amdgcn_sched_barrier(0);
-        between(i / UG);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-  };
-
-  // Rounds, software-pipelined: the second product of round r - 1 (matrix cores) alternates, a quarter at a time, with
-  // the bias + GELU of round r's slice (vector ALU).  A barrier per round puts all waves of the workgroup in the same
-  // phase; alternating in short stretches lets the two waves of a SIMD cover each other's vector work with MFMAs.
+  auto nothing = [&](int) __attribute__((always_inline)) {};
   {
     mlp_f32x16 h[2];
-    first(0, h);
-#pragma unroll
-    for (int u = 0; u < 4; ++u) finish_unit(0, u, h, h_l);
+    mlp64_slice<KK, 0>(x_l, XP, l32, hf, b1_l + w * 4, wf, h, [&](int s) __attribute__((always_inline)) { return wload(foff(0, s)); }, nothing);
+    gelu_piece(0, 1, h, h_l);
     __syncthreads();
     for (int r = 1; r < rounds; ++r) {
-      first(2 * r - 1, h);
+      mlp64_slice<KK, 0>(x_l, XP, l32, hf, b1_l + (NW * r + w) * 4, wf, h, [&](int s) __attribute__((always_inline)) { return wload(foff(2 * r - 1, s)); }, nothing);
       mlp_u32x4* hb = h_l + (r & 1) * (64 * HP);
-      second(2 * r, h_l + ((r - 1) & 1) * (64 * HP), [&](int q) __attribute__((always_inline)) { finish_unit(r, q, h, hb); });
+      mlp64_pair<2 * NW, GV>(h_l + ((r - 1) & 1) * (64 * HP), HP, l32, hf, wf, out, [&](int s) __attribute__((always_inline)) { return wload(foff(2 * r, s)); },
+                             [&](int i) __attribute__((always_inline)) { gelu_piece(i, 2 * NW, h, hb); });
       __syncthreads();
     }
-    second(last_blk, h_l + ((rounds - 1) & 1) * (64 * HP), [&](int) __attribute__((always_inline)) {});
+    mlp64_pair<2 * NW, 0>(h_l + ((rounds - 1) & 1) * (64 * HP), HP, l32, hf, wf, out, [&](int s) __attribute__((always_inline)) { return wload(foff(last_blk, s)); }, nothing);
   }
 
   // every wave holds its 64 features of Y^T for the 64 tokens: bias, residual, two 16-byte stores per block and lane
@@ -729,7 +774,7 @@ __global__ __launch_bounds__(C, (C >= 384 ? 1 : 2)) void mlp64_kernel(MlpArgs g)
 template <int C, int LNOUT>
 __global__ __launch_bounds__(C, (C >= 384 ? 1 : 2)) void mlp64p_kernel(MlpArgs g, int vec_lds) {
   constexpr int KK = C / 16, XS = C / 8, XP = XS + 1, NW = C / 64, NTHR = 64 * NW, RING = KK % 16 == 0 ? 16 : 8, HP = 4 * NW + 1, NQ = 3 * C / 32 / NW;
-  constexpr int UG = NW / 2;                            // steps of the second product between two quarters of the bias + GELU work
+  constexpr int GV = 48 / NW;                           // vector instructions behind an MFMA of the second product (bias + GELU)
   constexpr size_t TILE = (size_t)64 * XP * 16, HTILE = (size_t)64 * HP * 16;
   static_assert(C % 64 == 0 && KK % RING == 0 && 4 * NW == KK && NW % 2 == 0 && 2 * HTILE >= TILE, "block and alias assumptions");
   const SM_KARG MlpArgs* gk = kernarg_ptr<MlpArgs>();
@@ -751,6 +796,30 @@ __global__ __launch_bounds__(C, (C >= 384 ? 1 : 2)) void mlp64p_kernel(MlpArgs g
   const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(g.Wproj_p), 0, 2 * C * C, 0x00020000);
   const __amdgpu_buffer_rsrc_t rq = LNOUT == 2 ? __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(g.Wq_p), 0, 6 * C * C, 0x00020000) : rw;
   const int lo = lane * 16;
+  // In a net the weights of a block have left the caches when it runs, and all workgroups ask for the same ones at the same time:
+  // the ring (about 2000 clocks ahead) does not cover memory.  So the workgroups of an XCD bring every chunk of the stream (Wproj;
+  // a round of W1 and W2; a third of the QKV weight: 2 C^2 bytes each) into its L2 two to three rounds ahead, a word of every
+  // 128-byte line, two lines a lane.  Workgroups behind the first 256 find what those have brought (C = 256: all of it fits).
+  // 12544 tokens of C = 512 in a net of 24 blocks: 95 -> 76 us, every MFMA phase as fast as with warm caches.
+  constexpr int CHUNK_LOADS = C * C * 2 / 8192;         // of 64 lines
+  const int pf_waves = ((min((int)gridDim.x, 256) + 7) >> 3) * NW, pf_wave = blockIdx.x < 256 ? (int)(blockIdx.x >> 3) * NW + w : CHUNK_LOADS;
+  unsigned pf[2] = {0u, 0u};
+  auto prefetch = [&](int chunk) __attribute__((always_inline)) {
+    if (chunk >= 1 + rounds + (LNOUT == 2 ? 3 : 0)) return;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      asm volatile("" ::"v"(pf[i]));                    // (the last one has long arrived)
+      if (pf_wave + i * pf_waves >= CHUNK_LOADS) continue;
+      const int at = (pf_wave + i * pf_waves) * 8192 + lane * 128;
+      if (chunk == 0) pf[i] = __builtin_amdgcn_raw_buffer_load_b32(rp, at, 0, 0);
+      else if (chunk <= rounds) {
+        constexpr int HALF = C * C, ROW = 2 * NW * 1024;      // bytes of a round of W1 (in one run), of one feature block's part of a round of W2
+        const int q = at - HALF, rr = chunk - 1;
+        pf[i] = __builtin_amdgcn_raw_buffer_load_b32(rw, q < 0 ? rr * HALF + at : 2 * Hd * C + q / ROW * (nsub * 2048) + rr * ROW + q % ROW, 0, 0);
+      } else pf[i] = __builtin_amdgcn_raw_buffer_load_b32(rq, at, (chunk - 1 - rounds) * (2 * C * C), 0);
+    }
+  };
+  prefetch(0); prefetch(1); prefetch(2);
   // The wave's stream: 64 fragments of Wproj ((step, feature block) order), the MLP's blocks of 32 (see mlp64_kernel),
   // then NQ blocks of the QKV weight.  Which weight a refill reads is known where it is written, so each kind has its
   // own loader (descriptor and offset scalar) and the MFMA loops stay straight-line code.
@@ -816,63 +885,13 @@ __global__ __launch_bounds__(C, (C >= 384 ? 1 : 2)) void mlp64p_kernel(MlpArgs g
 
   mlp_f32x16 out[2][2];                                 // [feature block][token block]: the projection, then Y^T
   const mlp_u32x4 zero4[2] = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}};
-  // out[bt][tb] += W(step i, feature block bt) x tile(token block tb, step i) for `steps` steps: the wave's 64 features
-  // against a 64-token tile in LDS (row pitch `pitch` slots); refill(t) loads the fragment at position t of the call's
-  // stream (t >= 2 * steps: what follows it).  between(q) after steps 4 q .. 4 q + 3.
-  auto pair_product = [&](const mlp_u32x4* tile, int pitch, int steps, auto refill, auto between) __attribute__((always_inline)) {
-    int to = l32 * pitch + hf;
-    asm volatile("" : "+v"(to));
-    const int hi = 32 * pitch;
-    mlp_u32x4 ga[2][2] = {{tile[to], tile[to + hi]}, {tile[to + 2], tile[to + 2 + hi]}};
-#pragma unroll
-    for (int i = 0; i < KK; ++i) {
-      if (i < steps) {
-#pragma unroll
-        for (int bt = 0; bt < 2; ++bt) {
-          const int t = 2 * i + bt;
-          const mlp_bf16x8 wv = __builtin_bit_cast(mlp_bf16x8, wf[t % RING]);
-          out[bt][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv, __builtin_bit_cast(mlp_bf16x8, ga[i & 1][0]), out[bt][0], 0, 0, 0);
-          out[bt][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv, __builtin_bit_cast(mlp_bf16x8, ga[i & 1][1]), out[bt][1], 0, 0, 0);
-          wf[t % RING] = refill(t + RING);
-        }
-        if (i + 2 < steps) { ga[i & 1][0] = tile[to + 2 * (i + 2)]; ga[i & 1][1] = tile[to + 2 * (i + 2) + hi]; }
-        if (i % UG == UG - 1 && i / UG < 4) {
-          __builtin_amdgcn_sched_barrier(0);
-          between(i / UG);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-    }
-  };
-  // h[tb] = W(slice of block blk) x tile(token block tb): 32 hidden / output features of a slice for the 64 tokens
-  // between(q), q < 4, after every KK / 4 steps
-  auto slice_product = [&](const mlp_u32x4* tile, mlp_f32x16 (&h)[2], auto refill, auto between) __attribute__((always_inline)) {
-    int xo = l32 * XP + hf;
-    asm volatile("" : "+v"(xo));
-#pragma unroll
-    for (int e = 0; e < 16; ++e) { h[0][e] = 0.f; h[1][e] = 0.f; }
-    mlp_u32x4 fa[2][2] = {{tile[xo], tile[xo + 32 * XP]}, {tile[xo + 2], tile[xo + 2 + 32 * XP]}};
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      const mlp_bf16x8 wv = __builtin_bit_cast(mlp_bf16x8, wf[kk % RING]);
-      h[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv, __builtin_bit_cast(mlp_bf16x8, fa[kk & 1][0]), h[0], 0, 0, 0);
-      h[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv, __builtin_bit_cast(mlp_bf16x8, fa[kk & 1][1]), h[1], 0, 0, 0);
-      wf[kk % RING] = refill(kk + RING);
-      if (kk + 2 < KK) { fa[kk & 1][0] = tile[xo + 2 * (kk + 2)]; fa[kk & 1][1] = tile[xo + 2 * (kk + 2) + 32 * XP]; }
-      if (kk % (KK / 4) == KK / 4 - 1) {
-        __builtin_amdgcn_sched_barrier(0);
-        between(kk / (KK / 4));
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-  };
   auto nothing = [&](int) __attribute__((always_inline)) {};
   // ---- projection: x1 = A . Wproj^T + bproj + x0 for the wave's 64 features
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int e = 0; e < 16; ++e) out[i >> 1][i & 1][e] = 0.f;
-  pair_product(a_l, XP, KK, [&](int t) __attribute__((always_inline)) { return t < 2 * KK ? frag_p(t) : frag_m(0, t - 2 * KK); }, nothing);
+  mlp64_pair<KK, 0>(a_l, XP, l32, hf, wf, out, [&](int t) __attribute__((always_inline)) { return t < 2 * KK ? frag_p(t) : frag_m(0, t - 2 * KK); }, nothing);
 #pragma unroll
   for (int tb = 0; tb < 2; ++tb) {
     mlp_u32x4 x1[2][2];
@@ -914,26 +933,30 @@ __global__ __launch_bounds__(C, (C >= 384 ? 1 : 2)) void mlp64p_kernel(MlpArgs g
   __syncthreads();
 
   // ---- the MLP's rounds, as in mlp64_kernel (stream blocks 2 ..)
-  auto finish_unit = [&](int r, int u, const mlp_f32x16 (&h)[2], mlp_u32x4* hb) __attribute__((always_inline)) {
-    const int sc = NW * r + w, tb = u >> 1, gp = u & 1;
-    hb[(32 * tb + l32) * HP + w * 4 + 2 * gp + hf] = mlp_finish_half(h[tb], gp, b1_l[sc * 4 + 2 * gp + hf], zero4[0], true);
+  unsigned pk[4];
+  auto gelu_piece = [&](int i, int n, const mlp_f32x16 (&h)[2], mlp_u32x4* hb) __attribute__((always_inline)) {
+    mlp64_out_piece(i, n, h, pk, gelu_poly, [&](int tb, int gp, const mlp_u32x4& v) __attribute__((always_inline)) {
+      hb[(32 * tb + l32) * HP + w * 4 + 2 * gp + hf] = v;
+    });
   };
   {
     mlp_f32x16 h[2];
-    slice_product(x_l, h, [&](int s) __attribute__((always_inline)) { return frag_m(0, s); }, nothing);
-#pragma unroll
-    for (int u = 0; u < 4; ++u) finish_unit(0, u, h, h_l);
+    prefetch(3);
+    mlp64_slice<KK, 0>(x_l, XP, l32, hf, b1_l + w * 4, wf, h, [&](int s) __attribute__((always_inline)) { return frag_m(0, s); }, nothing);
+    gelu_piece(0, 1, h, h_l);
     __syncthreads();
     for (int r = 1; r < rounds; ++r) {
-      slice_product(x_l, h, [&](int s) __attribute__((always_inline)) { return frag_m(2 * r - 1, s); }, nothing);
+      prefetch(r + 3);
+      mlp64_slice<KK, 0>(x_l, XP, l32, hf, b1_l + (NW * r + w) * 4, wf, h, [&](int s) __attribute__((always_inline)) { return frag_m(2 * r - 1, s); }, nothing);
       mlp_u32x4* hb = h_l + (r & 1) * (64 * HP);
-      pair_product(h_l + ((r - 1) & 1) * (64 * HP), HP, 2 * NW, [&](int s) __attribute__((always_inline)) { return frag_m(2 * r, s); },
-                   [&](int q) __attribute__((always_inline)) { finish_unit(r, q, h, hb); });
+      mlp64_pair<2 * NW, GV>(h_l + ((r - 1) & 1) * (64 * HP), HP, l32, hf, wf, out, [&](int s) __attribute__((always_inline)) { return frag_m(2 * r, s); },
+                             [&](int i) __attribute__((always_inline)) { gelu_piece(i, 2 * NW, h, hb); });
       __syncthreads();
     }
+    prefetch(rounds + 3);
     // the last block of the MLP: what follows it in the stream is the first QKV slice (or nothing)
-    pair_product(h_l + ((rounds - 1) & 1) * (64 * HP), HP, 2 * NW,
-                 [&](int s) __attribute__((always_inline)) { return (LNOUT == 2 && s >= KK) ? frag_q(0, s - KK) : frag_m(lastm, s < KK ? s : KK - 1); }, nothing);
+    mlp64_pair<2 * NW, 0>(h_l + ((rounds - 1) & 1) * (64 * HP), HP, l32, hf, wf, out,
+                          [&](int s) __attribute__((always_inline)) { return (LNOUT == 2 && s >= KK) ? frag_q(0, s - KK) : frag_m(lastm, s < KK ? s : KK - 1); }, nothing);
   }
 
   // ---- Y = x1 + MLP, out in 64-byte pieces through the wave's 2 KiB of the X tile (not read since the last round's barrier)
@@ -979,27 +1002,41 @@ __global__ __launch_bounds__(C, (C >= 384 ? 1 : 2)) void mlp64p_kernel(MlpArgs g
     __syncthreads();
     normalised(g.ln2_eps, 4, yget, into(n_l));
     __syncthreads();
-    // bias and store of slice j (a token block u / 2 at a time, on odd u) are issued between the quarters of slice j + 1's product
-    auto emit_q = [&](int j, int u, const mlp_f32x16 (&h)[2]) __attribute__((always_inline)) {
-      if (!(u & 1)) return;
-      const int sc = w + NW * j, tb = u >> 1;
-      mlp_u32x4 qv[2];
-      mlp_finish(h[tb], b1_l[sc * 4 + hf], b1_l[sc * 4 + 2 + hf], zero4, false, qv);
-      emit((bf16_t*)g.Y2, 3, ro_l + 64 + 32 * tb, sc * 32, qv[0], qv[1]);      // same row map, rows three times as long
+    // slice j leaves while slice j + 1 is formed: its values in the first KK - 4 steps, a finished token block through the wave's
+    // stage one step later
+    mlp_u32x4 run[2];
+    auto emit_q = [&](int j, int kk, const mlp_f32x16 (&h)[2]) __attribute__((always_inline)) {
+      constexpr int S = KK - 4;
+#pragma unroll
+      for (int tb = 0; tb < 2; ++tb) {
+        if (kk == ((tb + 1) * S + 1) / 2) {
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const mlp_u32x4 v = mlp_stage_get(stage, lane, i);
+            const int64_t o = ro_l[64 + 32 * tb + 16 * i + (lane >> 2)];         // same row map as the norm's, rows three times as long
+            if (o >= 0) mlp_store16((bf16_t*)g.Y2 + o * 3 + (w + NW * j) * 32 + (lane & 3) * 8, v);
+          }
+        }
+      }
+      if (kk < S)
+        mlp64_out_piece(kk, S, h, pk, [](float a) __attribute__((always_inline)) { return a; }, [&](int, int gp, const mlp_u32x4& v) __attribute__((always_inline)) {
+          run[gp] = v;
+          if (gp) mlp_stage_put(stage, l32, hf, run[0], run[1]);
+        });
     };
     static_assert(NQ % 2 == 0, "slices are taken two at a time");
     mlp_f32x16 ha[2], hb2[2];
-    slice_product(n_l, ha, [&](int s) __attribute__((always_inline)) { return frag_q(0, s); }, nothing);
+    mlp64_slice<KK, 0>(n_l, XP, l32, hf, b1_l + w * 4, wf, ha, [&](int s) __attribute__((always_inline)) { return frag_q(0, s); }, nothing);
 #pragma unroll 1
     for (int j = 0; j < NQ; j += 2) {
-      slice_product(n_l, hb2, [&](int s) __attribute__((always_inline)) { return frag_q(j + 1, s); },
-                    [&](int u) __attribute__((always_inline)) { emit_q(j, u, ha); });
+      mlp64_slice<KK, 2>(n_l, XP, l32, hf, b1_l + (w + NW * (j + 1)) * 4, wf, hb2, [&](int s) __attribute__((always_inline)) { return frag_q(j + 1, s); },
+                         [&](int kk) __attribute__((always_inline)) { emit_q(j, kk, ha); });
       if (j + 2 < NQ) {
-        slice_product(n_l, ha, [&](int s) __attribute__((always_inline)) { return frag_q(j + 2, s); },
-                      [&](int u) __attribute__((always_inline)) { emit_q(j + 1, u, hb2); });
+        mlp64_slice<KK, 2>(n_l, XP, l32, hf, b1_l + (w + NW * (j + 2)) * 4, wf, ha, [&](int s) __attribute__((always_inline)) { return frag_q(j + 2, s); },
+                           [&](int kk) __attribute__((always_inline)) { emit_q(j + 1, kk, hb2); });
       } else {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) emit_q(j + 1, u, hb2);
+        for (int kk = 0; kk < KK; ++kk) emit_q(j + 1, kk, hb2);
       }
     }
   }
