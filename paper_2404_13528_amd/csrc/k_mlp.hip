@@ -81,21 +81,22 @@ __global__ void mlp_pack_kernel(const bf16_t* W1, const bf16_t* W2, mlp_u32x4* p
   packed[o] = *(const mlp_u32x4*)src;
 }
 
-// ROWS token rows -> LDS, rows at an odd pitch of 16-byte slots (rows past M as zeros), in two steps: request() puts every
-// row-offset lookup and then every load in flight, store() waits for them.  What a kernel requests in between (a second
-// tile, the weight stream) travels at the same time.
+// ROWS token rows -> LDS, rows at an odd pitch of 16-byte slots (rows past M as zeros), in steps: rows() puts every row-offset
+// lookup in flight, load() the loads, store() waits for them.  What a kernel requests in between (a second tile, the weight
+// stream) travels at the same time.
 template <int C, int NTHR, int ROWS>
 struct MlpTile {
   static constexpr int XS = C / 8, XP = XS + 1, NIT = (ROWS * XS + NTHR - 1) / NTHR;
   mlp_u32x4 v[NIT];
-  __device__ __forceinline__ void request(const bf16_t* X, int64_t row0, int64_t M, int ident, int64_t ld, const SM_KARG RowProg* rows) {
-    int64_t row[NIT], off[NIT];
+  int64_t off[NIT];
+  __device__ __forceinline__ void rows(int64_t row0, int64_t M, int ident, int64_t ld, const SM_KARG RowProg* prog) {
+    int64_t row[NIT];
 #pragma unroll
     for (int i = 0; i < NIT; ++i) row[i] = min(row0 + min((int)(threadIdx.x + i * NTHR) / XS, ROWS - 1), M - 1);
     if (ident) {
 #pragma unroll
       for (int i = 0; i < NIT; ++i) off[i] = row[i] * ld;
-    } else if (const int32_t* tab = rows->table) {
+    } else if (const int32_t* tab = prog->table) {
       int32_t t[NIT];
 #pragma unroll
       for (int i = 0; i < NIT; ++i) t[i] = tab[row[i]];
@@ -103,13 +104,19 @@ struct MlpTile {
       for (int i = 0; i < NIT; ++i) off[i] = t[i];
     } else {
 #pragma unroll
-      for (int i = 0; i < NIT; ++i) off[i] = eval_rows_k(rows, row[i]);
+      for (int i = 0; i < NIT; ++i) off[i] = eval_rows_k(prog, row[i]);
     }
+  }
+  __device__ __forceinline__ void load(const bf16_t* X) {
 #pragma unroll
     for (int i = 0; i < NIT; ++i) {
       const int s = threadIdx.x + i * NTHR, c = s - s / XS * XS;
       v[i] = *(const mlp_u32x4*)(X + off[i] + (s < ROWS * XS ? c : 0) * 8);
     }
+  }
+  __device__ __forceinline__ void request(const bf16_t* X, int64_t row0, int64_t M, int ident, int64_t ld, const SM_KARG RowProg* prog) {
+    rows(row0, M, ident, ld, prog);
+    load(X);
   }
   __device__ __forceinline__ void store(mlp_u32x4* x_l, int64_t row0, int64_t M) const {
 #pragma unroll
@@ -279,6 +286,47 @@ __device__ __forceinline__ void mlp_finish(const mlp_f32x16& h, const mlp_u32x4&
   for (int gp = 0; gp < 2; ++gp) outv[gp] = mlp_finish_half(h, gp, gp ? bias_w : bias_v, res[gp], gelu_on);
 }
 
+// an accumulator that starts from the biases of its 32 rows (four slots of eight, bf16, LDS)
+__device__ __forceinline__ void mlp_start_bias(mlp_f32x16& h, const mlp_u32x4* bias, int hf) {
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    const uint2 v = ((const uint2*)(bias + b))[hf];
+    h[4 * b] = __uint_as_float(v.x << 16); h[4 * b + 1] = __uint_as_float(v.x & 0xffff0000u);
+    h[4 * b + 2] = __uint_as_float(v.y << 16); h[4 * b + 3] = __uint_as_float(v.y & 0xffff0000u);
+  }
+}
+// four pairs of packed values (rows 8 b + 4 hf .. + 3 of b = 2 gp, 2 gp + 1) -> the lane's run of eight rows, 2 gp + hf
+__device__ __forceinline__ mlp_u32x4 mlp_run8(const unsigned (&pk)[4]) {
+  const auto s0 = __builtin_amdgcn_permlane32_swap(pk[0], pk[2], false, false);
+  const auto s1 = __builtin_amdgcn_permlane32_swap(pk[1], pk[3], false, false);
+  return mlp_u32x4{s0[0], s1[0], s0[1], s1[1]};
+}
+template <typename Act> __device__ __forceinline__ mlp_u32x4 mlp_run(const mlp_f32x16& h, int gp, Act act) {
+  unsigned pk[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) pk[i] = mlp_pack2(act(h[8 * gp + 2 * i]), act(h[8 * gp + 2 * i + 1]));
+  return mlp_run8(pk);
+}
+// acc += the wave's fragments wf x a 32-token tile in LDS (slot `at`: the lane's first of its row).  The order of issue is pinned
+// (a fence behind every step): the MFMA, the refill of its weight register with what refill(kk) asks for, and the tile's
+// fragment three steps ahead
+template <int KK, typename Refill>
+__device__ __forceinline__ void mlp32_product(const mlp_u32x4* tile, int at, mlp_u32x4 (&wf)[KK], mlp_f32x16& acc, Refill refill) {
+  asm volatile("" : "+v"(at));                          // opaque per call: the tile's fragments are re-read from LDS instead of being
+  mlp_u32x4 fb[3] = {tile[at], tile[at + 2], tile[at + 4]};      // hoisted into (and spilled from) registers
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) {
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(mlp_bf16x8, wf[kk]), __builtin_bit_cast(mlp_bf16x8, fb[kk % 3]), acc, 0, 0, 0);
+    wf[kk] = refill(kk);
+    if (kk + 3 < KK) fb[kk % 3] = tile[at + 2 * (kk + 3)];
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
 // vectors of C elements beside b1 in the kernel's LDS: b2; bproj, gamma, beta; gamma, beta of the second output; bq (three)
 constexpr int mlp_vectors(bool proj, int lnout) { return 1 + (proj ? 3 : 0) + (lnout ? 2 : 0) + (lnout == 2 ? 3 : 0); }
 
@@ -336,11 +384,12 @@ __global__ __launch_bounds__(64 * (C / 32), C <= 256 ? 4 : 3) void mlp_fused_ker
   if constexpr (PROJ) rp = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(g.Wproj_p), 0, 2 * C * C, 0x00020000);
   if constexpr (LNOUT == 2) rq = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(g.Wq_p), 0, 6 * C * C, 0x00020000);
 
-  // Everything the tile needs from memory is requested before anything is waited for, the rows before the weight stream (loads
-  // return in the order they were asked for): the tile, PROJ's residual x0 (through y_rows), the vectors, the row offsets
+  // Everything the tile needs from memory is requested before anything is waited for, in the order of its use (loads return in the
+  // order they were asked for): the tile, the row offsets and vectors, the weight stream, and behind its first fragments PROJ's
+  // residual x0 (through y_rows), which has the projection to arrive in
   MlpTile<C, NTHR, 32> xt, rt;
+  if constexpr (PROJ) rt.rows(row0, g.M, g.y_rows.identity, g.y_rows.ld, &gk->y_rows);
   xt.request((const bf16_t*)g.X, row0, g.M, g.x_rows.identity, g.x_rows.ld, &gk->x_rows);
-  if constexpr (PROJ) rt.request((const bf16_t*)g.resid0, row0, g.M, g.y_rows.identity, g.y_rows.ld, &gk->y_rows);
   if (tid < 32 || (LNOUT != 0 && tid < 64)) {
     const int64_t row = row0 + (tid & 31), prow = row < g.M ? row : g.M - 1;
     int64_t o;
@@ -364,8 +413,10 @@ __global__ __launch_bounds__(64 * (C / 32), C <= 256 ? 4 : 3) void mlp_fused_ker
   if constexpr (LNOUT == 2) for (int s = tid; s < 3 * XS; s += NTHR) vec_l[V_BQ * XS + s] = ((const mlp_u32x4*)g.bq)[s];
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk) wf[kk] = PROJ ? wload(rp, (w * KK + kk) * 1024) : wload(rw, (sc0 * KK + kk) * 1024);
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (PROJ) rt.load((const bf16_t*)g.resid0);
+  __builtin_amdgcn_sched_barrier(0);
   xt.store(PROJ ? a_l : x_l, row0, g.M);
-  if constexpr (PROJ) rt.store(x_l, row0, g.M);
   __syncthreads();
 
   const mlp_u32x4 zero4[2] = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}};
@@ -377,25 +428,12 @@ __global__ __launch_bounds__(64 * (C / 32), C <= 256 ? 4 : 3) void mlp_fused_ker
   for (int e = 0; e < 16; ++e) out[e] = 0.f;
   if constexpr (PROJ) {
     // wave w forms features 32 w ..+31 of x1
-    int ao = l32 * XP + hf;
-    asm volatile("" : "+v"(ao));
     mlp_f32x16 h;
 #pragma unroll
     for (int e = 0; e < 16; ++e) h[e] = 0.f;
-    mlp_u32x4 fb[3] = {a_l[ao], a_l[ao + 2], a_l[ao + 4]};       // LDS fragments three steps ahead of their MFMA
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      h = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(mlp_bf16x8, wf[kk]), __builtin_bit_cast(mlp_bf16x8, fb[kk % 3]), h, 0, 0, 0);
-      wf[kk] = wload(rw, (sc0 * KK + kk) * 1024);
-      if (kk + 3 < KK) fb[kk % 3] = a_l[ao + 2 * (kk + 3)];
-    }
-    __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);        // LDS fragment reads run three steps ahead of their MFMA
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    }
+    mlp32_product(a_l, l32 * XP + hf, wf, h, [&](int kk) __attribute__((always_inline)) { return wload(rw, (sc0 * KK + kk) * 1024); });
+    rt.store(x_l, row0, g.M);
+    __syncthreads();
     const mlp_u32x4 res[2] = {x_l[xs], x_l[xs + 2]};           // x0, of which every lane reads the slots that it overwrites below
     mlp_u32x4 x1[1][2];
     mlp_finish(h, vec_l[V_BP * XS + fs], vec_l[V_BP * XS + fs + 2], res, false, x1[0]);          // x1 rounded to bf16, as the separate Linear stores it
@@ -423,60 +461,31 @@ __global__ __launch_bounds__(64 * (C / 32), C <= 256 ? 4 : 3) void mlp_fused_ker
     const bool sc_ok = sc < nsub;
     const int scc = sc_ok ? sc : nsub - 1;
     const int nsc = sc + T < nsub ? sc + T : scc;
-    int xo = l32 * XP + hf;                              // opaque per round: the X fragments are re-read from LDS instead
-    asm volatile("" : "+v"(xo));                         // of being hoisted into (and spilled from) registers
     const int s0 = r * T;                                // first slice of the round
     const int rem = nsub - s0;                           // slices of W2 from this round's first to the end (>= 1)
     const int cur2 = W2o + s0 * 2048;                    // scalar: this round's W2 fragments of this wave, (slice, step) in order
     mlp_f32x16 h;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) h[e] = 0.f;
-    mlp_u32x4 fb[3] = {x_l[xo], x_l[xo + 2], x_l[xo + 4]};        // LDS fragments three steps ahead of their MFMA
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      h = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(mlp_bf16x8, wf[kk]), __builtin_bit_cast(mlp_bf16x8, fb[kk % 3]), h, 0, 0, 0);
-      if (kk + 3 < KK) fb[kk % 3] = x_l[xo + 2 * (kk + 3)];
-      // refill with the second product's fragment kk of this round; past the end of W2 the last valid pair again (its H is zero)
-      wf[kk] = wload(rw, cur2 + (kk < 2 * rem ? kk : (kk & 1) + 2 * (rem - 1)) * 1024);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);        // LDS fragment reads run three steps ahead of their MFMA
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    }
-    mlp_u32x4 hv[2];
-    const mlp_u32x4 bias_v = b1_l[scc * 4 + hf], bias_w = b1_l[scc * 4 + 2 + hf];
-    mlp_finish(h, bias_v, bias_w, zero4, true, hv);
+    mlp_start_bias(h, b1_l + scc * 4, hf);
+    // refills: the second product's fragments of this round; past the end of W2 the last valid pair again (its H is zero)
+    mlp32_product(x_l, l32 * XP + hf, wf, h, [&](int kk) __attribute__((always_inline)) { return wload(rw, cur2 + (kk < 2 * rem ? kk : (kk & 1) + 2 * (rem - 1)) * 1024); });
     mlp_u32x4* hb = h_l + (r & 1) * (32 * HP);
 #pragma unroll
-    for (int gp = 0; gp < 2; ++gp) hb[l32 * HP + w * 4 + 2 * gp + hf] = sc_ok ? hv[gp] : zero4[0];     // past the last slice: zeros
+    for (int gp = 0; gp < 2; ++gp) {
+      const mlp_u32x4 hv = mlp_run(h, gp, gelu_poly);
+      hb[l32 * HP + w * 4 + 2 * gp + hf] = sc_ok ? hv : zero4[0];     // past the last slice: zeros
+    }
     __syncthreads();
     // ---- second product: this wave's 32 output features over the round's T slices.  One barrier per round: the
     // other H buffer is written next, and nobody writes this one again before the barrier after that
-    int ho = l32 * HP + hf;
-    asm volatile("" : "+v"(ho));
-    mlp_u32x4 gb[3] = {hb[ho], hb[ho + 2], hb[ho + 4]};
-#pragma unroll
-    for (int i = 0; i < 2 * T; ++i) {                                       // i = 2 * (slice of the round) + step
-      out = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(mlp_bf16x8, wf[i]), __builtin_bit_cast(mlp_bf16x8, gb[i % 3]), out, 0, 0, 0);
-      if (i + 3 < 2 * T) gb[i % 3] = hb[ho + 2 * (i + 3)];
-      wf[i] = wload(rw, (nsc * KK + i) * 1024);                             // the wave's slice of the next round (after the last: a copy, unused)
-    }
-    __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
-#pragma unroll
-    for (int i = 0; i < 2 * T; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    }
+    // what follows in the stream: the wave's slice of the next round; after the last the Linear that follows, or nothing (a descriptor
+    // of no bytes: zeros, without a look at memory)
+    const bool last = r + 1 == rounds;
+    const __amdgpu_buffer_rsrc_t rn = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(LNOUT == 2 && last ? g.Wq_p : g.Wp), 0,
+                                                                        last ? (LNOUT == 2 ? 6 * C * C : 0) : 4 * Hd * C, 0x00020000);
+    const int next = (LNOUT == 2 && last ? w : nsc) * KK * 1024;
+    mlp32_product(hb, l32 * HP + hf, wf, out, [&](int i) __attribute__((always_inline)) { return wload(rn, next + i * 1024); });
   }
 
-  if constexpr (LNOUT == 2) {       // first fragments of the Linear that follows, under the epilogue below
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) wf[kk] = wload(rq, (w * KK + kk) * 1024);
-  }
   {
   // every wave holds its 32 features of Y^T complete: bias, residual, and out in 64-byte pieces through the wave's 2 KiB of
   // the X tile (nobody has read that since the last barrier)
@@ -525,28 +534,11 @@ __global__ __launch_bounds__(64 * (C / 32), C <= 256 ? 4 : 3) void mlp_fused_ker
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
         const int sc = w + T * j;
-        const mlp_u32x4 bias_v = vec_l[V_BQ * XS + sc * 4 + hf], bias_w = vec_l[V_BQ * XS + sc * 4 + 2 + hf];
-        int no = l32 * XP + hf;
-        asm volatile("" : "+v"(no));
         mlp_f32x16 h;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) h[e] = 0.f;
-        mlp_u32x4 fb[3] = {n_l[no], n_l[no + 2], n_l[no + 4]};
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-          h = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(mlp_bf16x8, wf[kk]), __builtin_bit_cast(mlp_bf16x8, fb[kk % 3]), h, 0, 0, 0);
-          if (kk + 3 < KK) fb[kk % 3] = n_l[no + 2 * (kk + 3)];
-          if (j < 2) wf[kk] = wload(rq, ((sc + T) * KK + kk) * 1024);
-        }
-        __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        }
-        mlp_u32x4 qv[2];
-        mlp_finish(h, bias_v, bias_w, zero4, false, qv);
+        mlp_start_bias(h, vec_l + V_BQ * XS + sc * 4, hf);
+        mlp32_product(n_l, l32 * XP + hf, wf, h, [&](int kk) __attribute__((always_inline)) { return j < 2 ? wload(rq, ((sc + T) * KK + kk) * 1024) : wf[kk]; });
+        const auto same = [](float a) __attribute__((always_inline)) { return a; };
+        const mlp_u32x4 qv[2] = {mlp_run(h, 0, same), mlp_run(h, 1, same)};
         emit((bf16_t*)g.Y2, 3, ro_l + 32, sc * 32, qv[0], qv[1]);        // same row map, rows three times as long
       }
     }
@@ -606,12 +598,7 @@ __device__ __forceinline__ void mlp64_slice(const mlp_u32x4* tile, int pitch, in
   int xo = l32 * pitch + hf;
   asm volatile("" : "+v"(xo));
   const int hi = 32 * pitch;
-#pragma unroll
-  for (int b = 0; b < 4; ++b) {                         // register 4 b + i of lane (token, hf) is feature 8 b + 4 hf + i
-    const uint2 v = ((const uint2*)(bias + b))[hf];
-    h[0][4 * b] = __uint_as_float(v.x << 16); h[0][4 * b + 1] = __uint_as_float(v.x & 0xffff0000u);
-    h[0][4 * b + 2] = __uint_as_float(v.y << 16); h[0][4 * b + 3] = __uint_as_float(v.y & 0xffff0000u);
-  }
+  mlp_start_bias(h[0], bias, hf);
   h[1] = h[0];
   mlp_u32x4 fa[2][2] = {{tile[xo], tile[xo + hi]}, {tile[xo + 2], tile[xo + 2 + hi]}};
   __builtin_amdgcn_sched_barrier(0);
@@ -639,11 +626,7 @@ __device__ __forceinline__ void mlp64_out_piece(int i, int n, const mlp_f32x16 (
   for (int d = 16 * i / n; d < 16 * (i + 1) / n; ++d) {
     const int tb = d >> 3, e = 2 * (d & 7);
     pk[d & 3] = mlp_pack2(act(h[tb][e]), act(h[tb][e + 1]));
-    if ((d & 3) == 3) {
-      const auto s0 = __builtin_amdgcn_permlane32_swap(pk[0], pk[2], false, false);
-      const auto s1 = __builtin_amdgcn_permlane32_swap(pk[1], pk[3], false, false);
-      put(tb, (d >> 2) & 1, mlp_u32x4{s0[0], s1[0], s0[1], s1[1]});
-    }
+    if ((d & 3) == 3) put(tb, (d >> 2) & 1, mlp_run8(pk));
   }
 }
 
@@ -840,12 +823,12 @@ __global__ __launch_bounds__(C, (C >= 384 ? 1 : 2)) void mlp64p_kernel(MlpArgs g
     j = j < NQ ? j : NQ - 1;
     return __builtin_amdgcn_raw_buffer_load_b128(rq, lo, ((w + NW * j) * KK + s) * 1024, 0);
   };
-  // The tile and the residual x0 (through y_rows) are requested together, before the weight stream (loads return in the order
-  // they were asked for).  One workgroup per CU has nothing to run beside its row phases, in which the matrix cores wait: tile,
+  // The tile is requested first, then the weight stream, the residual x0 (through y_rows) behind its first fragments: loads return in
+  // the order they were asked for, and x0 has the projection to arrive in.  One workgroup per CU has nothing to run beside its row phases, in which the matrix cores wait: tile,
   // projection's epilogue, both norms and Y took 23 of the 96 us of 12544 x 512 with the next QKV
   MlpTile<C, NTHR, 64> xt, rt;
+  rt.rows(row0, g.M, g.y_rows.identity, g.y_rows.ld, &gk->y_rows);
   xt.request((const bf16_t*)g.X, row0, g.M, g.x_rows.identity, g.x_rows.ld, &gk->x_rows);
-  rt.request((const bf16_t*)g.resid0, row0, g.M, g.y_rows.identity, g.y_rows.ld, &gk->y_rows);
   if (tid < (LNOUT != 0 ? 128 : 64)) {
     const int64_t row = row0 + (tid & 63), prow = row < g.M ? row : g.M - 1;
     int64_t o;
@@ -857,6 +840,9 @@ __global__ __launch_bounds__(C, (C >= 384 ? 1 : 2)) void mlp64p_kernel(MlpArgs g
   mlp_u32x4 wf[RING];
 #pragma unroll
   for (int s = 0; s < RING; ++s) wf[s] = frag_p(s);
+  __builtin_amdgcn_sched_barrier(0);
+  rt.load((const bf16_t*)g.resid0);
+  __builtin_amdgcn_sched_barrier(0);
   // vector i of C elements: a lane's slots are those of blocks 2 w + bt, runs 2 gp + hf
   auto vec = [&](int i) __attribute__((always_inline)) -> const mlp_u32x4* {
     return (const mlp_u32x4*)(i == 0 ? g.bproj : i == 1 ? g.norm_gamma : i == 2 ? g.norm_beta : i == 3 ? g.b2 : i == 4 ? g.ln2_gamma : g.ln2_beta);
@@ -880,7 +866,6 @@ __global__ __launch_bounds__(C, (C >= 384 ? 1 : 2)) void mlp64p_kernel(MlpArgs g
     for (int i = 0; i < NV; ++i) vec_l[i * XS + tid] = v[i];
   }
   xt.store(a_l, row0, g.M);
-  rt.store(x_l, row0, g.M);
   __syncthreads();
 
   mlp_f32x16 out[2][2];                                 // [feature block][token block]: the projection, then Y^T
@@ -892,6 +877,8 @@ __global__ __launch_bounds__(C, (C >= 384 ? 1 : 2)) void mlp64p_kernel(MlpArgs g
 #pragma unroll
     for (int e = 0; e < 16; ++e) out[i >> 1][i & 1][e] = 0.f;
   mlp64_pair<KK, 0>(a_l, XP, l32, hf, wf, out, [&](int t) __attribute__((always_inline)) { return t < 2 * KK ? frag_p(t) : frag_m(0, t - 2 * KK); }, nothing);
+  rt.store(x_l, row0, g.M);
+  __syncthreads();
 #pragma unroll
   for (int tb = 0; tb < 2; ++tb) {
     mlp_u32x4 x1[2][2];
