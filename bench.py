@@ -65,15 +65,15 @@ def kernel_model(label):
             by += 2 * C + 3 * C * C + 3 * C + 3 * M * C
             fl += 6.0 * M * C * C
         return by * e, fl
-    m = re.match(r"decode_(ln\+qkv\+rope\|ln\+fc1\+gelu|dense\+fc2\+res)_bf16\[(\d+),(\d+),(\d+)\]", label)
+    m = re.match(r"decode_(ln\+qkv\+rope\|ln\+fc1\+gelu|dense\+sum\+res)_bf16\[(\d+),(\d+),(\d+)\]", label)
     if m:      # skinny Linears of the decode step: the weight once, the token rows in and out, biases / norm vectors
         B, N, K = int(m.group(2)), int(m.group(3)), int(m.group(4))
         extra = 4 * K if m.group(1).startswith("ln") else (N + B * N)          # two norms' gamma / beta | second bias, residual
         return (N * K + N + B * K + B * N + extra) * e, 2.0 * B * N * K
-    m = re.match(r"decode_attention_bf16\[(\d+),(\d+),(\d+),(\d+)\]", label)
-    if m:
-        B, h, n, d = [int(m.group(i)) for i in range(1, 5)]
-        return B * h * (2 * n * d + 2 * d) * e, 4.0 * B * h * n * d
+    m = re.match(r"decode_attention\|fc2_bf16\[(\d+),(\d+),(\d+),(\d+)\]\+\[(\d+),(\d+),(\d+)\]", label)
+    if m:      # attention against the cache, and beside it W2 . hid (its fp32 parts are this form's own)
+        B, h, n, d, _, N, K = [int(m.group(i)) for i in range(1, 8)]
+        return (B * h * (2 * n * d + 2 * d) + N * K + B * K) * e, 4.0 * B * h * n * d + 2.0 * B * N * K
     m = re.match(r"cutgemm_bf16\[(\d+),(\d+),(\d+)\]", label)
     if m:      # cut over K: the operands (the fp32 parts are this form's own, as a fused operator's intermediates are)
         M, N, K = int(m.group(1)), int(m.group(2)), int(m.group(3))

@@ -24,7 +24,7 @@
 
 using namespace sm;
 
-namespace sm { int decode_attn_block(int d); int decode_counter_stride(); size_t decode_out_smem(int B, int E, int F, int nks); }      // keys of one block of the attention kernel (k_decode.hip)
+namespace sm { int decode_attn_block(int d); int decode_counter_stride(); }      // keys of one block of the attention kernel (k_decode.hip)
 
 namespace {
 
@@ -90,6 +90,12 @@ std::shared_ptr<DecodePlan> decode_plan(const sm_decode_cfg& c, std::string* err
   return p;
 }
 
+// activation rows of the longest of 64 splits over E and F together
+size_t split_rows_bytes(int B, int E, int F) {
+  const int KE = E / 16, KF = F / 16, nd = std::max(1, std::min(63, (int)((int64_t)64 * KE / (KE + KF))));
+  return (size_t)B * (std::max((KE + nd - 1) / nd, (KF + 63 - nd) / (64 - nd)) * 16 + 8) * 2;
+}
+
 int check_cfg(const sm_decode_cfg* c, const char* who) {
   if (!c) return fail(SM_ERR_INVALID_ARG, "%s: null configuration", who);
   if (c->dtype != SM_BF16) return fail(SM_ERR_UNSUPPORTED, "%s: bf16 only", who);
@@ -101,27 +107,18 @@ int check_cfg(const sm_decode_cfg* c, const char* who) {
   if (c->rot != 0 && c->rot != 32 && c->rot != 64) return fail(SM_ERR_SHAPE, "%s: rotary features must be 0, 32 or 64", who);
   if (c->L < 0 || c->cache_pitch < c->L) return fail(SM_ERR_SHAPE, "%s: the cache pitch must cover the cached tokens", who);
   if (decode_in_smem(c->B, c->E) > 160 * 1024) return fail(SM_ERR_SHAPE, "%s: B x E too large for the LDS token tile", who);
-  if (decode_out_smem(c->B, c->E, c->F, 64) > 48 * 1024) return fail(SM_ERR_SHAPE, "%s: B x (E + F) too large for the last kernel's LDS tile", who);
+  if (split_rows_bytes(c->B, c->E, c->F) > 48 * 1024) return fail(SM_ERR_SHAPE, "%s: B x (E + F) too large for a split's activation rows in LDS", who);
   return SM_OK;
 }
 
 size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 int attn_splits(const sm_decode_cfg& c) {
-  // about two workgroups per CU, each with at least two blocks of keys
+  // about one workgroup per CU, each with at least two blocks of keys
   const int bh = c.B * c.heads, block = decode_attn_block(c.E / c.heads), blocks = (c.L + 1 + block - 1) / block;
-  int s = (512 + bh - 1) / bh;
+  int s = (256 + bh - 1) / bh;
   s = std::min(s, std::max(1, blocks / 2));
   return std::max(1, std::min(s, 256));
 }
-int out_splits(const sm_decode_cfg& c) {
-  const int slices = c.E / 32, steps = (c.E + c.F) / 16;
-  int s = (256 + slices - 1) / slices;
-  s = std::min(s, std::max(1, steps / 32));          // at least 16 steps per wave
-  s = std::max(2, std::min(s, 64));                  // at least one split for each of the two matrices
-  while (s < 64 && decode_out_smem(c.B, c.E, c.F, s) > 48 * 1024) ++s;      // a split's activation rows must fit its LDS tile
-  return s;
-}
-
 struct Sizes { size_t qkv, hid, o, part_a, part_o, counters, small, total; };
 Sizes sizes(const sm_decode_cfg& c, int mode) {
   Sizes z;
@@ -130,8 +127,8 @@ Sizes sizes(const sm_decode_cfg& c, int mode) {
   z.hid = align256(B * c.F * 2);
   z.o = align256(B * E * 2);
   z.part_a = align256(B * h * attn_splits(c) * (d + 2) * sizeof(float));
-  z.part_o = align256((size_t)out_splits(c) * B * E * sizeof(float));
-  z.counters = align256((B * h + E / 32) * decode_counter_stride() * sizeof(int));
+  z.part_o = align256((size_t)decode_fc2_splits(c.B, c.E, c.F) * B * E * sizeof(float));
+  z.counters = align256(B * h * decode_counter_stride() * sizeof(int));
   z.small = mode == SM_EXPLICIT ? 5 * z.o : 0;       // q, new k, new v, unmerged output, spare
   z.total = z.qkv + z.hid + z.o + z.part_a + z.part_o + z.counters + z.small;
   return z;
@@ -187,7 +184,7 @@ extern "C" int sm_decode_step(const sm_decode_cfg* c, const sm_decode_weights* w
   a.ln2_g = (const unsigned short*)w->ln2_g; a.ln2_b = (const unsigned short*)w->ln2_b; a.eps = c->eps;
   a.wqkv_p_ = w->wqkv_p; a.w1_p_ = w->w1_p; a.bqkv = (const unsigned short*)w->bqkv; a.b1 = (const unsigned short*)w->b1;
   a.B = B; a.E = E; a.h = h; a.d = d; a.F = F; a.rot = c->rot; a.L = L; a.rope_base = c->rope_base;
-  a.hid = hid; a.counters = counters; a.n_counters = B * h + E / 32;
+  a.hid = hid; a.counters = counters; a.n_counters = B * h;
   // the fused Linear's result [B, h, 3, d] in its natural layout ...
   for (int t = 0; t < 3; ++t) { a.dst[t] = qkv + t * d; a.dst_b[t] = 3 * E; a.dst_h[t] = 3 * d; }
   if (el) {        // ... except that the new key / value rows go where the Concat would have put them
@@ -227,21 +224,23 @@ extern "C" int sm_decode_step(const sm_decode_cfg* c, const sm_decode_weights* w
     t.o = ou; t.o_b = E; t.o_h = d;
   }
   {
-    snprintf(label, sizeof(label), "decode_attention_bf16[%d,%d,%d,%d]", B, h, L + 1, d);
+    DecodeFc2Args f; std::memset(&f, 0, sizeof(f));
+    f.hid = hid; f.w2_p_ = w->w2_p; f.part = part_o; f.B = B; f.E = E; f.F = F; f.nf = decode_fc2_splits(B, E, F);
+    snprintf(label, sizeof(label), "decode_attention|fc2_bf16[%d,%d,%d,%d]+[%d,%d,%d]", B, h, L + 1, d, B, E, F);
     Timed tm(label, stream);
-    if (int e = launch_decode_attn(t, attn_splits(*c), stream)) return fail(SM_ERR_DEVICE, "sm_decode_step: attention launch failed (hip error %d)", e);
+    if (int e = launch_decode_mid(t, f, attn_splits(*c), stream)) return fail(SM_ERR_DEVICE, "sm_decode_step: attention launch failed (hip error %d)", e);
     count_compute();
   }
   if (!el) { if ((rc = copy_launch(plan->merge, tables, small + 3 * z.o, o_final, c->dtype, stream))) return rc; }
 
   DecodeOutArgs u; std::memset(&u, 0, sizeof(u));
-  u.o = o; u.hid = hid; u.x = (const unsigned short*)x; u.y = (unsigned short*)y;
-  u.wdense_p_ = w->wdense_p; u.w2_p_ = w->w2_p; u.bdense = (const unsigned short*)w->bdense; u.b2 = (const unsigned short*)w->b2;
-  u.part = part_o; u.counters = counters + (size_t)B * h * decode_counter_stride(); u.B = B; u.E = E; u.F = F;
+  u.o = o; u.x = (const unsigned short*)x; u.y = (unsigned short*)y;
+  u.wdense_p_ = w->wdense_p; u.bdense = (const unsigned short*)w->bdense; u.b2 = (const unsigned short*)w->b2;
+  u.part = part_o; u.nf = decode_fc2_splits(B, E, F); u.B = B; u.E = E;
   {
-    snprintf(label, sizeof(label), "decode_dense+fc2+res_bf16[%d,%d,%d]", B, E, E + F);
+    snprintf(label, sizeof(label), "decode_dense+sum+res_bf16[%d,%d,%d]", B, E, E);
     Timed tm(label, stream);
-    if (int e = launch_decode_out(u, out_splits(*c), stream)) return fail(SM_ERR_DEVICE, "sm_decode_step: last kernel launch failed (hip error %d)", e);
+    if (int e = launch_decode_out(u, stream)) return fail(SM_ERR_DEVICE, "sm_decode_step: last kernel launch failed (hip error %d)", e);
     count_compute();
   }
   return SM_OK;

@@ -142,7 +142,7 @@ struct DecodeInArgs {
   int B, E, h, d, F, rot, L; float rope_base;   // L: position of the new token (= number of cached tokens)
   unsigned short* dst[3]; int64_t dst_b[3], dst_h[3];   // feature e of head hh of token b of q / k / v goes to dst[t][b * dst_b[t] + hh * dst_h[t] + e]
   unsigned short* hid;                          // [B, F]
-  int* counters; int n_counters;                // zeroed here for the two kernels that follow
+  int* counters; int n_counters;                // zeroed here for the attention
 };
 struct DecodeAttnArgs {
   const unsigned short* q; int64_t q_b, q_h;    // query row of (b, hh) at q[b * q_b + hh * q_h]
@@ -151,17 +151,22 @@ struct DecodeAttnArgs {
   float* part; int* counters;                   // [B * h][splits][d + 2] floats; one counter per (b, hh), zero on entry
   int B, h, d, n_keys; float scale_log2e;
 };
+struct DecodeFc2Args {
+  const unsigned short* hid; const void* w2_p_; // [B, F], packed [E, F]
+  float* part;                                  // [nf][B][E]: sums over a split of F each
+  int B, E, F, nf;
+};
 struct DecodeOutArgs {
-  const unsigned short *o, *hid, *x; unsigned short* y;   // [B, E], [B, F], [B, E], [B, E]
-  const void *wdense_p_, *w2_p_; const unsigned short *bdense, *b2;
-  float* part; int* counters;                   // [splits][B][E] floats; one counter per 32 output features, zero on entry
-  int B, E, F;
-  int n_dense, per_max;                         // set by the launcher: K splits given to Wdense, most steps of any split
+  const unsigned short *o, *x; unsigned short* y;       // [B, E] each
+  const void* wdense_p_; const unsigned short *bdense, *b2;
+  const float* part; int nf;                    // of DecodeFc2Args
+  int B, E;
 };
 size_t decode_in_smem(int B, int E);
 int launch_decode_in(const DecodeInArgs& a, void* stream);
-int launch_decode_attn(const DecodeAttnArgs& a, int nsplit, void* stream);
-int launch_decode_out(const DecodeOutArgs& a, int nks, void* stream);
+int decode_fc2_splits(int B, int E, int F);
+int launch_decode_mid(const DecodeAttnArgs& a, const DecodeFc2Args& f, int nsplit, void* stream);      // attention and W2 . hid
+int launch_decode_out(const DecodeOutArgs& a, void* stream);
 // out [BH, L + 1, d] = Concat(cache [BH rows of pitch cache_bh_elems][L, d], fresh [BH, d]) along the token axis
 int launch_decode_concat(const void* cache, int64_t cache_bh_elems, const void* fresh, void* out, int BH, int L, int d, void* stream);
 

@@ -60,6 +60,17 @@ def test_decode_step_matches_the_oracle(B, E, h, L, F, rot, mode):
     run_case(B, E, h, L, F, rot, mode, seed=B + L, std=0.1)
 
 
+@pytest.mark.parametrize("B,E,h,L,F,rot", [
+    (2, 256, 1, 63, 8192, 64),      # W2 in eight splits, more than the last kernel asks for early; one block of keys, whole
+    (32, 1024, 8, 64, 1024, 32),    # activation rows of more pieces than wait in registers; one key more than a block
+    (1, 1088, 17, 127, 64, 32),     # K of no whole set of fragments in the first and last kernel; W2 of four steps: waves without any
+    (1, 256, 1, 255, 128, 64),      # four blocks of keys in two workgroups ...
+    (1, 256, 1, 256, 128, 64),      # ... and the first key of a fifth
+])
+def test_edges_of_the_splits(B, E, h, L, F, rot):
+    run_case(B, E, h, L, F, rot, sm.SM_ELIDED, seed=B + L, std=0.1)
+
+
 def test_modes_agree_and_cache_room_is_respected():
     y0, k0, v0 = run_case(4, 256, 2, 200, 512, 64, sm.SM_ELIDED, seed=11, std=0.1, pitch=260)
     y1, k1, v1 = run_case(4, 256, 2, 200, 512, 64, sm.SM_EXPLICIT, seed=11, std=0.1, pitch=260)
