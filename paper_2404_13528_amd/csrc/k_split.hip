@@ -35,6 +35,7 @@ namespace sm {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 sp_bf16x8;
 typedef float sp_f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned int sp_u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int sp_u32x2 __attribute__((ext_vector_type(2)));
 
 #define SP_GPTR(p) ((const __attribute__((address_space(1))) void*)(p))
 #define SP_LPTR(p) ((__attribute__((address_space(3))) void*)(p))
@@ -52,6 +53,44 @@ template <typename T> __device__ __forceinline__ void sp_unpack(sp_u32x4 v, floa
     for (int e = 0; e < 4; ++e) f[e] = __uint_as_float(v[e]);
   }
 }
+// CV adjacent elements as the words they take: to and from memory, and floats
+template <typename T, int CV> struct SpRun {
+  static constexpr int NWORD = CV * (int)sizeof(T) / 4, NV = NWORD / 4;      // words; 16-byte pieces of them
+  unsigned w[NWORD];
+  __device__ __forceinline__ void load(const T* p) {
+    if constexpr (NV > 0) {
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const sp_u32x4 q = ((const sp_u32x4*)p)[i];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[4 * i + e] = q[e];
+      }
+    } else if constexpr (NWORD == 2) { const sp_u32x2 q = *(const sp_u32x2*)p; w[0] = q[0]; w[1] = q[1]; }
+    else w[0] = *(const unsigned*)p;
+  }
+  __device__ __forceinline__ void store(T* p) const {
+    if constexpr (NV > 0) {
+#pragma unroll
+      for (int i = 0; i < NV; ++i) ((sp_u32x4*)p)[i] = sp_u32x4{w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]};
+    } else if constexpr (NWORD == 2) *(sp_u32x2*)p = sp_u32x2{w[0], w[1]};
+    else *(unsigned*)p = w[0];
+  }
+  __device__ __forceinline__ float get(int e) const {
+    if constexpr (sizeof(T) == 2) return __uint_as_float(e & 1 ? w[e / 2] & 0xffff0000u : w[e / 2] << 16);
+    else return __uint_as_float(w[e]);
+  }
+  __device__ __forceinline__ void pack(const float* f) {
+#pragma unroll
+    for (int i = 0; i < NWORD; ++i) {
+      if constexpr (sizeof(T) == 2) {
+        typedef float f32x2 __attribute__((ext_vector_type(2)));
+        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+        const f32x2 q = {f[2 * i], f[2 * i + 1]};
+        w[i] = __builtin_bit_cast(unsigned, __builtin_convertvector(q, bf16x2));
+      } else w[i] = __float_as_uint(f[i]);
+    }
+  }
+};
 template <typename T> __device__ __forceinline__ sp_u32x4 sp_pack(const float* f) {
   if constexpr (sizeof(T) == 2) return pack8(f);
   sp_u32x4 o;
@@ -79,7 +118,21 @@ __device__ __forceinline__ void split_norm(unsigned a_at, unsigned g_at, int nkt
   sp_u32x4 v[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) v[t] = lds_read16(row + min(t * TPT + t1, nkt - 1) * BM * 128);
-  wait_lds();
+  // gamma and beta: all on their way behind the row where it is short, else two pieces at a time where they are used
+  constexpr int NG = NT <= 4 ? NT : 2;
+  sp_u32x4 gv[NG], bv[NG];
+  auto norm_load = [&](int u0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < NG; ++u) {
+      const unsigned gc = min(c0 + (u0 + u) * 8 * TPT, K / VEC - 1);
+      gv[u] = lds_read16(g_at + gc * 16);
+      bv[u] = lds_read16(g_at + (K / VEC + gc) * 16);
+    }
+  };
+  if constexpr (NG == NT) {
+    norm_load(0);
+    asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(2 * NT) : "memory");      // (LDS reads return in order)
+  } else wait_lds();
   // the row stays in fp32 registers between the passes where there is room (unpacked again for each, the norm of 32 x 512 took 2.0 us
   // of a task)
   constexpr bool HELD = NT * VEC <= 64;
@@ -112,18 +165,12 @@ __device__ __forceinline__ void split_norm(unsigned a_at, unsigned g_at, int nkt
   }
   const float rstd = rsqrtf(lane_group_sum<TPR>(sq) / (float)K + eps);
 #pragma unroll
-  for (int u0 = 0; u0 < NT; u0 += 2) {
+  for (int u0 = 0; u0 < NT; u0 += NG) {
     if (u0 * TPT >= nkt) break;
-    sp_u32x4 gv[2], bv[2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const unsigned gc = min(c0 + (u0 + u) * 8 * TPT, K / VEC - 1);
-      gv[u] = lds_read16(g_at + gc * 16);
-      bv[u] = lds_read16(g_at + (K / VEC + gc) * 16);
-    }
+    if constexpr (NG != NT) norm_load(u0);
     wait_lds();
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
+    for (int u = 0; u < NG; ++u) {
       asm volatile("" : "+v"(gv[u]), "+v"(bv[u]));
       const int kt = (u0 + u) * TPT + t1;
       float* f = values(u0 + u, false);
@@ -149,7 +196,9 @@ __device__ __forceinline__ void split_task(const SM_KARG LinPhase* p, int M, int
   constexpr int VEC = Elem<T>::VEC, TILE = 8 * VEC, BM = 32 * MI, BN = 32 * WN, WK = NW / WN;
   constexpr int KS = 4 / MI, NS = 4;
   constexpr int EP = BN + 4;                               // pitch of the fp32 result tile
-  constexpr int OPR = BN / 8, NOUT = BM * OPR, NPASS = (NOUT + NTHR - 1) / NTHR;      // a thread finishes 8 columns of a row per pass
+  // a thread finishes CV columns of a row: two, four or eight, so that all of them work (with eight for every tile, a quarter of them
+  // did in a 32 x 32 one; with that and gamma and beta read ahead in the norm a net on one image takes 857 us instead of 884)
+  constexpr int CV = BM * BN / NTHR, OPR = BN / CV;
   const int N = p->N, K = p->K;
   const int nkt = (K + TILE - 1) / TILE;
   const int nst = RING ? (nkt + KS - 1) / KS : 0;
@@ -196,18 +245,10 @@ __device__ __forceinline__ void split_task(const SM_KARG LinPhase* p, int M, int
   // that waiting for it is not waiting for them
   const int32_t* ot = p->o_tab ? p->o_tab : (const int32_t*)p->W;
   const int32_t* rt = p->r_tab ? p->r_tab : (const int32_t*)p->W;
-  int oraw[NPASS], rraw[NPASS];
-  sp_u32x4 braw[NPASS][VEC == 4 ? 2 : 1];
-#pragma unroll
-  for (int q = 0; q < NPASS; ++q) {
-    const int o = tid + q * NTHR, r = row0 + o / OPR, c = n0 + (o % OPR) * 8;
-    const int gr = min(r, M - 1), gc = min(c, N - 8);
-    oraw[q] = ot[p->o_tab ? gr : 0];
-    rraw[q] = rt[p->r_tab ? gr : 0];
-    const T* bp = p->bias ? (const T*)p->bias + gc : (const T*)p->W;      // (no bias: any valid words, not used)
-    braw[q][0] = *(const sp_u32x4*)bp;
-    if constexpr (VEC == 4) braw[q][1] = *(const sp_u32x4*)(bp + 4);
-  }
+  const int orow = row0 + tid / OPR, ocol = n0 + (tid % OPR) * CV, og = min(orow, M - 1), oc = min(ocol, N - CV);
+  const int oraw = ot[p->o_tab ? og : 0], rraw = rt[p->r_tab ? og : 0];
+  SpRun<T, CV> bias;
+  bias.load(p->bias ? (const T*)p->bias + oc : (const T*)p->W);      // (no bias: any valid words, not used)
 
   if (LN && !keep) {
     const int nch = K / VEC;
@@ -232,18 +273,11 @@ __device__ __forceinline__ void split_task(const SM_KARG LinPhase* p, int M, int
     asm volatile("buffer_inv sc0" ::: "memory");           // their results are in this XCD's L2: drop what this CU's L1 holds
   }
   asrc = A + (p->a_tab ? (int64_t)araw * p->a_mul : (int64_t)agr * p->a_ld);
-  sp_u32x4 res[NPASS][VEC == 4 ? 2 : 1];
+  SpRun<T, CV> res;
+  if (p->res) res.load((const T*)p->res + (p->r_tab ? (int64_t)rraw : (int64_t)og * p->r_ld) + oc);
+  else {
 #pragma unroll
-  for (int q = 0; q < NPASS; ++q) {
-    if (p->res) {
-      const int o = tid + q * NTHR, gr = min(row0 + o / OPR, M - 1), gc = min(n0 + (o % OPR) * 8, N - 8);
-      const T* rsrc = (const T*)p->res + (p->r_tab ? (int64_t)rraw[q] : (int64_t)gr * p->r_ld) + gc;
-      res[q][0] = *(const sp_u32x4*)rsrc;
-      if constexpr (VEC == 4) res[q][1] = *(const sp_u32x4*)(rsrc + 4);
-    } else {
-      res[q][0] = sp_u32x4{0u, 0u, 0u, 0u};
-      if constexpr (VEC == 4) res[q][1] = sp_u32x4{0u, 0u, 0u, 0u};
-    }
+    for (int i = 0; i < SpRun<T, CV>::NWORD; ++i) res.w[i] = 0u;
   }
   sp_f32x16 acc[MI];
 #pragma unroll
@@ -339,46 +373,42 @@ __device__ __forceinline__ void split_task(const SM_KARG LinPhase* p, int M, int
       lds_write16(r_at + (((wk * BM + mi * 32 + l32) * EP) + wn * 32 + g4 * 8 + hf * 4) * 4,
                   sp_u32x4{__float_as_uint(acc[mi][4 * g4]), __float_as_uint(acc[mi][4 * g4 + 1]), __float_as_uint(acc[mi][4 * g4 + 2]), __float_as_uint(acc[mi][4 * g4 + 3])});
   wg_barrier();
+  // the thread's columns of the WK sums, in their order
+  constexpr int PW = CV < 4 ? CV : 4;                      // words per read
+  typedef unsigned int Part __attribute__((ext_vector_type(PW)));
+  Part part[WK][CV / PW];
 #pragma unroll
-  for (int q = 0; q < NPASS; ++q) {
-    const int o = min(tid + q * NTHR, NOUT - 1);
-    sp_u32x4 part[WK][2];
+  for (int w = 0; w < WK; ++w)
 #pragma unroll
-    for (int w = 0; w < WK; ++w)
-#pragma unroll
-      for (int e = 0; e < 2; ++e) part[w][e] = lds_read16(r_at + ((w * BM + o / OPR) * EP + (o % OPR) * 8 + e * 4) * 4);
-    wait_lds();
-    float v[8];
-#pragma unroll
-    for (int w = 0; w < WK; ++w)
-#pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        asm volatile("" : "+v"(part[w][e]));
-#pragma unroll
-        for (int x = 0; x < 4; ++x) v[e * 4 + x] = (w ? v[e * 4 + x] : 0.f) + __uint_as_float(part[w][e][x]);
-      }
-    if (p->bias) {
-      float bf[8];
-      sp_unpack<T>(braw[q][0], bf);
-      if constexpr (VEC == 4) sp_unpack<T>(braw[q][1], bf + 4);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] += bf[e];
+    for (int e = 0; e < CV / PW; ++e) {
+      const unsigned at = r_at + ((w * BM + tid / OPR) * EP + (tid % OPR) * CV + e * PW) * 4;
+      if constexpr (PW == 4) asm volatile("ds_read_b128 %0, %1" : "=v"(part[w][e]) : "v"(at) : "memory");
+      else asm volatile("ds_read_b64 %0, %1" : "=v"(part[w][e]) : "v"(at) : "memory");
     }
-    if (p->act == SM_ACT_GELU) {
+  wait_lds();
+  float v[CV];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = sizeof(T) == 2 ? gelu_poly(v[e]) : gelu_erf(v[e]);
-    }
-    float rf[8];
-    sp_unpack<T>(res[q][0], rf);
-    if constexpr (VEC == 4) sp_unpack<T>(res[q][1], rf + 4);
+  for (int w = 0; w < WK; ++w)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] += rf[e];
-    const int oo = tid + q * NTHR, r = row0 + oo / OPR, c = n0 + (oo % OPR) * 8;
-    if (oo < NOUT && r < M && c < N) {
-      T* dst = (T*)p->out + (p->o_tab ? (int64_t)oraw[q] * p->o_mul : (int64_t)r * p->o_ld) + c;
-      *(sp_u32x4*)dst = sp_pack<T>(v);
-      if constexpr (VEC == 4) *(sp_u32x4*)(dst + 4) = sp_pack<T>(v + 4);
+    for (int e = 0; e < CV / PW; ++e) {
+      asm volatile("" : "+v"(part[w][e]));
+#pragma unroll
+      for (int x = 0; x < PW; ++x) v[e * PW + x] = (w ? v[e * PW + x] : 0.f) + __uint_as_float(part[w][e][x]);
     }
+  if (p->bias) {
+#pragma unroll
+    for (int e = 0; e < CV; ++e) v[e] += bias.get(e);
+  }
+  if (p->act == SM_ACT_GELU) {
+#pragma unroll
+    for (int e = 0; e < CV; ++e) v[e] = sizeof(T) == 2 ? gelu_poly(v[e]) : gelu_erf(v[e]);
+  }
+#pragma unroll
+  for (int e = 0; e < CV; ++e) v[e] += res.get(e);
+  if (orow < M && ocol < N) {
+    SpRun<T, CV> out;
+    out.pack(v);
+    out.store((T*)p->out + (p->o_tab ? (int64_t)oraw * p->o_mul : (int64_t)orow * p->o_ld) + ocol);
   }
   if constexpr (CHAIN) { wait_mem(); wg_barrier();}
 }
