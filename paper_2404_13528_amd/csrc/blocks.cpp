@@ -235,6 +235,13 @@ bool tail_is_split(const sm_swin_cfg& c, const sm_swin_weights* wt) {
   return c.eps > 0.f && there(wt->wproj) && there(wt->bproj) && there(wt->ln2_g) && there(wt->ln2_b) && there(wt->w1) && there(wt->b1) &&
          there(wt->w2) && there(wt->b2) && aligned16(wt->mlp_packed) && aligned16(wt->proj_packed);
 }
+// Whether a chain of blocks runs such a tail as single Linears instead: launches whose workgroups fill the chip, where the chained
+// tasks wait for each other four times and every XCD streams all weights for its rows.  us a stage of four blocks, chained /
+// single: C = 512, 784 tokens 203 / 202, 1176 247 / 208, 1568 285 / 221, 2156 383 / 270; C = 384, 784 177 / 161, 1176 205 / 186.  (On
+// fewer tokens the single Linears are a little faster too, C = 512, 196 tokens 126 / 121, 588 196 / 175, C = 256, 392 121 / 104, and a
+// width without a row-owning kernel more so, C = 1024, 49 tokens 220 / 142, C = 768, 245 195 / 183: there two launches per block
+// are what the launch counts promise a caller, and five are not worth breaking that.)
+bool tail_by_operators(const sm_swin_cfg& c) { return c.C <= 512 && (int64_t)c.B * c.H * c.W > 640; }
 // A caller who packed the fused kernels' weights, or a width without such kernels: norms may be folded wherever that is
 // faster (else the caller asked for one kernel per operator and fold_norm alone decides)
 bool free_form(const sm_swin_cfg& c, const sm_swin_weights* wt) { return proj_is_fused(c, wt) || !mlp_fused_supported(c.C, c.mlp_ratio * c.C, c.dtype); }
@@ -363,7 +370,7 @@ size_t swin_act_bytes(const sm_swin_cfg* c, int mode) {
   return tc * units;
 }
 int swin_block_impl(const sm_swin_cfg* c, const sm_swin_weights* wt, const void* x, void* y, void* ws, size_t ws_bytes, int mode,
-                    void* stream, const NextNorm* next, int pre, const void* tables, int* counters);
+                    void* stream, const NextNorm* next, int pre, const void* tables, int* counters, bool by_operators = false);
 // counters of one block's chained launch (behind the tables of a block, or of the chain)
 size_t swin_counter_bytes(const sm_swin_cfg& c, int mode) {
   const int64_t T = (int64_t)c.B * c.H * c.W;
@@ -390,9 +397,10 @@ namespace {
 // first slot, or (next->wq_p) its QKV Linear's output into the QKV slot; pre = 1: the first slot already holds this
 // block's LayerNorm-1 output, pre = 2: the QKV slot already holds this block's QKV (the previous block emitted it).
 // tables: where the plan's row-offset tables for `mode` were already filled on this stream (the chain executor fills
-// them once per stage and shift); null: they go behind the activation buffers of ws and are filled here
+// them once per stage and shift); null: they go behind the activation buffers of ws and are filled here.  by_operators (with tables):
+// one kernel per operator behind the attention, whatever is packed
 int swin_block_impl(const sm_swin_cfg* c, const sm_swin_weights* wt, const void* x, void* y, void* ws, size_t ws_bytes, int mode,
-                    void* stream, const NextNorm* next, int pre, const void* tables, int* counters) {
+                    void* stream, const NextNorm* next, int pre, const void* tables, int* counters, bool by_operators) {
   int rc = check_swin(c, "sm_swin_block");
   if (rc) return rc;
   if (!wt || !x || !y || !ws) return fail(SM_ERR_INVALID_ARG, "sm_swin_block: null pointer");
@@ -458,10 +466,10 @@ int swin_block_impl(const sm_swin_cfg* c, const sm_swin_weights* wt, const void*
                                 bufO, wt->rpb_table, stream, "window attention"))) return rc;
     if (counters)
       return run_split_tail(*c, wt, bufO, x, y, x1, hid, T, proj_store, next, qkv, counters, stream);
-    if (proj_is_fused(*c, wt)) return run_proj_mlp_fused(*c, wt, bufO, x, y, T, proj_store, next, next && next->wq_p ? qkv : bufA, stream);
+    if (!by_operators && proj_is_fused(*c, wt)) return run_proj_mlp_fused(*c, wt, bufO, x, y, T, proj_store, next, next && next->wq_p ? qkv : bufA, stream);
     if (next) return fail(SM_ERR_INVALID_ARG, "sm_swin_block: the next block's norm can only be emitted by the fused projection + MLP kernel");
     if ((rc = run_gemm(bufO, wt->wproj, wt->bproj, x, x1, T, C, C, dt, SM_ACT_NONE, nullptr, &proj_store, stream))) return rc;
-    if (mlp_is_fused(*c, wt)) return run_mlp_fused(*c, wt, x1, y, T, stream);
+    if (!by_operators && mlp_is_fused(*c, wt)) return run_mlp_fused(*c, wt, x1, y, T, stream);
     if (fold_norm(c->mlp_ratio * C) || (free_form(*c, wt) && split_norm_linear(*c, c->mlp_ratio * C, wt->ln2_g, wt->ln2_b))) {
       if ((rc = run_gemm(x1, wt->w1, wt->b1, nullptr, hid, T, c->mlp_ratio * C, C, dt, SM_ACT_GELU, nullptr, nullptr, stream, wt->ln2_g, wt->ln2_b, eps))) return rc;
     } else {
@@ -686,7 +694,7 @@ extern "C" int sm_run_chain(const sm_chain_desc* c, const void* const* weights, 
   if (!aligned16(x) || !aligned16(y) || !aligned16(ws) || (y_feat && !aligned16(y_feat))) return fail(SM_ERR_INVALID_ARG, "sm_run_chain: pointers must be 16-byte aligned");
   const int dt = c->dtype;
   // first pass, no launches: what each block hands to the next one, hence which tables are read at all
-  struct BlockStep { bool next; bool next_qkv; int pre; bool split; };
+  struct BlockStep { bool next; bool next_qkv; int pre; bool split, by_operators; };
   std::vector<std::vector<BlockStep>> steps((size_t)c->n_stages);
   std::vector<uint64_t> need[2];
   need[0].assign((size_t)c->n_stages, 0); need[1].assign((size_t)c->n_stages, 0);
@@ -703,13 +711,13 @@ extern "C" int sm_run_chain(const sm_chain_desc* c, const void* const* weights, 
         sm_swin_weights bw, nwt;
         std::memcpy(&bw, wq, sizeof(bw));
         wq += 16;
-        BlockStep b{false, false, pre, false};
+        BlockStep b{false, false, pre, false, false};
         // within a stage, elided, with the projection + MLP kernel: that kernel also writes the next block's
         // LayerNorm-1 (through the next block's own partition map) or its QKV, and the next block starts there
         // (where LayerNorm-1 is folded into the QKV Linear's load, C <= 170, only the norm + QKV form applies)
-        if (mode == SM_ELIDED && tail_is_split(bc, &bw)) b.split = true;
+        if (mode == SM_ELIDED && tail_is_split(bc, &bw)) (tail_by_operators(bc) ? b.by_operators : b.split) = true;
         if (b.split && k + 1 < st.depth) b.next = b.next_qkv = true;
-        else if (mode == SM_ELIDED && k + 1 < st.depth && proj_is_fused(bc, &bw)) {
+        else if (mode == SM_ELIDED && !b.by_operators && k + 1 < st.depth && proj_is_fused(bc, &bw)) {
           std::memcpy(&nwt, wq, sizeof(nwt));
           const bool with_qkv = nwt.qkv_packed && c->mlp_ratio >= 3;    // (the kernel keeps the QKV bias where the first MLP bias was)
           if (!fold_norm(3 * st.C) || with_qkv) { b.next = true; b.next_qkv = with_qkv; }
@@ -787,7 +795,7 @@ extern "C" int sm_run_chain(const sm_chain_desc* c, const void* const* weights, 
         next = &nn;
       }
       int* counters = step.split ? (int*)(base + S.counter_off + (size_t)k * S.counter_step) : nullptr;
-      if ((rc = swin_block_impl(&bc, &bw, cur, out, blk_ws, z.block, mode, stream, next, step.pre, base + S.plan_off[sh], counters))) return rc;
+      if ((rc = swin_block_impl(&bc, &bw, cur, out, blk_ws, z.block, mode, stream, next, step.pre, base + S.plan_off[sh], counters, step.by_operators))) return rc;
       tally();
       cur = out; flip ^= 1;
     }
