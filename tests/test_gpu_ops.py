@@ -48,6 +48,18 @@ def test_layernorm_store_through_window_map(dtype, s):
 
 
 @pytest.mark.parametrize("dtype", DT)
+@pytest.mark.parametrize("B,C,H,W,G", [(1, 32, 40, 33, 1), (8, 16, 41, 50, 2), (1, 16, 64, 80, 2)])
+def test_groupnorm_in_two_kernels_at_their_edges(dtype, B, C, H, W, G):
+    """A group of more vectors than a thread holds (5280 in bf16: read again for the variance) and of exactly as many (5120);
+    264 workgroups of 64 tokens, the last of an image ragged (below 256 they take 32)."""
+    x = draw((B, C, H, W), 17, dtype, 2.0, -0.5)
+    g, b = draw((C,), 18, dtype, 0.2, 1.0), draw((C,), 19, dtype, 0.2)
+    y = sm.groupnorm(dev(x, dtype), dev(g, dtype), dev(b, dtype), G, tokens_out=True, split=True)
+    want = V.apply_chain(O.group_norm_nchw(to_np(x), G, to_np(g), to_np(b)), V.nchw_to_tokens_chain(B, C, H, W))
+    assert_close(y, want, dtype, "groupnorm", 4.0)
+
+
+@pytest.mark.parametrize("dtype", DT)
 @pytest.mark.parametrize("tokens_out", [False, True])
 @pytest.mark.parametrize("split", [False, True])
 @pytest.mark.parametrize("B,C,H,W,G", [(2, 64, 9, 7, 8), (2, 320, 8, 12, 32), (1, 40, 16, 13, 4)])
