@@ -236,12 +236,13 @@ bool tail_is_split(const sm_swin_cfg& c, const sm_swin_weights* wt) {
          there(wt->w2) && there(wt->b2) && aligned16(wt->mlp_packed) && aligned16(wt->proj_packed);
 }
 // Whether a chain of blocks runs such a tail as single Linears instead: launches whose workgroups fill the chip, where the chained
-// tasks wait for each other four times and every XCD streams all weights for its rows.  us a stage of four blocks, chained /
-// single: C = 512, 784 tokens 203 / 202, 1176 247 / 208, 1568 285 / 221, 2156 383 / 270; C = 384, 784 177 / 161, 1176 205 / 186.  (On
-// fewer tokens the single Linears are a little faster too, C = 512, 196 tokens 126 / 121, 588 196 / 175, C = 256, 392 121 / 104, and a
-// width without a row-owning kernel more so, C = 1024, 49 tokens 220 / 142, C = 768, 245 195 / 183: there two launches per block
-// are what the launch counts promise a caller, and five are not worth breaking that.)
-bool tail_by_operators(const sm_swin_cfg& c) { return c.C <= 512 && (int64_t)c.B * c.H * c.W > 640; }
+// tasks wait for each other four times and every XCD streams all weights for its rows.  From three row tiles of 64 on an XCD on: us a
+// stage of four blocks, chained / single: C = 512, 784 tokens 203 / 202, 1176 247 / 208, 1568 285 / 221, 2156 383 / 270; C = 384, 784
+// 177 / 161, 980 183 / 183 (a net with six such blocks 659 / 667), 1176 205 / 186.  (On fewer tokens the single Linears are often
+// a little faster too, C = 512, 196 tokens 126 / 121, 588 196 / 175, C = 256, 392 121 / 104, and at a width without a row-owning
+// kernel more so, C = 1024, 49 tokens 220 / 142, C = 768, 245 195 / 183: there two launches per block are what the launch counts
+// promise a caller.)
+bool tail_by_operators(const sm_swin_cfg& c) { return c.C <= 512 && (int64_t)c.B * c.H * c.W > 1024; }
 // A caller who packed the fused kernels' weights, or a width without such kernels: norms may be folded wherever that is
 // faster (else the caller asked for one kernel per operator and fold_norm alone decides)
 bool free_form(const sm_swin_cfg& c, const sm_swin_weights* wt) { return proj_is_fused(c, wt) || !mlp_fused_supported(c.C, c.mlp_ratio * c.C, c.dtype); }

@@ -342,3 +342,15 @@ def test_long_k_tiles(M, N, K, act):
     want = torch.nn.functional.silu(z[:, :N // 2]) * z[:, N // 2:] if act == "swiglu" else z
     got = sm.linear(A.cuda(), W.cuda(), None, act=act).float()
     assert (got - want).norm().item() <= 4e-3 * want.norm().item()      # bf16 result: relative rounding 2^-9, fp32 sums
+
+
+@pytest.mark.parametrize("B,C,single", [(20, 384, False), (21, 384, True), (21, 512, True)])
+def test_chains_of_more_than_two_row_tiles_per_xcd_run_single_linears(B, C, single):
+    """980 and 1029 tokens, 21 windows: the last tiles of 64 rows are cut."""
+    h = C // 32
+    x, blocks = Wl.swin_stage_case(B, 7, 7, C, h, 7, 2, seed=B)
+    chain = sm.SwinChain(B, [(C, h, 2, 7, 7)], 7, {"stages": [[dev_params(p, torch.bfloat16) for p in blocks]]}, torch.bfloat16)
+    got, xd = [], dev(x, torch.bfloat16)
+    labels = _labels(lambda: got.append(chain(xd)))
+    assert any(l.startswith("split_proj+ln+mlp") for l in labels) != single and any("mlp_bf16" in l for l in labels) != single, labels
+    assert_bf16_close(got[0], swin.swin_stage(to_np(x), [np_params(p) for p in blocks], 7, 7, 7, h), "stage", x=to_np(x))
