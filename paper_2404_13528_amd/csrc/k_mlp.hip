@@ -783,7 +783,8 @@ __global__ __launch_bounds__(C, (C >= 384 ? 1 : 2)) void mlp64p_kernel(MlpArgs g
   // the ring (about 2000 clocks ahead) does not cover memory.  So the workgroups of an XCD bring every chunk of the stream (Wproj;
   // a round of W1 and W2; a third of the QKV weight: 2 C^2 bytes each) into its L2 two to three rounds ahead, a word of every
   // 128-byte line, two lines a lane.  Workgroups behind the first 256 find what those have brought (C = 256: all of it fits).
-  // 12544 tokens of C = 512 in a net of 24 blocks: 95 -> 76 us, every MFMA phase as fast as with warm caches.
+  // 12544 tokens of C = 512 in a net of 24 blocks, mean of its 17 launches: 110.7 -> 93.9 us, every MFMA phase in as many clocks as with
+  // warm caches.
   constexpr int CHUNK_LOADS = C * C * 2 / 8192;         // of 64 lines
   const int pf_waves = ((min((int)gridDim.x, 256) + 7) >> 3) * NW, pf_wave = blockIdx.x < 256 ? (int)(blockIdx.x >> 3) * NW + w : CHUNK_LOADS;
   unsigned pf[2] = {0u, 0u};
