@@ -39,6 +39,7 @@ typedef unsigned int sp_u32x2 __attribute__((ext_vector_type(2)));
 
 #define SP_GPTR(p) ((const __attribute__((address_space(1))) void*)(p))
 #define SP_LPTR(p) ((__attribute__((address_space(3))) void*)(p))
+#define SP_LDS16(at) ((const __attribute__((address_space(3))) sp_u32x4*)(uintptr_t)(at))
 
 // LDS accesses as assembly: next to outstanding LDS-DMA loads the compiler would wait for all of them first
 __device__ __forceinline__ void lds_write16(unsigned addr, sp_u32x4 v) { asm volatile("ds_write_b128 %0, %1" ::"v"(addr), "v"(v) : "memory"); }
@@ -118,21 +119,24 @@ __device__ __forceinline__ void split_norm(unsigned a_at, unsigned g_at, int nkt
   sp_u32x4 v[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) v[t] = lds_read16(row + min(t * TPT + t1, nkt - 1) * BM * 128);
-  // gamma and beta: all on their way behind the row where it is short, else two pieces at a time where they are used
+  wait_lds();
+  // gamma and beta: all on their way under the statistics where the row is short, else two pieces at a time where they are used.
+  // Loads that the compiler sees (no LDS-DMA is outstanding here, for which it would wait): it may move or keep such a register across
+  // the statistics as it likes, and waits before the first use of one
   constexpr int NG = NT <= 4 ? NT : 2;
   sp_u32x4 gv[NG], bv[NG];
   auto norm_load = [&](int u0) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < NG; ++u) {
       const unsigned gc = min(c0 + (u0 + u) * 8 * TPT, K / VEC - 1);
-      gv[u] = lds_read16(g_at + gc * 16);
-      bv[u] = lds_read16(g_at + (K / VEC + gc) * 16);
+      gv[u] = *SP_LDS16(g_at + gc * 16);
+      bv[u] = *SP_LDS16(g_at + (K / VEC + gc) * 16);
     }
   };
   if constexpr (NG == NT) {
     norm_load(0);
-    asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(2 * NT) : "memory");      // (LDS reads return in order)
-  } else wait_lds();
+    __builtin_amdgcn_sched_barrier(0);
+  }
   // the row stays in fp32 registers between the passes where there is room (unpacked again for each, the norm of 32 x 512 took 2.0 us
   // of a task)
   constexpr bool HELD = NT * VEC <= 64;
@@ -168,10 +172,8 @@ __device__ __forceinline__ void split_norm(unsigned a_at, unsigned g_at, int nkt
   for (int u0 = 0; u0 < NT; u0 += NG) {
     if (u0 * TPT >= nkt) break;
     if constexpr (NG != NT) norm_load(u0);
-    wait_lds();
 #pragma unroll
     for (int u = 0; u < NG; ++u) {
-      asm volatile("" : "+v"(gv[u]), "+v"(bv[u]));
       const int kt = (u0 + u) * TPT + t1;
       float* f = values(u0 + u, false);
       float g8[8], b8[8];

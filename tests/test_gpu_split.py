@@ -20,6 +20,8 @@ pytestmark = pytest.mark.gpu
     (196, 512, 2048, False, "none", True),       # ring, four and more stages
     (500, 520, 320, True, "none", True),         # 64-row tiles, both ends cut
     (97, 128, 384, True, "none", True),
+    (33, 64, 512, True, "none", False),          # bf16: the longest row whose gamma and beta travel under its statistics,
+    (33, 64, 528, True, "gelu", True),           # and the next, which asks for them piece by piece
     (257, 4104, 2064, False, "none", True),      # more 64-row tiles than CUs, a long K, all ends cut
 ])
 def test_split_linear(M, N, K, norm, act, res, dtype):
