@@ -314,7 +314,11 @@ __global__ __launch_bounds__(512) void groupnorm_kernel(GroupNormArgs a) {
 // ---- GroupNorm in two kernels (the caller provides scratch for the statistics): every CU takes part, all
 // global accesses are 16-byte vectors, and the token-major store goes through an LDS transpose so that it writes
 // whole token rows.
-template <typename T>
+// NR vectors a thread are requested together (one at a time, each waits for memory); a group that they cover is not read again for
+// the second pass.  NR follows from the group (gn_batch), because requests past its end are not free.  64 groups in bf16, us, one at a time /
+// ten together / as dealt here: 80 vectors a group 3.5 / 4.2 / 3.4 (two), 2880 6.0 / 4.9 / 4.4 (six), 5120 7.9 / 5.2 / 5.2 (ten),
+// 5280 8.6 / 6.6 / 5.5 (twelve), 10240 13.0 / 7.4 / 7.6 (twice ten)
+template <typename T, int NR>
 __global__ __launch_bounds__(512) void gn_stats_kernel(GroupNormArgs a) {
   __shared__ float red[8];
   constexpr int VEC = Elem<T>::VEC;
@@ -322,9 +326,6 @@ __global__ __launch_bounds__(512) void gn_stats_kernel(GroupNormArgs a) {
   const int cpg = a.C / a.G;
   const int64_t nv = (int64_t)cpg * a.HW / VEC;                 // the group is one contiguous run of cpg * HW elements
   const V* x = (const V*)((const T*)a.x + (int64_t)blockIdx.x * cpg * a.HW);
-  // NR vectors a thread are requested together (one at a time, each waits for memory: 64 groups of 10 x 4096 elements took 7.6 us,
-  // now 5.0); a group that they cover is not read again for the second pass
-  constexpr int NR = 10;
   V v[NR];
   auto request = [&](int64_t i0) __attribute__((always_inline)) {
 #pragma unroll
@@ -371,8 +372,10 @@ __global__ __launch_bounds__(256) void gn_apply_nchw_kernel(GroupNormArgs a) {
   ((V*)a.y)[i] = pack<T>(f);
 }
 
-// channel-major in, token-major out: a workgroup owns TT tokens of one image, all channels
-template <typename T, int TT>
+// channel-major in, token-major out: a workgroup owns TT tokens of one image, all channels.  NR vectors a thread, and what scales
+// them, are requested together, as many as divide the tile evenly (2 x 320 x 4096 in 64-token tiles, one at a time: 12.0 us; five in
+// 32-token ones 6.5)
+template <typename T, int TT, int NR>
 __global__ __launch_bounds__(256) void gn_apply_tokens_kernel(GroupNormArgs a) {
   constexpr int VEC = Elem<T>::VEC;
   typedef typename Vec16<T>::type V;
@@ -383,9 +386,6 @@ __global__ __launch_bounds__(256) void gn_apply_tokens_kernel(GroupNormArgs a) {
   const int cpg = a.C / a.G;
   constexpr int TV = TT / VEC;                                   // vectors per channel inside the tile
   const T* x = (const T*)a.x + (int64_t)b * a.C * a.HW;
-  // NR vectors a thread, and what scales them, are requested together (one at a time, each waits for memory: 2 x 320 x 4096
-  // in 64-token tiles 12.6 us, now 6.5 in 32-token ones)
-  constexpr int NR = 5;
   for (int p0 = threadIdx.x; p0 < a.C * TV; p0 += 256 * NR) {
     V v[NR];
     float mean[NR], rstd[NR], ga[NR], be[NR];
@@ -424,37 +424,43 @@ static bool groupnorm_split(const GroupNormArgs& a) {
 }
 int groupnorm_launches(const GroupNormArgs& a) { return groupnorm_split(a) ? 2 : 1; }
 
+// Vectors a thread requests together where `threads` of them share n: the fewest rounds of at most CAP, dealt evenly, rounded up to
+// a multiple of STEP
+template <int CAP, int STEP> static int gn_batch(int64_t n, int threads) {
+  const int64_t per = (n + threads - 1) / threads, rounds = (per + CAP - 1) / CAP;
+  return (int)((per + rounds - 1) / rounds + STEP - 1) / STEP * STEP;
+}
+template <typename T, int TT, int NR = 1>
+static int gn_apply_tokens_launch(const GroupNormArgs& a, int nr, hipStream_t s) {
+  if constexpr (NR < 6) if (nr > NR) return gn_apply_tokens_launch<T, TT, NR + 1>(a, nr, s);
+  const size_t smem = (size_t)TT * (a.C + Elem<T>::VEC) * sizeof(T);
+  static size_t granted = 0;
+  if (smem > granted) {
+    const hipError_t e = hipFuncSetAttribute((const void*)gn_apply_tokens_kernel<T, TT, NR>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e != hipSuccess) return (int)e;
+    granted = smem;
+  }
+  gn_apply_tokens_kernel<T, TT, NR><<<dim3((unsigned)((a.HW + TT - 1) / TT), (unsigned)a.B), dim3(256), smem, s>>>(a);
+  return (int)hipGetLastError();
+}
+template <typename T, int NR = 2>
+static void gn_stats_launch(const GroupNormArgs& a, int nr, hipStream_t s) {
+  if constexpr (NR < 12) if (nr > NR) return gn_stats_launch<T, NR + 2>(a, nr, s);
+  gn_stats_kernel<T, NR><<<dim3((unsigned)(a.B * a.G)), dim3(512), 0, s>>>(a);
+}
 template <typename T>
 static int groupnorm_split_launch(const GroupNormArgs& a, hipStream_t s) {
   constexpr int VEC = Elem<T>::VEC;
-  gn_stats_kernel<T><<<dim3((unsigned)(a.B * a.G)), dim3(512), 0, s>>>(a);
+  gn_stats_launch<T>(a, gn_batch<12, 2>((int64_t)(a.C / a.G) * a.HW / VEC, 512), s);
   if (!a.tokens_out) {
     const int64_t nv = (int64_t)a.B * a.C * (a.HW / VEC);
     gn_apply_nchw_kernel<T><<<dim3((unsigned)((nv + 255) / 256)), dim3(256), 0, s>>>(a);
     return (int)hipGetLastError();
   }
-  const size_t row = (size_t)(a.C + VEC) * sizeof(T);
   // 64 tokens a workgroup (whole cache lines of bf16 channels) where that gives every CU one, else 32
-  if (64 * row <= 160 * 1024 && (int64_t)(a.HW + 63) / 64 * a.B >= 256) {
-    const size_t smem = 64 * row;
-    static size_t granted = 0;
-    if (smem > granted) {
-      const hipError_t e = hipFuncSetAttribute((const void*)gn_apply_tokens_kernel<T, 64>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-      if (e != hipSuccess) return (int)e;
-      granted = smem;
-    }
-    gn_apply_tokens_kernel<T, 64><<<dim3((unsigned)((a.HW + 63) / 64), (unsigned)a.B), dim3(256), smem, s>>>(a);
-  } else {
-    const size_t smem = 32 * row;
-    static size_t granted = 0;
-    if (smem > granted) {
-      const hipError_t e = hipFuncSetAttribute((const void*)gn_apply_tokens_kernel<T, 32>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-      if (e != hipSuccess) return (int)e;
-      granted = smem;
-    }
-    gn_apply_tokens_kernel<T, 32><<<dim3((unsigned)((a.HW + 31) / 32), (unsigned)a.B), dim3(256), smem, s>>>(a);
-  }
-  return (int)hipGetLastError();
+  if ((size_t)64 * (a.C + VEC) * sizeof(T) <= 160 * 1024 && (int64_t)(a.HW + 63) / 64 * a.B >= 256)
+    return gn_apply_tokens_launch<T, 64>(a, gn_batch<6, 1>((int64_t)a.C * (64 / VEC), 256), s);
+  return gn_apply_tokens_launch<T, 32>(a, gn_batch<6, 1>((int64_t)a.C * (32 / VEC), 256), s);
 }
 
 int launch_groupnorm(const GroupNormArgs& a, void* stream) {

@@ -48,12 +48,35 @@ def test_layernorm_store_through_window_map(dtype, s):
 
 
 @pytest.mark.parametrize("dtype", DT)
-@pytest.mark.parametrize("B,C,H,W,G", [(1, 32, 40, 33, 1), (8, 16, 41, 50, 2), (1, 16, 64, 80, 2)])
+@pytest.mark.parametrize("B,C,H,W,G", [(1, 32, 40, 33, 1), (8, 16, 41, 56, 2), (1, 16, 64, 80, 2)])
 def test_groupnorm_in_two_kernels_at_their_edges(dtype, B, C, H, W, G):
-    """A group of more vectors than a thread holds (5280 in bf16: read again for the variance) and of exactly as many (5120);
-    264 workgroups of 64 tokens, the last of an image ragged (below 256 they take 32)."""
+    """Groups of 5280 and 5120 vectors in bf16 (a batch of twelve per thread with a ragged end, one of ten without), twice as many in fp32
+    (read again for the variance); 288 workgroups of 64 tokens, the last of an image ragged (below 256 they take 32)."""
+    assert H * W % 8 == 0 and C % 8 == 0      # whole vectors: else one kernel does it
     x = draw((B, C, H, W), 17, dtype, 2.0, -0.5)
     g, b = draw((C,), 18, dtype, 0.2, 1.0), draw((C,), 19, dtype, 0.2)
+    y = sm.groupnorm(dev(x, dtype), dev(g, dtype), dev(b, dtype), G, tokens_out=True, split=True)
+    want = V.apply_chain(O.group_norm_nchw(to_np(x), G, to_np(g), to_np(b)), V.nchw_to_tokens_chain(B, C, H, W))
+    assert_close(y, want, dtype, "groupnorm", 4.0)
+
+
+@pytest.mark.parametrize("dtype", DT)
+@pytest.mark.parametrize("B,C,H,W,G", [
+    (1, 384, 8, 33, 48),     # bf16: 264 vectors a group, a batch of two; 6 vectors a thread in the tile
+    (1, 320, 8, 33, 10),     # 1056: four; 5
+    (1, 64, 8, 33, 1),       # 2112: six; 1
+    (1, 104, 8, 33, 1),      # 3432: eight; 2
+    (1, 128, 8, 33, 1),      # 4224: ten; 2
+    (1, 168, 8, 33, 1),      # 5544: twelve; 3
+    (1, 192, 8, 33, 1),      # 6336: two rounds of eight; 3
+    (1, 256, 8, 32, 2),      # 4096: eight, whole; 4
+    (1, 448, 8, 33, 2),      # 7392: two rounds of eight; two rounds of 4
+    (8, 200, 41, 56, 8),     # 64-token tiles: two rounds of 4, the last one cut
+])
+def test_groupnorm_batches(dtype, B, C, H, W, G):
+    assert H * W % 8 == 0 and C % 8 == 0
+    x = draw((B, C, H, W), 20, dtype, 2.0, -0.5)
+    g, b = draw((C,), 21, dtype, 0.2, 1.0), draw((C,), 22, dtype, 0.2)
     y = sm.groupnorm(dev(x, dtype), dev(g, dtype), dev(b, dtype), G, tokens_out=True, split=True)
     want = V.apply_chain(O.group_norm_nchw(to_np(x), G, to_np(g), to_np(b)), V.nchw_to_tokens_chain(B, C, H, W))
     assert_close(y, want, dtype, "groupnorm", 4.0)
