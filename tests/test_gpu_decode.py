@@ -62,10 +62,13 @@ def test_decode_step_matches_the_oracle(B, E, h, L, F, rot, mode):
 
 @pytest.mark.parametrize("B,E,h,L,F,rot", [
     (2, 256, 1, 63, 8192, 64),      # W2 in eight splits, more than the last kernel asks for early; one block of keys, whole
-    (32, 1024, 8, 64, 1024, 32),    # activation rows of more pieces than wait in registers; one key more than a block
+    (32, 1024, 8, 64, 1024, 32),    # the last kernel: more pieces of activation rows than wait in registers (W2: just as many); one key more than a block
     (1, 1088, 17, 127, 64, 32),     # K of no whole set of fragments in the first and last kernel; W2 of four steps: waves without any
     (1, 256, 1, 255, 128, 64),      # four blocks of keys in two workgroups ...
     (1, 256, 1, 256, 128, 64),      # ... and the first key of a fifth
+    (9, 2048, 8, 20, 8192, 64),     # W2: a piece of its rows more per thread than waits in registers
+    (12, 2048, 8, 20, 8192, 64),    # ... five splits of F, the last one shorter
+    (30, 2048, 8, 20, 8192, 64),    # ... eleven: the largest batch at this width
 ])
 def test_edges_of_the_splits(B, E, h, L, F, rot):
     run_case(B, E, h, L, F, rot, sm.SM_ELIDED, seed=B + L, std=0.1)
