@@ -492,7 +492,8 @@ def test_linear_with_packed_weight_row_maps_and_refusals():
 
 
 @pytest.mark.parametrize("M,C,Hd", [(70, 128, 96), (200, 256, 1024), (6272, 384, 1536), (130, 512, 1536), (12544, 512, 2048),
-                                    (16400, 256, 1024), (16387, 384, 1536)])     # large grids: 64-token tiles
+                                    (16400, 256, 1024), (16387, 384, 1536),      # large grids: 64-token tiles
+                                    (70, 512, 10240), (70, 512, 10496), (70, 512, 12288)])      # vectors in LDS; read from memory; the widest
 def test_mlp_fused_with_projection(M, C, Hd):
     # x1 = A . Wp^T + bp + x0, y = x1 + MLP(LayerNorm(x1)) in one kernel; x0 read and y written through a row map
     dtype = torch.bfloat16

@@ -191,6 +191,20 @@ def test_row_owning_tail_above_the_chain(B, H, C):
     assert_bf16_close(got[0], swin.swin_stage(to_np(x), [np_params(p) for p in blocks], H, H, 7, h), "stage", x=to_np(x))
 
 
+@pytest.mark.parametrize("ratio", [18, 19])
+def test_row_owning_tail_with_a_very_wide_hidden_layer(ratio):
+    """C = 512: the kernel's vectors in LDS, and beside a hidden layer whose bias takes their place."""
+    B, H, C, h = 12, 14, 512, 16
+    dr = Wl.Draw(ratio, True)
+    x = dr.normal(B, H * H, C)
+    blocks = [Wl.swin_block_params(dr, C, h, 7, ratio) for _ in range(2)]
+    chain = sm.SwinChain(B, [(C, h, 2, H, H)], 7, {"stages": [[dev_params(p, torch.bfloat16) for p in blocks]]}, torch.bfloat16, mlp_ratio=ratio)
+    got, xd = [], dev(x, torch.bfloat16)
+    labels = _labels(lambda: got.append(chain(xd)))
+    assert "proj+ln+mlp_bf16[%d,%d,%d]+ln+qkv" % (B * H * H, ratio * C, C) in labels, labels
+    assert_bf16_close(got[0], swin.swin_stage(to_np(x), [np_params(p) for p in blocks], H, H, 7, h), "stage", x=to_np(x))
+
+
 @pytest.mark.parametrize("M,N,K,dtype,norm,act,res", [
     (1100, 1000, 128, BF16, None, "gelu", True),         # LDS-DMA staging, ragged rows and columns
     (1100, 1000, 104, BF16, None, "gelu", True),         # register staging, a cut K-tile
