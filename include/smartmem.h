@@ -414,7 +414,8 @@ int sm_attn_block(const sm_attn_cfg*, const void* const* weights, const void* x,
  *     result, the attention output is stored head-merged; k_out, v_out must be NULL.  Three kernels.
  *   SM_EXPLICIT: every Slice / Permute / Concat / Reshape of the exported graph that moves data is a copy kernel:
  *     k_out, v_out: device [B, heads, L + 1, d] receive the grown caches (k_cache / v_cache are only read).
- * Limits: B <= 32, E a multiple of 64 (<= 8192), d in {64, 128, 256}, F a multiple of 64, rot in {0, 32, 64}.
+ * Limits: B <= 32, E a multiple of 64 (<= 8192), d in {64, 128, 256}, F a multiple of 64, rot in {0, 32, 64}; B (E + 648) <= 81920
+ * (at E = 2048: 30 sequences), and B rows of a 64th of E + F, whole shares to each, within 48 KiB (B = 32, E = 768: F to 23808).
  * Workspace from sm_decode_step_workspace_bytes; nothing in it has to survive between calls.  Calls on one stream
  * are ordered; calls that share a workspace on different streams race. */
 typedef struct {

@@ -90,7 +90,8 @@ std::shared_ptr<DecodePlan> decode_plan(const sm_decode_cfg& c, std::string* err
   return p;
 }
 
-// activation rows of the longest of 64 splits over E and F together
+// The call's limit on B x (E + F): E and F dealt to 64 shares by their sizes, the rows of the longest share within 48 KiB.  The kernels
+// need less (W2 alone is split, up to 64 ways: decode_fc2_splits always finds a split whose rows fit under this limit)
 size_t split_rows_bytes(int B, int E, int F) {
   const int KE = E / 16, KF = F / 16, nd = std::max(1, std::min(63, (int)((int64_t)64 * KE / (KE + KF))));
   return (size_t)B * (std::max((KE + nd - 1) / nd, (KF + 63 - nd) / (64 - nd)) * 16 + 8) * 2;
@@ -106,8 +107,8 @@ int check_cfg(const sm_decode_cfg* c, const char* who) {
   if (c->F < 64 || c->F % 64) return fail(SM_ERR_SHAPE, "%s: MLP width must be a multiple of 64", who);
   if (c->rot != 0 && c->rot != 32 && c->rot != 64) return fail(SM_ERR_SHAPE, "%s: rotary features must be 0, 32 or 64", who);
   if (c->L < 0 || c->cache_pitch < c->L) return fail(SM_ERR_SHAPE, "%s: the cache pitch must cover the cached tokens", who);
-  if (decode_in_smem(c->B, c->E) > 160 * 1024) return fail(SM_ERR_SHAPE, "%s: B x E too large for the LDS token tile", who);
-  if (split_rows_bytes(c->B, c->E, c->F) > 48 * 1024) return fail(SM_ERR_SHAPE, "%s: B x (E + F) too large for a split's activation rows in LDS", who);
+  if (decode_in_smem(c->B, c->E) > 160 * 1024) return fail(SM_ERR_SHAPE, "%s: B x E too large for the first kernel's LDS token tile", who);
+  if (split_rows_bytes(c->B, c->E, c->F) > 48 * 1024) return fail(SM_ERR_SHAPE, "%s: B x (E + F) too large", who);
   return SM_OK;
 }
 

@@ -19,6 +19,14 @@ def test_workspace_query_plans_the_step():
     assert lib.sm_decode_step_workspace_bytes(C.byref(cfg(B=1, E=64, heads=1, F=64, rot=0, L=0, pitch=1)), sm.SM_ELIDED) > 0
 
 
+def test_limits_of_batch_and_widths():
+    """What is taken and what is refused at the edges that the header names."""
+    lib = sm.lib()
+    for c, taken in ((cfg(B=30), True), (cfg(B=31), False), (cfg(B=32, E=768, heads=12, F=23808), True), (cfg(B=32, E=768, heads=12, F=23872), False),
+                     (cfg(B=9, E=8192, heads=32, F=32768), True), (cfg(B=10, E=8192, heads=32, F=32768), False)):
+        assert (lib.sm_decode_step_workspace_bytes(C.byref(c), sm.SM_ELIDED) > 0) == taken, c
+
+
 def test_refusals():
     lib = sm.lib()
     bad = [cfg(B=33), cfg(B=0), cfg(E=2000), cfg(heads=5), cfg(E=2048, heads=64), cfg(F=100), cfg(rot=48), cfg(L=-1),
