@@ -455,6 +455,8 @@ __global__ __launch_bounds__(64 * (C / 32), C <= 256 ? 4 : 3) void mlp_fused_ker
     __syncthreads();
   }
 
+  {
+  const int lane = mlp_lane(), l32 = lane & 31, hf = lane >> 5;
   for (int r = 0; r < rounds; ++r) {
     // ---- first product: this wave's slice of the round -> H (bias, GELU, bf16) into LDS
     const int sc = r * T + w;
@@ -484,6 +486,7 @@ __global__ __launch_bounds__(64 * (C / 32), C <= 256 ? 4 : 3) void mlp_fused_ker
                                                                         last ? (LNOUT == 2 ? 6 * C * C : 0) : 4 * Hd * C, 0x00020000);
     const int next = (LNOUT == 2 && last ? w : nsc) * KK * 1024;
     mlp32_product(hb, l32 * HP + hf, wf, out, [&](int i) __attribute__((always_inline)) { return wload(rn, next + i * 1024); });
+  }
   }
 
   {
