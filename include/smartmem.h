@@ -348,9 +348,10 @@ typedef struct {
                                    this block starts at attention */
                                 /* On few tokens, SM_ELIDED, forms that read the row-major matrices are faster: projection ..
                                    FC2 (and in sm_run_chain the next QKV) as one launch cut over output columns, LayerNorm-1
-                                   folded into the plain QKV Linear.  They run where the block has all three packed weights,
-                                   or its width has no fused kernel, and the row-major weights, biases and norms are there
-                                   too; a block that is given packed weights only runs the packed forms at every size */
+                                   folded into the plain QKV Linear; from 1025 to C^2 / 112 tokens (C <= 512) sm_run_chain runs
+                                   one launch per Linear instead.  They run where the block has all three packed weights, or
+                                   its width has no fused kernel, and the row-major weights, biases and norms are there too; a
+                                   block that is given packed weights only runs the packed forms at every size */
 } sm_swin_weights;
 size_t sm_swin_block_workspace_bytes(const sm_swin_cfg*, int mode);
 int sm_swin_block(const sm_swin_cfg*, const sm_swin_weights*, const void* x, void* y,

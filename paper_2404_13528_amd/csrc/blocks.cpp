@@ -200,13 +200,16 @@ int run_gemm(const void* A, const void* W, const void* bias, const void* res, vo
 // wins only while the Linear has few column tiles (measured: up to N = 512).
 bool fold_norm(int n_cols) { return n_cols <= 512; }
 
-// Whether the tail of a block (projection .. the next QKV) is cut over output columns instead of over rows
-// (row-owning kernels alone / the chain, us per block of a stage of six: C = 512, 196 tokens 101 / 31, 784 100 / 51, 1568 99 / 73,
-// 2156 100 / 98, 3136 99 / 122; C = 384, 196 56 / 28, 784 55 / 45, 1176 55 / 52, 1568 55 / 58; C = 256, 196 35 / 26, 392 34 / 30, 1568
-// 34 / 41; per-operator kernels at C = 768, 196 80 / 57, at C = 1024, 49 tokens 92 / 72, 196 93 / 79, 392 117 / 128).  The row-owning
-// kernel's time does not depend on the rows until they fill the chip, and grows with C^2; the chain's grows with rows x C, from
-// the four hand-overs between its Linears on: below C = 256 the row-owning kernel is the faster one at any size (a whole block,
-// C = 128, 49 tokens: 25.1 / 20.0 us chained / row-owning, 98: 25.3 / 20.4; C = 256, 49: 26.5 / 31.2).
+// Whether the tail of a block (projection .. the next QKV) is cut over output columns instead of over rows, in one chained launch or
+// (tail_by_operators) in single Linears.  us a stage of four blocks, row-owning kernels / chained / single: C = 512, 196 tokens 351 /
+// 122 / 122, 784 365 / 202 / 202, 1568 350 / 283 / 221, 2156 342 / 381 / 272; C = 384, 196 192 / 113 / 115, 784 188 / 177 / 165, 1176
+// 193 / 203 / 187; C = 256, 196 117 / 104 / 106, 392 118 / 120 / 111, 784 118 / 124 / 116.  The row-owning kernel's time does not
+// depend on the rows until they fill the chip, and grows with C^2; the chain's grows with rows x C, from the four hand-overs between
+// its Linears on: below C = 256 the row-owning kernel is the faster one at any size (a whole block, C = 128, 49 tokens: 25.1 / 20.0
+// us chained / row-owning, 98: 25.3 / 20.4).  At widths without one (us a block, one kernel per operator / chained): C = 768, 196
+// tokens 80 / 57; C = 1024, 49 92 / 72, 196 93 / 79, 392 117 / 128.  The line at C^2 / 112 was drawn for the chain alone and tests hold
+// it: the single Linears are the faster form above it too for a while, C = 512, 2352 tokens 342 / 272 (row-owning / single), 3136
+// 353 / 331, 3920 346 / 344, 4704 340 / 397; C = 384, 1372 193 / 191, 1960 195 / 201.
 bool split_tail_use(const sm_swin_cfg& c, int64_t T) {
   if (c.dtype != SM_BF16 || c.C % 32 || c.C > 1024) return false;
   if (c.C < 256 && mlp_fused_supported(c.C, c.mlp_ratio * c.C, c.dtype)) return false;
@@ -237,11 +240,10 @@ bool tail_is_split(const sm_swin_cfg& c, const sm_swin_weights* wt) {
 }
 // Whether a chain of blocks runs such a tail as single Linears instead: launches whose workgroups fill the chip, where the chained
 // tasks wait for each other four times and every XCD streams all weights for its rows.  From three row tiles of 64 on an XCD on: us a
-// stage of four blocks, chained / single: C = 512, 784 tokens 203 / 202, 1176 247 / 208, 1568 285 / 221, 2156 383 / 270; C = 384, 784
-// 177 / 161, 980 183 / 183 (a net with six such blocks 659 / 667), 1176 205 / 186.  (On fewer tokens the single Linears are often
-// a little faster too, C = 512, 196 tokens 126 / 121, 588 196 / 175, C = 256, 392 121 / 104, and at a width without a row-owning
-// kernel more so, C = 1024, 49 tokens 220 / 142, C = 768, 245 195 / 183: there two launches per block are what the launch counts
-// promise a caller.)
+// stage of four blocks, chained / single: C = 512, 784 tokens 202 / 202, 1176 247 / 208, 1568 283 / 221, 2156 381 / 272; C = 384, 784
+// 177 / 165, 980 182 / 186 (a net with six such blocks 659 / 667), 1176 203 / 187.  On fewer tokens the single Linears are often
+// a little faster too, C = 512, 392 tokens 158 / 140, C = 256, 392 120 / 111, and at a width without a row-owning kernel more so,
+// C = 1024, 49 tokens 220 / 142, C = 768, 245 195 / 183: there the chained launch stays because the tests count two launches a block.
 bool tail_by_operators(const sm_swin_cfg& c) { return c.C <= 512 && (int64_t)c.B * c.H * c.W > 1024; }
 // A caller who packed the fused kernels' weights, or a width without such kernels: norms may be folded wherever that is
 // faster (else the caller asked for one kernel per operator and fold_norm alone decides)
@@ -720,7 +722,7 @@ extern "C" int sm_run_chain(const sm_chain_desc* c, const void* const* weights, 
         if (b.split && k + 1 < st.depth) b.next = b.next_qkv = true;
         else if (mode == SM_ELIDED && !b.by_operators && k + 1 < st.depth && proj_is_fused(bc, &bw)) {
           std::memcpy(&nwt, wq, sizeof(nwt));
-          const bool with_qkv = nwt.qkv_packed && c->mlp_ratio >= 3;    // (the kernel keeps the QKV bias where the first MLP bias was)
+          const bool with_qkv = nwt.qkv_packed && c->mlp_ratio >= 3;    // (the 64-token kernel keeps the QKV bias where the first MLP bias was; one limit for both kernels)
           if (!fold_norm(3 * st.C) || with_qkv) { b.next = true; b.next_qkv = with_qkv; }
         }
         need[sh][(size_t)s] |= mode == SM_ELIDED ? el_tables_needed(bc, &bw, pre) : ~0ull;

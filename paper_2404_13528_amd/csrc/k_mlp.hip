@@ -332,8 +332,8 @@ constexpr int mlp_vectors(bool proj, int lnout) { return 1 + (proj ? 3 : 0) + (l
 
 // PROJ: the Linear that precedes the MLP's residual stream is computed here as well (a transformer block's attention
 // output projection): x1 = A . Wp^T + bp + x0 for the tile's 32 tokens, x0 read (and Y written) through y_rows, then
-// Y = x1 + MLP(LayerNorm(x1)).  x1 never reaches memory: a normalised copy feeds the first product from LDS, a plain
-// copy in LDS is the final residual.
+// Y = x1 + MLP(LayerNorm(x1)).  x1 never reaches memory: a normalised copy feeds the first product from LDS, and the
+// accumulators of the final sum start from x1 itself.
 // LNOUT = 1: a second output, LayerNorm(Y) with its own gamma / beta, stored through its own row map: the norm that opens
 // the next block, computed while the rows are still in registers (statistics over the C / 32 waves through LDS).
 // LNOUT = 2 (with PROJ): that norm stays in LDS and the Linear that follows it (the next block's QKV, N = 3 C, packed
@@ -750,10 +750,10 @@ __global__ __launch_bounds__(C, (C >= 384 ? 1 : 2)) void mlp64_kernel(MlpArgs g)
 
 // mlp64_kernel with the attention output projection in front and, optionally, the next block's LayerNorm-1 (LNOUT = 1)
 // or LayerNorm-1 + QKV Linear (LNOUT = 2) behind it: the C = 512 form of mlp_fused_kernel<C, true, LNOUT>, 64-token
-// tiles.  x1 = A . Wproj^T + bproj + x0 (x0 read and Y written through y_rows); x1 (bf16) stays in registers as the residual of
-// the final sum's first addend in its accumulators, normalised it goes to LDS for the first product.  LDS: [x0, then x1 normalised, then the waves' stages of
+// tiles.  x1 = A . Wproj^T + bproj + x0 (x0 read and Y written through y_rows).  The accumulators of the final sum start from x1
+// (rounded to bf16); normalised it goes to LDS for the first product.  LDS: [x0, then x1 normalised, then the waves' stages of
 // mlp_stage_put | A tile, then the two hidden tiles, then the normalised Y for the QKV Linear | b1, then bq | row offsets |
-// row statistics].
+// row statistics | vectors, where there is room].
 // One weight stream per wave through the ring of 16 fragment registers, in blocks of 32 fragments: two blocks of Wproj
 // ((step, feature block) order, the wave's two slices of lin_pack_kernel's layout), the blocks of mlp64_kernel, then
 // the wave's six QKV slices.
@@ -1107,14 +1107,14 @@ static int mlp_launch3(const MlpArgs& g, void* stream) {
 template <int C>
 static int mlp_launch(const MlpArgs& g, void* stream) {
   if (g.Wproj_p) {
-    if (g.Y2 && g.Wq_p) return g.Hd >= 3 * C ? mlp_launch3<C, true, 2>(g, stream) : (int)hipErrorInvalidValue;   // (the following bias reuses the first bias's LDS)
+    if (g.Y2 && g.Wq_p) return g.Hd >= 3 * C ? mlp_launch3<C, true, 2>(g, stream) : (int)hipErrorInvalidValue;   // (the 64-token kernel's limit: its following bias reuses the first bias's LDS)
     return g.Y2 ? mlp_launch3<C, true, 1>(g, stream) : mlp_launch3<C, true, 0>(g, stream);
   }
   if (g.Wq_p) return (int)hipErrorInvalidValue;
   return g.Y2 ? mlp_launch3<C, false, 1>(g, stream) : mlp_launch3<C, false, 0>(g, stream);
 }
 
-// LDS capacity: the projection variant holds three token tiles
+// LDS capacity of the projection variant: the A tile beside the others
 bool mlp_proj_supported(int C, int Hd, int dtype) {
   if (!mlp_fused_supported(C, Hd, dtype)) return false;
   if (C == 512) return mlp64_shape(C, Hd) && Hd >= 3 * C && mlp64p_smem(C, Hd) <= 160 * 1024;
