@@ -433,13 +433,9 @@ template <int CAP, int STEP> static int gn_batch(int64_t n, int threads) {
 template <typename T, int TT, int NR = 1>
 static int gn_apply_tokens_launch(const GroupNormArgs& a, int nr, hipStream_t s) {
   if constexpr (NR < 6) if (nr > NR) return gn_apply_tokens_launch<T, TT, NR + 1>(a, nr, s);
-  const size_t smem = (size_t)TT * (a.C + Elem<T>::VEC) * sizeof(T);
-  static size_t granted = 0;
-  if (smem > granted) {
-    const hipError_t e = hipFuncSetAttribute((const void*)gn_apply_tokens_kernel<T, TT, NR>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) return (int)e;
-    granted = smem;
-  }
+  const size_t smem = (size_t)TT * (a.C + Elem<T>::VEC) * sizeof(T);      // (at most the CU's: groupnorm_split)
+  static const hipError_t allowed = hipFuncSetAttribute((const void*)gn_apply_tokens_kernel<T, TT, NR>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  if (allowed != hipSuccess) return (int)allowed;
   gn_apply_tokens_kernel<T, TT, NR><<<dim3((unsigned)((a.HW + TT - 1) / TT), (unsigned)a.B), dim3(256), smem, s>>>(a);
   return (int)hipGetLastError();
 }
